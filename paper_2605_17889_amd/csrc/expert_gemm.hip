@@ -74,8 +74,8 @@ int launch_grouped(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, co
     static std::atomic<uint64_t> attr_set{0};
     const long long max_mt = most_row_tiles(R, E, Cfg::BM);
     return launch_tiles(env, attr_set, gemm::grouped_gemm_kernel<Cfg>, Cfg::SMEM, Cfg::NTHREADS,
-                        max_mt * (N / Cfg::BN_OUT), s, A, B0, B1, C, offsets, row_index, index_div,
-                        E, N, K);
+                        max_mt * (N / Cfg::BN_OUT), s, A, B0, B1, C, offsets, row_index,
+                        gemm::RowDiv(index_div), E, N, K);
 }
 
 // The pipelined kernel with operand rings of NA and NB stages; tiles of at most HalfCfg::BM rows
@@ -93,7 +93,7 @@ int launch_ring(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, const
     const long long grid = max_mt * (N / Cfg::BN_OUT) + kXcds * ((cus / 2 + kXcds - 1) / kXcds + 1);
     return launch_tiles(env, attr_set, gemm::grouped_gemm_ring_kernel<Cfg, HalfCfg, NA, NB>,
                         gemm::RingCfg<Cfg, NA, NB>::SMEM, Cfg::NTHREADS, grid, s, A, B0, B1, C,
-                        offsets, row_index, index_div, E, N, K, cus);
+                        offsets, row_index, gemm::RowDiv(index_div), E, N, K, cus);
 }
 
 // Tile configuration by average rows per expert. All configurations give identical bits.
