@@ -96,58 +96,103 @@ int launch_ring(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, const
                         offsets, row_index, gemm::RowDiv(index_div), E, N, K, cus);
 }
 
-// Tile configuration by average rows per expert. All configurations give identical bits.
-int pick_config(const GemmEnv& env, int R, int E, int nt_large, int nt_mid) {
-    if (env.forced_config >= 0) return env.forced_config;
-    // 0: pipelined 256-row tiles (with half-height tails). 1: 128-row tiles (generic kernel).
-    // 2: a few dozen rows per expert (64-row tiles). 3: a handful (32-row tiles, deep weight
-    // ring). 4: 96-row tiles of four wavefronts side by side (groups of 33 to 96 rows: a quarter
-    // fewer matrix instructions and fragment reads per k-step than the 128-row tile, and room
-    // for a deeper weight ring in the down projection). Per-expert counts are not known on the
-    // host, so the choice prices a uniform routing: the average group and its standard deviation.
-    const double avg = static_cast<double>(R) / (E > 0 ? E : 1);
-    const double sigma = std::sqrt(avg);
-    const double upper = avg + 2.0 * sigma;
-    if (upper <= 32.0) return 3;
-    if (avg <= 32.0) return 2;
-    if (upper <= 96.0) return 4;
-    if (upper <= 256.0) {
-        // one row tile per expert either way: the padded rows decide, the large tiles priced at
-        // 0.8 of the time per padded row of the 128-row ones (measured on micro-batches of 64 to
-        // 512 tokens at the 8x22B shape)
-        const double padded_mid = std::ceil(upper / 128.0) * 128.0;
-        return 256.0 * 0.8 <= padded_mid ? 0 : 1;
-    }
-    // Several row tiles per expert. Launch time in units of one full 256-row tile, for groups
-    // one standard deviation below and above the mean: a large tile costs 1, a tail of at most
-    // 128 rows 0.55 (half-height tile), a 128-row tile of the generic kernel 0.8. A launch of
-    // many rounds of tiles (one workgroup per compute unit) costs its tiles; one of fewer than
-    // four rounds costs whole rounds, a last round under half full 0.55 with the large tiles
-    // (it is split), and the large tiles 1.25 times their count then (fewer, longer tiles
-    // balance worse). Measured on micro-batches of 1024 and 2048 tokens at the 8x22B shape,
-    // where the two GEMMs of one call want different answers.
-    const int cus = compute_units(env.device);
-    double units0 = 0.0, tiles0 = 0.0, tiles1 = 0.0;
-    for (const double m : {std::max(1.0, avg - sigma), avg + sigma}) {
-        const double full = std::floor(m / 256.0), tail = m - full * 256.0;
-        units0 += 0.5 * (full + (tail <= 0.0 ? 0.0 : tail <= 128.0 ? 0.55 : 1.0));
-        tiles0 += 0.5 * std::ceil(m / 256.0);
-        tiles1 += 0.5 * std::ceil(m / 128.0);
-    }
-    const double scale0 = static_cast<double>(E) * nt_large, scale1 = static_cast<double>(E) * nt_mid;
-    units0 *= scale0;
-    tiles0 *= scale0;
-    tiles1 *= scale1;
-    double t0, t1;
+// Expected row tiles of height h: groups one standard deviation below and above the mean.
+double mean_row_tiles(double avg, double sigma, int h) {
+    return 0.5 * (std::ceil(std::max(1.0, avg - sigma) / h) + std::ceil((avg + sigma) / h));
+}
+
+// The n-tiles of one projection in each kind of tile, and what the small tiles of config 2 cost.
+struct NTiles {
+    int large, mid, small;
+    double mid_step;             // k-step of the 96- and 128-row tiles, of a 256-row tile's
+    double small_alone, small_pair;   // k-step of a 64-row tile alone on a compute unit / of two on one
+};
+
+// Large tiles against 128-row ones when experts have several row tiles. Launch time in units of one
+// full 256-row tile for the given row tiles: a large tile costs 1, a tail of at most 128 rows 0.55
+// (half-height tile), a 128-row tile of the generic kernel 0.8. A launch of many rounds of tiles
+// (one workgroup per compute unit) costs its tiles; one of fewer than four rounds costs whole
+// rounds, a last round under half full 0.55 with the large tiles (it is split), and the large
+// tiles 1.25 times their count then (fewer, longer tiles balance worse). Measured on
+// micro-batches of 1024 and 2048 tokens at the 8x22B shape, where the two GEMMs of one call want
+// different answers.
+double large_minus_mid(double units0, double tiles0, double tiles1, int cus) {
+    double t0;
     if (tiles0 >= 4.0 * cus) {
         t0 = units0 / cus;
     } else {
         const double whole = std::floor(tiles0 / cus), rem = tiles0 - whole * cus;
         t0 = 1.25 * (whole + (rem <= 0.0 ? 0.0 : rem <= 0.5 * cus ? 0.55 : 1.0));
     }
-    t1 = 0.8 * (tiles1 >= 4.0 * cus ? tiles1 / cus : std::ceil(tiles1 / cus));
-    return t0 <= t1 ? 0 : 1;
+    return t0 - 0.8 * (tiles1 >= 4.0 * cus ? tiles1 / cus : std::ceil(tiles1 / cus));
 }
+
+// Tile configuration by average rows per expert. All configurations give identical bits.
+int pick_config(const GemmEnv& env, int R, int E, const NTiles& nt) {
+    if (env.forced_config >= 0) return env.forced_config;
+    // 0: pipelined 256-row tiles (with half-height tails). 1: 128-row tiles (generic kernel).
+    // 2: up to 64 rows per expert (64-row tiles, two workgroups per compute unit). 3: up to 32
+    // (32-row tiles). 4: 96-row tiles of four wavefronts side by side (groups of 65 to 96 rows: a
+    // quarter fewer matrix instructions and fragment reads per k-step than the 128-row tile, and
+    // room for a deeper weight ring in the down projection). Per-expert counts are not known on
+    // the host, so the choice prices a uniform routing: the average group and its standard deviation.
+    const double avg = static_cast<double>(R) / (E > 0 ? E : 1);
+    const double sigma = std::sqrt(avg);
+    const double upper = avg + 2.0 * sigma;
+    if (upper <= 32.0) return 3;
+    // The 64-row tiles against the 96-row ones, gate/up + down: 500 tokens through 128 experts of
+    // 2048 x 768 200 us against 210, 200 tokens through 8 of 4096 x 14336 487 against 519; with a few
+    // experts past 64 rows (560 tokens through 64 experts of 2048 x 1408) 207 against 196.
+    if (upper <= 64.0) return 2;
+    const int cus = compute_units(env.device);
+    int config;
+    if (upper <= 96.0) {
+        config = 4;
+    } else if (upper <= 256.0) {
+        // one row tile per expert either way: the padded rows decide, the large tiles priced at
+        // 0.8 of the time per padded row of the 128-row ones (measured on micro-batches of 64 to
+        // 512 tokens at the 8x22B shape)
+        const double padded_mid = std::ceil(upper / 128.0) * 128.0;
+        config = 256.0 * 0.8 <= padded_mid ? 0 : 1;
+    } else {
+        // several row tiles per expert, for groups one standard deviation below and above the mean
+        double units0[2], tiles0[2], tiles1[2];
+        for (int i = 0; i < 2; ++i) {
+            const double m = i == 0 ? std::max(1.0, avg - sigma) : avg + sigma;
+            const double full = std::floor(m / 256.0), tail = m - full * 256.0;
+            units0[i] = E * nt.large * (full + (tail <= 0.0 ? 0.0 : tail <= 128.0 ? 0.55 : 1.0));
+            tiles0[i] = E * nt.large * std::ceil(m / 256.0);
+            tiles1[i] = E * nt.mid * std::ceil(m / 128.0);
+        }
+        double diff;
+        if (E == 1)        // a single group is one or the other, not half of each
+            diff = large_minus_mid(units0[0], tiles0[0], tiles1[0], cus) +
+                   large_minus_mid(units0[1], tiles0[1], tiles1[1], cus);
+        else
+            diff = large_minus_mid(0.5 * (units0[0] + units0[1]), 0.5 * (tiles0[0] + tiles0[1]),
+                                   0.5 * (tiles1[0] + tiles1[1]), cus);
+        config = diff <= 0.0 ? 0 : 1;
+    }
+    // A launch of at most one such tile per compute unit takes one tile's time however many compute
+    // units idle: small tiles are worth their extra loads if they use the idle ones. Units of a
+    // k-step of a full 256-row tile (about 1 us), measured on one expert of 4096 x 14336 (512 rows,
+    // down projection: 125 us with large tiles, 94 and 87 us with 64-row ones of 128 and 64 columns).
+    const int rows = config == 0 ? 256 : config == 1 ? 128 : 96;
+    const double tiles = E * mean_row_tiles(avg, sigma, rows) * (config == 0 ? nt.large : nt.mid);
+    if (tiles <= cus) {
+        const double step = config != 0 ? nt.mid_step : tiles <= 0.5 * cus ? 0.56 : 1.0;
+        const double small = E * mean_row_tiles(avg, sigma, 64) * nt.small;
+        const double fill = small <= cus ? nt.small_alone : nt.small_pair * std::ceil(small / (2.0 * cus));
+        if (fill < 0.9 * step) return 2;
+    }
+    return config;
+}
+
+// Experts that R rows are expected to touch.
+double touched_experts(int R, int E) { return E * (1.0 - std::exp(-static_cast<double>(R) / E)); }
+
+// Workgroups of `tiles` tiles that find a free slot per round, over the slots of those rounds.
+double last_round_use(double tiles, double slots) { return tiles / (slots * std::ceil(tiles / slots)); }
 
 // Large tiles: four wavefronts of 128 x 128 outputs (one per SIMD) or eight of 128 x 64. The
 // four-wavefront form addresses a weight row by a 32-bit byte offset from the expert's matrix.
@@ -174,28 +219,41 @@ using GateUpHalf1W  = Config<128, 256, 64, 2, 2, 3, true>;
 using DownLarge1W   = Config<256, 256, 64, 2, 2, 2, false>;
 using DownHalf1W    = Config<128, 256, 64, 2, 2, 3, false>;
 using GateUpMid   = Config<128, 256, 64, 2, 4, 3, true>;   // also the half-height tile of GateUpLarge
-using GateUpSmall = Config<64, 128, 64, 1, 2, 4, true>;
+// 64 rows: four wavefronts of 32 rows share a workgroup, and its ring leaves room for a second
+// workgroup on the compute unit, so that one streams weights while the other looks its tile up,
+// waits for its first loads or stores; the two-wavefront tile with a four-stage ring of its own
+// (one workgroup per compute unit) took 134 us at 500 tokens through 128 experts of 2048 x 768, gate/up,
+// this one 126.5 us, and the down projection 86 -> 74 us
+using GateUpSmall  = Config<64, 128, 64, 2, 2, 3, true>;
+using GateUpSmallS = Config<64, 128, 64, 2, 2, 3, true, true>;
+using DownSmallWide  = Config<64, 128, 64, 2, 2, 3, false>;
+using DownSmallWideS = Config<64, 128, 64, 2, 2, 3, false, true>;
+using DownSmall  = Config<64, 64, 64, 2, 2, 5, false>;    // more tiles
+using DownSmallS = Config<64, 64, 64, 2, 2, 5, false, true>;
 using DownLarge   = Config<256, 256, 64, 2, 4, 2, false>;
 using DownMid     = Config<128, 128, 64, 2, 2, 4, false>;
 using DownMidWide = Config<128, 256, 64, 2, 4, 3, false>;
-using DownSmall   = Config<64, 64, 64, 1, 2, 4, false>;
 using GateUpMidS   = Config<128, 256, 64, 2, 4, 3, true, true>;
-using GateUpSmallS = Config<64, 128, 64, 1, 2, 4, true, true>;
 using DownMidS     = Config<128, 128, 64, 2, 2, 4, false, true>;
 using DownMidWideS = Config<128, 256, 64, 2, 4, 3, false, true>;
-using DownSmallS   = Config<64, 64, 64, 1, 2, 4, false, true>;
-// a handful of rows per expert (decode): 32-row tiles leave LDS for seven 16 KB weight stages
 using GateUpMid96  = Config<96, 256, 64, 1, 4, 3, true>;
 using GateUpMid96S = Config<96, 256, 64, 1, 4, 3, true, true>;
 using DownMid96      = Config<96, 128, 64, 1, 4, 5, false>;
 using DownMid96S     = Config<96, 128, 64, 1, 4, 5, false, true>;
 using DownMid96Wide  = Config<96, 256, 64, 1, 4, 3, false>;
 using DownMid96WideS = Config<96, 256, 64, 1, 4, 3, false, true>;
-using GateUpTiny   = Config<32, 128, 64, 1, 2, 7, true>;
-using GateUpTinyS  = Config<32, 128, 64, 1, 2, 7, true, true>;
-using DownTiny     = Config<32, 128, 64, 1, 2, 7, false>;
-using DownTinyS    = Config<32, 128, 64, 1, 2, 7, false, true>;
-using DownTinyNarrowS = Config<32, 64, 64, 1, 2, 11, false, true>;   // more, narrower tiles
+// A handful of rows per expert (decode). Four stages let two gate/up workgroups (three of the narrow
+// down tiles) share a compute unit: at 2048 x 768 and 128 experts a tile has 32 or 12 k-steps, and with
+// one workgroup per compute unit its lookup and first loads were a fifth of its time (37 tokens:
+// gate/up 122 -> 114 us, down 72 -> 54 us). Seven stages where one workgroup per compute unit divides
+// into whole rounds and two do not.
+using GateUpTiny      = Config<32, 128, 64, 2, 2, 4, true>;
+using GateUpTinyS     = Config<32, 128, 64, 2, 2, 4, true, true>;
+using GateUpTinyDeepS = Config<32, 128, 64, 2, 2, 7, true, true>;
+using GateUpFewS      = Config<16, 64, 64, 1, 1, 5, true, true>;    // one or two tokens: more tiles
+using DownTiny     = Config<32, 64, 64, 2, 2, 4, false>;
+using DownTinyS    = Config<32, 64, 64, 2, 2, 4, false, true>;
+using DownFewS     = Config<16, 32, 64, 1, 1, 8, false, true>;
 
 }  // namespace
 
@@ -209,7 +267,7 @@ int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_inde
                   const moe_bf16* W1, const moe_bf16* W3, moe_bf16* H, hipStream_t s) {
     if (R == 0) return MOE_OK;
     const moe_bf16* x_perm = a;
-    int config = pick_config(env, R_hint, E, f / 128, f / 128);
+    int config = pick_config(env, R_hint, E, NTiles{f / 128, f / 128, f / 64, 0.82, 0.41, 0.58});
     if (config == 0 && d / 64 < 3) config = 1;     // the pipelined kernel needs three k-steps
     switch (config) {
         case 0:
@@ -225,8 +283,20 @@ int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_inde
                 return launch_grouped<GateUpMid96S>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
             return launch_grouped<GateUpMid96>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
         case 3:
-            if (single_m_tile(env, R_hint, E, 32))
+            if (single_m_tile(env, R_hint, E, 32)) {
+                const double nt = touched_experts(R_hint, E) * (f / 64);
+                const int cus = compute_units(env.device);
+                // 16-row tiles of half the width while they fit three to a compute unit at once:
+                // one token through 8 of 128 experts of 2048 x 768 12.7 against 14.3 us, three
+                // tokens 27 against 31; four tokens (more than one round) 46 against 41
+                if (2.0 * nt <= 2.5 * cus && single_m_tile(env, R_hint, E, 16))
+                    return launch_grouped<GateUpFewS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
+                // 16 tokens through 8 experts of 4096 x 14336, 7 rounds of one workgroup per compute unit or
+                // 3.5 of two: 280 against 284 us; 4 tokens at 6144 x 16384, 6 or 3 rounds: 397 against 367
+                if (last_round_use(nt, 2.0 * cus) < 0.93 * last_round_use(nt, cus))
+                    return launch_grouped<GateUpTinyDeepS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
                 return launch_grouped<GateUpTinyS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
+            }
             return launch_grouped<GateUpTiny>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
         default:
             if (single_m_tile(env, R_hint, E, 64))
@@ -243,7 +313,9 @@ int launch_down_as(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets
                    int d, int f, int E, const moe_bf16* W2, moe_bf16* y_perm, hipStream_t s) {
     if (R == 0) return MOE_OK;
     const bool wide_mid = static_cast<long long>(E) * (d / 256) >= 160 && d % 256 == 0;
-    int config = pick_config(env, R_hint, E, d / 256, wide_mid ? d / 256 : d / 128);
+    const int cus = compute_units(env.device);
+    int config = pick_config(env, R_hint, E, NTiles{d / 256, wide_mid ? d / 256 : d / 128, d / 64,
+                                                    wide_mid ? 0.82 : 0.6, 0.27, 0.38});
     if (config == 0 && f / 64 < 3) config = 1;     // the pipelined kernel needs three k-steps
     switch (config) {
         case 0:
@@ -272,17 +344,23 @@ int launch_down_as(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets
                 return launch_grouped<Out<F32, DownMid96S>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
             return launch_grouped<Out<F32, DownMid96>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
         case 3:
-            // with fewer routed rows than experts only about R experts have a tile: narrower
-            // tiles so that their weights still stream through most compute units
-            if (static_cast<long long>(R_hint < E ? R_hint : E) * (d / 128) < 192 && single_m_tile(env, R_hint, E, 32))
-                return launch_grouped<Out<F32, DownTinyNarrowS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
-            if (d % 128 == 0) {
-                if (single_m_tile(env, R_hint, E, 32))
-                    return launch_grouped<Out<F32, DownTinyS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
-                return launch_grouped<Out<F32, DownTiny>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
+            if (single_m_tile(env, R_hint, E, 32)) {
+                // 32-column tiles where 64-column ones would leave compute units without any: one
+                // token through 2 of 8 experts of 4096 x 14336 51 against 66 us
+                if (touched_experts(R_hint, E) * (d / 64) < cus && single_m_tile(env, R_hint, E, 16))
+                    return launch_grouped<Out<F32, DownFewS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
+                return launch_grouped<Out<F32, DownTinyS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
             }
-            [[fallthrough]];
+            return launch_grouped<Out<F32, DownTiny>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
         default:
+            // 128 columns where that makes two rounds of two workgroups per compute unit (500 tokens
+            // through 128 experts of 2048 x 768: 74 against 79 us), else 64 (110 tokens through 8 experts
+            // of 6144 x 16384, 384 or 768 tiles: 297 against 264 us)
+            if (touched_experts(R_hint, E) * (d / 128) >= 3.5 * cus) {
+                if (single_m_tile(env, R_hint, E, 64))
+                    return launch_grouped<Out<F32, DownSmallWideS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
+                return launch_grouped<Out<F32, DownSmallWide>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
+            }
             if (single_m_tile(env, R_hint, E, 64))
                 return launch_grouped<Out<F32, DownSmallS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
             return launch_grouped<Out<F32, DownSmall>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);

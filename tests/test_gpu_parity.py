@@ -382,6 +382,49 @@ def test_expert_ffn_configs_agree_bitwise():
     ctx.close()
 
 
+@pytest.mark.parametrize("d,f,rows", [
+    (512, 256, [1, 0, 0, 1, 0, 0, 0, 0]),            # 16-row tiles (at most 16 rows expected)
+    (512, 256, [16, 0, 17, 0, 1, 0, 0, 26]),         # the same with groups past one and past two tiles
+    (512, 14336, [4, 0, 33, 1, 2, 9, 8, 7]),         # 32-row tiles with the deep ring
+    (2048, 256, [32, 0, 1, 33, 65, 31, 2, 16] * 4),  # 32-row tiles, two workgroups per compute unit
+    (2048, 128, [43, 64, 0, 65, 1, 33, 130, 8] * 8), # 64-row tiles, 128 and 64 columns wide
+    (1024, 384, [63, 64, 65, 1, 0, 129]),            # 64-row tiles instead of a few 96-row ones
+    (512, 1024, [512]),                              # ... and instead of a few 256-row ones
+])
+@pytest.mark.parametrize("fp32_outputs", [False, True])
+def test_automatic_tile_choice_agrees_bitwise(d, f, rows, fp32_outputs):
+    """The tile that the row count picks against the 128-row configuration, which the oracle checks."""
+    say(f"automatic tiles d={d} f={f} rows={rows[:8]} x {len(rows)} fp32={fp32_outputs}")
+    E, R = len(rows), sum(rows)
+    g = torch.Generator(device="cuda").manual_seed(d + f + R)
+    rnd = lambda *shape: (torch.randn(*shape, generator=g, device="cuda") * 0.05).bfloat16()
+    W1, W3, W2 = rnd(E, f, d), rnd(E, f, d), rnd(E, d, f)
+    x = rnd(R, d)
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(rows)]), dtype=torch.int32, device="cuda")
+    ctx = B.MoeContext(R, d, f, E, 1)
+    outs = []
+    for config in (-1, 1):
+        B.moe_set_gemm_config(ctx, config)
+        if fp32_outputs:     # only the layer call keeps fp32 rows: route by the first E input columns
+            B.moe_set_expert_output_fp32(ctx, True)
+            xr = x.clone()
+            xr[:, :E] = 0
+            xr[torch.arange(R, device="cuda"), torch.repeat_interleave(
+                torch.arange(E, device="cuda"), torch.tensor(rows, device="cuda"))] = 64.0
+            wr = torch.zeros(d, E, device="cuda")
+            wr[:E] = torch.eye(E, device="cuda")
+            y = torch.full((R, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+            B.moe_layer_forward(ctx, xr, wr, None, W1, W3, W2, R, y)
+        else:
+            y = torch.full((R, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+            B.moe_expert_ffn(ctx, x, offsets, R, W1, W3, W2, y)
+        torch.cuda.synchronize()
+        outs.append(bits(y))
+    assert not np.isnan(bf16_to_f64(outs[0])).any()
+    assert np.array_equal(outs[0], outs[1])
+    ctx.close()
+
+
 @pytest.mark.parametrize("T,d,k", [(1, 512, 1), (50, 512, 2), (33, 1024, 3), (256, 4096, 2),
                                    (100, 1024, 17), (7, 512, 64)])   # up to the largest k supported
 def test_combine_parity(T, d, k):
