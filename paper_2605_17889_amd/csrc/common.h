@@ -33,12 +33,19 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
 int launch_route(const moe_bf16* x, const float* w_router, const float* bias, int T, int d, int E,
                  int k, int32_t* topk_idx, float* topk_w, float* logits_out,
                  float* logits_scratch, hipStream_t s);
+int launch_route_logits(const moe_bf16* x, const float* w_router, const float* bias, int T, int d, int E,
+                        float* logits, hipStream_t s);
 int launch_route_from_logits(const float* logits, int T, int E, int k, int32_t* topk_idx,
                              float* topk_w, hipStream_t s);
 size_t permute_scratch_ints(int R_max, int E);
 int permute_launches(int R);     // kernels that launch_permute enqueues for R ids
 int launch_permute(const int32_t* topk_idx, int R, int E, int32_t* counts, int32_t* offsets,
                    int32_t* perm, int32_t* inv_perm, int32_t* scratch, hipStream_t s);
+// Selection, gates and permutation of a few tokens (E > 16) in one workgroup, and up to how many tokens
+// that is shorter than the two launches.
+bool select_permute_fits(int T, int E, int k);
+int launch_select_permute(const float* logits, int T, int E, int k, int32_t* topk_idx, float* topk_w,
+                          int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv_perm, hipStream_t s);
 int launch_gather(const moe_bf16* x, const int32_t* perm, const int32_t* offsets, int R, int d,
                   int k, int E, moe_bf16* x_perm, hipStream_t s);
 // Where and how a context launches its expert GEMMs: its device and the tuning knobs of

@@ -111,20 +111,33 @@ void* expert_out(moe_ctx* c) {
     return c->y_perm_f32 ? static_cast<void*>(c->y_perm_f32) : static_cast<void*>(c->y_perm);
 }
 
+// Routing and permutation of a layer call into the context's tables. For a few tokens through more
+// than 16 experts the selection runs in the permutation's launch and counts as that stage.
+int route_and_permute(moe_ctx* c, const moe_bf16* x, const float* w_router, const float* bias, int T,
+                      hipStream_t s) {
+    const moe_shape& sh = c->shape;
+    const int d = sh.d_model, E = sh.E, k = sh.k, R = T * k;
+    const bool together = select_permute_fits(T, E, k);
+    const int rc = run_stage(c, MOE_STAGE_ROUTE, 1, s, [&] {
+        return together ? launch_route_logits(x, w_router, bias, T, d, E, c->logits, s)
+                        : launch_route(x, w_router, bias, T, d, E, k, c->topk_idx, c->topk_w, nullptr, c->logits, s);
+    });
+    if (rc != MOE_OK) return rc;
+    return run_stage(c, MOE_STAGE_PERMUTE, permute_launches(R), s, [&] {
+        return together ? launch_select_permute(c->logits, T, E, k, c->topk_idx, c->topk_w, c->counts,
+                                                c->offsets, c->perm, c->inv_perm, s)
+                        : launch_permute(c->topk_idx, R, E, c->counts, c->offsets, c->perm, c->inv_perm,
+                                         c->scratch, s);
+    });
+}
+
 int forward_chunk(moe_ctx* c, const moe_bf16* x, const float* w_router, const float* bias,
                   const moe_bf16* W1, const moe_bf16* W3, const moe_bf16* W2, int T, moe_bf16* y,
                   hipStream_t s) {
     const moe_shape& sh = c->shape;
     const int d = sh.d_model, f = sh.d_ff, E = sh.E, k = sh.k, R = T * k;
     int rc;
-    rc = run_stage(c, MOE_STAGE_ROUTE, 1, s, [&] {
-        return launch_route(x, w_router, bias, T, d, E, k, c->topk_idx, c->topk_w, nullptr, c->logits, s);
-    });
-    if (rc != MOE_OK) return rc;
-    rc = run_stage(c, MOE_STAGE_PERMUTE, permute_launches(R), s, [&] {
-        return launch_permute(c->topk_idx, R, E, c->counts, c->offsets, c->perm, c->inv_perm,
-                              c->scratch, s);
-    });
+    rc = route_and_permute(c, x, w_router, bias, T, s);
     if (rc != MOE_OK) return rc;
     // The row gather x -> x_perm is fused into the gate/up kernel's operand loads (it reads
     // token row perm[p] / k directly) whenever a token row's byte offset fits 32 bits.
@@ -410,14 +423,7 @@ int moe_layer_forward_streamed(moe_ctx* c, const moe_bf16* x, const float* w_rou
     // The first two transfers start at once and run under the routing and the resident experts.
     for (int j = 0; j < n_streamed && j < 2; ++j)
         if ((rc = enqueue_copy(j)) != MOE_OK) return rc;
-    rc = run_stage(c, MOE_STAGE_ROUTE, 1, s, [&] {
-        return launch_route(x, w_router, bias, T, d, E, k, c->topk_idx, c->topk_w, nullptr, c->logits, s);
-    });
-    if (rc != MOE_OK) return rc;
-    rc = run_stage(c, MOE_STAGE_PERMUTE, permute_launches(R), s, [&] {
-        return launch_permute(c->topk_idx, R, E, c->counts, c->offsets, c->perm, c->inv_perm,
-                              c->scratch, s);
-    });
+    rc = route_and_permute(c, x, w_router, bias, T, s);
     if (rc != MOE_OK) return rc;
     // experts [e0, e0 + n) with weights at w1/w3/w2; rows outside those groups are not touched
     auto ffn = [&](int e0, int n, const moe_bf16* w1, const moe_bf16* w3, const moe_bf16* w2) -> int {

@@ -13,7 +13,7 @@
 // Up to 4096 ids the three steps run in one workgroup (permute_small_kernel).
 #include <mutex>
 
-#include "common.h"
+#include "route_select.h"
 
 // Segment tables of moe_permute_static(): device memory that exists from load time, so that the
 // call allocates nothing. 2 * kStaticTableInts ints (histograms, then start positions).
@@ -237,41 +237,50 @@ __global__ __launch_bounds__(kBlockWaves* kWave) void scatter_many_kernel(
     }
 }
 
-// All three steps in one workgroup of 16 wavefronts for up to 16 segments (R <= 4096: decode
-// batches), with the per-segment tables in LDS instead of global memory: one launch, not three.
+// All three steps in one workgroup of 16 wavefronts, with the per-wavefront tables in LDS instead of
+// segment tables in global memory: one launch, not three. Wavefront w owns the KEEP * 64 consecutive
+// ids from w * KEEP * 64 on (R <= 1024 * KEEP) and holds them in registers from the count to the scatter.
 constexpr int kSmallWaves = 16;
-__global__ __launch_bounds__(kSmallWaves* kWave) void permute_small_kernel(
-    const int32_t* __restrict__ topk_idx, int R, int E, int32_t* __restrict__ counts,
-    int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm) {
-    __shared__ int32_t table[kSmallWaves][kMaxExperts];   // per segment: count, then start position
-    __shared__ int32_t tot[kMaxExperts];
-    __shared__ int32_t off[kMaxExperts + 1];
+constexpr int kMaxKeep = 4;
+struct SmallTables {
+    int32_t table[kSmallWaves][kMaxExperts];              // per wavefront: count, then start position
+    int32_t tot[kMaxExperts];
+    int32_t off[kMaxExperts + 1];
+};
+template <int KEEP>
+__device__ __forceinline__ void permute_block(SmallTables& sm, const int32_t* ids, int R, int E,
+                                              int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
+                                              int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm) {
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wv = tid / kWave;
-    const int64_t base = static_cast<int64_t>(wv) * kSegIds;
-    volatile int32_t* mine = table[wv];       // read and written across lanes: never cached
-    int my[kRounds];
-    uint64_t same[kRounds];
+    const int base = wv * KEEP * kWave;
+    const int waves = min(kSmallWaves, (R + KEEP * kWave - 1) / (KEEP * kWave));   // that own any id
+    volatile int32_t* mine = sm.table[wv];    // read and written across lanes: never cached
+    int my[KEEP];
+    uint64_t same[KEEP];
+#pragma unroll
+    for (int r = 0; r < KEEP; ++r) {
+        const int i = base + r * kWave + lane;
+        my[r] = (i < R) ? ids[i] : -1;
+    }
     for (int e = lane; e < E; e += kWave) mine[e] = 0;
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-        const int64_t i = base + r * kWave + lane;
-        my[r] = (i < R) ? topk_idx[i] : -1;
+    for (int r = 0; r < KEEP; ++r) {
         if (my[r] < 0 || my[r] >= E) my[r] = -1;
         same[r] = same_value_lanes(my[r]);
         if (my[r] >= 0 && (same[r] & lanemask_lt(lane)) == 0) mine[my[r]] += __popcll(same[r]);
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    if (tid < E) {                            // segments of one expert, in order
+    if (tid < E) {                            // wavefronts' counts of one expert, in order
         int run = 0;
-        for (int g = 0; g < kSmallWaves; ++g) {
-            const int v = table[g][tid];
-            table[g][tid] = run;
+        for (int g = 0; g < waves; ++g) {
+            const int v = sm.table[g][tid];
+            sm.table[g][tid] = run;
             run += v;
         }
-        tot[tid] = run;
+        sm.tot[tid] = run;
     }
     __syncthreads();
     if (tid < kWave) {                        // exclusive prefix over the experts, 4 per lane
@@ -279,7 +288,7 @@ __global__ __launch_bounds__(kSmallWaves* kWave) void permute_small_kernel(
 #pragma unroll
         for (int w = 0; w < kExpertWords; ++w) {
             const int x = tid * kExpertWords + w;
-            part[w] = x < E ? tot[x] : 0;
+            part[w] = x < E ? sm.tot[x] : 0;
             sum += part[w];
         }
         int incl = sum;
@@ -291,21 +300,22 @@ __global__ __launch_bounds__(kSmallWaves* kWave) void permute_small_kernel(
 #pragma unroll
         for (int w = 0; w < kExpertWords; ++w) {
             const int x = tid * kExpertWords + w;
-            if (x < E) off[x] = run;
+            if (x < E) sm.off[x] = run;
             run += part[w];
         }
-        if (tid == kWave - 1) off[E] = incl;
+        if (tid == kWave - 1) sm.off[E] = incl;
     }
     __syncthreads();
     if (tid < E) {
-        counts[tid] = tot[tid];
-        offsets[tid] = off[tid];
+        counts[tid] = sm.tot[tid];
+        offsets[tid] = sm.off[tid];
     }
-    if (tid == 0) offsets[E] = off[E];
-    for (int e = lane; e < E; e += kWave) mine[e] += off[e];   // start positions of this segment
+    if (tid == 0) offsets[E] = sm.off[E];
+    if (wv >= waves) return;
+    for (int e = lane; e < E; e += kWave) mine[e] += sm.off[e];   // start positions of this wavefront's ids
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-        const int64_t i = base + r * kWave + lane;
+    for (int r = 0; r < KEEP; ++r) {
+        const int i = base + r * kWave + lane;
         int pos = -1;
         if (my[r] >= 0) pos = mine[my[r]] + __popcll(same[r] & lanemask_lt(lane));
         __builtin_amdgcn_wave_barrier();      // every lane of a set has read before its first lane writes
@@ -313,9 +323,38 @@ __global__ __launch_bounds__(kSmallWaves* kWave) void permute_small_kernel(
         __builtin_amdgcn_wave_barrier();
         if (i < R) {
             inv_perm[i] = pos;
-            if (pos >= 0) perm[pos] = static_cast<int32_t>(i);
+            if (pos >= 0) perm[pos] = i;
         }
     }
+}
+
+template <int KEEP>
+__global__ __launch_bounds__(kSmallWaves* kWave) void permute_small_kernel(
+    const int32_t* __restrict__ topk_idx, int R, int E, int32_t* __restrict__ counts,
+    int32_t* __restrict__ offsets, int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm) {
+    __shared__ SmallTables sm;
+    permute_block<KEEP>(sm, topk_idx, R, E, counts, offsets, perm, inv_perm);
+}
+
+// Selection and gates from the logits, then the permutation, for R = T * k <= 1024 ids: the ids go
+// from the one to the other through LDS, and a launch with the two latencies around it is saved.
+template <int EW>
+__global__ __launch_bounds__(kSmallWaves* kWave) void select_permute_kernel(
+    const float* __restrict__ logits, int T, int E, int k, int32_t* __restrict__ topk_idx,
+    float* __restrict__ topk_w, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
+    int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm) {
+    __shared__ SmallTables sm;
+    __shared__ int32_t ids[kSmallWaves * kWave];
+    for (int t0 = 0; t0 < T; t0 += kSmallWaves * kWave / 16) {
+        const int t = t0 + threadIdx.x / 16;
+        select_by_16_lanes<EW>(logits, t, t < T, threadIdx.x & 15, E, k, [&](int s, int e, float w) {
+            topk_idx[t * k + s] = e;
+            topk_w[t * k + s] = w;
+            ids[t * k + s] = e;
+        });
+    }
+    __syncthreads();
+    permute_block<1>(sm, ids, T * k, E, counts, offsets, perm, inv_perm);
 }
 
 // One block per permuted row: x_perm[p,:] = x[perm[p] / k, :], 16 bytes per lane per step.
@@ -342,14 +381,23 @@ size_t permute_scratch_ints(int R_max, int E) {
     return 2 * nseg * static_cast<size_t>(E);           // seg_hist + seg_base
 }
 
-int permute_launches(int R) { return (R + kSegIds - 1) / kSegIds <= kSmallWaves ? 1 : 3; }
+// R up to which one workgroup does the whole permutation: 4096 ids of 8 experts take it 6.1 us where three
+// launches take about 12, but 8000 ids of 128 experts 15.2 us (16 ids per lane) against 11.7.
+constexpr int kSmallIds = kSmallWaves * kWave * kMaxKeep;
+
+int permute_launches(int R) { return R <= kSmallIds ? 1 : 3; }
 
 int launch_permute(const int32_t* topk_idx, int R, int E, int32_t* counts, int32_t* offsets,
                    int32_t* perm, int32_t* inv_perm, int32_t* seg_tables, hipStream_t s) {
     const int nseg = (R + kSegIds - 1) / kSegIds;
-    if (nseg <= kSmallWaves) {
-        hipLaunchKernelGGL(permute_small_kernel, dim3(1), dim3(kSmallWaves * kWave), 0, s, topk_idx,
-                           R, E, counts, offsets, perm, inv_perm);
+    if (R <= kSmallIds) {
+        const dim3 block(kSmallWaves * kWave);
+        if (R <= kSmallWaves * kWave)
+            hipLaunchKernelGGL(permute_small_kernel<1>, dim3(1), block, 0, s, topk_idx, R, E, counts,
+                               offsets, perm, inv_perm);
+        else
+            hipLaunchKernelGGL(permute_small_kernel<kMaxKeep>, dim3(1), block, 0, s, topk_idx, R, E, counts,
+                               offsets, perm, inv_perm);
         return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
     }
     int32_t* seg_hist = seg_tables;
@@ -364,6 +412,25 @@ int launch_permute(const int32_t* topk_idx, int R, int E, int32_t* counts, int32
     if (nseg > 0)
         hipLaunchKernelGGL(many ? scatter_many_kernel : scatter_kernel, dim3(blocks),
                            dim3(kBlockWaves * kWave), 0, s, topk_idx, R, E, seg_base, perm, inv_perm);
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+}
+
+// More tokens than one pass of the workgroup selects (64) would lengthen the kernel by as much as the
+// launch that it saves.
+bool select_permute_fits(int T, int E, int k) {
+    return E > 16 && T <= 64 && T * k <= kSmallWaves * kWave;
+}
+
+int launch_select_permute(const float* logits, int T, int E, int k, int32_t* topk_idx, float* topk_w,
+                          int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv_perm, hipStream_t s) {
+#define MOE_SELP(EW)                                                                                   \
+    hipLaunchKernelGGL(select_permute_kernel<EW>, dim3(1), dim3(kSmallWaves* kWave), 0, s, logits, T, E, \
+                       k, topk_idx, topk_w, counts, offsets, perm, inv_perm)
+    if (E <= 32) MOE_SELP(2);
+    else if (E <= 64) MOE_SELP(4);
+    else if (E <= 128) MOE_SELP(8);
+    else MOE_SELP(16);
+#undef MOE_SELP
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 

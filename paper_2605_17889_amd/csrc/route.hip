@@ -15,7 +15,7 @@
 #include <atomic>
 #include <type_traits>
 
-#include "common.h"
+#include "route_select.h"
 
 namespace moe {
 namespace {
@@ -161,76 +161,17 @@ __global__ __launch_bounds__(256) void route_kernel(const uint16_t* __restrict__
     }
 }
 
-// Selection and gates for more than 16 experts: 16 lanes per token (four tokens per wavefront),
-// lane g of a token's group holds the logits of experts g, g+16, g+32, ... (EW of them). Each of
-// the k rounds takes the largest remaining logit of the group (ties -> lower expert index, NaN
-// below every number): first inside the lane, ascending, then by four exchange steps of
-// (value, index) pairs over the 16 lanes; "larger value, then lower index" is a total order, so
-// the result does not depend on how the lanes are paired. The gates are the softmax over the selected logits,
-// accumulated in slot order like select_and_gate().
+// Selection and gates for more than 16 experts: 16 lanes per token (four tokens per wavefront).
 template <int EW>
 __global__ __launch_bounds__(256) void route_select_kernel(const float* __restrict__ logits, int T,
                                                            int E, int k,
                                                            int32_t* __restrict__ topk_idx,
                                                            float* __restrict__ topk_w) {
-    constexpr int G = 16;
-    const int g = threadIdx.x & (G - 1);
-    const int t = (blockIdx.x * blockDim.x + threadIdx.x) / G;
-    const bool live = t < T;                              // whole groups; shuffles stay in a group
-    float v[EW];
-#pragma unroll
-    for (int w = 0; w < EW; ++w) {
-        const int e = w * G + g;
-        const float l = (live && e < E) ? logits[static_cast<size_t>(t) * E + e] : -INFINITY;
-        v[w] = (l != l) ? -INFINITY : l;
-    }
-    unsigned taken = 0;                                   // bit w: expert w*16+g is selected
-    float top = 0.f, den = 0.f;
-    float my_w[4] = {0.f, 0.f, 0.f, 0.f};                 // lane g keeps slots g, g+16, g+32, g+48
-    int my_idx[4] = {0, 0, 0, 0};
-    for (int s = 0; s < k; ++s) {
-        // best of this lane: ascending expert index, strict '>' keeps the lower index on ties
-        float bv = 0.f;
-        int be = -1;
-#pragma unroll
-        for (int w = 0; w < EW; ++w) {
-            const int e = w * G + g;
-            if (e < E && !((taken >> w) & 1u) && (be < 0 || v[w] > bv)) { bv = v[w]; be = e; }
-        }
-        // best of the group: larger value, then lower index; lanes without a candidate lose
-        // (data-parallel-primitive moves inside a row of 16 lanes: rotate by 8, by 4, then swap
-        // inside quads at distance 2 and 1; after the four steps every lane has seen all 16)
-        auto take = [&](float ov, int oe) {
-            const bool other = oe >= 0 && (be < 0 || ov > bv || (ov == bv && oe < be));
-            if (other) { bv = ov; be = oe; }
-        };
-#define MOE_DPP_STEP(CTRL)                                                                        \
-        take(__int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(bv), CTRL, 0xf, 0xf, false)), \
-             __builtin_amdgcn_update_dpp(0, be, CTRL, 0xf, 0xf, false))
-        MOE_DPP_STEP(0x128);      // row_ror:8
-        MOE_DPP_STEP(0x124);      // row_ror:4
-        MOE_DPP_STEP(0x4e);       // quad_perm:[2,3,0,1]
-        MOE_DPP_STEP(0xb1);       // quad_perm:[1,0,3,2]
-#undef MOE_DPP_STEP
-        if ((be & (G - 1)) == g) taken |= 1u << (be >> 4);    // be >= 0 because k <= E
-        if (s == 0) top = bv;
-        const float w = expf(bv - top);
-        den += w;
-        if ((s & (G - 1)) == g) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if ((s >> 4) == j) { my_w[j] = w; my_idx[j] = be; }
-        }
-    }
-    if (!live) return;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int s = j * G + g;
-        if (s < k) {
-            topk_idx[static_cast<size_t>(t) * k + s] = my_idx[j];
-            topk_w[static_cast<size_t>(t) * k + s] = my_w[j] / den;
-        }
-    }
+    const int t = (blockIdx.x * blockDim.x + threadIdx.x) / 16;
+    select_by_16_lanes<EW>(logits, t, t < T, threadIdx.x & 15, E, k, [&](int s, int e, float w) {
+        topk_idx[static_cast<size_t>(t) * k + s] = e;
+        topk_w[static_cast<size_t>(t) * k + s] = w;
+    });
 }
 
 // Fast path for E in {8, 16}: the same arithmetic, but the 512 x E slice of W_r that a chunk
@@ -704,6 +645,155 @@ __global__ __launch_bounds__(256) void route_logits_mfma_kernel(const uint16_t* 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load may still target LDS at the end
 }
 
+// Logits of a few tokens: decode, and batches that leave most compute units without a tile of the
+// kernels above. What counts there is the chain of latencies of one workgroup, not throughput. A
+// workgroup takes TOK tokens and EG experts; its four wavefronts split the EXPERTS (EG / 4 each), so
+// that a chunk of 512 elements is a few multiply-adds, and the whole of a token row and of the
+// W_r slice (d up to 2048 with 16 experts, 3584 with 8; a ring of that depth beyond) is on its way to
+// LDS before the first chunk is used: one memory latency in all instead of one per chunk. Every
+// (token, expert) accumulator sees the canonical order. With SELECT (EG == E) the workgroup also
+// selects and stores the gates; otherwise only the logits are stored.
+// Replayed back to back, before -> after: one token, E = 128, d = 2048, selection included 15.8 -> 10.3 us;
+// 16 tokens, E = 8, d = 4096 10.7 -> 7.5 us; 256 tokens at d = 6144 14.3 -> 9.6 us.
+//
+// LDS: a chunk is 64 slices of 8 rows x EG experts (lane l's share, 32 EG bytes) in 16-byte pieces; piece
+// p of slice l sits at position p ^ (l & 15), so that the same piece of 16 consecutive lanes is spread
+// over all banks. The direct-to-LDS loads permute their source addresses accordingly.
+template <int EG, int TOK>
+struct RouteFew {
+    static constexpr int W_BYTES = 512 * EG * 4, X_BYTES = 4096;      // x: one row of 512 per wavefront
+    static constexpr int STAGE = W_BYTES + X_BYTES;
+    static constexpr int NSTAGE = EG == 8 ? 7 : 4;
+    static constexpr int LOADS = EG / 2 + 1;                          // per wavefront and chunk
+    static constexpr int SMEM = NSTAGE * STAGE + TOK * EG * 4;
+    static_assert(SMEM <= 160 * 1024 && (NSTAGE - 1) * LOADS < 64, "LDS and load counter");
+    static_assert(TOK == 1 || TOK == 4, "x rows: one per wavefront, or the same for all");
+};
+
+// Waits until at most `chunks` chunks of N loads each are still on their way (chunks <= MAX).
+template <int N, int MAX>
+__device__ __forceinline__ void wait_chunks(int chunks) {
+    if constexpr (MAX > 0) {
+        if (chunks < MAX) return wait_chunks<N, MAX - 1>(chunks);
+    }
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N * MAX) : "memory");
+}
+
+template <int EG, int TOK, bool SELECT>
+__global__ __launch_bounds__(256) void route_few_kernel(const uint16_t* __restrict__ x,
+                                                        const float* __restrict__ wr,
+                                                        const float* __restrict__ bias, int T, int d,
+                                                        int E, int k, int32_t* __restrict__ topk_idx,
+                                                        float* __restrict__ topk_w,
+                                                        float* __restrict__ logits_out) {
+    using R = RouteFew<EG, TOK>;
+    constexpr int NE = EG / 4;                          // experts per wavefront
+    constexpr int SLICE = 32 * EG;                      // bytes of a lane's 8 x EG weights
+    constexpr int WL = EG / 2;                          // W_r loads per wavefront and chunk
+    extern __shared__ __attribute__((aligned(1024))) unsigned char rsm[];
+    float* all_logits = reinterpret_cast<float*>(rsm + R::NSTAGE * R::STAGE);     // [TOK][EG]
+
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int t0 = blockIdx.x * TOK, e0 = blockIdx.y * EG;
+    const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(rsm));
+
+    uint32_t w_voff[WL];
+#pragma unroll
+    for (int i = 0; i < WL; ++i) {
+        const int at = (wave * WL + i) * 1024 + lane * 16;            // byte inside the stage's W_r part
+        const int s = at / SLICE, p = ((at % SLICE) / 16) ^ (s & 15);
+        w_voff[i] = (static_cast<uint32_t>(8 * s + p / NE) * E + 4 * (p % NE)) * 4u;
+    }
+    // tokens past the end read the last one; never stored
+    const uint16_t* x_row = x + static_cast<size_t>(min(t0 + (TOK == 1 ? 0 : wave), T - 1)) * d;
+    auto issue = [&](int j, int st) {
+        const uint32_t sb = lds0 + st * R::STAGE;
+        const float* w_base = wr + static_cast<size_t>(512 * j) * E + e0;
+#pragma unroll
+        for (int i = 0; i < WL; ++i) dma16_to_lds(w_base, w_voff[i], sb + (wave * WL + i) * 1024);
+        dma16_to_lds(x_row + 512 * j, lane * 16u, sb + R::W_BYTES + wave * 1024);
+    };
+
+    const int chunks = d / 512;
+    for (int j = 0; j < R::NSTAGE && j < chunks; ++j) issue(j, j);
+
+    float acc[TOK * NE];                                // [token][expert of the wavefront]
+#pragma unroll
+    for (int n = 0; n < TOK * NE; ++n) acc[n] = 0.f;
+    int st = 0;
+    for (int j = 0; j < chunks; ++j) {
+        wait_chunks<R::LOADS, R::NSTAGE - 1>(min(chunks - 1 - j, R::NSTAGE - 1));   // chunk j has landed
+        __builtin_amdgcn_s_barrier();                                               // ... for everyone
+        asm volatile("" ::: "memory");
+        const unsigned char* sb = rsm + st * R::STAGE;
+        u32x4 xv[TOK];
+#pragma unroll
+        for (int q = 0; q < TOK; ++q)
+            xv[q] = *reinterpret_cast<const u32x4*>(sb + R::W_BYTES + (TOK == 1 ? wave : q) * 1024 + lane * 16);
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            // this wavefront's NE weights of row v: a 16-byte piece, or half of one
+            const int first = wave * NE;
+            const int piece = (v * NE + first / 4) ^ (lane & 15);
+            const unsigned char* wp = sb + lane * SLICE + piece * 16 + (first % 4) * 4;
+            float w[NE];
+#pragma unroll
+            for (int e = 0; e < NE; ++e) w[e] = reinterpret_cast<const float*>(wp)[e];
+#pragma unroll
+            for (int q = 0; q < TOK; ++q) {
+                const uint32_t word = xv[q][v >> 1];
+                const float xf = __uint_as_float((v & 1) ? (word & 0xffff0000u) : (word << 16));
+#pragma unroll
+                for (int e = 0; e < NE; ++e) acc[q * NE + e] = fmaf(xf, w[e], acc[q * NE + e]);
+            }
+        }
+        if (j + R::NSTAGE < chunks) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();               // everyone has read the stage
+            issue(j + R::NSTAGE, st);
+        }
+        st = st + 1 == R::NSTAGE ? 0 : st + 1;
+    }
+
+    halving_reduce<TOK * NE>(acc, lane);
+    constexpr int SPREAD = kWave / (TOK * NE);          // lanes that end with the same sum
+    const int n = lane / SPREAD, q = n / NE, el = wave * NE + n % NE, t = t0 + q;
+    if (lane % SPREAD == 0) {
+        const float l = bias != nullptr ? acc[0] + bias[e0 + el] : acc[0];
+        if (SELECT) all_logits[q * EG + el] = l;
+        if (t < T && logits_out != nullptr) logits_out[static_cast<size_t>(t) * E + e0 + el] = l;
+    }
+    if constexpr (SELECT) {
+        __syncthreads();
+        if (threadIdx.x < TOK && t0 + static_cast<int>(threadIdx.x) < T) {
+            float l[EG];
+#pragma unroll
+            for (int e = 0; e < EG; ++e) l[e] = all_logits[threadIdx.x * EG + e];
+            const size_t at = static_cast<size_t>(t0 + threadIdx.x) * k;
+            select_and_gate<EG>(l, E, k, topk_idx + at, topk_w + at);
+        }
+    }
+}
+
+template <int EG, int TOK, bool SELECT>
+int launch_route_few(const moe_bf16* x, const float* wr, const float* bias, int T, int d, int E, int k,
+                     int32_t* idx, float* w, float* logits_out, hipStream_t s) {
+    int device = 0;
+    if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= 64) return MOE_ERR_HIP;
+    static std::atomic<uint64_t> attr_set{0};           // one bit per device, as for the GEMM kernels
+    if (!(attr_set.load(std::memory_order_acquire) & (1ull << device))) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(route_few_kernel<EG, TOK, SELECT>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize,
+                                RouteFew<EG, TOK>::SMEM) != hipSuccess)
+            return MOE_ERR_HIP;
+        attr_set.fetch_or(1ull << device, std::memory_order_release);
+    }
+    hipLaunchKernelGGL((route_few_kernel<EG, TOK, SELECT>), dim3((T + TOK - 1) / TOK, E / EG), dim3(256),
+                       (RouteFew<EG, TOK>::SMEM), s, x, wr, bias, T, d, E, k, idx, w, logits_out);
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+}
+
 template <int E_, int TOK, int WAVES>
 int launch_route_lds(const moe_bf16* x, const float* wr, const float* bias, int T, int d, int k,
                      int32_t* idx, float* w, float* logits_out, hipStream_t s) {
@@ -752,6 +842,9 @@ int launch_select_groups(const float* logits, int T, int E, int k, int32_t* idx,
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
+// Workgroups of the few-token kernel at most: one per compute unit (its LDS allows no second).
+constexpr int kFewBlocks = 256;
+
 }  // namespace
 
 // `logits_scratch` [T, E] fp32 is only used for more than 16 experts, and only if the caller
@@ -761,54 +854,73 @@ int launch_route(const moe_bf16* x, const float* w_router, const float* bias, in
                  float* logits_scratch, hipStream_t s) {
     if (T == 0) return MOE_OK;
     if (E > 16) {
-        // logits by expert groups of 16 with W_r staged in LDS, then the selection
         float* logits = logits_out ? logits_out : logits_scratch;
         if (!logits) return MOE_ERR_INVALID_ARG;
-        constexpr int TOK = 4;
-        const dim3 grid((T + 4 * TOK - 1) / (4 * TOK), (E + 15) / 16);
-        // Full groups and at least 128 tiles of 64 tokens x 16 experts: the matrix-core form. One
-        // tile takes it about as long as 130 k (token, expert) pairs take the vector-unit
-        // kernel, whatever the number of tiles up to one per compute unit (measured crossover).
-        if (E % 16 == 0 && static_cast<long long>((T + 63) / 64) * (E / 16) >= 128) {
-            int device = 0;
-            if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= 64) return MOE_ERR_HIP;
-            static std::atomic<uint64_t> attr_set{0};     // one bit per device, as for the GEMM kernels
-            if (!(attr_set.load(std::memory_order_acquire) & (1ull << device))) {
-                if (hipFuncSetAttribute(reinterpret_cast<const void*>(route_logits_mfma_kernel),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize,
-                                        RouteMfma::SMEM) != hipSuccess)
-                    return MOE_ERR_HIP;
-                attr_set.fetch_or(1ull << device, std::memory_order_release);
-            }
-            // one workgroup per compute unit (LDS and registers allow no more), each working
-            // through its share of the tiles with the operand ring running across tile borders
-            const long long tiles = static_cast<long long>(((T + 63) / 64 + kXcds - 1) / kXcds) * kXcds * (E / 16);
-            static std::atomic<int> cus_of[64];           // compute units per device, asked once
-            int cus = cus_of[device].load(std::memory_order_relaxed);
-            if (cus == 0) {
-                if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
-                    cus <= 0)
-                    return MOE_ERR_HIP;
-                cus_of[device].store(cus, std::memory_order_relaxed);
-            }
-            const long long grid = std::min<long long>(tiles, std::max(kXcds, cus / kXcds * kXcds));
-            hipLaunchKernelGGL(route_logits_mfma_kernel, dim3(static_cast<unsigned>(grid)),
-                               dim3(256), RouteMfma::SMEM, s, x, w_router, bias, T, d, E, logits);
-        }
-        else if (E % 16 == 0)     // every group full and 16-byte aligned: vector loads of W_r
-            hipLaunchKernelGGL((route_logits_group_kernel<TOK, true>), grid, dim3(256), 0, s, x,
-                               w_router, bias, T, d, E, logits);
-        else
-            hipLaunchKernelGGL((route_logits_group_kernel<TOK, false>), grid, dim3(256), 0, s, x,
-                               w_router, bias, T, d, E, logits);
-        if (hipGetLastError() != hipSuccess) return MOE_ERR_HIP;
-        return launch_route_from_logits(logits, T, E, k, topk_idx, topk_w, s);
+        const int rc = launch_route_logits(x, w_router, bias, T, d, E, logits, s);
+        return rc != MOE_OK ? rc : launch_route_from_logits(logits, T, E, k, topk_idx, topk_w, s);
     }
+    // One round of few-token workgroups: 1024 tokens of 4096 take 8.1 us against 11.4 with the kernels
+    // below, 2048 tokens (two rounds) 14.3 against 11.8.
+    const int few = (T + 3) / 4;
+    if (E == 8 && few <= kFewBlocks)
+        return launch_route_few<8, 4, true>(x, w_router, bias, T, d, E, k, topk_idx, topk_w, logits_out, s);
+    if (E == 16 && few <= kFewBlocks)
+        return launch_route_few<16, 4, true>(x, w_router, bias, T, d, E, k, topk_idx, topk_w, logits_out, s);
     // 8 wavefronts share one staged slice of W_r: half the staging work per token of 4-wave blocks
     if (E == 8) return launch_route_lds<8, 2, 8>(x, w_router, bias, T, d, k, topk_idx, topk_w, logits_out, s);
     if (E == 16) return launch_route_lds<16, 2, 8>(x, w_router, bias, T, d, k, topk_idx, topk_w, logits_out, s);
     if (E <= 8) return launch_route_t<8, 4>(x, w_router, bias, T, d, E, k, topk_idx, topk_w, logits_out, s);
     return launch_route_t<16, 2>(x, w_router, bias, T, d, E, k, topk_idx, topk_w, logits_out, s);
+}
+
+// Router logits [T, E] for more than 16 experts, by groups of 16 experts.
+int launch_route_logits(const moe_bf16* x, const float* w_router, const float* bias, int T, int d, int E,
+                        float* logits, hipStream_t s) {
+    if (T == 0) return MOE_OK;
+    constexpr int TOK = 4;
+    const dim3 grid((T + 4 * TOK - 1) / (4 * TOK), (E + 15) / 16);
+    // one round of few-token workgroups, a token each while that fits (37 tokens through 128 experts in
+    // two rounds of one token 14.2 us, in one of four 12.0; 100 in one 12.9, 192 in two 17.1 against 16.4)
+    if (E % 16 == 0 && static_cast<long long>(T) * (E / 16) <= kFewBlocks)
+        return launch_route_few<16, 1, false>(x, w_router, bias, T, d, E, 0, nullptr, nullptr, logits, s);
+    if (E % 16 == 0 && static_cast<long long>((T + 3) / 4) * (E / 16) <= kFewBlocks)
+        return launch_route_few<16, 4, false>(x, w_router, bias, T, d, E, 0, nullptr, nullptr, logits, s);
+    // Full groups and at least 128 tiles of 64 tokens x 16 experts: the matrix-core form. One
+    // tile takes it about as long as 130 k (token, expert) pairs take the vector-unit
+    // kernel, whatever the number of tiles up to one per compute unit (measured crossover).
+    if (E % 16 == 0 && static_cast<long long>((T + 63) / 64) * (E / 16) >= 128) {
+        int device = 0;
+        if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= 64) return MOE_ERR_HIP;
+        static std::atomic<uint64_t> attr_set{0};     // one bit per device, as for the GEMM kernels
+        if (!(attr_set.load(std::memory_order_acquire) & (1ull << device))) {
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(route_logits_mfma_kernel),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    RouteMfma::SMEM) != hipSuccess)
+                return MOE_ERR_HIP;
+            attr_set.fetch_or(1ull << device, std::memory_order_release);
+        }
+        // one workgroup per compute unit (LDS and registers allow no more), each working
+        // through its share of the tiles with the operand ring running across tile borders
+        const long long tiles = static_cast<long long>(((T + 63) / 64 + kXcds - 1) / kXcds) * kXcds * (E / 16);
+        static std::atomic<int> cus_of[64];           // compute units per device, asked once
+        int cus = cus_of[device].load(std::memory_order_relaxed);
+        if (cus == 0) {
+            if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
+                cus <= 0)
+                return MOE_ERR_HIP;
+            cus_of[device].store(cus, std::memory_order_relaxed);
+        }
+        const long long grid = std::min<long long>(tiles, std::max(kXcds, cus / kXcds * kXcds));
+        hipLaunchKernelGGL(route_logits_mfma_kernel, dim3(static_cast<unsigned>(grid)),
+                           dim3(256), RouteMfma::SMEM, s, x, w_router, bias, T, d, E, logits);
+    } else if (E % 16 == 0) { // every group full and 16-byte aligned: vector loads of W_r
+        hipLaunchKernelGGL((route_logits_group_kernel<TOK, true>), grid, dim3(256), 0, s, x,
+                           w_router, bias, T, d, E, logits);
+    } else {
+        hipLaunchKernelGGL((route_logits_group_kernel<TOK, false>), grid, dim3(256), 0, s, x,
+                           w_router, bias, T, d, E, logits);
+    }
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
 int launch_route_from_logits(const float* logits, int T, int E, int k, int32_t* topk_idx,

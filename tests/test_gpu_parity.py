@@ -105,6 +105,44 @@ def test_route_bit_exact(T, d, E, k, use_bias):
     ctx.close()
 
 
+@pytest.mark.parametrize("T,d,E,k", [
+    # few-token kernel: 1 or 4 tokens per workgroup, reductions up to and past its ring (4 chunks of 512
+    # with 16 experts per workgroup, 7 with 8), the last token count that it takes and the first that it does not
+    (1, 512, 8, 2), (5, 3584, 8, 1), (3, 4096, 8, 8), (1024, 512, 8, 2), (1025, 512, 8, 2), (6, 7680, 8, 3),
+    (1, 2048, 16, 2), (7, 2560, 16, 16), (1024, 512, 16, 1),
+    (1, 2048, 128, 8), (32, 512, 128, 8), (33, 2560, 128, 8), (128, 1024, 128, 2), (129, 512, 128, 8),
+    (1, 4608, 256, 64), (16, 512, 256, 8), (17, 512, 256, 3), (85, 2048, 48, 5),
+])
+def test_route_few_tokens_bit_exact(T, d, E, k):
+    test_route_bit_exact(T, d, E, k, T % 2 == 1)
+
+
+@pytest.mark.parametrize("E", [17, 64, 100, 256])
+@pytest.mark.parametrize("T,k", [(1, 17), (16, 17), (63, 2), (64, 16), (65, 16), (61, 17)])
+def test_layer_selects_and_permutes_few_tokens_like_the_stage_calls(T, k, E):
+    """Up to 64 tokens and 1024 ids the layer call selects and permutes in one launch."""
+    say(f"select + permute T={T} k={k} E={E}")
+    d, f = 512, 128
+    g = torch.Generator(device="cuda").manual_seed(T * 1000 + E)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    x, wr, bias = rnd(T, d).bfloat16(), rnd(d, E) * 0.02, rnd(E) * 0.3
+    W1, W3, W2 = ((rnd(*s) * 0.05).bfloat16() for s in ((E, f, d), (E, f, d), (E, d, f)))
+    ctx = B.MoeContext(T, d, f, E, k)
+    y = torch.empty((T, d), dtype=torch.bfloat16, device="cuda")
+    B.moe_layer_forward(ctx, x, wr, bias, W1, W3, W2, T, y)
+    got = fetch_routing(ctx, T)
+    i32 = lambda *s: torch.empty(s, dtype=torch.int32, device="cuda")
+    idx, w = i32(T, k), torch.empty((T, k), dtype=torch.float32, device="cuda")
+    counts, offsets, perm, inv = i32(E), i32(E + 1), i32(T * k), i32(T * k)
+    B.moe_route(ctx, x, wr, bias, T, idx, w)
+    B.moe_permute(ctx, idx, T, counts, offsets, perm, inv)
+    torch.cuda.synchronize()
+    want = {"topk_idx": idx, "topk_w": w, "counts": counts, "offsets": offsets, "perm": perm, "inv_perm": inv}
+    for name, t in want.items():
+        assert np.array_equal(np.asarray(got[name]).reshape(-1), t.cpu().numpy().reshape(-1)), name
+    ctx.close()
+
+
 def test_route_matrix_core_logits_extreme_values():
     """The matrix-core logits kernel (E a multiple of 16, many tokens) must round every
     multiply-add like fmaf, denormal products and sums, signed zeros and wide exponent ranges
