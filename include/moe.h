@@ -180,7 +180,7 @@ int moe_layer_forward_microbatched(moe_ctx* ctx, const moe_bf16* x, const float*
  * to page-locked memory (hipHostMalloc or an equivalent allocator; pageable memory makes the
  * copies synchronous), which must stay unchanged until the work enqueued by the call has finished.
  * The first call allocates two device staging slots of 3*d_model*d_ff*2 bytes each, a copy
- * stream and four events, kept until moe_destroy (MOE_ERR_WORKSPACE if the allocation fails).
+ * stream and six events, kept until moe_destroy (MOE_ERR_WORKSPACE if the allocation fails).
  * Transfers run on the library's copy stream; all kernels run on `stream`, resident experts
  * first, then each streamed expert as its weights arrive. The output equals moe_layer_forward's
  * bit for bit (same kernels, same accumulation chains). 0 <= n_streamed <= E. Calls on one

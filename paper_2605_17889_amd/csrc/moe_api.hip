@@ -34,9 +34,11 @@ struct moe_ctx {
     // streamed experts (created by the first moe_layer_forward_streamed call, kept until destroy)
     hipStream_t copy_stream;
     unsigned char* slot[2];     // device staging, each W1_e | W3_e | W2_e of one expert
-    hipEvent_t ready[2];        // recorded on copy_stream: the slot holds its expert
+    hipEvent_t ready_up[2];     // recorded on copy_stream: the slot holds W1 and W3 of its expert
+    hipEvent_t ready[2];        // ... and W2
     hipEvent_t freed[2];        // recorded on the caller's stream: the slot's GEMMs are enqueued
     bool freed_valid[2];
+    int next_slot;              // slot of the next call's first streamed expert
 };
 
 namespace {
@@ -169,14 +171,14 @@ int ensure_streaming(moe_ctx* c) {
     const size_t bytes = static_cast<size_t>(3) * c->shape.d_model * c->shape.d_ff * sizeof(moe_bf16);
     void* p = nullptr;
     hipStream_t st = nullptr;
-    hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
+    hipEvent_t ev[6] = {};
     int made = 0;
     int rc = MOE_OK;
     if (hipMalloc(&p, 2 * bytes) != hipSuccess) {
         (void)hipGetLastError();
         return MOE_ERR_WORKSPACE;
     }
-    for (; made < 4; ++made)
+    for (; made < 6; ++made)
         if (hipEventCreateWithFlags(&ev[made], hipEventDisableTiming) != hipSuccess) { rc = MOE_ERR_HIP; break; }
     if (rc == MOE_OK && hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess)   // default priority
         rc = MOE_ERR_HIP;
@@ -191,6 +193,7 @@ int ensure_streaming(moe_ctx* c) {
     for (int i = 0; i < 2; ++i) {
         c->ready[i] = ev[i];
         c->freed[i] = ev[2 + i];
+        c->ready_up[i] = ev[4 + i];
         c->freed_valid[i] = false;
     }
     c->copy_stream = st;
@@ -264,6 +267,7 @@ int moe_create(moe_ctx** out, const moe_shape* shape, int device_id) {
     for (auto& v : c->prof_launches) v = 0;
     c->copy_stream = nullptr;
     c->slot[0] = c->slot[1] = nullptr;
+    c->next_slot = 0;
     *out = c;
     return MOE_OK;
 }
@@ -276,6 +280,7 @@ int moe_destroy(moe_ctx* c) {
         if (hipStreamSynchronize(c->copy_stream) != hipSuccess) rc = MOE_ERR_HIP;
         (void)hipStreamDestroy(c->copy_stream);
         for (int i = 0; i < 2; ++i) {
+            (void)hipEventDestroy(c->ready_up[i]);
             (void)hipEventDestroy(c->ready[i]);
             (void)hipEventDestroy(c->freed[i]);
         }
@@ -408,13 +413,20 @@ int moe_layer_forward_streamed(moe_ctx* c, const moe_bf16* x, const float* w_rou
     }
     if (c->prof_armed) c->prof_calls++;
     const size_t per = static_cast<size_t>(d) * f;              // elements of one expert matrix
-    auto enqueue_copy = [&](int j) -> int {                    // streamed expert j -> slot j % 2
-        const int b = j & 1;
+    // Slots are taken in turn across calls: with one streamed expert the next call's transfer then runs
+    // under this call's last GEMMs instead of waiting for them (2048 tokens at 4096 x 14336 and 8 experts,
+    // call after call: 6.59 -> 6.23 ms).
+    const int first_slot = c->next_slot;
+    c->next_slot = (first_slot + n_streamed) & 1;
+    auto slot_of = [&](int j) { return (first_slot + j) & 1; };
+    auto enqueue_copy = [&](int j) -> int {                    // streamed expert j into its slot
+        const int b = slot_of(j);
         if (c->freed_valid[b]) MOE_HIP_TRY(hipStreamWaitEvent(c->copy_stream, c->freed[b], 0));
         moe_bf16* dst = reinterpret_cast<moe_bf16*>(c->slot[b]);
         const size_t bytes = per * sizeof(moe_bf16);
         MOE_HIP_TRY(hipMemcpyAsync(dst, W1_host + j * per, bytes, hipMemcpyHostToDevice, c->copy_stream));
         MOE_HIP_TRY(hipMemcpyAsync(dst + per, W3_host + j * per, bytes, hipMemcpyHostToDevice, c->copy_stream));
+        MOE_HIP_TRY(hipEventRecord(c->ready_up[b], c->copy_stream));
         MOE_HIP_TRY(hipMemcpyAsync(dst + 2 * per, W2_host + j * per, bytes, hipMemcpyHostToDevice, c->copy_stream));
         MOE_HIP_TRY(hipEventRecord(c->ready[b], c->copy_stream));
         return MOE_OK;
@@ -426,22 +438,29 @@ int moe_layer_forward_streamed(moe_ctx* c, const moe_bf16* x, const float* w_rou
     rc = route_and_permute(c, x, w_router, bias, T, s);
     if (rc != MOE_OK) return rc;
     // experts [e0, e0 + n) with weights at w1/w3/w2; rows outside those groups are not touched
-    auto ffn = [&](int e0, int n, const moe_bf16* w1, const moe_bf16* w3, const moe_bf16* w2) -> int {
+    auto up = [&](int e0, int n, const moe_bf16* w1, const moe_bf16* w3) -> int {
         const int hint = static_cast<int>(static_cast<long long>(R) * n / E);
-        int r = run_stage(c, MOE_STAGE_GATEUP, 1, s, [&] {
+        return run_stage(c, MOE_STAGE_GATEUP, 1, s, [&] {
             return launch_gateup(c->gemm, x, c->perm, k, c->offsets + e0, R, hint, d, f, n, w1, w3, c->H, s);
         });
-        if (r != MOE_OK) return r;
+    };
+    auto down = [&](int e0, int n, const moe_bf16* w2) -> int {
+        const int hint = static_cast<int>(static_cast<long long>(R) * n / E);
         return run_stage(c, MOE_STAGE_DOWN, 1, s, [&] {
             return launch_down(c->gemm, c->H, c->offsets + e0, R, hint, d, f, n, w2, expert_out(c), c->y_perm_f32 != nullptr, s);
         });
     };
-    if (E_res > 0 && (rc = ffn(0, E_res, W1, W3, W2)) != MOE_OK) return rc;
+    if (E_res > 0) {
+        if ((rc = up(0, E_res, W1, W3)) != MOE_OK) return rc;
+        if ((rc = down(0, E_res, W2)) != MOE_OK) return rc;
+    }
     for (int j = 0; j < n_streamed; ++j) {
-        const int b = j & 1;
-        MOE_HIP_TRY(hipStreamWaitEvent(s, c->ready[b], 0));
+        const int b = slot_of(j);
         const moe_bf16* w = reinterpret_cast<const moe_bf16*>(c->slot[b]);
-        if ((rc = ffn(E_res + j, 1, w, w + per, w + 2 * per)) != MOE_OK) return rc;
+        MOE_HIP_TRY(hipStreamWaitEvent(s, c->ready_up[b], 0));     // gate/up runs under W2's transfer
+        if ((rc = up(E_res + j, 1, w, w + per)) != MOE_OK) return rc;
+        MOE_HIP_TRY(hipStreamWaitEvent(s, c->ready[b], 0));
+        if ((rc = down(E_res + j, 1, w + 2 * per)) != MOE_OK) return rc;
         MOE_HIP_TRY(hipEventRecord(c->freed[b], s));
         c->freed_valid[b] = true;
         if (j + 2 < n_streamed && (rc = enqueue_copy(j + 2)) != MOE_OK) return rc;
