@@ -363,9 +363,14 @@ __device__ __forceinline__ f32x4 mma16(const bf16x8& w, const bf16x8& x, const f
 __device__ __forceinline__ void mma16_agpr(const bf16x8& w, const bf16x8& x, f32x4& acc) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
 }
-// Wait states between the last MFMA and the first ordinary read of its result.
-__device__ __forceinline__ void mfma_drain() {
+// Wait states between the last MFMA and the first ordinary read of its result. `last` are the
+// accumulators of the last MFMAs: the empty statements keep the compiler from reading them ahead of
+// the wait (older ones have left the matrix pipe by then, whenever they are read).
+template <int N>
+__device__ __forceinline__ void mfma_drain(f32x4 (&last)[N]) {
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < N; ++j) asm volatile("" : "+a"(last[j]));
 }
 
 // All k-substeps of one stage: acc[i][j] += A_i * B_j, k ascending.
@@ -728,7 +733,7 @@ __device__ __forceinline__ void ring_tile(const TileCoord& tc, unsigned char* sm
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    mfma_drain();                                    // accumulator writes settle before MFMAs
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");   // accumulator writes settle before MFMAs
 
     const int KT = K / BK;                           // >= max(NA, NB) (checked by the launcher)
     constexpr int NMAX = NA < NB ? NB : NA;
@@ -786,7 +791,7 @@ __device__ __forceinline__ void ring_tile(const TileCoord& tc, unsigned char* sm
         run(F{}, T{});                               // no row of this wavefront is in the tile
         return;
     }
-    mfma_drain();
+    mfma_drain(acc[TM - 1]);
     store_tile<Cfg>(acc, tc, fp, wm, wn, C, N);
 }
 
@@ -794,17 +799,18 @@ __device__ __forceinline__ void ring_tile(const TileCoord& tc, unsigned char* sm
 // sees whole cache lines. In the accumulator layout a lane holds four consecutive columns of one
 // row per fragment, so a direct store writes sixteen separate 32-byte pieces; 256 compute units
 // finishing their tiles together then queue at the L2 for thousands of cycles. Here a wavefront
-// writes the sixteen rows of fragment row i into a small region of its own in the now idle
-// operand stages and reads them back 16 bytes per lane, whole rows at a time, so that each store
-// instruction covers full 128-byte lines; the region is reused for the next fragment row. LDS
-// serves a wavefront's requests in order, so neither the read after the write nor the next
-// write after the read needs a wait. The 16-byte chunks of a row are XOR-swizzled by the row so
-// that both the writes (16 rows at one column) and the reads (whole rows) spread over all banks.
-template <class Cfg>
+// writes the sixteen rows of fragment row i into a small region of its own (`stage`) and reads them
+// back 16 bytes per lane, whole rows at a time, so that each store instruction covers full 128-byte
+// lines; the region is reused for the next fragment row. LDS serves a wavefront's requests in
+// order, so neither the read after the write nor the next write after the read needs a wait, and
+// the next row is converted and written while the reads of this one are on their way. The 16-byte
+// chunks of a row are XOR-swizzled by the row so that both the writes (16 rows at one column) and
+// the reads (whole rows) spread over all banks. `before_stores` runs once, ahead of the first store.
+template <class Cfg, class Before>
 __device__ __forceinline__ void store_tile_via_lds(const f32x4 (&acc)[Cfg::TM][8], const TileCoord& tc,
                                                    const FragPlan<Cfg>& fp, int wave, int lane,
-                                                   unsigned char* smem, uint16_t* __restrict__ C,
-                                                   int ldc) {
+                                                   unsigned char* stages, uint16_t* __restrict__ C,
+                                                   int ldc, Before&& before_stores) {
     constexpr bool DUAL = Cfg::DUAL, F32 = out_is_f32<Cfg>::value;
     constexpr int TM = Cfg::TM, WN = Cfg::WN;
     constexpr int COLS = DUAL ? 64 : 128;            // output columns of this wavefront
@@ -815,9 +821,9 @@ __device__ __forceinline__ void store_tile_via_lds(const f32x4 (&acc)[Cfg::TM][8
     constexpr int SWM = (CP < 16 ? CP : 16) - 1;     // the swizzle permutes chunks inside 256 bytes
     constexpr int NJ = DUAL ? 4 : 8;                 // output fragments per fragment row
     constexpr int RPI = 64 / CP;                     // rows per store instruction
-    static_assert(Cfg::TN == 8 && Cfg::NW * 16 * ROWB <= 2 * Cfg::A_BYTES, "fits the A ring");
+    static_assert(Cfg::TN == 8 && Cfg::NW * 16 * ROWB <= Cfg::B_BYTES, "fits one B stage");
     const int wm = wave / WN, wn = wave % WN;
-    unsigned char* stage = smem + wave * (16 * ROWB);
+    unsigned char* stage = stages + wave * (16 * ROWB);
     const uint32_t wswz = (fp.frag_row >> RSH) & SWM;
     unsigned char* wbase = stage + fp.frag_row * ROWB;
     const int rrow = lane / CP, rchunk = lane % CP;
@@ -826,8 +832,7 @@ __device__ __forceinline__ void store_tile_via_lds(const f32x4 (&acc)[Cfg::TM][8
                            static_cast<size_t>(tc.row0 + wm * Cfg::WTM) * row_bytes +
                            static_cast<size_t>(tc.nt * Cfg::BN_OUT + wn * COLS) * ESZ + rchunk * 16;
     const int rows_here = tc.rows - wm * Cfg::WTM;   // rows of this wavefront inside the tile
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
+    auto write_row = [&](int i) {
 #pragma unroll
         for (int jj = 0; jj < NJ; ++jj) {
             const int j = DUAL ? (jj & 1) + (jj >> 1) * 4 : jj;     // gate fragments; up = j + 2
@@ -845,15 +850,27 @@ __device__ __forceinline__ void store_tile_via_lds(const f32x4 (&acc)[Cfg::TM][8
                 *reinterpret_cast<bf16x4*>(wbase + chunk + (fp.frag_kg & 1) * 8) = o;
             }
         }
+        MOE_FENCE();                                 // one fragment row's registers at a time
+    };
+    write_row(0);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        bf16x8 v[16 / RPI];
 #pragma unroll
         for (int q = 0; q < 16 / RPI; ++q) {
             const int rl = q * RPI + rrow;                          // row inside the fragment row
             const uint32_t chunk = (static_cast<uint32_t>(rchunk) ^ ((rl >> RSH) & SWM)) * 16;
-            const bf16x8 v = *reinterpret_cast<const bf16x8*>(stage + rl * ROWB + chunk);
-            const int r = i * 16 + rl;
-            if (r < rows_here) *reinterpret_cast<bf16x8*>(cbase + static_cast<size_t>(r) * row_bytes) = v;
+            v[q] = *reinterpret_cast<const bf16x8*>(stage + rl * ROWB + chunk);
         }
-        MOE_FENCE();                                 // one fragment row's registers at a time
+        MOE_FENCE();
+        if (i + 1 < TM) write_row(i + 1);
+        if (i == 0) before_stores();
+#pragma unroll
+        for (int q = 0; q < 16 / RPI; ++q) {
+            const int r = i * 16 + q * RPI + rrow;
+            if (r < rows_here) *reinterpret_cast<bf16x8*>(cbase + static_cast<size_t>(r) * row_bytes) = v[q];
+        }
+        MOE_FENCE();
     }
 }
 
@@ -1065,9 +1082,11 @@ __device__ __forceinline__ void prologue_1w(const TileCoord& tc, LoadPlan1W<Cfg>
     }
 }
 
-// From the landing of k-step 0 to the last MFMA: on return every load has landed, every
-// wavefront has passed the closing barrier (nobody reads a stage any more) and the accumulators
-// hold the tile.
+// From the landing of k-step 0 to the last MFMA: on return the accumulators hold the tile and the
+// B stage of the last k-step (last_b_stage) is idle: every wavefront had read it at that k-step's
+// barrier, and the refills of the last k-steps, which may still be on their way, go to the others.
+template <class Cfg, int NB>
+__device__ __forceinline__ int last_b_stage(int K) { return (K / Cfg::BK - 1) % NB; }
 template <class Cfg, int NA, int NB>
 __device__ __forceinline__ void mainloop_1w(f32x4 (&acc)[Cfg::TM][8], LoadPlan1W<Cfg>& lp,
                                             const FragPlan<Cfg>& fp, unsigned char* smem, int wave,
@@ -1112,9 +1131,7 @@ __device__ __forceinline__ void mainloop_1w(f32x4 (&acc)[Cfg::TM][8], LoadPlan1W
         kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1], kt, KT);
         kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1], kt + 1, KT);
     }
-    wait_vmcnt<0>();                                 // the refills of the last k-steps, never read
-    __builtin_amdgcn_s_barrier();                    // ... have all landed; nobody reads a stage any more
-    mfma_drain();                                    // before anything else touches the accumulators
+    mfma_drain(acc[TM - 1]);                         // before anything else touches the accumulators
 }
 
 template <class Cfg, int NA, int NB>
@@ -1133,7 +1150,13 @@ __device__ __forceinline__ void ring_tile_1w(const TileCoord& tc, unsigned char*
     fp.init(lane, wave / Cfg::WN, wave % Cfg::WN);
     f32x4 acc[Cfg::TM][Cfg::TN];
     mainloop_1w<Cfg, NA, NB>(acc, lp, fp, smem, wave, K);
-    store_tile_via_lds<Cfg>(acc, tc, fp, wave, lane, smem, C, N);
+    // The refills of the last k-steps must have landed before the workgroup gives its LDS back. Waiting for
+    // them here instead of between the last MFMA and the first conversion (with a barrier), and writing
+    // the next fragment row under the reads of this one: layer 745 -> 739 us at 8192 tokens through 128
+    // experts of 2048 x 768, 592 -> 586 us at 5003 through 64 of 2048 x 1408.
+    store_tile_via_lds<Cfg>(acc, tc, fp, wave, lane,
+                            smem + RingCfg<Cfg, NA, NB>::A_RING + last_b_stage<Cfg, NB>(K) * Cfg::B_BYTES, C, N,
+                            [] { wait_vmcnt<0>(); });
 }
 
 // Tiles are enumerated at Cfg::BM rows. A tile that holds at most HalfCfg::BM = Cfg::BM / 2 rows
