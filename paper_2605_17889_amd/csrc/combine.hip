@@ -11,7 +11,6 @@ namespace {
 
 constexpr int kMaxSlots = 64;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // One block per token; each thread owns 8 consecutive columns per step (one 16-byte vector of
 // bf16 expert outputs, or two of fp32 ones with YF32).
@@ -32,27 +31,38 @@ __global__ __launch_bounds__(256) void combine_kernel(const void* __restrict__ y
         float acc[8];
 #pragma unroll
         for (int v = 0; v < 8; ++v) acc[v] = 0.f;
-        for (int s = 0; s < k; ++s) {
-            const int p = row[s];
-            if (static_cast<unsigned>(p) >= static_cast<unsigned>(R)) continue;  // dropped row
-            const float g = gate[s];
-            if constexpr (YF32) {
-                const f32x4* src =
-                    reinterpret_cast<const f32x4*>(static_cast<const float*>(y_perm) + static_cast<size_t>(p) * d) + 2 * c;
-                const f32x4 lo = src[0], hi = src[1];       // (non-temporal loads measured 3 % slower here)
-                const float w[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        // the rows of four slots are on their way together; slots are still added one after the other
+        for (int s0 = 0; s0 < k; s0 += 4) {
+            constexpr int N = YF32 ? 2 : 1;
+            u32x4 q[4][N];
+            bool on[4];
 #pragma unroll
-                for (int v = 0; v < 8; ++v) acc[v] = fmaf(g, w[v], acc[v]);
-            } else {
-                // each expert-output row is read once, by this block: a non-temporal load (9 % faster
-                // with 8 rows of 4 KB per token, and the next call's router finds its rows cached)
-                const u32x4 q = __builtin_nontemporal_load(
-                    reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(y_perm) + static_cast<size_t>(p) * d) + c);
-                const uint32_t w[4] = {q[0], q[1], q[2], q[3]};
+            for (int i = 0; i < 4; ++i) {
+                const int p = s0 + i < k ? row[s0 + i] : -1;
+                on[i] = static_cast<unsigned>(p) < static_cast<unsigned>(R);         // else a dropped row
+                const size_t at = static_cast<size_t>(on[i] ? p : 0) * d;
+                if (!on[i]) continue;
+                if constexpr (YF32) {                // (non-temporal loads measured 3 % slower here)
+                    const u32x4* src = reinterpret_cast<const u32x4*>(static_cast<const float*>(y_perm) + at) + 2 * c;
+                    q[i][0] = src[0];
+                    q[i][1] = src[1];
+                } else {
+                    // each expert-output row is read once, by this block: a non-temporal load (9 % faster
+                    // with 8 rows of 4 KB per token, and the next call's router finds its rows cached)
+                    q[i][0] = __builtin_nontemporal_load(
+                        reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(y_perm) + at) + c);
+                }
+            }
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    acc[2 * v] = fmaf(g, __uint_as_float(w[v] << 16), acc[2 * v]);
-                    acc[2 * v + 1] = fmaf(g, __uint_as_float(w[v] & 0xffff0000u), acc[2 * v + 1]);
+            for (int i = 0; i < 4; ++i) {
+                if (!on[i]) continue;
+                const float g = gate[s0 + i];
+#pragma unroll
+                for (int v = 0; v < 8; ++v) {
+                    float w;
+                    if constexpr (YF32) w = __uint_as_float(q[i][v >> 2][v & 3]);
+                    else w = __uint_as_float((v & 1) ? (q[i][0][v >> 1] & 0xffff0000u) : (q[i][0][v >> 1] << 16));
+                    acc[v] = fmaf(g, w, acc[v]);
                 }
             }
         }
