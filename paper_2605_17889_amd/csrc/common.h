@@ -46,6 +46,11 @@ int launch_permute(const int32_t* topk_idx, int R, int E, int32_t* counts, int32
 bool select_permute_fits(int T, int E, int k);
 int launch_select_permute(const float* logits, int T, int E, int k, int32_t* topk_idx, float* topk_w,
                           int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv_perm, hipStream_t s);
+// The same for larger batches in two launches: selection with the histograms of its ids, then the scatter.
+bool select_hist_fits(int T, int E, int k);
+int launch_select_hist_permute(const float* logits, int T, int E, int k, int32_t* topk_idx, float* topk_w,
+                               int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv_perm,
+                               int32_t* seg_tables, hipStream_t s);
 int launch_gather(const moe_bf16* x, const int32_t* perm, const int32_t* offsets, int R, int d,
                   int k, int E, moe_bf16* x_perm, hipStream_t s);
 // Where and how a context launches its expert GEMMs: its device and the tuning knobs of

@@ -113,23 +113,27 @@ void* expert_out(moe_ctx* c) {
     return c->y_perm_f32 ? static_cast<void*>(c->y_perm_f32) : static_cast<void*>(c->y_perm);
 }
 
-// Routing and permutation of a layer call into the context's tables. For a few tokens through more
-// than 16 experts the selection runs in the permutation's launch and counts as that stage.
+// Routing and permutation of a layer call into the context's tables. Through more than 16 experts the
+// selection usually runs in a launch of the permutation and counts as that stage.
 int route_and_permute(moe_ctx* c, const moe_bf16* x, const float* w_router, const float* bias, int T,
                       hipStream_t s) {
     const moe_shape& sh = c->shape;
     const int d = sh.d_model, E = sh.E, k = sh.k, R = T * k;
-    const bool together = select_permute_fits(T, E, k);
+    const bool few = select_permute_fits(T, E, k), many = select_hist_fits(T, E, k);
     const int rc = run_stage(c, MOE_STAGE_ROUTE, 1, s, [&] {
-        return together ? launch_route_logits(x, w_router, bias, T, d, E, c->logits, s)
-                        : launch_route(x, w_router, bias, T, d, E, k, c->topk_idx, c->topk_w, nullptr, c->logits, s);
+        return few || many
+                   ? launch_route_logits(x, w_router, bias, T, d, E, c->logits, s)
+                   : launch_route(x, w_router, bias, T, d, E, k, c->topk_idx, c->topk_w, nullptr, c->logits, s);
     });
     if (rc != MOE_OK) return rc;
-    return run_stage(c, MOE_STAGE_PERMUTE, permute_launches(R), s, [&] {
-        return together ? launch_select_permute(c->logits, T, E, k, c->topk_idx, c->topk_w, c->counts,
-                                                c->offsets, c->perm, c->inv_perm, s)
-                        : launch_permute(c->topk_idx, R, E, c->counts, c->offsets, c->perm, c->inv_perm,
-                                         c->scratch, s);
+    return run_stage(c, MOE_STAGE_PERMUTE, few ? 1 : many ? 2 : permute_launches(R), s, [&] {
+        if (few)
+            return launch_select_permute(c->logits, T, E, k, c->topk_idx, c->topk_w, c->counts, c->offsets,
+                                         c->perm, c->inv_perm, s);
+        if (many)
+            return launch_select_hist_permute(c->logits, T, E, k, c->topk_idx, c->topk_w, c->counts, c->offsets,
+                                              c->perm, c->inv_perm, c->scratch, s);
+        return launch_permute(c->topk_idx, R, E, c->counts, c->offsets, c->perm, c->inv_perm, c->scratch, s);
     });
 }
 

@@ -118,9 +118,13 @@ def test_route_few_tokens_bit_exact(T, d, E, k):
 
 
 @pytest.mark.parametrize("E", [17, 64, 100, 256])
-@pytest.mark.parametrize("T,k", [(1, 17), (16, 17), (63, 2), (64, 16), (65, 16), (61, 17)])
-def test_layer_selects_and_permutes_few_tokens_like_the_stage_calls(T, k, E):
-    """Up to 64 tokens and 1024 ids the layer call selects and permutes in one launch."""
+@pytest.mark.parametrize("T,k", [
+    (1, 17), (16, 17), (63, 2), (64, 16), (65, 16), (61, 17),
+    (1024, 4), (1025, 4), (1366, 3), (257, 16), (256, 17), (321, 17), (2000, 8),
+])
+def test_layer_selects_and_permutes_like_the_stage_calls(T, k, E):
+    """Up to 64 tokens and 1024 ids the layer call selects and permutes in one launch; with more than
+    4096 ids and at least four per token it counts every 64 tokens' ids while it selects them."""
     say(f"select + permute T={T} k={k} E={E}")
     d, f = 512, 128
     g = torch.Generator(device="cuda").manual_seed(T * 1000 + E)
@@ -314,6 +318,14 @@ def test_permute_bit_exact(T, E, k, seed, empty):
     assert np.array_equal(bits(xp), xp_ref)
     assert int(counts.sum()) == R
     ctx.close()
+
+
+@pytest.mark.parametrize("T,E,k", [
+    # one workgroup up to 4096 ids, two launches with a workgroup per 1024 ids up to 512 of them, then three
+    (4096, 16, 1), (4097, 16, 1), (1024, 8, 5), (1025, 256, 8), (3, 3, 3), (65537, 100, 8), (65536, 7, 7),
+])
+def test_permute_bit_exact_where_the_launches_change(T, E, k):
+    test_permute_bit_exact(T, E, k, T + E, False)
 
 
 # ---------------------------------------------------------------- expert FFN and combine
