@@ -272,13 +272,15 @@ __device__ __forceinline__ void permute_block(SmallTables& sm, const int32_t* id
         const int i = base + r * kWave + lane;
         my[r] = (i < last) ? ids[i] : -1;
     }
-    for (int e = lane; e < E; e += kWave) mine[e] = 0;
+    if (wv < waves) {                         // the tables of the others are not read
+        for (int e = lane; e < E; e += kWave) mine[e] = 0;
 #pragma unroll
-    for (int r = 0; r < KEEP; ++r) {
-        if (my[r] < 0 || my[r] >= E) my[r] = -1;
-        same[r] = same_value_lanes(my[r]);
-        if (my[r] >= 0 && (same[r] & lanemask_lt(lane)) == 0) mine[my[r]] += __popcll(same[r]);
-        __builtin_amdgcn_wave_barrier();
+        for (int r = 0; r < KEEP; ++r) {
+            if (my[r] < 0 || my[r] >= E) my[r] = -1;
+            same[r] = same_value_lanes(my[r]);
+            if (my[r] >= 0 && (same[r] & lanemask_lt(lane)) == 0) mine[my[r]] += __popcll(same[r]);
+            __builtin_amdgcn_wave_barrier();
+        }
     }
     __syncthreads();
     if (tid < E) {                            // wavefronts' counts of one expert, in order
@@ -336,6 +338,9 @@ __global__ __launch_bounds__(kSmallWaves* kWave) void select_permute_kernel(
     __shared__ int32_t ids[kSmallWaves * kWave];
     for (int t0 = 0; t0 < T; t0 += kSmallWaves * kWave / 16) {
         const int t = t0 + threadIdx.x / 16;
+        // a wavefront without a token leaves its SIMD to the chains of those that have some (here and in
+        // permute_block: layer call of one token through 8 of 128 experts 35.9 -> 34.8 us)
+        if (t0 + __builtin_amdgcn_readfirstlane(threadIdx.x / 16) >= T) break;
         select_by_16_lanes<EW>(logits, t, t < T, threadIdx.x & 15, E, k, [&](int s, int e, float w) {
             topk_idx[t * k + s] = e;
             topk_w[t * k + s] = w;
