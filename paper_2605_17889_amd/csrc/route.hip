@@ -845,6 +845,12 @@ int launch_select_groups(const float* logits, int T, int E, int k, int32_t* idx,
 // Workgroups of the few-token kernel at most: one per compute unit (its LDS allows no second).
 constexpr int kFewBlocks = 256;
 
+// The few-token kernel loads x and W_r straight into LDS, 16 bytes per lane, which wants addresses that are
+// multiples of 16. Views that start elsewhere stay with the kernels whose loads go through registers.
+bool few_aligned(const moe_bf16* x, const float* wr) {
+    return ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(wr)) & 15) == 0;
+}
+
 }  // namespace
 
 // `logits_scratch` [T, E] fp32 is only used for more than 16 experts, and only if the caller
@@ -861,7 +867,7 @@ int launch_route(const moe_bf16* x, const float* w_router, const float* bias, in
     }
     // One round of few-token workgroups: 1024 tokens of 4096 take 8.1 us against 11.4 with the kernels
     // below, 2048 tokens (two rounds) 14.3 against 11.8.
-    const int few = (T + 3) / 4;
+    const int few = few_aligned(x, w_router) ? (T + 3) / 4 : kFewBlocks + 1;
     if (E == 8 && few <= kFewBlocks)
         return launch_route_few<8, 4, true>(x, w_router, bias, T, d, E, k, topk_idx, topk_w, logits_out, s);
     if (E == 16 && few <= kFewBlocks)
@@ -881,9 +887,10 @@ int launch_route_logits(const moe_bf16* x, const float* w_router, const float* b
     const dim3 grid((T + 4 * TOK - 1) / (4 * TOK), (E + 15) / 16);
     // one round of few-token workgroups, a token each while that fits (37 tokens through 128 experts in
     // two rounds of one token 14.2 us, in one of four 12.0; 100 in one 12.9, 192 in two 17.1 against 16.4)
-    if (E % 16 == 0 && static_cast<long long>(T) * (E / 16) <= kFewBlocks)
+    const bool few = E % 16 == 0 && few_aligned(x, w_router);
+    if (few && static_cast<long long>(T) * (E / 16) <= kFewBlocks)
         return launch_route_few<16, 1, false>(x, w_router, bias, T, d, E, 0, nullptr, nullptr, logits, s);
-    if (E % 16 == 0 && static_cast<long long>((T + 3) / 4) * (E / 16) <= kFewBlocks)
+    if (few && static_cast<long long>((T + 3) / 4) * (E / 16) <= kFewBlocks)
         return launch_route_few<16, 4, false>(x, w_router, bias, T, d, E, 0, nullptr, nullptr, logits, s);
     // Full groups and at least 128 tiles of 64 tokens x 16 experts: the matrix-core form. One
     // tile takes it about as long as 130 k (token, expert) pairs take the vector-unit

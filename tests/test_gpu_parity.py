@@ -117,6 +117,29 @@ def test_route_few_tokens_bit_exact(T, d, E, k):
     test_route_bit_exact(T, d, E, k, T % 2 == 1)
 
 
+@pytest.mark.parametrize("T,E,k", [(5, 8, 2), (3, 16, 2), (1, 128, 8), (33, 64, 6)])
+def test_route_few_tokens_with_a_router_matrix_off_16_bytes(T, E, k):
+    """A W_r that starts 4 bytes past a multiple of 16, as a view into a packed buffer does."""
+    say(f"route, W_r off 16 bytes: T={T} E={E}")
+    d = 1024
+    rng = np.random.default_rng(T + E)
+    x, wr = rand_bits(rng, (T, d), 1.0), rng.normal(0, 0.02, size=(d, E)).astype(np.float32)
+    packed = torch.zeros(d * E + 4, device="cuda")
+    view = packed[1:1 + d * E].view(d, E)
+    view.copy_(dev(wr))
+    assert view.data_ptr() % 16 == 4
+    ctx = B.MoeContext(T, d, 256, E, k)
+    idx = torch.empty((T, k), dtype=torch.int32, device="cuda")
+    g = torch.empty((T, k), dtype=torch.float32, device="cuda")
+    lg = torch.empty((T, E), dtype=torch.float32, device="cuda")
+    B.moe_route(ctx, dev(bf16_tensor_from_bits(x)), view, None, T, idx, g, lg)
+    torch.cuda.synchronize()
+    want = ref.logits(x, wr, None)
+    assert np.array_equal(lg.cpu().numpy().view(np.uint32), want.view(np.uint32))
+    assert np.array_equal(idx.cpu().numpy(), ref.topk(want, k)[0])
+    ctx.close()
+
+
 @pytest.mark.parametrize("E", [17, 64, 100, 256])
 @pytest.mark.parametrize("T,k", [
     (1, 17), (16, 17), (63, 2), (64, 16), (65, 16), (61, 17),
