@@ -107,6 +107,7 @@ struct NTiles {
     double mid_step;             // k-step of the 96- and 128-row tiles, of a 256-row tile's
     double small_alone, small_pair;   // k-step of a 64-row tile alone on a compute unit / of two on one
     double weight_mb;            // of the launched experts
+    int ksteps;                  // of the reduction
 };
 
 // Large tiles against 128-row ones when experts have several row tiles. Launch time in units of one
@@ -178,7 +179,10 @@ int pick_config(const GemmEnv& env, int R, int E, const NTiles& nt) {
     // units idle: small tiles are worth their extra loads if they use the idle ones. Units of a
     // k-step of a full 256-row tile (about 1 us), measured on one expert of 4096 x 14336 (512 rows,
     // down projection: 125 us with large tiles, 94 and 87 us with 64-row ones of 128 and 64 columns;
-    // 181 against 124 us when the weights come from memory, which a compute unit reads at 60 GB/s).
+    // 181 against 124 us when the weights come from memory, which a compute unit reads at 60 GB/s). What a
+    // tile costs outside its reduction is added in k-steps, and decides where that is short (layer call of
+    // 512 tokens through 8 experts of 512 x 1024 27.9 us with large gate/up tiles, 26.6 with 64-row ones; 900
+    // tokens 29.1 and 28.1).
     const int rows = config == 0 ? 256 : config == 1 ? 128 : 96;
     const double tiles = E * mean_row_tiles(avg, sigma, rows) * (config == 0 ? nt.large : nt.mid);
     if (tiles <= cus) {
@@ -186,7 +190,7 @@ int pick_config(const GemmEnv& env, int R, int E, const NTiles& nt) {
         const double small = E * mean_row_tiles(avg, sigma, 64) * nt.small;
         const double rounds = std::floor(small / (2.0 * cus)), rem = small - rounds * 2.0 * cus;
         const double fill = rounds * nt.small_pair + (rem <= 0.0 ? 0.0 : rem <= cus ? nt.small_alone : nt.small_pair);
-        if (fill < 0.9 * step) return 2;
+        if ((nt.ksteps + 3.0) * fill < 0.9 * (nt.ksteps + 6.0) * step) return 2;
     }
     return config;
 }
@@ -271,7 +275,7 @@ int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_inde
     if (R == 0) return MOE_OK;
     const moe_bf16* x_perm = a;
     int config = pick_config(env, R_hint, E, NTiles{f / 128, f / 128, f / 64, 0.82, 0.41, 0.58,
-                                                    4e-6 * E * d * f});
+                                                    4e-6 * E * d * f, d / 64});
     if (config == 0 && d / 64 < 3) config = 1;     // the pipelined kernel needs three k-steps
     switch (config) {
         case 0:
@@ -319,7 +323,7 @@ int launch_down_as(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets
     const bool wide_mid = static_cast<long long>(E) * (d / 256) >= 160 && d % 256 == 0;
     const int cus = compute_units(env.device);
     int config = pick_config(env, R_hint, E, NTiles{d / 256, wide_mid ? d / 256 : d / 128, d / 64,
-                                                    wide_mid ? 0.82 : 0.6, 0.27, 0.38, 2e-6 * E * d * f});
+                                                    wide_mid ? 0.82 : 0.6, 0.27, 0.38, 2e-6 * E * d * f, f / 64});
     if (config == 0 && f / 64 < 3) config = 1;     // the pipelined kernel needs three k-steps
     switch (config) {
         case 0:

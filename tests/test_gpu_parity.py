@@ -463,6 +463,7 @@ def test_expert_ffn_configs_agree_bitwise():
     (2048, 128, [43, 64, 0, 65, 1, 33, 130, 8] * 8), # 64-row tiles, 128 and 64 columns wide
     (1024, 384, [63, 64, 65, 1, 0, 129]),            # 64-row tiles instead of a few 96-row ones
     (512, 1024, [512]),                              # ... and instead of a few 256-row ones
+    (512, 1024, [128, 0, 256, 65, 64, 129, 191, 192]),   # ... of a short reduction
 ])
 @pytest.mark.parametrize("fp32_outputs", [False, True])
 def test_automatic_tile_choice_agrees_bitwise(d, f, rows, fp32_outputs):
