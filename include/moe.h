@@ -14,7 +14,10 @@
  *     row-major, densely packed (the one exception: the *_host arguments of
  *     moe_layer_forward_streamed are HOST pointers to page-locked memory). bf16 tensors are
  *     raw 16-bit patterns (moe_bf16). The library never frees a caller pointer and never uses
- *     one after the work that the call enqueued has finished.
+ *     one after the work that the call enqueued has finished. The expert GEMMs load 16 bytes at a
+ *     time straight into LDS: there x (or x_perm), W1, W3 and W2 start at multiples of 16 bytes
+ *     (not checked). moe_route takes x and w_router from any element on; the router kernels that
+ *     load straight into LDS are only taken for addresses that are multiples of 16.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream). Calls enqueue
  *     work and return without synchronising the host; results are ready when the stream is.
  *   - Return value: MOE_OK or a negative moe_status. Arguments are checked on the host, and

@@ -845,9 +845,10 @@ int launch_select_groups(const float* logits, int T, int E, int k, int32_t* idx,
 // Workgroups of the few-token kernel at most: one per compute unit (its LDS allows no second).
 constexpr int kFewBlocks = 256;
 
-// The few-token kernel loads x and W_r straight into LDS, 16 bytes per lane, which wants addresses that are
-// multiples of 16. Views that start elsewhere stay with the kernels whose loads go through registers.
-bool few_aligned(const moe_bf16* x, const float* wr) {
+// The few-token and the matrix-core kernels load x and W_r straight into LDS, 16 bytes per lane, which wants
+// addresses that are multiples of 16. Views that start elsewhere go to the kernels whose loads pass through
+// registers, at every token count.
+bool direct_to_lds_aligned(const moe_bf16* x, const float* wr) {
     return ((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(wr)) & 15) == 0;
 }
 
@@ -867,7 +868,7 @@ int launch_route(const moe_bf16* x, const float* w_router, const float* bias, in
     }
     // One round of few-token workgroups: 1024 tokens of 4096 take 8.1 us against 11.4 with the kernels
     // below, 2048 tokens (two rounds) 14.3 against 11.8.
-    const int few = few_aligned(x, w_router) ? (T + 3) / 4 : kFewBlocks + 1;
+    const int few = direct_to_lds_aligned(x, w_router) ? (T + 3) / 4 : kFewBlocks + 1;
     if (E == 8 && few <= kFewBlocks)
         return launch_route_few<8, 4, true>(x, w_router, bias, T, d, E, k, topk_idx, topk_w, logits_out, s);
     if (E == 16 && few <= kFewBlocks)
@@ -887,15 +888,15 @@ int launch_route_logits(const moe_bf16* x, const float* w_router, const float* b
     const dim3 grid((T + 4 * TOK - 1) / (4 * TOK), (E + 15) / 16);
     // one round of few-token workgroups, a token each while that fits (37 tokens through 128 experts in
     // two rounds of one token 14.2 us, in one of four 12.0; 100 in one 12.9, 192 in two 17.1 against 16.4)
-    const bool few = E % 16 == 0 && few_aligned(x, w_router);
-    if (few && static_cast<long long>(T) * (E / 16) <= kFewBlocks)
+    const bool direct = E % 16 == 0 && direct_to_lds_aligned(x, w_router);
+    if (direct && static_cast<long long>(T) * (E / 16) <= kFewBlocks)
         return launch_route_few<16, 1, false>(x, w_router, bias, T, d, E, 0, nullptr, nullptr, logits, s);
-    if (few && static_cast<long long>((T + 3) / 4) * (E / 16) <= kFewBlocks)
+    if (direct && static_cast<long long>((T + 3) / 4) * (E / 16) <= kFewBlocks)
         return launch_route_few<16, 4, false>(x, w_router, bias, T, d, E, 0, nullptr, nullptr, logits, s);
     // Full groups and at least 128 tiles of 64 tokens x 16 experts: the matrix-core form. One
     // tile takes it about as long as 130 k (token, expert) pairs take the vector-unit
     // kernel, whatever the number of tiles up to one per compute unit (measured crossover).
-    if (E % 16 == 0 && static_cast<long long>((T + 63) / 64) * (E / 16) >= 128) {
+    if (direct && static_cast<long long>((T + 63) / 64) * (E / 16) >= 128) {
         int device = 0;
         if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= 64) return MOE_ERR_HIP;
         static std::atomic<uint64_t> attr_set{0};     // one bit per device, as for the GEMM kernels
@@ -920,7 +921,7 @@ int launch_route_logits(const moe_bf16* x, const float* w_router, const float* b
         const long long grid = std::min<long long>(tiles, std::max(kXcds, cus / kXcds * kXcds));
         hipLaunchKernelGGL(route_logits_mfma_kernel, dim3(static_cast<unsigned>(grid)),
                            dim3(256), RouteMfma::SMEM, s, x, w_router, bias, T, d, E, logits);
-    } else if (E % 16 == 0) { // every group full and 16-byte aligned: vector loads of W_r
+    } else if (E % 16 == 0) { // every group full: vector loads of W_r
         hipLaunchKernelGGL((route_logits_group_kernel<TOK, true>), grid, dim3(256), 0, s, x,
                            w_router, bias, T, d, E, logits);
     } else {

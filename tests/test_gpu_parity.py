@@ -140,6 +140,36 @@ def test_route_few_tokens_with_a_router_matrix_off_16_bytes(T, E, k):
     ctx.close()
 
 
+@pytest.mark.parametrize("x_off,w_off", [(0, 1), (1, 0), (4, 3)])
+@pytest.mark.parametrize("T,E,k", [
+    (5, 8, 2), (3, 16, 2), (1, 128, 8), (33, 64, 6),      # where aligned views take the few-token kernel
+    (1024, 128, 8), (2049, 64, 6), (500, 256, 8),         # ... and the matrix-core kernel
+])
+def test_route_of_views_off_16_bytes(T, E, k, x_off, w_off):
+    """x and W_r that start x_off and w_off elements past a multiple of 16 bytes: the kernels that load
+    straight into LDS assume 16-byte addresses, so both views have to be kept away from them."""
+    say(f"route, views off 16 bytes: T={T} E={E} x+{2 * x_off} W_r+{4 * w_off} bytes")
+    d = 512
+    rng = np.random.default_rng(T + E)
+    x, wr = rand_bits(rng, (T, d), 1.0), rng.normal(0, 0.02, size=(d, E)).astype(np.float32)
+    view = {}
+    for name, off, t in (("x", x_off, bf16_tensor_from_bits(x)), ("w", w_off, torch.from_numpy(wr))):
+        packed = torch.zeros(t.numel() + 8, dtype=t.dtype, device="cuda")
+        view[name] = packed[off:off + t.numel()].view(t.shape)
+        view[name].copy_(t)
+        assert view[name].data_ptr() % 16 == off * t.element_size()
+    ctx = B.MoeContext(T, d, 256, E, k)
+    idx = torch.empty((T, k), dtype=torch.int32, device="cuda")
+    g = torch.empty((T, k), dtype=torch.float32, device="cuda")
+    lg = torch.empty((T, E), dtype=torch.float32, device="cuda")
+    B.moe_route(ctx, view["x"], view["w"], None, T, idx, g, lg)
+    torch.cuda.synchronize()
+    want = ref.logits(x, wr, None)
+    assert np.array_equal(lg.cpu().numpy().view(np.uint32), want.view(np.uint32))
+    assert np.array_equal(idx.cpu().numpy(), ref.topk(want, k)[0])
+    ctx.close()
+
+
 @pytest.mark.parametrize("E", [17, 64, 100, 256])
 @pytest.mark.parametrize("T,k", [
     (1, 17), (16, 17), (63, 2), (64, 16), (65, 16), (61, 17),
