@@ -71,9 +71,11 @@ typedef enum {
     MOE_ERR_HIP = -4                /* a HIP runtime call or launch reported an error */
 } moe_status;
 
-/* Stages of the layer, in execution order; indices into moe_profile_end()'s array. */
+/* Stages of the layer, in execution order; indices into moe_profile_end()'s array. With more than
+ * 16 experts the top-k and the gates run in a launch of the permutation, and count as that stage,
+ * for T <= 64 with T*k <= 1024 and for T <= 32768 with T*k > 4096 and k >= 4. */
 enum {
-    MOE_STAGE_ROUTE = 0,            /* router logits + top-k + gates */
+    MOE_STAGE_ROUTE = 0,            /* router logits + top-k + gates (but see above) */
     MOE_STAGE_PERMUTE = 1,          /* histogram, scan, stable scatter */
     MOE_STAGE_GATHER = 2,           /* x -> x_perm row gather */
     MOE_STAGE_GATEUP = 3,           /* grouped GEMM  H = SiLU(Xp W1^T) * (Xp W3^T) */

@@ -33,6 +33,7 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
 int launch_route(const moe_bf16* x, const float* w_router, const float* bias, int T, int d, int E,
                  int k, int32_t* topk_idx, float* topk_w, float* logits_out,
                  float* logits_scratch, hipStream_t s);
+int route_launches(int E);       // kernels that launch_route enqueues for a call of at least one token
 int launch_route_logits(const moe_bf16* x, const float* w_router, const float* bias, int T, int d, int E,
                         float* logits, hipStream_t s);
 int launch_route_from_logits(const float* logits, int T, int E, int k, int32_t* topk_idx,

@@ -120,7 +120,7 @@ int route_and_permute(moe_ctx* c, const moe_bf16* x, const float* w_router, cons
     const moe_shape& sh = c->shape;
     const int d = sh.d_model, E = sh.E, k = sh.k, R = T * k;
     const bool few = select_permute_fits(T, E, k), many = select_hist_fits(T, E, k);
-    const int rc = run_stage(c, MOE_STAGE_ROUTE, 1, s, [&] {
+    const int rc = run_stage(c, MOE_STAGE_ROUTE, few || many ? 1 : route_launches(E), s, [&] {
         return few || many
                    ? launch_route_logits(x, w_router, bias, T, d, E, c->logits, s)
                    : launch_route(x, w_router, bias, T, d, E, k, c->topk_idx, c->topk_w, nullptr, c->logits, s);

@@ -854,6 +854,9 @@ bool direct_to_lds_aligned(const moe_bf16* x, const float* wr) {
 
 }  // namespace
 
+// Through up to 16 experts the kernel that makes the logits selects as well.
+int route_launches(int E) { return E > 16 ? 2 : 1; }
+
 // `logits_scratch` [T, E] fp32 is only used for more than 16 experts, and only if the caller
 // does not ask for the logits anyway.
 int launch_route(const moe_bf16* x, const float* w_router, const float* bias, int T, int d, int E,

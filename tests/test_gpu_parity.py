@@ -1071,6 +1071,33 @@ def test_profile_stage_times_of_layer_and_expert_ffn():
     ctx.close()
 
 
+@pytest.mark.parametrize("T,E,k,route,permute", [
+    (300, 8, 2, 1, 1),      # up to 16 experts the router kernel selects; up to 4096 ids one permutation launch
+    (2100, 8, 2, 1, 2),     # ... then two
+    (64, 64, 16, 1, 1),     # 64 tokens, 1024 ids: selected and permuted in one launch
+    (65, 64, 16, 2, 1),     # one token more: logits and selection, then the permutation
+    (1024, 64, 4, 2, 1),    # 4096 ids, the most of one permutation launch
+    (1025, 64, 4, 1, 2),    # more: logits, then selection with histograms and scatter
+    (1400, 64, 3, 2, 2),    # fewer than four ids per token: logits and selection, then histograms and scatter
+])
+def test_profile_counts_the_launches_of_routing_and_permutation(T, E, k, route, permute):
+    say(f"stage profiling, launches: T={T} E={E} k={k}")
+    d, f = 512, 128
+    g = torch.Generator(device="cuda").manual_seed(T)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    x, wr = rnd(T, d).bfloat16(), rnd(d, E) * 0.02
+    W1, W3, W2 = ((rnd(*s) * 0.05).bfloat16() for s in ((E, f, d), (E, f, d), (E, d, f)))
+    ctx = B.MoeContext(T, d, f, E, k)
+    y = torch.empty((T, d), dtype=torch.bfloat16, device="cuda")
+    B.moe_profile_begin(ctx, 2)
+    for _ in range(2):
+        B.moe_layer_forward(ctx, x, wr, None, W1, W3, W2, T, y)
+    _, launches, calls = B.moe_profile_end(ctx)
+    assert calls == 2
+    assert (launches["route"], launches["permute"]) == (2 * route, 2 * permute)
+    ctx.close()
+
+
 def test_permute_drops_out_of_range_experts():
     """An expert index outside [0, E) is dropped from every group: inv_perm = -1, counts and
     offsets only cover the valid ids, and the remaining ids keep their stable order."""
