@@ -354,8 +354,8 @@ __global__ __launch_bounds__(kSmallWaves* kWave) void select_permute_kernel(
 // Batches of more than 4096 ids, up to kMaxParts parts of consecutive ids: a histogram of every part, then
 // one workgroup per part that sums the histograms before it (and all of them, for the offsets) by itself
 // and scatters its ids. Reading every histogram in every workgroup costs less than the launch and the
-// lone workgroup of scan_kernel: 8192 tokens through 8 of 128 experts 14.5 -> 8.8 us, 16384 tokens through 2 of
-// 8 11.8 -> 7.9, and still 45.7 -> 18.4 at 520000 ids of 128 experts.
+// lone workgroup of scan_kernel, by moe_permute_static in a graph, three launches -> two: 65536 ids of 128 experts
+// 14.5 -> 7.4 us, 16384 of 8 11.2 -> 6.6, 520000 of 17 23.7 -> 10.5, 16384 of one 8.3 -> 7.0.
 constexpr int kMaxParts = 512;
 constexpr int kPartIds = kSmallThreads;                   // ids of a part that part_hist_kernel counts
 constexpr int kPartTokens = kSmallThreads / 16;           // tokens of one that select_hist_kernel counts
@@ -400,15 +400,28 @@ __global__ __launch_bounds__(kSmallThreads) void part_scatter_kernel(
     __shared__ int32_t all[kSmallThreads], before[kSmallThreads];   // [slice of the parts][expert]
     __shared__ int32_t below[kMaxExperts];
     const int tid = threadIdx.x, part = blockIdx.x, parts = gridDim.x;
-    const int slices = kSmallThreads / E;                 // >= 4 because E <= 256
+    // One thread per expert adds the slices up, so they are few: at most one per part and 64 in all (as many as
+    // threads allow, 1024 for one expert, took 18.1 us for 16384 ids of one expert and 12.0 of two, where three
+    // launches take 8.3 and 8.7; now 7.0 and 6.8). A thread then has up to 8 parts of few experts and up to 128 of
+    // 256, read eight at a time: one after the other in the remainder of an unrolled loop, 520000 ids of 8
+    // experts took 14.0 us, now 9.3.
+    const int slices = min(kSmallThreads / E, min(parts, 64));
     const int e = tid % E, q = tid / E;
     if (q < slices) {
+        constexpr int N = 8;
         int sum = 0, lower = 0;
-#pragma unroll 16
-        for (int g = q; g < parts; g += slices) {
-            const int v = part_hist[static_cast<size_t>(g) * E + e];
-            sum += v;
-            lower += g < part ? v : 0;
+        for (int g0 = q; g0 < parts; g0 += N * slices) {
+            int v[N];
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int g = g0 + i * slices;
+                v[i] = g < parts ? part_hist[static_cast<size_t>(g) * E + e] : 0;
+            }
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                sum += v[i];
+                lower += g0 + i * slices < part ? v[i] : 0;
+            }
         }
         all[tid] = sum;
         before[tid] = lower;

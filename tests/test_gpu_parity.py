@@ -381,6 +381,35 @@ def test_permute_bit_exact_where_the_launches_change(T, E, k):
     test_permute_bit_exact(T, E, k, T + E, False)
 
 
+@pytest.mark.parametrize("T,k,E", [
+    (4097, 1, 1), (524288, 1, 1), (2049, 2, 2), (70000, 1, 2), (30000, 3, 3), (262144, 2, 4),
+    (65536, 8, 8), (4098, 1, 255),
+])
+def test_permute_static_in_two_launches(T, k, E):
+    """Few experts make the workgroups of the second launch many slices of the parts' histograms to add up,
+    many experts few; every form against a stable sort. Ids outside [0, E) are dropped."""
+    check_permute_static(T, k, E, 0.02)
+
+
+def check_permute_static(T, k, E, dropped):
+    say(f"permute_static T={T} k={k} E={E}")
+    rng = np.random.default_rng(T + E)
+    flat = rng.integers(0, E, size=T * k).astype(np.int32)
+    flat[rng.random(T * k) < dropped] = E
+    flat[:: 4999] = -1
+    valid = (flat >= 0) & (flat < E)
+    order = np.argsort(np.where(valid, flat, E), kind="stable")[:valid.sum()]
+    counts, offsets, perm, inv = (torch.full((n,), -7, dtype=torch.int32, device="cuda") for n in (E, E + 1, T * k, T * k))
+    B.moe_permute_static(dev(flat), T, k, E, counts, offsets, perm, inv)
+    torch.cuda.synchronize()
+    want = np.bincount(flat[valid], minlength=E)
+    assert np.array_equal(counts.cpu().numpy(), want)
+    assert np.array_equal(offsets.cpu().numpy(), np.concatenate([[0], np.cumsum(want)]))
+    assert np.array_equal(perm.cpu().numpy()[:order.size], order)
+    inv_h = inv.cpu().numpy()
+    assert np.array_equal(inv_h[order], np.arange(order.size)) and np.all(inv_h[~valid] == -1)
+
+
 # ---------------------------------------------------------------- expert FFN and combine
 @pytest.mark.parametrize("config", [0, 0 + 128, 0 + 256, 0 + 512, 1, 2, 3, 4, 2 + 16, 3 + 32, 4 + 16, 4 + 32])   # +16 / +32: cached / non-temporal weights
 @pytest.mark.parametrize("d,f,rows", [
