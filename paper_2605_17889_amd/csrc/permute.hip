@@ -250,6 +250,7 @@ __global__ __launch_bounds__(kBlockWaves* kWave) void scatter_many_kernel(
 constexpr int kSmallWaves = 16;
 constexpr int kSmallThreads = kSmallWaves * kWave;
 constexpr int kMaxKeep = 4;
+constexpr int kPartTokens = kSmallThreads / 16;           // tokens that one workgroup selects at once
 struct SmallTables {
     int32_t table[kSmallWaves][kMaxExperts];              // per wavefront: count, then start position
     int32_t tot[kMaxExperts];
@@ -336,17 +337,15 @@ __global__ __launch_bounds__(kSmallWaves* kWave) void select_permute_kernel(
     int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm) {
     __shared__ SmallTables sm;
     __shared__ int32_t ids[kSmallWaves * kWave];
-    for (int t0 = 0; t0 < T; t0 += kSmallWaves * kWave / 16) {
-        const int t = t0 + threadIdx.x / 16;
-        // a wavefront without a token leaves its SIMD to the chains of those that have some (here and in
-        // permute_block: layer call of one token through 8 of 128 experts 35.9 -> 34.8 us)
-        if (t0 + __builtin_amdgcn_readfirstlane(threadIdx.x / 16) >= T) break;
+    const int t = threadIdx.x / 16;                       // T <= kPartTokens: one pass
+    // a wavefront without a token leaves its SIMD to the chains of those that have some (here and in
+    // permute_block: layer call of one token through 8 of 128 experts 35.9 -> 34.8 us)
+    if (__builtin_amdgcn_readfirstlane(t) < T)
         select_by_16_lanes<EW>(logits, t, t < T, threadIdx.x & 15, E, k, [&](int s, int e, float w) {
             topk_idx[t * k + s] = e;
             topk_w[t * k + s] = w;
             ids[t * k + s] = e;
         });
-    }
     __syncthreads();
     permute_block<1, false>(sm, ids, 0, T * k, E, counts, offsets, perm, inv_perm);
 }
@@ -358,7 +357,6 @@ __global__ __launch_bounds__(kSmallWaves* kWave) void select_permute_kernel(
 // 14.5 -> 7.4 us, 16384 of 8 11.2 -> 6.6, 520000 of 17 23.7 -> 10.5, 16384 of one 8.3 -> 7.0.
 constexpr int kMaxParts = 512;
 constexpr int kPartIds = kSmallThreads;                   // ids of a part that part_hist_kernel counts
-constexpr int kPartTokens = kSmallThreads / 16;           // tokens of one that select_hist_kernel counts
 
 __global__ __launch_bounds__(kSmallThreads) void part_hist_kernel(const int32_t* __restrict__ topk_idx, int R,
                                                                  int E, int32_t* __restrict__ part_hist) {
@@ -445,9 +443,10 @@ __global__ __launch_bounds__(kSmallThreads) void part_scatter_kernel(
             offsets[tid] = sm.off[tid];
         }
         if (tid == 0) offsets[E] = sm.off[E];
-        __syncthreads();
     }
-    if (tid < E) sm.off[tid] += below[tid];               // read after the barriers of permute_block
+    // each entry by the thread that has just read it; off[E] stays; the others read after the barriers of
+    // permute_block
+    if (tid < E) sm.off[tid] += below[tid];
     const int first = part * part_ids;
     permute_block<KEEP, true>(sm, topk_idx, first, min(R, first + part_ids), E, counts, offsets, perm, inv_perm);
 }
@@ -486,10 +485,9 @@ int permute_launches(int R) {
 
 int launch_permute(const int32_t* topk_idx, int R, int E, int32_t* counts, int32_t* offsets,
                    int32_t* perm, int32_t* inv_perm, int32_t* seg_tables, hipStream_t s) {
-    const int nseg = (R + kSegIds - 1) / kSegIds;
     if (R <= kSmallIds) {
-        const dim3 block(kSmallWaves * kWave);
-        if (R <= kSmallWaves * kWave)
+        const dim3 block(kSmallThreads);
+        if (R <= kSmallThreads)
             hipLaunchKernelGGL(permute_small_kernel<1>, dim3(1), block, 0, s, topk_idx, R, E, counts,
                                offsets, perm, inv_perm);
         else
@@ -504,25 +502,24 @@ int launch_permute(const int32_t* topk_idx, int R, int E, int32_t* counts, int32
                            kPartIds, seg_tables, counts, offsets, perm, inv_perm);
         return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
     }
+    const int nseg = (R + kSegIds - 1) / kSegIds;
     int32_t* seg_hist = seg_tables;
     int32_t* seg_base = seg_tables + static_cast<size_t>(nseg) * E;
     const int blocks = (nseg + kBlockWaves - 1) / kBlockWaves;
     const bool many = E > 16;            // one ballot per expert below, 9 per round above
-    if (nseg > 0)
-        hipLaunchKernelGGL(many ? hist_many_kernel : hist_kernel, dim3(blocks),
-                           dim3(kBlockWaves * kWave), 0, s, topk_idx, R, E, seg_hist);
+    hipLaunchKernelGGL(many ? hist_many_kernel : hist_kernel, dim3(blocks),
+                       dim3(kBlockWaves * kWave), 0, s, topk_idx, R, E, seg_hist);
     hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, s, seg_hist, nseg, E, counts, offsets,
                        seg_base);
-    if (nseg > 0)
-        hipLaunchKernelGGL(many ? scatter_many_kernel : scatter_kernel, dim3(blocks),
-                           dim3(kBlockWaves * kWave), 0, s, topk_idx, R, E, seg_base, perm, inv_perm);
+    hipLaunchKernelGGL(many ? scatter_many_kernel : scatter_kernel, dim3(blocks),
+                       dim3(kBlockWaves * kWave), 0, s, topk_idx, R, E, seg_base, perm, inv_perm);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
-// More tokens than one pass of the workgroup selects (64) would lengthen the kernel by as much as the
+// More tokens than one pass of the workgroup selects would lengthen the kernel by as much as the
 // launch that it saves.
 bool select_permute_fits(int T, int E, int k) {
-    return E > 16 && T <= 64 && T * k <= kSmallWaves * kWave;
+    return E > 16 && T <= kPartTokens && T * k <= kSmallThreads;
 }
 
 int launch_select_permute(const float* logits, int T, int E, int k, int32_t* topk_idx, float* topk_w,
