@@ -29,6 +29,10 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
         if (e__ != hipSuccess) return MOE_ERR_HIP; \
     } while (0)
 
+// Compute units of a device (0..63), asked once. Large tiles and the router's workgroups run in rounds of
+// that many.
+int compute_units(int device);
+
 // Launch wrappers (defined in the .hip files). Each returns a moe_status and only enqueues.
 int launch_route(const moe_bf16* x, const float* w_router, const float* bias, int T, int d, int E,
                  int k, int32_t* topk_idx, float* topk_w, float* logits_out,
@@ -58,7 +62,7 @@ int launch_gather(const moe_bf16* x, const int32_t* perm, const int32_t* offsets
 // moe_set_gemm_config (all settings give identical bits).
 struct GemmEnv {
     int device = 0;
-    int forced_config = -1;           // -1: automatic; 0..3: force a tile configuration
+    int forced_config = -1;           // -1: automatic; 0..4: force a tile configuration
     int stream_mode = -1;             // -1: automatic; 0: weights never non-temporal; 1: always
     bool materialise_gather = false;  // layer calls write x_perm instead of fusing the gather
     bool split_last_round = true;     // large tiles: halve the tiles of a last round under half full

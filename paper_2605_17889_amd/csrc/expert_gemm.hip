@@ -17,14 +17,7 @@
 #include "expert_gemm_kernel.h"
 
 namespace moe {
-namespace {
 
-using gemm::Config;
-template <bool F32, class Cfg>
-using Out = std::conditional_t<F32, gemm::F32Out<Cfg>, Cfg>;
-
-
-// Compute units of a device (rounds of the pipelined kernel are that many tiles long).
 int compute_units(int device) {
     static std::atomic<int> cached[64];
     int n = cached[device].load(std::memory_order_relaxed);
@@ -37,6 +30,12 @@ int compute_units(int device) {
     }
     return n;
 }
+
+namespace {
+
+using gemm::Config;
+template <bool F32, class Cfg>
+using Out = std::conditional_t<F32, gemm::F32Out<Cfg>, Cfg>;
 
 template <class Kernel, class... Args>
 int launch_tiles(const GemmEnv& env, std::atomic<uint64_t>& attr_set, Kernel kern, int smem,

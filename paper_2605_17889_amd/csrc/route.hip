@@ -777,10 +777,8 @@ __global__ __launch_bounds__(256) void route_few_kernel(const uint16_t* __restri
 }
 
 template <int EG, int TOK, bool SELECT>
-int launch_route_few(const moe_bf16* x, const float* wr, const float* bias, int T, int d, int E, int k,
+int launch_route_few(int device, const moe_bf16* x, const float* wr, const float* bias, int T, int d, int E, int k,
                      int32_t* idx, float* w, float* logits_out, hipStream_t s) {
-    int device = 0;
-    if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= 64) return MOE_ERR_HIP;
     static std::atomic<uint64_t> attr_set{0};           // one bit per device, as for the GEMM kernels
     if (!(attr_set.load(std::memory_order_acquire) & (1ull << device))) {
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(route_few_kernel<EG, TOK, SELECT>),
@@ -842,8 +840,11 @@ int launch_select_groups(const float* logits, int T, int E, int k, int32_t* idx,
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
-// Workgroups of the few-token kernel at most: one per compute unit (its LDS allows no second).
-constexpr int kFewBlocks = 256;
+// The calling thread's device, or -1 if there is none that the tables per device have room for.
+int current_device() {
+    int device = -1;
+    return hipGetDevice(&device) == hipSuccess && device >= 0 && device < 64 ? device : -1;
+}
 
 // The few-token and the matrix-core kernels load x and W_r straight into LDS, 16 bytes per lane, which wants
 // addresses that are multiples of 16. Views that start elsewhere go to the kernels whose loads pass through
@@ -869,13 +870,15 @@ int launch_route(const moe_bf16* x, const float* w_router, const float* bias, in
         const int rc = launch_route_logits(x, w_router, bias, T, d, E, logits, s);
         return rc != MOE_OK ? rc : launch_route_from_logits(logits, T, E, k, topk_idx, topk_w, s);
     }
-    // One round of few-token workgroups: 1024 tokens of 4096 take 8.1 us against 11.4 with the kernels
-    // below, 2048 tokens (two rounds) 14.3 against 11.8.
-    const int few = direct_to_lds_aligned(x, w_router) ? (T + 3) / 4 : kFewBlocks + 1;
-    if (E == 8 && few <= kFewBlocks)
-        return launch_route_few<8, 4, true>(x, w_router, bias, T, d, E, k, topk_idx, topk_w, logits_out, s);
-    if (E == 16 && few <= kFewBlocks)
-        return launch_route_few<16, 4, true>(x, w_router, bias, T, d, E, k, topk_idx, topk_w, logits_out, s);
+    const int device = current_device();
+    if (device < 0) return MOE_ERR_HIP;
+    // One round of few-token workgroups, one per compute unit (their LDS allows no second): 1024 tokens of
+    // 4096 take 8.1 us against 11.4 with the kernels below, 2048 tokens (two rounds) 14.3 against 11.8.
+    const bool few = direct_to_lds_aligned(x, w_router) && (T + 3) / 4 <= compute_units(device);
+    if (E == 8 && few)
+        return launch_route_few<8, 4, true>(device, x, w_router, bias, T, d, E, k, topk_idx, topk_w, logits_out, s);
+    if (E == 16 && few)
+        return launch_route_few<16, 4, true>(device, x, w_router, bias, T, d, E, k, topk_idx, topk_w, logits_out, s);
     // 8 wavefronts share one staged slice of W_r: half the staging work per token of 4-wave blocks
     if (E == 8) return launch_route_lds<8, 2, 8>(x, w_router, bias, T, d, k, topk_idx, topk_w, logits_out, s);
     if (E == 16) return launch_route_lds<16, 2, 8>(x, w_router, bias, T, d, k, topk_idx, topk_w, logits_out, s);
@@ -887,21 +890,22 @@ int launch_route(const moe_bf16* x, const float* w_router, const float* bias, in
 int launch_route_logits(const moe_bf16* x, const float* w_router, const float* bias, int T, int d, int E,
                         float* logits, hipStream_t s) {
     if (T == 0) return MOE_OK;
+    const int device = current_device();
+    if (device < 0) return MOE_ERR_HIP;
+    const int cus = compute_units(device);
     constexpr int TOK = 4;
     const dim3 grid((T + 4 * TOK - 1) / (4 * TOK), (E + 15) / 16);
     // one round of few-token workgroups, a token each while that fits (37 tokens through 128 experts in
     // two rounds of one token 14.2 us, in one of four 12.0; 100 in one 12.9, 192 in two 17.1 against 16.4)
     const bool direct = E % 16 == 0 && direct_to_lds_aligned(x, w_router);
-    if (direct && static_cast<long long>(T) * (E / 16) <= kFewBlocks)
-        return launch_route_few<16, 1, false>(x, w_router, bias, T, d, E, 0, nullptr, nullptr, logits, s);
-    if (direct && static_cast<long long>((T + 3) / 4) * (E / 16) <= kFewBlocks)
-        return launch_route_few<16, 4, false>(x, w_router, bias, T, d, E, 0, nullptr, nullptr, logits, s);
+    if (direct && static_cast<long long>(T) * (E / 16) <= cus)
+        return launch_route_few<16, 1, false>(device, x, w_router, bias, T, d, E, 0, nullptr, nullptr, logits, s);
+    if (direct && static_cast<long long>((T + 3) / 4) * (E / 16) <= cus)
+        return launch_route_few<16, 4, false>(device, x, w_router, bias, T, d, E, 0, nullptr, nullptr, logits, s);
     // Full groups and at least 128 tiles of 64 tokens x 16 experts: the matrix-core form. One
     // tile takes it about as long as 130 k (token, expert) pairs take the vector-unit
     // kernel, whatever the number of tiles up to one per compute unit (measured crossover).
     if (direct && static_cast<long long>((T + 63) / 64) * (E / 16) >= 128) {
-        int device = 0;
-        if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= 64) return MOE_ERR_HIP;
         static std::atomic<uint64_t> attr_set{0};     // one bit per device, as for the GEMM kernels
         if (!(attr_set.load(std::memory_order_acquire) & (1ull << device))) {
             if (hipFuncSetAttribute(reinterpret_cast<const void*>(route_logits_mfma_kernel),
@@ -913,14 +917,6 @@ int launch_route_logits(const moe_bf16* x, const float* w_router, const float* b
         // one workgroup per compute unit (LDS and registers allow no more), each working
         // through its share of the tiles with the operand ring running across tile borders
         const long long tiles = static_cast<long long>(((T + 63) / 64 + kXcds - 1) / kXcds) * kXcds * (E / 16);
-        static std::atomic<int> cus_of[64];           // compute units per device, asked once
-        int cus = cus_of[device].load(std::memory_order_relaxed);
-        if (cus == 0) {
-            if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
-                cus <= 0)
-                return MOE_ERR_HIP;
-            cus_of[device].store(cus, std::memory_order_relaxed);
-        }
         const long long grid = std::min<long long>(tiles, std::max(kXcds, cus / kXcds * kXcds));
         hipLaunchKernelGGL(route_logits_mfma_kernel, dim3(static_cast<unsigned>(grid)),
                            dim3(256), RouteMfma::SMEM, s, x, w_router, bias, T, d, E, logits);
