@@ -129,6 +129,23 @@ double large_minus_mid(double units0, double tiles0, double tiles1, int cus) {
 }
 
 // Tile configuration by average rows per expert. All configurations give identical bits.
+//
+// The measured constants of this rule and of the variants in launch_gateup and launch_down, and what each stands
+// on ("cold": a graph of calls with other weights every time, 1.2 GB and more of them; else the same ones):
+//   0.8         a 128-row tile (or its padded row) against a 256-row one: micro-batches of 64 to 512 tokens
+//               at 6144 x 16384, 8 experts; 0.55 a half-height tile, 1.25 large tiles in under four rounds:
+//               micro-batches of 1024 and 2048 tokens there
+//   0.82, 0.6   k-step of a 96- or 128-row tile (256 or 128 columns), 0.41 / 0.58 and 0.27 / 0.38 of one 64-row
+//               tile alone on a compute unit / of two: one expert of 4096 x 14336, 512 rows (below)
+//   0.56, 0.8   k-step of a 256-row tile where at most half the compute units have one, weights from cache / from
+//   (64 MB)     memory. The line only has to keep large weights from the lower price: 512 rows through one
+//               expert of 4096 x 14336 234 us a layer cold with 0.8, 293 with 0.56. Layers of up to 64 MB differ
+//               by -4 to +5 % either way, cold or not (1024 rows through 4 of 2048 x 1408 cold 82.7 us with 0.56,
+//               80.8 with 0.8; 1600 through 8 of 2048 x 768 61.6 and 64.5), and of three such layers, 256 to 6000
+//               rows, none is over 1 % slower cold than with the 128- or the 256-row tiles throughout
+//   + 3, + 6    a tile's cost outside its reduction, in k-steps, and 0.9 the margin that small tiles have to win by:
+//               512 and 900 tokens through 8 experts of 512 x 1024 (below)
+//   0.93        seven stages against four, 2.5 16-row gate/up tiles, 3.5 128 columns down: where they are used
 int pick_config(const GemmEnv& env, int R, int E, const NTiles& nt) {
     if (env.forced_config >= 0) return env.forced_config;
     // 0: pipelined 256-row tiles (with half-height tails). 1: 128-row tiles (generic kernel).
@@ -293,9 +310,13 @@ int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_inde
             if (single_m_tile(env, R_hint, E, 32)) {
                 const double nt = touched_experts(R_hint, E) * (f / 64);
                 const int cus = compute_units(env.device);
-                // 16-row tiles of half the width while they fit three to a compute unit at once:
-                // one token through 8 of 128 experts of 2048 x 768 12.7 against 14.3 us, three
-                // tokens 27 against 31; four tokens (more than one round) 46 against 41
+                // 16-row tiles of half the width while up to two and a half of them go to a compute unit. Layer
+                // calls with cold weights, against the 32-row tiles: one token through 8 of 128 experts of 2048 x
+                // 768 (0.7 per compute unit) 37.0 and 39.0 us, 2 through 6 of 64 of 2048 x 1408 (1.9) 56 and 64, 8
+                // through 4 of 64 of 4096 x 768 (2.4) 103 and 111; below the line none was slower by over 1 %.
+                // Three fit at once, but from 2.5 to 3.0 the sides are mixed: 10 tokens, 4 of 32 of 1024 x 1024
+                // (2.85) 37.5 and 39.4, but 30, 2 of 16 of 2048 x 1536 (2.93) 69.9 and 67.2, and 90, 2 of 24 of
+                // 1024 x 1024 (3.0) 49.3 and 45.2; past it they lose (5 tokens, 8 of 128, 3.2: 80 and 72)
                 if (2.0 * nt <= 2.5 * cus && single_m_tile(env, R_hint, E, 16))
                     return launch_grouped<GateUpFewS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
                 // 16 tokens through 8 experts of 4096 x 14336, 7 rounds of one workgroup per compute unit or
@@ -360,9 +381,11 @@ int launch_down_as(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets
             }
             return launch_grouped<Out<F32, DownTiny>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
         default:
-            // 128 columns where that makes two rounds of two workgroups per compute unit (500 tokens
-            // through 128 experts of 2048 x 768: 74 against 79 us), else 64 (110 tokens through 8 experts
-            // of 6144 x 16384, 384 or 768 tiles: 297 against 264 us)
+            // 128 columns where that makes about two rounds of two workgroups per compute unit, else 64. Layer calls
+            // with cold weights, 128 against 64 columns: 500 tokens through 128 experts of 2048 x 768 (8 tiles of 128
+            // columns per compute unit) 239 and 243 us, 448 through 56 of 2048 x 1024, 4 per token (3.5) 149.2 and
+            // 150.5; 110 tokens through 8 of 6144 x 16384 (1.5) 806 and 783. In between the sides are mixed (3.0: 384
+            // tokens through 48 of 2048 x 1024 128.7 and 134.6, 192 through 24 of 4096 x 2048 242 and 238)
             if (touched_experts(R_hint, E) * (d / 128) >= 3.5 * cus) {
                 if (single_m_tile(env, R_hint, E, 64))
                     return launch_grouped<Out<F32, DownSmallWideS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
