@@ -200,6 +200,14 @@ def test_layer_selects_and_permutes_like_the_stage_calls(T, k, E):
     ctx.close()
 
 
+@pytest.mark.parametrize("T,k,E", [
+    (32768, 4, 256), (32769, 4, 256),      # the last batch whose histograms are counted with the selection, and the next
+    (32768, 5, 17), (65, 64, 64), (127, 64, 256), (4097, 63, 100),      # up to 4096 ids in a part of 64 tokens
+])
+def test_layer_selects_and_permutes_like_the_stage_calls_at_the_limits(T, k, E):
+    test_layer_selects_and_permutes_like_the_stage_calls(T, k, E)
+
+
 def test_route_matrix_core_logits_extreme_values():
     """The matrix-core logits kernel (E a multiple of 16, many tokens) must round every
     multiply-add like fmaf, denormal products and sums, signed zeros and wide exponent ranges
@@ -388,6 +396,16 @@ def test_permute_bit_exact_where_the_launches_change(T, E, k):
 def test_permute_static_in_two_launches(T, k, E):
     """Few experts make the workgroups of the second launch many slices of the parts' histograms to add up,
     many experts few; every form against a stable sort. Ids outside [0, E) are dropped."""
+    check_permute_static(T, k, E, 0.02)
+
+
+@pytest.mark.parametrize("T,k,E", [
+    (524289, 1, 1), (262145, 2, 3), (65537, 8, 8), (300001, 2, 16),      # one ballot per expert
+    (524289, 1, 17), (100000, 6, 24),                                    # one per bit of its index
+])
+def test_permute_static_in_three_launches(T, k, E):
+    """The least ids of the form that counts and scatters by wavefronts, and more, on both sides of the
+    number of experts where its kernels change."""
     check_permute_static(T, k, E, 0.02)
 
 
@@ -926,6 +944,37 @@ def test_layer_streamed_back_to_back_without_host_sync(n_streamed):
     torch.cuda.synchronize()
     for i, y in enumerate(ys):
         assert np.array_equal(bits(y), want[i]), f"call {i} used another call's weights"
+    ctx.close()
+
+
+def test_layer_streamed_calls_of_changing_counts_without_host_sync():
+    """Streamed calls with other numbers of streamed experts one behind the other, the two staging slots
+    taken in turn across them: after an odd count the next call starts with the other slot, whose last expert
+    may belong to the same call or to one before. Every call has weights of its own and a stream that is busy
+    beforehand; gate/up may start when W1 and W3 have landed, the down projection when W2 has."""
+    cfg = synth.PRESETS["tiny"]
+    counts = [1, 2, 1, 3, 3, 1, 0, 8, 1, 1, 5, 2]
+    say(f"layer tiny, streamed calls of {counts} experts back to back")
+    E, T = cfg.E, cfg.T
+    ctx = B.MoeContext(T, cfg.d_model, cfg.d_ff, E, cfg.k)
+    base = synth.make_layer(cfg, "cuda")
+    calls = []
+    for i, n in enumerate(counts):
+        W = synth.make_experts(dataclasses.replace(cfg, seed=40 + i % 5), "cuda")
+        L = dict(base, W1=W[0], W3=W[1], W2=W[2])
+        host = [pinned_tail(L[m], n) if n else None for m in ("W1", "W3", "W2")]
+        dev_w = [L[m][:E - n].contiguous() if n < E else None for m in ("W1", "W3", "W2")]
+        y = torch.full((T, cfg.d_model), float("nan"), dtype=torch.bfloat16, device="cuda")
+        calls.append((n, host, dev_w, y, bits(run_layer(cfg, L, ctx=ctx)[0]).copy()))
+    busy = torch.randn((8192, 8192), device="cuda", dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    for _ in range(40):                       # tens of milliseconds of queued work
+        busy = (busy @ busy).clamp_(-1, 1)
+    for n, host, dev_w, y, _ in calls:
+        B.moe_layer_forward_streamed(ctx, base["x"], base["w_router"], base["bias"], *dev_w, *host, n, T, y)
+    torch.cuda.synchronize()
+    for i, (n, _, _, y, want) in enumerate(calls):
+        assert np.array_equal(bits(y), want), f"call {i} ({n} streamed) used another call's weights"
     ctx.close()
 
 
