@@ -130,7 +130,7 @@ int moe_permute(moe_ctx* ctx, const int32_t* topk_idx, int32_t T, int32_t* count
 /* moe_permute's grouping for callers that cannot allocate device memory or create a context
  * (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): no
  * moe_ctx, no allocation of any kind. The segment tables that moe_permute keeps in the context
- * workspace live in a static device array of the library instead (1 MiB per GPU, held until the
+ * workspace live in a static device array of the library instead (512 KiB per GPU, held until the
  * process ends), so the size is bounded: ceil(T*k / 256) * E <= 65536 (e.g. T*k <= 2,097,152 ids
  * at E = 8, 65,536 ids at E = 256); larger inputs return MOE_ERR_UNSUPPORTED_SHAPE. Same outputs
  * as moe_permute bit for bit (same kernels); no row gather. 1 <= k <= min(E, 64), E <= 256.
