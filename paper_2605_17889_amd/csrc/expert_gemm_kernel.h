@@ -247,6 +247,27 @@ __device__ __forceinline__ TileCoord locate_tile(const int32_t* __restrict__ off
     return tc;
 }
 
+// Where a tile's reduction starts: at k-step first(), running to the end and round to the steps before it. The
+// workgroups of a launch of about one round start together and stay in step, so that with all of them at
+// the same k their weight rows, a whole reduction apart, fall on few memory channels at a time. The start
+// depends on the expert of the layer and the block of kRotateCols output columns alone, so that every tile
+// configuration and every call form sums an element in the same order, and the tiles of an expert that
+// share activation rows in an L2 (large tiles: 8 x 4 resident at a time) mostly stay at the same k.
+constexpr int kRotateCols = 1024;
+struct KStart {
+    int mul;       // k-steps between neighbouring blocks, or 0: all at k = 0
+    int e0;        // the layer's number of the launch's first expert
+    int blocks;    // blocks of kRotateCols columns per expert
+    template <class Cfg>
+    __device__ __forceinline__ int first(const TileCoord& tc, int ksteps) const {
+        static_assert(kRotateCols % Cfg::BN_OUT == 0, "a tile lies in one block");
+        if (Cfg::DUAL || mul == 0) return 0;
+        int rem;
+        div_small(((e0 + tc.expert) * blocks + tc.nt * Cfg::BN_OUT / kRotateCols) * mul, ksteps, rem);
+        return rem;
+    }
+};
+
 // LDS tile layout: rows of BK bf16 in 16-byte chunks; logical chunk c of row r is stored at
 // chunk position c ^ swz(r). LDS has 64 four-byte banks and a 16-byte read is served 16 lanes
 // at a time; the 16 lanes of a fragment read the same logical chunk of 16 consecutive rows,
@@ -547,7 +568,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
     const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ row_index, RowDiv index_div,
-    int E, int N, int K) {
+    KStart kstart, int E, int N, int K) {
     constexpr int BM = Cfg::BM, BK = Cfg::BK, WN = Cfg::WN;
     constexpr int TM = Cfg::TM, TN = Cfg::TN, LPW = Cfg::LPW, NSTAGE = Cfg::NSTAGE;
 
@@ -574,9 +595,14 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
 
     // ---- main loop: ring of NSTAGE stages, NSTAGE-1 k-steps of loads in flight.
     const int KT = K / BK;
+    int kload = kstart.first<Cfg>(tc, KT);     // k-step of the next load
+    auto issue = [&](int st) {
+        lp.issue_all(st * Cfg::STAGE_BYTES, static_cast<size_t>(kload) * BK);
+        kload = kload + 1 == KT ? 0 : kload + 1;
+    };
 #pragma unroll
     for (int s = 0; s < NSTAGE - 1; ++s)
-        if (s < KT) lp.issue_all(s * Cfg::STAGE_BYTES, static_cast<size_t>(s) * BK);
+        if (s < KT) issue(s);
     int stage = 0;
     for (int kt = 0; kt < KT; ++kt) {
         // The loads of k-step kt are the oldest in flight; up to NSTAGE-2 newer steps may stay
@@ -584,10 +610,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
         if (kt + NSTAGE - 2 < KT) wait_vmcnt<(NSTAGE - 2) * LPW>(); else wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();          // stage `stage` is complete for every wavefront
                                                // and stage (stage-1) is no longer being read
-        const int nk = kt + NSTAGE - 1;
-        if (nk < KT)
-            lp.issue_all((stage == 0 ? NSTAGE - 1 : stage - 1) * Cfg::STAGE_BYTES,
-                         static_cast<size_t>(nk) * BK);
+        if (kt + NSTAGE - 1 < KT) issue(stage == 0 ? NSTAGE - 1 : stage - 1);
         mma_stage<Cfg>(smem + stage * Cfg::STAGE_BYTES, fp, acc);
         stage = (stage + 1 == NSTAGE) ? 0 : stage + 1;
     }
@@ -709,7 +732,7 @@ __device__ __forceinline__ void ring_tile(const TileCoord& tc, unsigned char* sm
                                           const uint16_t* __restrict__ B0,
                                           const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
                                           const int32_t* __restrict__ row_index, RowDiv index_div,
-                                          int N, int K) {
+                                          KStart kstart, int N, int K) {
     using R = RingCfg<Cfg, NA, NB>;
     constexpr int BM = Cfg::BM, BK = Cfg::BK, WN = Cfg::WN, TM = Cfg::TM, TN = Cfg::TN;
     constexpr int LA = R::LA, LB = R::LB, AB = Cfg::A_BYTES, BB = Cfg::B_BYTES;
@@ -737,13 +760,18 @@ __device__ __forceinline__ void ring_tile(const TileCoord& tc, unsigned char* sm
 
     const int KT = K / BK;                           // >= max(NA, NB) (checked by the launcher)
     constexpr int NMAX = NA < NB ? NB : NA;
+    const int k0 = kstart.first<Cfg>(tc, KT);
+    auto k_offset = [&](int step) {                  // of the step-th k-step of this tile
+        step += k0;
+        return static_cast<size_t>(step >= KT ? step - KT : step) * BK;
+    };
 
     auto run = [&](auto compute_tag, auto partial_tag) {
         constexpr bool COMPUTE = decltype(compute_tag)::value, PARTIAL = decltype(partial_tag)::value;
         // prologue: fill both rings in the order the k-loop would have issued them
 #pragma unroll
         for (int s = 0; s < NMAX; ++s) {
-            const size_t koff = static_cast<size_t>(s) * BK;
+            const size_t koff = k_offset(s);
             if (R::A_FIRST) {
                 if (s < NA) for (int i = 0; i < LA; ++i) if (!PARTIAL || lp.a_on[i]) lp.issue_a(i, s * AB, koff);
                 if (s < NB) for (int i = 0; i < LB; ++i) lp.issue_b(i, R::A_RING + s * BB, koff);
@@ -773,7 +801,7 @@ __device__ __forceinline__ void ring_tile(const TileCoord& tc, unsigned char* sm
             ring_kstep<Cfg, NA, NB, COMPUTE, PARTIAL, RT>(
                 acc, fa, fx, fb0, fb1, pa[1] + ra * AB, pb[1] + rb * BB, pa[0] + ra1 * AB,
                 pb[0] + rb1 * BB, lp, ra * AB, R::A_RING + rb * BB,
-                static_cast<size_t>(kt + NA) * BK, static_cast<size_t>(kt + NB) * BK, kt + NA < KT,
+                k_offset(kt + NA), k_offset(kt + NB), kt + NA < KT,
                 kt + NB < KT, kt + 1 < KT);
             ra = ra1; rb = rb1;
         };
@@ -903,12 +931,16 @@ struct LoadPlan1W {
     const uint16_t* b_ptr[2];       // expert's W (and W3 with DUAL) + current k offset of the B loads
     uint32_t a_voff[LA], b_voff[LB];
     uint32_t a_lds, b_lds;          // this wavefront's first load inside an A / B stage
+    int ksteps, wrap;               // of the reduction; of those, up to its end (then it starts over at k = 0)
     __device__ __forceinline__ void init(const TileCoord& tc, int wave, int lane, const uint16_t* A,
                                          const uint16_t* B0, const uint16_t* B1,
-                                         const int32_t* row_index, RowDiv index_div, int N, int K) {
+                                         const int32_t* row_index, RowDiv index_div, KStart kstart, int N, int K) {
         const int lrow = lane / Cfg::CPR, lpos = lane % Cfg::CPR;
-        a_ptr = a_origin(A, tc, row_index, K);
-        const size_t expert_off = static_cast<size_t>(tc.expert) * N * K;
+        ksteps = K / Cfg::BK;
+        const int k0 = kstart.first<Cfg>(tc, ksteps);
+        wrap = ksteps - k0;
+        a_ptr = a_origin(A, tc, row_index, K) + k0 * Cfg::BK;
+        const size_t expert_off = static_cast<size_t>(tc.expert) * N * K + k0 * Cfg::BK;
         b_ptr[0] = B0 + expert_off;
         b_ptr[1] = Cfg::DUAL ? B1 + expert_off : b_ptr[0];
         int src[LA];
@@ -926,6 +958,12 @@ struct LoadPlan1W {
         }
         a_lds = wave * LA * 1024;
         b_lds = wave * LB * 1024;
+    }
+    // elements to move a pointer by once the tile's k-step `step` is loaded: none past the last one
+    __device__ __forceinline__ int advance(int step) const {
+        const int on = step + 1 < ksteps ? Cfg::BK : 0;
+        if constexpr (Cfg::DUAL) return on;
+        return step + 1 == wrap && on ? (1 - ksteps) * Cfg::BK : on;
     }
     // weight matrix of B load i (W1 and W3 rows alternate in blocks of 32 tile rows)
     __device__ __forceinline__ const uint16_t* b_src(int wave, int i) const {
@@ -980,8 +1018,7 @@ template <class Cfg, int NA, int NB>
 __device__ __forceinline__ void kstep_1w(f32x4 (&acc)[Cfg::TM][8], bf16x8 (&fa)[2][Cfg::TM],
                                          bf16x8 (&fb)[2][8], RingState1W& rs, LoadPlan1W<Cfg>& lp,
                                          int wave, const unsigned char* pa0, const unsigned char* pa1,
-                                         const unsigned char* pb0, const unsigned char* pb1, int kt,
-                                         int KT) {
+                                         const unsigned char* pb0, const unsigned char* pb1, int kt) {
     using R = RingCfg<Cfg, NA, NB>;
     constexpr int TM = Cfg::TM, NM = TM * 8, NR = TM + 8;      // MFMAs and fragment reads per half
     constexpr int LA = LoadPlan1W<Cfg>::LA, LB = LoadPlan1W<Cfg>::LB;
@@ -1008,6 +1045,7 @@ __device__ __forceinline__ void kstep_1w(f32x4 (&acc)[Cfg::TM][8], bf16x8 (&fa)[
     };
     // ---- first half: MFMAs on f[0]; read f[1] (second half of this k-step); the eight B loads
     //      (with DUAL: four loads of W1 rows, then four of W3 rows)
+    int a_adv = 0, b_adv = 0;
     auto first = [&](auto mtag) {
         constexpr int m = decltype(mtag)::value, i = m >> 3, j = m & 7, n = m / (NM / 8);
         const void* src = lp.b_src(wave, n < 8 ? n : 0);
@@ -1017,10 +1055,11 @@ __device__ __forceinline__ void kstep_1w(f32x4 (&acc)[Cfg::TM][8], bf16x8 (&fa)[
         // the B pointers move on behind the last B load (MFMA 7 * NM / 8 + 3) while a later k-step exists
         constexpr int after_loads = 7 * (NM / 8) + 4;
         if constexpr (m == (after_loads < NM ? after_loads + 1 : NM - 1)) {
-            lp.b_ptr[0] += (kt + NB < KT) ? Cfg::BK : 0;
-            if (Cfg::DUAL) lp.b_ptr[1] += (kt + NB < KT) ? Cfg::BK : 0;
+            lp.b_ptr[0] += b_adv;
+            if (Cfg::DUAL) lp.b_ptr[1] += b_adv;
             MOE_FENCE();
         }
+        if constexpr (m == NM - 6) { b_adv = lp.advance(kt + NB - 1); MOE_FENCE(); }
     };
     // ---- second half: MFMAs on f[1]; read f[0] of k-step kt+1; the A loads; the next k-step's
     //      ring addresses, one small step behind an MFMA at a time
@@ -1042,7 +1081,8 @@ __device__ __forceinline__ void kstep_1w(f32x4 (&acc)[Cfg::TM][8], bf16x8 (&fa)[
         if constexpr (m == 17) { nx.pb_n0 = pb0 + sb2; MOE_FENCE(); }
         if constexpr (m == 18) { nx.a_region = sa1 + lp.a_lds; MOE_FENCE(); }
         if constexpr (m == 21) { nx.b_region = R::A_RING + rs.sb + lp.b_lds; MOE_FENCE(); }
-        if constexpr (m == NM - 3) { lp.a_ptr += (kt + NA + 1 < KT) ? Cfg::BK : 0; MOE_FENCE(); }
+        if constexpr (m == 22) { a_adv = lp.advance(kt + NA); MOE_FENCE(); }
+        if constexpr (m == NM - 3) { lp.a_ptr += a_adv; MOE_FENCE(); }
     };
     static_for<NM>(first);
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(LB) : "memory");
@@ -1062,22 +1102,22 @@ __device__ __forceinline__ void prologue_1w(const TileCoord& tc, LoadPlan1W<Cfg>
                                             const uint16_t* __restrict__ B0,
                                             const uint16_t* __restrict__ B1,
                                             const int32_t* __restrict__ row_index, RowDiv index_div,
-                                            int N, int K) {
+                                            KStart kstart, int N, int K) {
     using R = RingCfg<Cfg, NA, NB>;
-    constexpr int BK = Cfg::BK, LA = R::LA, LB = R::LB, AB = Cfg::A_BYTES, BB = Cfg::B_BYTES;
+    constexpr int LA = R::LA, LB = R::LB, AB = Cfg::A_BYTES, BB = Cfg::B_BYTES;
     static_assert(NB - 1 == NA, "prologue order");
-    lp.init(tc, wave, lane, A, B0, B1, row_index, index_div, N, K);
+    lp.init(tc, wave, lane, A, B0, B1, row_index, index_div, kstart, N, K);
 #pragma unroll
     for (int s = 0; s < NA; ++s) {
 #pragma unroll
         for (int i = 0; i < LA; ++i) dma16(lp.a_ptr, lp.a_voff[i], s * AB + lp.a_lds + i * 1024);
-        lp.a_ptr += BK;
+        lp.a_ptr += lp.advance(s);
         if (s < NB - 1) {
 #pragma unroll
             for (int i = 0; i < LB; ++i)
                 dma16(lp.b_src(wave, i), lp.b_voff[i], R::A_RING + s * BB + lp.b_lds + i * 1024);
-            lp.b_ptr[0] += BK;
-            if (Cfg::DUAL) lp.b_ptr[1] += BK;
+            lp.b_ptr[0] += lp.advance(s);
+            if (Cfg::DUAL) lp.b_ptr[1] += lp.advance(s);
         }
     }
 }
@@ -1128,8 +1168,8 @@ __device__ __forceinline__ void mainloop_1w(f32x4 (&acc)[Cfg::TM][8], LoadPlan1W
     // two k-steps per trip (K is a multiple of 128 for every supported shape): the loop's own
     // compare-and-branch then falls between MFMAs half as often
     for (int kt = 0; kt < KT; kt += 2) {
-        kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1], kt, KT);
-        kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1], kt + 1, KT);
+        kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1], kt);
+        kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1], kt + 1);
     }
     mfma_drain(acc[TM - 1]);                         // before anything else touches the accumulators
 }
@@ -1140,12 +1180,12 @@ __device__ __forceinline__ void ring_tile_1w(const TileCoord& tc, unsigned char*
                                              const uint16_t* __restrict__ B0,
                                              const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
                                              const int32_t* __restrict__ row_index, RowDiv index_div,
-                                             int N, int K) {
+                                             KStart kstart, int N, int K) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     LoadPlan1W<Cfg> lp;
-    prologue_1w<Cfg, NA, NB>(tc, lp, wave, lane, A, B0, B1, row_index, index_div, N, K);
+    prologue_1w<Cfg, NA, NB>(tc, lp, wave, lane, A, B0, B1, row_index, index_div, kstart, N, K);
     FragPlan<Cfg> fp;
     fp.init(lane, wave / Cfg::WN, wave % Cfg::WN);
     f32x4 acc[Cfg::TM][Cfg::TN];
@@ -1169,7 +1209,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_ring_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
     const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ row_index, RowDiv index_div,
-    int E, int N, int K, int split_cus) {
+    KStart kstart, int E, int N, int K, int split_cus) {
     static_assert(HalfCfg::BM * 2 == Cfg::BM && HalfCfg::BN == Cfg::BN && HalfCfg::BK == Cfg::BK &&
                   HalfCfg::NTHREADS == Cfg::NTHREADS && HalfCfg::DUAL == Cfg::DUAL, "same n-tiling");
     static_assert(RingCfg<HalfCfg, NA, NB>::SMEM <= RingCfg<Cfg, NA, NB>::SMEM, "LDS of the full tile");
@@ -1180,14 +1220,14 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_ring_kernel(
     // four wavefronts of (128 or 64) x 128 outputs run the one-wavefront-per-SIMD pipeline
     if (tc.rows <= HalfCfg::BM) {
         if constexpr (HalfCfg::NW == 4 && HalfCfg::TN == 8)
-            ring_tile_1w<HalfCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, N, K);
+            ring_tile_1w<HalfCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, kstart, N, K);
         else
-            ring_tile<HalfCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, N, K);
+            ring_tile<HalfCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, kstart, N, K);
     } else {
         if constexpr (Cfg::NW == 4 && Cfg::TN == 8)
-            ring_tile_1w<Cfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, N, K);
+            ring_tile_1w<Cfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, kstart, N, K);
         else
-            ring_tile<Cfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, N, K);
+            ring_tile<Cfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, kstart, N, K);
     }
 }
 

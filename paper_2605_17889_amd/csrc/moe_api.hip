@@ -162,7 +162,7 @@ int forward_chunk(moe_ctx* c, const moe_bf16* x, const float* w_router, const fl
     });
     if (rc != MOE_OK) return rc;
     rc = run_stage(c, MOE_STAGE_DOWN, 1, s, [&] {
-        return launch_down(c->gemm, c->H, c->offsets, R, R, d, f, E, W2, expert_out(c), c->y_perm_f32 != nullptr, s);
+        return launch_down(c->gemm, c->H, c->offsets, R, R, d, f, 0, E, W2, expert_out(c), c->y_perm_f32 != nullptr, s);
     });
     if (rc != MOE_OK) return rc;
     return run_stage(c, MOE_STAGE_COMBINE, 1, s, [&] {
@@ -349,7 +349,7 @@ int moe_expert_ffn(moe_ctx* c, const moe_bf16* x_perm, const int32_t* offsets, i
     });
     if (rc != MOE_OK) return rc;
     return run_stage(c, MOE_STAGE_DOWN, 1, s, [&] {
-        return launch_down(c->gemm, c->H, offsets, R, R, sh.d_model, sh.d_ff, sh.E, W2, y_perm, false, s);
+        return launch_down(c->gemm, c->H, offsets, R, R, sh.d_model, sh.d_ff, 0, sh.E, W2, y_perm, false, s);
     });
 }
 
@@ -451,7 +451,7 @@ int moe_layer_forward_streamed(moe_ctx* c, const moe_bf16* x, const float* w_rou
     auto down = [&](int e0, int n, const moe_bf16* w2) -> int {
         const int hint = static_cast<int>(static_cast<long long>(R) * n / E);
         return run_stage(c, MOE_STAGE_DOWN, 1, s, [&] {
-            return launch_down(c->gemm, c->H, c->offsets + e0, R, hint, d, f, n, w2, expert_out(c), c->y_perm_f32 != nullptr, s);
+            return launch_down(c->gemm, c->H, c->offsets + e0, R, hint, d, f, e0, n, w2, expert_out(c), c->y_perm_f32 != nullptr, s);
         });
     };
     if (E_res > 0) {

@@ -1057,6 +1057,38 @@ def test_layer_other_expert_shapes(T, d, f, E, k, use_bias):
     ctx.close()
 
 
+@pytest.mark.parametrize("T,d,f,E,k", [
+    (600, 1536, 2048, 10, 2),      # the shortest staggered reduction; starts at its first, last and last but one k-step
+    (90, 512, 2176, 40, 3),        # k-steps that seven does not divide, one block of columns
+])
+def test_layer_staggered_reductions(T, d, f, E, k):
+    """The down projection of a long reduction starts at another k per expert and block of columns: every
+    tile configuration and call form has to start at the same one."""
+    say(f"layer T={T} d={d} f={f} E={E} k={k}: staggered reductions")
+    cfg = synth.LayerConfig("custom", T, d, f, E, k, seed=77)
+    L = synth.make_layer(cfg, "cuda")
+    Hh = host_layer(L)
+    y, ctx = run_layer(cfg, L)
+    tokens = np.arange(0, T, 7, dtype=np.int32)
+    want, _, _ = ref.layer_tokens(Hh["x"], Hh["w_router"], None, Hh["W1"], Hh["W3"], Hh["W2"], k, tokens)
+    assert_close_ffn(bits(y)[tokens], want, "staggered reductions")
+    same = lambda other, what: np.testing.assert_array_equal(bits(other), bits(y), what)
+    for config in ALL_TILE_CONFIGS:
+        B.moe_set_gemm_config(ctx, config)
+        same(run_layer(cfg, L, ctx=ctx)[0], f"config {config}")
+    B.moe_set_gemm_config(ctx, -1)
+    for m in (1, 37, 512):
+        same(run_layer(cfg, L, micro=m, ctx=ctx)[0], f"micro-batches of {m}")
+    n = 3
+    host = [pinned_tail(L[name], n) for name in ("W1", "W3", "W2")]
+    dev_w = [L[name][:E - n].contiguous() for name in ("W1", "W3", "W2")]
+    ys = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    B.moe_layer_forward_streamed(ctx, L["x"], L["w_router"], L["bias"], *dev_w, *host, n, T, ys)
+    torch.cuda.synchronize()
+    same(ys, "streamed")
+    ctx.close()
+
+
 # ---------------------------------------------- expert outputs kept in fp32 until the combine
 @pytest.mark.parametrize("T,d,f,E,k", [
     (256, 512, 1024, 8, 2),        # the tiny preset's shape: one short row tile per expert
