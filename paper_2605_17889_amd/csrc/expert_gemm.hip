@@ -146,7 +146,8 @@ double large_minus_mid(double units0, double tiles0, double tiles1, int cus) {
 //               rows, none is over 1 % slower cold than with the 128- or the 256-row tiles throughout
 //   + 3, + 6    a tile's cost outside its reduction, in k-steps, and 0.9 the margin that small tiles have to win by:
 //               512 and 900 tokens through 8 experts of 512 x 1024 (below)
-//   0.93        seven stages against four, 2.5 16-row gate/up tiles, 3.5 128 columns down: where they are used
+//   0.93        seven stages against four, and one 128-column tile per compute unit down; 2.5 narrow gate/up
+//               tiles, 3.5 128 columns down: where they are used
 int pick_config(const GemmEnv& env, int R, int E, const NTiles& nt) {
     if (env.forced_config >= 0) return env.forced_config;
     // 0: pipelined 256-row tiles (with half-height tails). 1: 128-row tiles (generic kernel).
@@ -212,6 +213,12 @@ int pick_config(const GemmEnv& env, int R, int E, const NTiles& nt) {
     return config;
 }
 
+// Expected row tiles of height h of a launch.
+double row_tiles(int R, int E, int h) {
+    const double avg = static_cast<double>(R) / (E > 0 ? E : 1);
+    return E * mean_row_tiles(avg, std::sqrt(avg), h);
+}
+
 // Experts that R rows are expected to touch.
 double touched_experts(int R, int E) { return E * (1.0 - std::exp(-static_cast<double>(R) / E)); }
 
@@ -274,10 +281,16 @@ using DownMid96WideS = Config<96, 256, 64, 1, 4, 3, false, true>;
 using GateUpTiny      = Config<32, 128, 64, 2, 2, 4, true>;
 using GateUpTinyS     = Config<32, 128, 64, 2, 2, 4, true, true>;
 using GateUpTinyDeepS = Config<32, 128, 64, 2, 2, 7, true, true>;
-using GateUpFewS      = Config<16, 64, 64, 1, 1, 5, true, true>;    // one or two tokens: more tiles
+// A few tokens: more, narrower tiles. Four wavefronts (two, down) share their loads, which leave a wavefront
+// one by one, some 100 cycles apart: one wavefront per tile took 16.2 us for gate/up of one token through 8 of
+// 128 experts of 2048 x 768, four take 14.4, and 13.5 with the deep ring where no second tile has to fit; down
+// of one token through 2 of 8 of 4096 x 14336 61 -> 46 us, of 6144 x 16384 76 -> 70.
+using GateUpFewS     = Config<32, 64, 64, 2, 2, 4, true, true>;
+using GateUpFewDeepS = Config<32, 64, 64, 2, 2, 6, true, true>;
 using DownTiny     = Config<32, 64, 64, 2, 2, 4, false>;
 using DownTinyS    = Config<32, 64, 64, 2, 2, 4, false, true>;
-using DownFewS     = Config<16, 32, 64, 1, 1, 8, false, true>;
+using DownFew      = Config<16, 32, 64, 1, 2, 6, false>;
+using DownFewS     = Config<16, 32, 64, 1, 2, 6, false, true>;
 
 }  // namespace
 
@@ -312,15 +325,16 @@ int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_inde
             if (single_m_tile(env, R_hint, E, 32)) {
                 const double nt = touched_experts(R_hint, E) * (f / 64);
                 const int cus = compute_units(env.device);
-                // 16-row tiles of half the width while up to two and a half of them go to a compute unit. Layer
-                // calls with cold weights, against the 32-row tiles: one token through 8 of 128 experts of 2048 x
-                // 768 (0.7 per compute unit) 37.0 and 39.0 us, 2 through 6 of 64 of 2048 x 1408 (1.9) 56 and 64, 8
-                // through 4 of 64 of 4096 x 768 (2.4) 103 and 111; below the line none was slower by over 1 %.
-                // Three fit at once, but from 2.5 to 3.0 the sides are mixed: 10 tokens, 4 of 32 of 1024 x 1024
-                // (2.85) 37.5 and 39.4, but 30, 2 of 16 of 2048 x 1536 (2.93) 69.9 and 67.2, and 90, 2 of 24 of
-                // 1024 x 1024 (3.0) 49.3 and 45.2; past it they lose (5 tokens, 8 of 128, 3.2: 80 and 72)
-                if (2.0 * nt <= 2.5 * cus && single_m_tile(env, R_hint, E, 16))
+                // Tiles of half the width while up to two and a half of them go to a compute unit, gate/up against
+                // the 128-column ones: one token through 8 of 128 experts of 2048 x 768 (0.75 per compute unit) 13.5
+                // and 16.8 us, 2 (1.4) 21.7 and 22.8, 2 through 6 of 64 of 2048 x 1408 (2.1) 29.8 and 34.9, 64
+                // through 2 of 8 of 512 x 1024 (1.0) 8.1 and 9.0; past the line they lose (5 tokens, 8 of 128, 3.3:
+                // 41.8 and 41.2; 4 tokens, 6 of 64, 4.0: 46.9 and 43.4)
+                if (2.0 * nt <= 2.5 * cus) {
+                    if (2.0 * nt <= cus)
+                        return launch_grouped<GateUpFewDeepS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
                     return launch_grouped<GateUpFewS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
+                }
                 // 16 tokens through 8 experts of 4096 x 14336, 7 rounds of one workgroup per compute unit or
                 // 3.5 of two: 280 against 284 us; 4 tokens at 6144 x 16384, 6 or 3 rounds: 397 against 367
                 if (last_round_use(nt, 2.0 * cus) < 0.93 * last_round_use(nt, cus))
@@ -395,15 +409,24 @@ int launch_down_as(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets
         case 3:
             if (one_wide_each && single_m_tile(env, R_hint, E, 64))
                 return launch_grouped<Out<F32, DownSmallWideS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
-            if (single_m_tile(env, R_hint, E, 32)) {
-                // 32-column tiles where 64-column ones would leave compute units without any: one
-                // token through 2 of 8 experts of 4096 x 14336 51 against 66 us
-                if (touched_experts(R_hint, E) * (d / 64) < cus && single_m_tile(env, R_hint, E, 16))
+            // 32-column tiles where 64-column ones would leave compute units without any: one token through 2 of
+            // 8 experts of 4096 x 14336 46 against 70 us; and while all of their row tiles find one: 64 tokens
+            // through 2 of 8 of 512 x 1024 7.6 against 8.9 us
+            if (touched_experts(R_hint, E) * (d / 64) < cus) {
+                if (single_m_tile(env, R_hint, E, 16))
                     return launch_grouped<Out<F32, DownFewS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+                if (row_tiles(R_hint, E, 16) * (d / 32) <= cus)
+                    return launch_grouped<Out<F32, DownFew>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+            }
+            if (single_m_tile(env, R_hint, E, 32)) {
                 return launch_grouped<Out<F32, DownTinyS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
             }
             return launch_grouped<Out<F32, DownTiny>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
         default:
+            // 32-row tiles where the 64-row ones would leave half of the compute units without any: 256 tokens through
+            // 2 of 8 experts of 512 x 1024 (96 tiles) 9.2 against 10.2 us, 600 (192 tiles) 10.9 against 10.2
+            if (row_tiles(R_hint, E, 64) * (d / 64) <= 0.5 * cus)
+                return launch_grouped<Out<F32, DownTiny>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
             // 128 columns where that makes about two rounds of two workgroups per compute unit, else 64. Layer calls
             // with cold weights, 128 against 64 columns: 500 tokens through 128 experts of 2048 x 768 (8 tiles of 128
             // columns per compute unit) 239 and 243 us, 448 through 56 of 2048 x 1024, 4 per token (3.5) 149.2 and

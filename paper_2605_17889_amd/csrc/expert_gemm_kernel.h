@@ -3,7 +3,7 @@
 //   C[p, n] = sum_k A[p, k] * B_e[n, k]           for the rows p of expert e's group,
 // both operands contiguous along k ("NT"), bf16 in, fp32 accumulation on
 // v_mfma_f32_16x16x32_bf16, bf16 out. With DUAL, a tile carries BN/2 rows of W1 and the
-// matching BN/2 rows of W3 (interleaved in blocks of 32) and stores SiLU(gate)*up.
+// matching BN/2 rows of W3 (interleaved in blocks of 32 or 16) and stores SiLU(gate)*up.
 //
 // Data path: global memory -> LDS by direct-to-LDS loads (no VGPR staging); LDS -> VGPR by
 // 16-byte reads of a swizzled layout; MFMA. Tiles are enumerated on the device from `offsets`.
@@ -323,9 +323,10 @@ struct Config {
     static constexpr int NIA = BM / RPI, NIB = BN / RPI;   // wavefront loads per stage
     static constexpr int LPW = (NIA + NIB) / NW;           // ... per wavefront
     static constexpr int BN_OUT = DUAL ? BN / 2 : BN;      // output columns per tile
+    static constexpr int DB = WTN % 64 == 0 ? 32 : 16;     // DUAL: rows of W1, then as many of W3, in turn
     static_assert(BK == 64 || BK == 32, "LDS rows of 128 or 64 bytes");
     static_assert(BM % (WM * 16) == 0 && BN % (WN * 16) == 0, "wave tile");
-    static_assert(!DUAL || WTN % 64 == 0, "gate/up blocks of 32+32 rows must live in one wave");
+    static_assert(!DUAL || WTN % (2 * DB) == 0, "gate and up of a column must live in one wave");
     static_assert(NIA % NW == 0 && NIB % NW == 0, "loads must split evenly over wavefronts");
     static_assert(NSTAGE >= 2 && SMEM <= 160 * 1024, "LDS budget");
 };
@@ -414,13 +415,14 @@ __device__ __forceinline__ void mma_stage(const unsigned char* s, const FragPlan
 
 // Epilogue. Result layout of the transposed 16x16 tile: lane holds activation row (lane & 15)
 // and the four output columns 4 * (lane >> 4) + r in registers r = 0..3. With DUAL, B-tile rows
-// come in blocks of 32 W1 rows followed by the 32 W3 rows of the same output columns, so
-// accumulator tiles j and j + 2 (j & 2 == 0) are gate and up of the same columns.
+// come in blocks of DB W1 rows followed by the DB W3 rows of the same output columns, so accumulator
+// tiles j and j + P (P = DB / 16, j & P == 0) are gate and up of the same columns.
 template <class Cfg>
 __device__ __forceinline__ void store_tile(const f32x4 (&acc)[Cfg::TM][Cfg::TN], const TileCoord& tc,
                                            const FragPlan<Cfg>& fp, int wm, int wn,
                                            uint16_t* __restrict__ C, int ldc) {
     constexpr bool DUAL = Cfg::DUAL;
+    constexpr int DB = Cfg::DB, P = DB / 16;
 #pragma unroll
     for (int i = 0; i < Cfg::TM; ++i) {
         const int row = wm * Cfg::WTM + i * 16 + fp.frag_row;
@@ -428,9 +430,9 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[Cfg::TM][Cfg::TN],
         uint16_t* crow = C + static_cast<size_t>(tc.row0 + row) * ldc + tc.nt * Cfg::BN_OUT + 4 * fp.frag_kg;
 #pragma unroll
         for (int j = 0; j < Cfg::TN; ++j) {
-            if (DUAL && (j & 2)) continue;
+            if (DUAL && (j & P)) continue;
             const int r0 = wn * Cfg::WTN + j * 16;                 // first B-tile row of tile j
-            const int col = DUAL ? (r0 >> 6) * 32 + (r0 & 31) : r0;
+            const int col = DUAL ? r0 / (2 * DB) * DB + r0 % DB : r0;
             if constexpr (out_is_f32<Cfg>::value) {
                 float* frow = reinterpret_cast<float*>(C) + static_cast<size_t>(tc.row0 + row) * ldc +
                               tc.nt * Cfg::BN_OUT + 4 * fp.frag_kg;
@@ -440,7 +442,7 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[Cfg::TM][Cfg::TN],
             bf16x4 o;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float v = DUAL ? silu(acc[i][j][r]) * acc[i][DUAL ? j + 2 : j][r] : acc[i][j][r];
+                const float v = DUAL ? silu(acc[i][j][r]) * acc[i][DUAL ? j + P : j][r] : acc[i][j][r];
                 o[r] = static_cast<__bf16>(v);                     // round to nearest even
             }
             *reinterpret_cast<bf16x4*>(crow + col) = o;
@@ -449,7 +451,7 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[Cfg::TM][Cfg::TN],
 }
 
 // Weight row (and matrix) that tile row r0 of the B tile comes from. With DUAL the tile rows
-// alternate between W1 and W3 in blocks of 32.
+// alternate between W1 and W3 in blocks of Cfg::DB.
 template <class Cfg>
 __device__ __forceinline__ const uint16_t* weight_row_ptr(const TileCoord& tc, int r0,
                                                           const uint16_t* B0, const uint16_t* B1,
@@ -457,9 +459,9 @@ __device__ __forceinline__ const uint16_t* weight_row_ptr(const TileCoord& tc, i
     int col0;
     const uint16_t* base;
     if (Cfg::DUAL) {
-        const int b32 = r0 >> 5;
-        col0 = tc.nt * Cfg::BN_OUT + (b32 >> 1) * 32 + (r0 & 31);
-        base = (b32 & 1) ? B1 : B0;
+        const int block = r0 / Cfg::DB;
+        col0 = tc.nt * Cfg::BN_OUT + (block >> 1) * Cfg::DB + r0 % Cfg::DB;
+        base = (block & 1) ? B1 : B0;
     } else {
         col0 = tc.nt * Cfg::BN_OUT + r0;
         base = B0;
