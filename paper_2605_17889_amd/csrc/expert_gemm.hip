@@ -78,9 +78,10 @@ int launch_grouped(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, co
                         gemm::RowDiv(index_div), kstart, E, N, K);
 }
 
-// The pipelined kernel with operand rings of NA and NB stages; tiles of at most HalfCfg::BM rows
-// and the tiles of a last round that is less than half full run at half height.
-template <class Cfg, class HalfCfg, int NA, int NB>
+// The pipelined kernel with operand rings of NA and NB stages; tiles of at most LowCfg::BM rows run at three
+// quarters of the height, tiles of at most HalfCfg::BM rows and the tiles of a last round that is less than
+// half full at half of it.
+template <class Cfg, class LowCfg, class HalfCfg, int NA, int NB>
 int launch_ring(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, const moe_bf16* B1, moe_bf16* C,
                 const int32_t* offsets, const int32_t* row_index, int index_div, gemm::KStart kstart,
                 int R, int E, int N, int K, hipStream_t s) {
@@ -91,7 +92,7 @@ int launch_ring(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, const
     const long long max_mt = most_row_tiles(R, E, Cfg::BM);
     // split tiles take two slots each: at most ceil(cus / 2 / 8) more slots in every XCD's range
     const long long grid = max_mt * (N / Cfg::BN_OUT) + kXcds * ((cus / 2 + kXcds - 1) / kXcds + 1);
-    return launch_tiles(env, attr_set, gemm::grouped_gemm_ring_kernel<Cfg, HalfCfg, NA, NB>,
+    return launch_tiles(env, attr_set, gemm::grouped_gemm_ring_kernel<Cfg, LowCfg, HalfCfg, NA, NB>,
                         gemm::RingCfg<Cfg, NA, NB>::SMEM, Cfg::NTHREADS, grid, s, A, B0, B1, C,
                         offsets, row_index, gemm::RowDiv(index_div), kstart, E, N, K, cus);
 }
@@ -244,10 +245,13 @@ bool single_m_tile(const GemmEnv& env, int R, int E, int BM) {
 
 //                      BM   BN  BK WM WN NSTAGE DUAL [STREAM_B]
 using GateUpLarge = Config<256, 256, 64, 2, 4, 2, true>;
-// one wavefront per SIMD: 2 x 2 wavefronts of 128 x 128 outputs, or of 64 x 128 at half height
+// one wavefront per SIMD: 2 x 2 wavefronts of 128 x 128 outputs, of 96 x 128 at three quarters of the height or
+// of 64 x 128 at half
 using GateUpLarge1W = Config<256, 256, 64, 2, 2, 2, true>;
+using GateUpLow1W   = Config<192, 256, 64, 2, 2, 2, true>;
 using GateUpHalf1W  = Config<128, 256, 64, 2, 2, 3, true>;
 using DownLarge1W   = Config<256, 256, 64, 2, 2, 2, false>;
+using DownLow1W     = Config<192, 256, 64, 2, 2, 2, false>;
 using DownHalf1W    = Config<128, 256, 64, 2, 2, 3, false>;
 using GateUpMid   = Config<128, 256, 64, 2, 4, 3, true>;   // also the half-height tile of GateUpLarge
 // 64 rows: four wavefronts of 32 rows share a workgroup, and its ring leaves room for a second
@@ -311,8 +315,8 @@ int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_inde
     switch (config) {
         case 0:
             if (use_one_wave_per_simd(env, f, d))
-                return launch_ring<GateUpLarge1W, GateUpHalf1W, 2, 3>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
-            return launch_ring<GateUpLarge, GateUpMid, 2, 3>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
+                return launch_ring<GateUpLarge1W, GateUpLow1W, GateUpHalf1W, 2, 3>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
+            return launch_ring<GateUpLarge, GateUpLarge, GateUpMid, 2, 3>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
         case 1:
             if (single_m_tile(env, R_hint, E, 128))
                 return launch_grouped<GateUpMidS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
@@ -383,8 +387,8 @@ int launch_down_as(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets
     switch (config) {
         case 0:
             if (use_one_wave_per_simd(env, d, f))
-                return launch_ring<Out<F32, DownLarge1W>, Out<F32, DownHalf1W>, 2, 3>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
-            return launch_ring<Out<F32, DownLarge>, Out<F32, DownMidWide>, 2, 3>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+                return launch_ring<Out<F32, DownLarge1W>, Out<F32, DownLow1W>, Out<F32, DownHalf1W>, 2, 3>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+            return launch_ring<Out<F32, DownLarge>, Out<F32, DownLarge>, Out<F32, DownMidWide>, 2, 3>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
         case 1:
             // HBM-bound: wide tiles stream more bytes per workgroup, but only if there are
             // enough of them to occupy the 256 compute units (about one m-tile per expert).

@@ -111,7 +111,14 @@ __device__ __forceinline__ int slot_to_tile(int total, int split_cus, int xcd, i
 // mt m-tiles form ceil(mt / kGroupM) groups of nearly equal height (the first `extra` groups hold
 // one tile more), so that a short tail tile sweeps the n-tiles together with full tiles of its
 // expert and finds the weight tiles in L2.
-template <int BM>
+//
+// With QUARTERS the m-tiles are as many, but the last ones are a quarter lower: as many as there are whole
+// quarters of padding (at most three; a single tile takes them all, two tiles with three of them are 3/4 and
+// 1/2 high). 576 rows are 3 x 192 instead of 2 x 256 and a half-height tile of 64: a k-step of 192 rows takes
+// 1536 cycles of matrix instructions and 56 loads, one of 128 rows, bound by its 48 loads, hardly less than
+// that. 8192 tokens through 128 experts of 2048 x 768 (430 to 620 rows each): gate/up 359 -> 347 us, down
+// 244.5 -> 239; 5003 through 64 of 2048 x 1408 gate/up 292 -> 287.
+template <int BM, bool QUARTERS>
 __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m_e, int local, int NT, int half) {
     TileCoord tc{kNoTile, 0, 0, 0};
     const int mt = (m_e + BM - 1) / BM;
@@ -132,8 +139,15 @@ __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m
     int mi;                                                // m-tile: first inside its group, then of the expert
     tc.nt = div_small(in, gm, mi);
     mi += head;
-    tc.row0 = row_e + mi * BM;
-    tc.rows = min(BM, m_e - mi * BM);
+    int first = mi * BM, height = BM;
+    if constexpr (QUARTERS) {
+        constexpr int Q = BM / 4;
+        const int lower = 4 * mt - (m_e + Q - 1) / Q;      // whole quarters of padding
+        if (mi >= mt - lower) height = BM - Q;
+        first -= Q * max(0, mi - max(0, mt - lower));
+    }
+    tc.row0 = row_e + first;
+    tc.rows = min(height, m_e - first);
     if (half >= 0) {
         const int h0 = half * (BM / 2);
         if (tc.rows <= h0) {                               // the tile has no lower half
@@ -168,7 +182,7 @@ __device__ __forceinline__ int lane_prefix_sum(int v) {
 // reads of memory that the kernel never writes, so they come through the scalar cache (a hit
 // for every workgroup of a compute unit after the first) and the search is a handful of scalar
 // instructions instead of vector loads, a prefix sum across lanes and a ballot.
-template <int BM>
+template <int BM, bool QUARTERS>
 __device__ __forceinline__ TileCoord locate_tile_scalar8(const int32_t* __restrict__ offsets, int NT,
                                                          int split_cus, int xcd, int slot) {
     int off[9];
@@ -195,13 +209,13 @@ __device__ __forceinline__ TileCoord locate_tile_scalar8(const int32_t* __restri
             m_e = off[i + 1] - off[i];
             row_e = off[i];
         }
-    return tile_in_expert<BM>(e, row_e, m_e, L - start, NT, half);
+    return tile_in_expert<BM, QUARTERS>(e, row_e, m_e, L - start, NT, half);
 }
 
-template <int BM>
+template <int BM, bool QUARTERS>
 __device__ __forceinline__ TileCoord locate_tile_at(const int32_t* __restrict__ offsets, int E,
                                                     int NT, int split_cus, int xcd, int slot) {
-    if (E == 8) return locate_tile_scalar8<BM>(offsets, NT, split_cus, xcd, slot);
+    if (E == 8) return locate_tile_scalar8<BM, QUARTERS>(offsets, NT, split_cus, xcd, slot);
     constexpr int EPL = kMaxExperts / kWave;               // experts per lane
     const int e0 = (threadIdx.x & (kWave - 1)) * EPL;
     int off[EPL + 1], tiles[EPL], sum = 0;
@@ -230,15 +244,15 @@ __device__ __forceinline__ TileCoord locate_tile_at(const int32_t* __restrict__ 
         }
     static_assert(EPL == 4, "in-lane search");
     const int src = __builtin_ctzll(hit);
-    return tile_in_expert<BM>(__builtin_amdgcn_readlane(e, src), __builtin_amdgcn_readlane(row_e, src),
-                              __builtin_amdgcn_readlane(m_e, src), L - __builtin_amdgcn_readlane(start, src),
-                              NT, half);
+    return tile_in_expert<BM, QUARTERS>(
+        __builtin_amdgcn_readlane(e, src), __builtin_amdgcn_readlane(row_e, src),
+        __builtin_amdgcn_readlane(m_e, src), L - __builtin_amdgcn_readlane(start, src), NT, half);
 }
 
-template <int BM>
+template <int BM, bool QUARTERS = false>
 __device__ __forceinline__ TileCoord locate_tile(const int32_t* __restrict__ offsets, int E,
                                                  int NT, int split_cus = 0) {
-    TileCoord tc = locate_tile_at<BM>(offsets, E, NT, split_cus, blockIdx.x % kXcds, blockIdx.x / kXcds);
+    TileCoord tc = locate_tile_at<BM, QUARTERS>(offsets, E, NT, split_cus, blockIdx.x % kXcds, blockIdx.x / kXcds);
     // the same in every lane: into scalar registers, where the load addresses are formed
     tc.expert = __builtin_amdgcn_readfirstlane(tc.expert);
     tc.row0 = __builtin_amdgcn_readfirstlane(tc.row0);
@@ -904,6 +918,8 @@ __device__ __forceinline__ void store_tile_via_lds(const f32x4 (&acc)[Cfg::TM][8
     }
 }
 
+template <class T> struct type_tag { using type = T; };
+
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>) in order
 template <int N, int I = 0, class F>
 __device__ __forceinline__ void static_for(F&& f) {
@@ -1025,8 +1041,8 @@ __device__ __forceinline__ void kstep_1w(f32x4 (&acc)[Cfg::TM][8], bf16x8 (&fa)[
     constexpr int TM = Cfg::TM, NM = TM * 8, NR = TM + 8;      // MFMAs and fragment reads per half
     constexpr int LA = LoadPlan1W<Cfg>::LA, LB = LoadPlan1W<Cfg>::LB;
     constexpr uint32_t AB = Cfg::A_BYTES, BB = Cfg::B_BYTES;
-    static_assert((TM == 8 || TM == 4) && Cfg::TN == 8 && LA == TM && LB == 8 && NA == 2,
-                  "128 or 64 rows x 128 columns per wavefront");
+    static_assert((TM == 8 || TM == 6 || TM == 4) && Cfg::TN == 8 && LA == TM && LB == 8 && NA == 2,
+                  "128, 96 or 64 rows x 128 columns per wavefront");
     const uint32_t a_region = rs.a_region, b_region = rs.b_region;
     const unsigned char *pa_h1 = rs.pa_h1, *pb_h1 = rs.pb_h1, *pa_n0 = rs.pa_n0, *pb_n0 = rs.pb_n0;
     // fragment read r of a half goes out behind MFMA r * SPAN / NR: B fragments first (every MFMA
@@ -1201,36 +1217,39 @@ __device__ __forceinline__ void ring_tile_1w(const TileCoord& tc, unsigned char*
                             [] { wait_vmcnt<0>(); });
 }
 
-// Tiles are enumerated at Cfg::BM rows. A tile that holds at most HalfCfg::BM = Cfg::BM / 2 rows
-// (an expert's short tail, or a half of a tile of the last, partial round: see locate_tile) runs
-// the same pipeline at half height: it issues half the MFMAs and A loads, and takes about 0.6 of
-// the time of a full tile. Every output element is still one accumulator chain over k, so the
-// bits do not depend on which height computed it.
-template <class Cfg, class HalfCfg, int NA, int NB>
+// Tiles are enumerated at Cfg::BM rows, the last ones of an expert lower (see tile_in_expert). A tile that
+// holds at most HalfCfg::BM = Cfg::BM / 2 rows (an expert's only or second tile, or a half of a tile of the
+// last, partial round: see locate_tile) runs the same pipeline at half height, one of at most LowCfg::BM =
+// Cfg::BM * 3 / 4 rows at three quarters (LowCfg = Cfg: at full height). Every output element is still one
+// accumulator chain over k, so the bits do not depend on which height computed it.
+template <class Cfg, class LowCfg, class HalfCfg, int NA, int NB>
 __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_ring_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
     const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ row_index, RowDiv index_div,
     KStart kstart, int E, int N, int K, int split_cus) {
+    constexpr bool QUARTERS = LowCfg::BM != Cfg::BM;
     static_assert(HalfCfg::BM * 2 == Cfg::BM && HalfCfg::BN == Cfg::BN && HalfCfg::BK == Cfg::BK &&
                   HalfCfg::NTHREADS == Cfg::NTHREADS && HalfCfg::DUAL == Cfg::DUAL, "same n-tiling");
-    static_assert(RingCfg<HalfCfg, NA, NB>::SMEM <= RingCfg<Cfg, NA, NB>::SMEM, "LDS of the full tile");
+    static_assert((!QUARTERS || LowCfg::BM * 4 == Cfg::BM * 3) && LowCfg::BN == Cfg::BN && LowCfg::BK == Cfg::BK &&
+                  LowCfg::NTHREADS == Cfg::NTHREADS && LowCfg::DUAL == Cfg::DUAL, "same n-tiling");
+    static_assert(RingCfg<HalfCfg, NA, NB>::SMEM <= RingCfg<Cfg, NA, NB>::SMEM &&
+                  RingCfg<LowCfg, NA, NB>::SMEM <= RingCfg<Cfg, NA, NB>::SMEM, "LDS of the full tile");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
-    const TileCoord tc = locate_tile<Cfg::BM>(offsets, E, N / Cfg::BN_OUT, split_cus);
+    const TileCoord tc = locate_tile<Cfg::BM, QUARTERS>(offsets, E, N / Cfg::BN_OUT, split_cus);
     if (tc.expert < 0) return;                       // uniform for the whole workgroup
-    // four wavefronts of (128 or 64) x 128 outputs run the one-wavefront-per-SIMD pipeline
-    if (tc.rows <= HalfCfg::BM) {
-        if constexpr (HalfCfg::NW == 4 && HalfCfg::TN == 8)
-            ring_tile_1w<HalfCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, kstart, N, K);
+    // four wavefronts of (128, 96 or 64) x 128 outputs run the one-wavefront-per-SIMD pipeline
+    auto run = [&](auto cfg_tag) {
+        using TileCfg = typename decltype(cfg_tag)::type;
+        if constexpr (TileCfg::NW == 4 && TileCfg::TN == 8)
+            ring_tile_1w<TileCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, kstart, N, K);
         else
-            ring_tile<HalfCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, kstart, N, K);
-    } else {
-        if constexpr (Cfg::NW == 4 && Cfg::TN == 8)
-            ring_tile_1w<Cfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, kstart, N, K);
-        else
-            ring_tile<Cfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, kstart, N, K);
-    }
+            ring_tile<TileCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, kstart, N, K);
+    };
+    if (tc.rows <= HalfCfg::BM) run(type_tag<HalfCfg>{});
+    else if (QUARTERS && tc.rows <= LowCfg::BM) run(type_tag<LowCfg>{});
+    else run(type_tag<Cfg>{});
 }
 
 }  // namespace gemm

@@ -579,6 +579,41 @@ def test_automatic_tile_choice_agrees_bitwise(d, f, rows, fp32_outputs):
     ctx.close()
 
 
+@pytest.mark.parametrize("rows", [
+    [1, 64, 65, 128, 129, 192, 193, 256, 0, 257],                    # one tile; two from 257 rows on
+    [320, 321, 384, 385, 448, 449, 512, 513],                        # eight experts: the lookup on the scalar unit
+    [576, 577, 640, 641, 704, 705, 768, 769, 2049, 2240, 2241],      # three and more, two groups of tiles
+])
+@pytest.mark.parametrize("fp32_outputs", [False, True])
+def test_large_tiles_of_every_height(rows, fp32_outputs):
+    """256-, 192- and 128-row tiles and split last rounds against the 128-row configuration."""
+    d, f = 512, 256
+    say(f"large tiles rows={rows} fp32={fp32_outputs}")
+    E, R = len(rows), sum(rows)
+    g = torch.Generator(device="cuda").manual_seed(R)
+    rnd = lambda *shape: (torch.randn(*shape, generator=g, device="cuda") * 0.05).bfloat16()
+    W1, W3, W2 = rnd(E, f, d), rnd(E, f, d), rnd(E, d, f)
+    xr = rnd(R, d)                         # routed by the first E input columns
+    xr[:, :E] = 0
+    xr[torch.arange(R, device="cuda"), torch.repeat_interleave(
+        torch.arange(E, device="cuda"), torch.tensor(rows, device="cuda"))] = 64.0
+    wr = torch.zeros(d, E, device="cuda")
+    wr[:E] = torch.eye(E, device="cuda")
+    ctx = B.MoeContext(R, d, f, E, 1)
+    B.moe_set_expert_output_fp32(ctx, fp32_outputs)
+    outs = []
+    for config in (1, 0, 0 + 128, 0 + 256):
+        B.moe_set_gemm_config(ctx, config)
+        y = torch.full((R, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        B.moe_layer_forward(ctx, xr, wr, None, W1, W3, W2, R, y)
+        torch.cuda.synchronize()
+        outs.append(bits(y))
+    assert not np.isnan(bf16_to_f64(outs[0])).any()
+    for other in outs[1:]:
+        assert np.array_equal(outs[0], other)
+    ctx.close()
+
+
 @pytest.mark.parametrize("T,d,k", [(1, 512, 1), (50, 512, 2), (33, 1024, 3), (256, 4096, 2),
                                    (100, 1024, 17), (7, 512, 64)])   # up to the largest k supported
 def test_combine_parity(T, d, k):
