@@ -296,35 +296,54 @@ using DownTinyS    = Config<32, 64, 64, 2, 2, 4, false, true>;
 using DownFew      = Config<16, 32, 64, 1, 2, 6, false>;
 using DownFewS     = Config<16, 32, 64, 1, 2, 6, false, true>;
 
+// Start of the reductions of K for N output columns: staggered over long ones, thirteen k-steps from block to block
+// of columns, or one where a reduction has fewer than 64. Before -> after, cold weights.
+// Down: 2 tokens through 8 experts of 4096 x 14336 87 -> 72 us, 16 140 -> 139, 40 150 -> 140, 256 158 -> 153, 2048
+// 508 -> 491 (one apart: 16 tokens 157, 256 174); 6144 x 16384, 16 tokens 267 -> 244, 256 266 -> 248, 4096
+// 1323 -> 1310; 32 experts of 2048 x 2048, 4 per token, 16 tokens 46 -> 39, 500 68 -> 49 (thirteen apart 40 and 50).
+// Gate/up: 4096 x 14336, 16 tokens 286 -> 275, 64 291 -> 280, 256 331 to 350 (with the place of the weights in
+// memory) -> 314, 1024 500 -> 488 (one apart 288, 288, 317, 485); 6144 x 16384, 16 tokens 492 -> 465; 128 experts of 2048 x 768,
+// 500 tokens 140 to 153 -> 129 to 135, 1000 148 -> 141, 2000 163 -> 157 (thirteen apart 136, 143, 159); 32 of
+// 2048 x 2048, 500 tokens 127 -> 91. Reductions whose rows are no power of two apart gain nothing and lose nothing
+// (32 experts of 3072 x 3072), 6144 x 16384 at 8192 tokens neither.
+// A reduction of 12 or 22 steps only loses the sharing between large tiles (down, 8192 tokens through 128 experts of
+// 2048 x 768 248 -> 255 us).
+gemm::KStart reduction_start(bool dual, int e0, int N, int K) {
+    if (K < 2048) return gemm::KStart{0, 0, 0};
+    const int cols = gemm::KStart::columns(dual);
+    return gemm::KStart{K < 4096 ? 1 : 13, e0, (N + cols - 1) / cols};
+}
+
 }  // namespace
 
 // `a` is the grouped activation matrix [R, d] when row_index is NULL; otherwise it is the
 // token matrix [T, d] and grouped row p reads token row_index[p] / index_div (the caller makes
 // sure that T * d * 2 bytes fit a 32-bit offset). R bounds the rows of the E launched experts
 // (it sizes the grid); R_hint is how many rows they are expected to hold together (it picks the
-// tile configuration): the two differ when a call covers a subset of a layer's experts.
+// tile configuration): the two differ when a call covers a subset of a layer's experts, which are
+// then the layer's experts e0, e0 + 1, ...
 int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_index, int index_div,
-                  const int32_t* offsets, int R, int R_hint, int d, int f, int E,
+                  const int32_t* offsets, int R, int R_hint, int d, int f, int e0, int E,
                   const moe_bf16* W1, const moe_bf16* W3, moe_bf16* H, hipStream_t s) {
     if (R == 0) return MOE_OK;
     const moe_bf16* x_perm = a;
-    const gemm::KStart kZero{0, 0, 0};       // every tile from k = 0
+    const gemm::KStart ks = reduction_start(true, e0, f, d);
     int config = pick_config(env, R_hint, E, NTiles{f / 128, f / 128, f / 64, 0.82, 0.41, 0.58,
                                                     4e-6 * E * d * f, d / 64});
     if (config == 0 && d / 64 < 3) config = 1;     // the pipelined kernel needs three k-steps
     switch (config) {
         case 0:
             if (use_one_wave_per_simd(env, f, d))
-                return launch_ring<GateUpLarge1W, GateUpLow1W, GateUpHalf1W, 2, 3>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
-            return launch_ring<GateUpLarge, GateUpLarge, GateUpMid, 2, 3>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
+                return launch_ring<GateUpLarge1W, GateUpLow1W, GateUpHalf1W, 2, 3>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
+            return launch_ring<GateUpLarge, GateUpLarge, GateUpMid, 2, 3>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
         case 1:
             if (single_m_tile(env, R_hint, E, 128))
-                return launch_grouped<GateUpMidS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
-            return launch_grouped<GateUpMid>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
+                return launch_grouped<GateUpMidS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
+            return launch_grouped<GateUpMid>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
         case 4:
             if (single_m_tile(env, R_hint, E, 96))
-                return launch_grouped<GateUpMid96S>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
-            return launch_grouped<GateUpMid96>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
+                return launch_grouped<GateUpMid96S>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
+            return launch_grouped<GateUpMid96>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
         case 3:
             if (single_m_tile(env, R_hint, E, 32)) {
                 const double nt = touched_experts(R_hint, E) * (f / 64);
@@ -336,43 +355,31 @@ int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_inde
                 // 41.8 and 41.2; 4 tokens, 6 of 64, 4.0: 46.9 and 43.4)
                 if (2.0 * nt <= 2.5 * cus) {
                     if (2.0 * nt <= cus)
-                        return launch_grouped<GateUpFewDeepS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
-                    return launch_grouped<GateUpFewS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
+                        return launch_grouped<GateUpFewDeepS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
+                    return launch_grouped<GateUpFewS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
                 }
                 // 16 tokens through 8 experts of 4096 x 14336, 7 rounds of one workgroup per compute unit or
                 // 3.5 of two: 280 against 284 us; 4 tokens at 6144 x 16384, 6 or 3 rounds: 397 against 367
                 if (last_round_use(nt, 2.0 * cus) < 0.93 * last_round_use(nt, cus))
-                    return launch_grouped<GateUpTinyDeepS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
-                return launch_grouped<GateUpTinyS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
+                    return launch_grouped<GateUpTinyDeepS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
+                return launch_grouped<GateUpTinyS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
             }
-            return launch_grouped<GateUpTiny>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
+            return launch_grouped<GateUpTiny>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
         default:
             if (single_m_tile(env, R_hint, E, 64))
-                return launch_grouped<GateUpSmallS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
-            return launch_grouped<GateUpSmall>(env, x_perm, W1, W3, H, offsets, row_index, index_div, kZero, R, E, f, d, s);
+                return launch_grouped<GateUpSmallS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
+            return launch_grouped<GateUpSmall>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
     }
 }
 
 namespace {
-
-// Start of the down projection's reductions: staggered over long ones, thirteen k-steps apart. Before -> after, cold
-// weights: 2 tokens through 8 experts of 4096 x 14336 87 -> 72 us, 16 140 -> 139, 40 150 -> 140, 256 158 -> 153,
-// 2048 508 -> 491; 6144 x 16384, 16 tokens 267 -> 244, 256 266 -> 248, 4096 1323 -> 1310; 32 experts of 2048 x 2048, 4
-// per token, 16 tokens 49 -> 40, 4096 134 -> 133. Seven apart 16 tokens of 4096 x 14336 take 146 us, one apart 148.
-// A reduction of 12 or 22 steps only loses the sharing between large tiles (8192 tokens through 128 experts of
-// 2048 x 768 248 -> 255 us), and so do gate/up launches, whose many rounds of tiles are out of step anyway
-// (16 tokens of 4096 x 14336 281 -> 290 us with the same stagger, 299 by expert alone).
-gemm::KStart down_start(int e0, int N, int K) {
-    if (K < 2048) return gemm::KStart{0, 0, 0};
-    return gemm::KStart{13, e0, (N + gemm::kRotateCols - 1) / gemm::kRotateCols};
-}
 
 // F32: the same tilings with a float output matrix (gemm::F32Out).
 template <bool F32>
 int launch_down_as(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets, int R, int R_hint,
                    int d, int f, int e0, int E, const moe_bf16* W2, moe_bf16* y_perm, hipStream_t s) {
     if (R == 0) return MOE_OK;
-    const gemm::KStart ks = down_start(e0, d, f);
+    const gemm::KStart ks = reduction_start(false, e0, d, f);
     const bool wide_mid = static_cast<long long>(E) * (d / 256) >= 160 && d % 256 == 0;
     const int cus = compute_units(env.device);
     // Tiles of 128 columns make one per compute unit: the row tiles of 32 and 64 rows are then 64 x 128 (64 x 64 for

@@ -41,6 +41,7 @@ struct TileCoord {
     int row0;        // first row (in the permuted matrix) of the tile
     int rows;        // valid rows in the tile (1..BM)
     int nt;          // n-tile index
+    int height;      // rows that its workgroup computes: BM, 3/4 BM (see tile_in_expert) or BM / 2
 };
 
 // Map a workgroup to its tile. Logical tile order: expert by expert; inside an expert, groups
@@ -107,20 +108,27 @@ __device__ __forceinline__ int slot_to_tile(int total, int split_cus, int xcd, i
     return xcd * per + tile_slot;
 }
 
+constexpr int kLowGateUpK = 4096;    // gate/up reductions below this have tiles of three quarters
+
 // Coordinates of tile `local` of the expert whose group is rows [row_e, row_e + m_e). The expert's
 // mt m-tiles form ceil(mt / kGroupM) groups of nearly equal height (the first `extra` groups hold
 // one tile more), so that a short tail tile sweeps the n-tiles together with full tiles of its
 // expert and finds the weight tiles in L2.
 //
-// With QUARTERS the m-tiles are as many, but the last ones are a quarter lower: as many as there are whole
+// With `quarters` the m-tiles are as many, but the last ones are a quarter lower: as many as there are whole
 // quarters of padding (at most three; a single tile takes them all, two tiles with three of them are 3/4 and
 // 1/2 high). 576 rows are 3 x 192 instead of 2 x 256 and a half-height tile of 64: a k-step of 192 rows takes
 // 1536 cycles of matrix instructions and 56 loads, one of 128 rows, bound by its 48 loads, hardly less than
 // that. 8192 tokens through 128 experts of 2048 x 768 (430 to 620 rows each): gate/up 359 -> 347 us, down
 // 244.5 -> 239; 5003 through 64 of 2048 x 1408 gate/up 292 -> 287.
-template <int BM, bool QUARTERS>
-__device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m_e, int local, int NT, int half) {
-    TileCoord tc{kNoTile, 0, 0, 0};
+// A workgroup that ends early is out of step with those whose rows and weights it shares in L2, which long gate/up
+// reductions pay for: there tiles are not cut, and a tail of more than half a tile computes a whole one
+// (8 experts of 6144 x 16384, 16384 tokens with a skewed load 9.15 ms, cut 9.45; 8192 tokens 4.81 and 4.79; of
+// 4096 x 14336, 8192 skewed 2.81 and 2.84). Down, same layers: 4.62 and 4.64 ms, 2.51 and 2.47, 1.46 and 1.45.
+template <int BM>
+__device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m_e, int local, int NT, int half,
+                                                    bool quarters) {
+    TileCoord tc{kNoTile, 0, 0, 0, 0};
     const int mt = (m_e + BM - 1) / BM;
     const int ngroups = (mt + kGroupM - 1) / kGroupM;
     int gm = mt, head = 0, in = local;
@@ -139,15 +147,16 @@ __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m
     int mi;                                                // m-tile: first inside its group, then of the expert
     tc.nt = div_small(in, gm, mi);
     mi += head;
-    int first = mi * BM, height = BM;
-    if constexpr (QUARTERS) {
+    int first = mi * BM;
+    tc.height = BM;
+    if (quarters) {
         constexpr int Q = BM / 4;
         const int lower = 4 * mt - (m_e + Q - 1) / Q;      // whole quarters of padding
-        if (mi >= mt - lower) height = BM - Q;
+        if (mi >= mt - lower) tc.height = BM - Q;
         first -= Q * max(0, mi - max(0, mt - lower));
     }
     tc.row0 = row_e + first;
-    tc.rows = min(height, m_e - first);
+    tc.rows = min(tc.height, m_e - first);
     if (half >= 0) {
         const int h0 = half * (BM / 2);
         if (tc.rows <= h0) {                               // the tile has no lower half
@@ -157,6 +166,7 @@ __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m
         tc.row0 += h0;
         tc.rows = min(BM / 2, tc.rows - h0);
     }
+    if (tc.rows <= BM / 2) tc.height = BM / 2;
     tc.expert = expert;
     return tc;
 }
@@ -182,9 +192,9 @@ __device__ __forceinline__ int lane_prefix_sum(int v) {
 // reads of memory that the kernel never writes, so they come through the scalar cache (a hit
 // for every workgroup of a compute unit after the first) and the search is a handful of scalar
 // instructions instead of vector loads, a prefix sum across lanes and a ballot.
-template <int BM, bool QUARTERS>
+template <int BM>
 __device__ __forceinline__ TileCoord locate_tile_scalar8(const int32_t* __restrict__ offsets, int NT,
-                                                         int split_cus, int xcd, int slot) {
+                                                         int split_cus, bool quarters, int xcd, int slot) {
     int off[9];
 #pragma unroll
     for (int e = 0; e < 9; ++e) off[e] = offsets[e];
@@ -197,7 +207,7 @@ __device__ __forceinline__ TileCoord locate_tile_scalar8(const int32_t* __restri
     }
     int half;
     const int L = slot_to_tile(total, split_cus, xcd, slot, half);
-    if (L < 0 || L >= total) return TileCoord{kNoTile, 0, 0, 0};
+    if (L < 0 || L >= total) return TileCoord{kNoTile, 0, 0, 0, 0};
     int e = 0;
 #pragma unroll
     for (int i = 0; i < 7; ++i) e += (L >= incl[i]) ? 1 : 0;      // first expert whose range holds L
@@ -209,13 +219,13 @@ __device__ __forceinline__ TileCoord locate_tile_scalar8(const int32_t* __restri
             m_e = off[i + 1] - off[i];
             row_e = off[i];
         }
-    return tile_in_expert<BM, QUARTERS>(e, row_e, m_e, L - start, NT, half);
+    return tile_in_expert<BM>(e, row_e, m_e, L - start, NT, half, quarters);
 }
 
-template <int BM, bool QUARTERS>
+template <int BM>
 __device__ __forceinline__ TileCoord locate_tile_at(const int32_t* __restrict__ offsets, int E,
-                                                    int NT, int split_cus, int xcd, int slot) {
-    if (E == 8) return locate_tile_scalar8<BM, QUARTERS>(offsets, NT, split_cus, xcd, slot);
+                                                    int NT, int split_cus, bool quarters, int xcd, int slot) {
+    if (E == 8) return locate_tile_scalar8<BM>(offsets, NT, split_cus, quarters, xcd, slot);
     constexpr int EPL = kMaxExperts / kWave;               // experts per lane
     const int e0 = (threadIdx.x & (kWave - 1)) * EPL;
     int off[EPL + 1], tiles[EPL], sum = 0;
@@ -230,7 +240,7 @@ __device__ __forceinline__ TileCoord locate_tile_at(const int32_t* __restrict__ 
     const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
     int half;
     const int L = slot_to_tile(total, split_cus, xcd, slot, half);
-    if (L < 0 || L >= total) return TileCoord{kNoTile, 0, 0, 0};
+    if (L < 0 || L >= total) return TileCoord{kNoTile, 0, 0, 0, 0};
     // the one lane whose experts hold the tile finds the expert, then hands it to all
     int start = incl - sum, e = e0, row_e = off[0], m_e = off[1] - off[0];
     const uint64_t hit = __ballot(L >= start && L < incl);
@@ -244,40 +254,45 @@ __device__ __forceinline__ TileCoord locate_tile_at(const int32_t* __restrict__ 
         }
     static_assert(EPL == 4, "in-lane search");
     const int src = __builtin_ctzll(hit);
-    return tile_in_expert<BM, QUARTERS>(
+    return tile_in_expert<BM>(
         __builtin_amdgcn_readlane(e, src), __builtin_amdgcn_readlane(row_e, src),
-        __builtin_amdgcn_readlane(m_e, src), L - __builtin_amdgcn_readlane(start, src), NT, half);
+        __builtin_amdgcn_readlane(m_e, src), L - __builtin_amdgcn_readlane(start, src), NT, half, quarters);
 }
 
-template <int BM, bool QUARTERS = false>
+template <int BM>
 __device__ __forceinline__ TileCoord locate_tile(const int32_t* __restrict__ offsets, int E,
-                                                 int NT, int split_cus = 0) {
-    TileCoord tc = locate_tile_at<BM, QUARTERS>(offsets, E, NT, split_cus, blockIdx.x % kXcds, blockIdx.x / kXcds);
+                                                 int NT, int split_cus = 0, bool quarters = false) {
+    TileCoord tc = locate_tile_at<BM>(offsets, E, NT, split_cus, quarters, blockIdx.x % kXcds, blockIdx.x / kXcds);
     // the same in every lane: into scalar registers, where the load addresses are formed
     tc.expert = __builtin_amdgcn_readfirstlane(tc.expert);
     tc.row0 = __builtin_amdgcn_readfirstlane(tc.row0);
     tc.rows = __builtin_amdgcn_readfirstlane(tc.rows);
     tc.nt = __builtin_amdgcn_readfirstlane(tc.nt);
+    tc.height = __builtin_amdgcn_readfirstlane(tc.height);
     return tc;
 }
 
 // Where a tile's reduction starts: at k-step first(), running to the end and round to the steps before it. The
 // workgroups of a launch of about one round start together and stay in step, so that with all of them at
 // the same k their weight rows, a whole reduction apart, fall on few memory channels at a time. The start
-// depends on the expert of the layer and the block of kRotateCols output columns alone, so that every tile
-// configuration and every call form sums an element in the same order, and the tiles of an expert that
-// share activation rows in an L2 (large tiles: 8 x 4 resident at a time) mostly stay at the same k.
-constexpr int kRotateCols = 1024;
+// depends on the expert of the layer and the block of output columns alone, so that every tile configuration and
+// every call form sums an element in the same order, and the tiles of an expert that share activation rows in
+// an L2 (large tiles: 8 x 4 resident at a time) mostly stay at the same k. Down: blocks of 1024 columns (16 tokens at
+// 6144 x 16384 246 to 253 us, 262 to 267 with 2048). Gate/up has more columns and keeps the large tiles together
+// with blocks of 4096 (8192 tokens at 6144 x 16384 4650 us, with 1024 4665, without a stagger 4646; 1024 tokens at
+// 4096 x 14336 470, 470 and 486).
 struct KStart {
     int mul;       // k-steps between neighbouring blocks, or 0: all at k = 0
     int e0;        // the layer's number of the launch's first expert
-    int blocks;    // blocks of kRotateCols columns per expert
+    int blocks;    // blocks of columns per expert
+    static constexpr int columns(bool dual) { return dual ? 4096 : 1024; }    // of a block
     template <class Cfg>
     __device__ __forceinline__ int first(const TileCoord& tc, int ksteps) const {
-        static_assert(kRotateCols % Cfg::BN_OUT == 0, "a tile lies in one block");
-        if (Cfg::DUAL || mul == 0) return 0;
+        constexpr int COLS = columns(Cfg::DUAL);
+        static_assert(COLS % Cfg::BN_OUT == 0, "a tile lies in one block");
+        if (mul == 0) return 0;
         int rem;
-        div_small(((e0 + tc.expert) * blocks + tc.nt * Cfg::BN_OUT / kRotateCols) * mul, ksteps, rem);
+        div_small(((e0 + tc.expert) * blocks + tc.nt * Cfg::BN_OUT / COLS) * mul, ksteps, rem);
         return rem;
     }
 };
@@ -945,22 +960,23 @@ __device__ __forceinline__ void static_for(F&& f) {
 template <class Cfg>
 struct LoadPlan1W {
     static constexpr int LA = Cfg::NIA / Cfg::NW, LB = Cfg::NIB / Cfg::NW;
-    const uint16_t* a_ptr;          // A origin + current k offset of the A loads
-    const uint16_t* b_ptr[2];       // expert's W (and W3 with DUAL) + current k offset of the B loads
+    const char *a_base, *b_base[2]; // A origin; the expert's W (and W3 with DUAL)
+    const char *a_ptr, *b_ptr[2];   // the same at the k of the next A / B loads
+    uint32_t k, k_first, k_end;     // in bytes: k of the latest of those, of the tile's first k-step, end of the reduction
     uint32_t a_voff[LA], b_voff[LB];
     uint32_t a_lds, b_lds;          // this wavefront's first load inside an A / B stage
-    int ksteps, wrap;               // of the reduction; of those, up to its end (then it starts over at k = 0)
     __device__ __forceinline__ void init(const TileCoord& tc, int wave, int lane, const uint16_t* A,
                                          const uint16_t* B0, const uint16_t* B1,
                                          const int32_t* row_index, RowDiv index_div, KStart kstart, int N, int K) {
         const int lrow = lane / Cfg::CPR, lpos = lane % Cfg::CPR;
-        ksteps = K / Cfg::BK;
-        const int k0 = kstart.first<Cfg>(tc, ksteps);
-        wrap = ksteps - k0;
-        a_ptr = a_origin(A, tc, row_index, K) + k0 * Cfg::BK;
-        const size_t expert_off = static_cast<size_t>(tc.expert) * N * K + k0 * Cfg::BK;
-        b_ptr[0] = B0 + expert_off;
-        b_ptr[1] = Cfg::DUAL ? B1 + expert_off : b_ptr[0];
+        k_end = K * 2u;
+        k = k_first = kstart.first<Cfg>(tc, K / Cfg::BK) * Cfg::ROW_BYTES;
+        a_base = reinterpret_cast<const char*>(a_origin(A, tc, row_index, K));
+        const size_t expert_off = static_cast<size_t>(tc.expert) * N * K;
+        b_base[0] = reinterpret_cast<const char*>(B0 + expert_off);
+        b_base[1] = Cfg::DUAL ? reinterpret_cast<const char*>(B1 + expert_off) : b_base[0];
+        set_a();
+        set_b();
         int src[LA];
         source_rows<LA, Cfg::RPI>(src, tc, wave * LA * Cfg::RPI + lrow, row_index, index_div);
 #pragma unroll
@@ -977,14 +993,16 @@ struct LoadPlan1W {
         a_lds = wave * LA * 1024;
         b_lds = wave * LB * 1024;
     }
-    // elements to move a pointer by once the tile's k-step `step` is loaded: none past the last one
-    __device__ __forceinline__ int advance(int step) const {
-        const int on = step + 1 < ksteps ? Cfg::BK : 0;
-        if constexpr (Cfg::DUAL) return on;
-        return step + 1 == wrap && on ? (1 - ksteps) * Cfg::BK : on;
+    // k of the next k-step, round at the end of the reduction; past the tile's last k-step it stays there
+    __device__ __forceinline__ uint32_t after_k() const { return k + Cfg::ROW_BYTES == k_end ? 0u : k + Cfg::ROW_BYTES; }
+    __device__ __forceinline__ void next_k(uint32_t after) { k = after == k_first ? k : after; }
+    __device__ __forceinline__ void set_a() { a_ptr = a_base + k; }
+    __device__ __forceinline__ void set_b() {
+        b_ptr[0] = b_base[0] + k;
+        if (Cfg::DUAL) b_ptr[1] = b_base[1] + k;
     }
     // weight matrix of B load i (W1 and W3 rows alternate in blocks of 32 tile rows)
-    __device__ __forceinline__ const uint16_t* b_src(int wave, int i) const {
+    __device__ __forceinline__ const char* b_src(int wave, int i) const {
         return b_ptr[Cfg::DUAL ? (((wave * LB + i) * Cfg::RPI) >> 5) & 1 : 0];
     }
 };
@@ -1006,8 +1024,9 @@ __device__ __forceinline__ void mma16_then_dma(const bf16x8& w, const bf16x8& x,
 // Every k-step runs exactly this code, without a branch: the accumulators are operands of inline
 // assembly, which the compiler does not know to be MFMAs, so it must never find a reason (a join
 // of two paths, a second loop) to move them between registers next to one. The first half issues
-// the B loads of k-step kt-1+NB, the second half the A loads of k-step kt+NA. Past the end of the
-// reduction the pointers stop advancing: the loads of the last k-steps fetch the last 64 k again
+// the B loads of k-step kt-1+NB, the second half the A loads of k-step kt+NA, which is the same one. Past the
+// end of the reduction the pointers stop advancing: the loads of the last k-steps fetch the last 64 k again (which
+// are in L2; starting over at the first ones cost 1 % of the 6144 x 16384 gate/up)
 // into stages that nobody reads any more, which keeps the number of loads in flight, and with it
 // the load-counter value to wait for, the same in every k-step. Likewise the last k-step reads
 // "next" fragments from a stage that holds nothing new; they are never used.
@@ -1036,7 +1055,7 @@ template <class Cfg, int NA, int NB>
 __device__ __forceinline__ void kstep_1w(f32x4 (&acc)[Cfg::TM][8], bf16x8 (&fa)[2][Cfg::TM],
                                          bf16x8 (&fb)[2][8], RingState1W& rs, LoadPlan1W<Cfg>& lp,
                                          int wave, const unsigned char* pa0, const unsigned char* pa1,
-                                         const unsigned char* pb0, const unsigned char* pb1, int kt) {
+                                         const unsigned char* pb0, const unsigned char* pb1) {
     using R = RingCfg<Cfg, NA, NB>;
     constexpr int TM = Cfg::TM, NM = TM * 8, NR = TM + 8;      // MFMAs and fragment reads per half
     constexpr int LA = LoadPlan1W<Cfg>::LA, LB = LoadPlan1W<Cfg>::LB;
@@ -1063,21 +1082,21 @@ __device__ __forceinline__ void kstep_1w(f32x4 (&acc)[Cfg::TM][8], bf16x8 (&fa)[
     };
     // ---- first half: MFMAs on f[0]; read f[1] (second half of this k-step); the eight B loads
     //      (with DUAL: four loads of W1 rows, then four of W3 rows)
-    int a_adv = 0, b_adv = 0;
+    uint32_t after = 0;
     auto first = [&](auto mtag) {
         constexpr int m = decltype(mtag)::value, i = m >> 3, j = m & 7, n = m / (NM / 8);
         const void* src = lp.b_src(wave, n < 8 ? n : 0);
         mma16_slot<m, NM / 8, 8>(fb[0][j], fa[0][i], acc[i][j], b_region, lp.b_voff, src);
         MOE_FENCE();
         read_behind(mtag, std::integral_constant<int, SPAN1>{}, fb[1], fa[1], pb_h1, pa_h1);
-        // the B pointers move on behind the last B load (MFMA 7 * NM / 8 + 3) while a later k-step exists
+        // the B pointers move on behind the last B load (MFMA 7 * NM / 8 + 3)
         constexpr int after_loads = 7 * (NM / 8) + 4;
         if constexpr (m == (after_loads < NM ? after_loads + 1 : NM - 1)) {
-            lp.b_ptr[0] += b_adv;
-            if (Cfg::DUAL) lp.b_ptr[1] += b_adv;
+            lp.set_b();
             MOE_FENCE();
         }
-        if constexpr (m == NM - 6) { b_adv = lp.advance(kt + NB - 1); MOE_FENCE(); }
+        if constexpr (m == NM - 6) { after = lp.after_k(); MOE_FENCE(); }
+        if constexpr (m == NM - 5) { lp.next_k(after); MOE_FENCE(); }
     };
     // ---- second half: MFMAs on f[1]; read f[0] of k-step kt+1; the A loads; the next k-step's
     //      ring addresses, one small step behind an MFMA at a time
@@ -1099,8 +1118,7 @@ __device__ __forceinline__ void kstep_1w(f32x4 (&acc)[Cfg::TM][8], bf16x8 (&fa)[
         if constexpr (m == 17) { nx.pb_n0 = pb0 + sb2; MOE_FENCE(); }
         if constexpr (m == 18) { nx.a_region = sa1 + lp.a_lds; MOE_FENCE(); }
         if constexpr (m == 21) { nx.b_region = R::A_RING + rs.sb + lp.b_lds; MOE_FENCE(); }
-        if constexpr (m == 22) { a_adv = lp.advance(kt + NA); MOE_FENCE(); }
-        if constexpr (m == NM - 3) { lp.a_ptr += a_adv; MOE_FENCE(); }
+        if constexpr (m == NM - 3) { lp.set_a(); MOE_FENCE(); }
     };
     static_for<NM>(first);
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(LB) : "memory");
@@ -1129,14 +1147,12 @@ __device__ __forceinline__ void prologue_1w(const TileCoord& tc, LoadPlan1W<Cfg>
     for (int s = 0; s < NA; ++s) {
 #pragma unroll
         for (int i = 0; i < LA; ++i) dma16(lp.a_ptr, lp.a_voff[i], s * AB + lp.a_lds + i * 1024);
-        lp.a_ptr += lp.advance(s);
-        if (s < NB - 1) {
 #pragma unroll
-            for (int i = 0; i < LB; ++i)
-                dma16(lp.b_src(wave, i), lp.b_voff[i], R::A_RING + s * BB + lp.b_lds + i * 1024);
-            lp.b_ptr[0] += lp.advance(s);
-            if (Cfg::DUAL) lp.b_ptr[1] += lp.advance(s);
-        }
+        for (int i = 0; i < LB; ++i)
+            dma16(lp.b_src(wave, i), lp.b_voff[i], R::A_RING + s * BB + lp.b_lds + i * 1024);
+        lp.next_k(lp.after_k());
+        lp.set_a();
+        lp.set_b();
     }
 }
 
@@ -1186,8 +1202,8 @@ __device__ __forceinline__ void mainloop_1w(f32x4 (&acc)[Cfg::TM][8], LoadPlan1W
     // two k-steps per trip (K is a multiple of 128 for every supported shape): the loop's own
     // compare-and-branch then falls between MFMAs half as often
     for (int kt = 0; kt < KT; kt += 2) {
-        kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1], kt);
-        kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1], kt + 1);
+        kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1]);
+        kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1]);
     }
     mfma_drain(acc[TM - 1]);                         // before anything else touches the accumulators
 }
@@ -1218,9 +1234,9 @@ __device__ __forceinline__ void ring_tile_1w(const TileCoord& tc, unsigned char*
 }
 
 // Tiles are enumerated at Cfg::BM rows, the last ones of an expert lower (see tile_in_expert). A tile that
-// holds at most HalfCfg::BM = Cfg::BM / 2 rows (an expert's only or second tile, or a half of a tile of the
-// last, partial round: see locate_tile) runs the same pipeline at half height, one of at most LowCfg::BM =
-// Cfg::BM * 3 / 4 rows at three quarters (LowCfg = Cfg: at full height). Every output element is still one
+// holds at most HalfCfg::BM = Cfg::BM / 2 rows (an expert's short tail, or a half of a tile of the last,
+// partial round: see locate_tile) runs the same pipeline at half height, one that was cut to LowCfg::BM =
+// Cfg::BM * 3 / 4 rows at three quarters (LowCfg = Cfg: none is). Every output element is still one
 // accumulator chain over k, so the bits do not depend on which height computed it.
 template <class Cfg, class LowCfg, class HalfCfg, int NA, int NB>
 __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_ring_kernel(
@@ -1228,16 +1244,17 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_ring_kernel(
     const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ row_index, RowDiv index_div,
     KStart kstart, int E, int N, int K, int split_cus) {
-    constexpr bool QUARTERS = LowCfg::BM != Cfg::BM;
+    constexpr bool LOW = LowCfg::BM != Cfg::BM;
     static_assert(HalfCfg::BM * 2 == Cfg::BM && HalfCfg::BN == Cfg::BN && HalfCfg::BK == Cfg::BK &&
                   HalfCfg::NTHREADS == Cfg::NTHREADS && HalfCfg::DUAL == Cfg::DUAL, "same n-tiling");
-    static_assert((!QUARTERS || LowCfg::BM * 4 == Cfg::BM * 3) && LowCfg::BN == Cfg::BN && LowCfg::BK == Cfg::BK &&
+    static_assert((!LOW || LowCfg::BM * 4 == Cfg::BM * 3) && LowCfg::BN == Cfg::BN && LowCfg::BK == Cfg::BK &&
                   LowCfg::NTHREADS == Cfg::NTHREADS && LowCfg::DUAL == Cfg::DUAL, "same n-tiling");
     static_assert(RingCfg<HalfCfg, NA, NB>::SMEM <= RingCfg<Cfg, NA, NB>::SMEM &&
                   RingCfg<LowCfg, NA, NB>::SMEM <= RingCfg<Cfg, NA, NB>::SMEM, "LDS of the full tile");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
-    const TileCoord tc = locate_tile<Cfg::BM, QUARTERS>(offsets, E, N / Cfg::BN_OUT, split_cus);
+    const TileCoord tc = locate_tile<Cfg::BM>(offsets, E, N / Cfg::BN_OUT, split_cus,
+                                              LOW && (!Cfg::DUAL || K < kLowGateUpK));
     if (tc.expert < 0) return;                       // uniform for the whole workgroup
     // four wavefronts of (128, 96 or 64) x 128 outputs run the one-wavefront-per-SIMD pipeline
     auto run = [&](auto cfg_tag) {
@@ -1247,8 +1264,8 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_ring_kernel(
         else
             ring_tile<TileCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, kstart, N, K);
     };
-    if (tc.rows <= HalfCfg::BM) run(type_tag<HalfCfg>{});
-    else if (QUARTERS && tc.rows <= LowCfg::BM) run(type_tag<LowCfg>{});
+    if (tc.height == HalfCfg::BM) run(type_tag<HalfCfg>{});
+    else if (LOW && tc.height == LowCfg::BM) run(type_tag<LowCfg>{});
     else run(type_tag<Cfg>{});
 }
 

@@ -1098,9 +1098,11 @@ def test_layer_other_expert_shapes(T, d, f, E, k, use_bias):
 @pytest.mark.parametrize("T,d,f,E,k", [
     (600, 1536, 2048, 10, 2),      # the shortest staggered reduction; starts at its first, last and last but one k-step
     (90, 512, 2176, 40, 3),        # k-steps that seven does not divide, one block of columns
+    (600, 2048, 4224, 10, 2),      # gate/up: the shortest staggered reduction, two blocks of columns, the second partial
+    (300, 4096, 256, 33, 2),       # ... and one of 64 k-steps, thirteen apart
 ])
 def test_layer_staggered_reductions(T, d, f, E, k):
-    """The down projection of a long reduction starts at another k per expert and block of columns: every
+    """A long reduction starts at another k per expert and block of columns: every
     tile configuration and call form has to start at the same one."""
     say(f"layer T={T} d={d} f={f} E={E} k={k}: staggered reductions")
     cfg = synth.LayerConfig("custom", T, d, f, E, k, seed=77)
