@@ -111,32 +111,10 @@ struct NTiles {
     int ksteps;                  // of the reduction
 };
 
-// Large tiles against 128-row ones when experts have several row tiles. Launch time in units of one
-// full 256-row tile for the given row tiles: a large tile costs 1, a tail of at most 128 rows 0.55
-// (half-height tile), a 128-row tile of the generic kernel 0.8. A launch of many rounds of tiles
-// (one workgroup per compute unit) costs its tiles; one of fewer than four rounds costs whole
-// rounds, a last round under half full 0.55 with the large tiles (it is split), and the large
-// tiles 1.25 times their count then (fewer, longer tiles balance worse). Measured on
-// micro-batches of 1024 and 2048 tokens at the 8x22B shape, where the two GEMMs of one call want
-// different answers.
-double large_minus_mid(double units0, double tiles0, double tiles1, int cus) {
-    double t0;
-    if (tiles0 >= 4.0 * cus) {
-        t0 = units0 / cus;
-    } else {
-        const double whole = std::floor(tiles0 / cus), rem = tiles0 - whole * cus;
-        t0 = 1.25 * (whole + (rem <= 0.0 ? 0.0 : rem <= 0.5 * cus ? 0.55 : 1.0));
-    }
-    return t0 - 0.8 * (tiles1 >= 4.0 * cus ? tiles1 / cus : std::ceil(tiles1 / cus));
-}
-
 // Tile configuration by average rows per expert. All configurations give identical bits.
 //
 // The measured constants of this rule and of the variants in launch_gateup and launch_down, and what each stands
 // on ("cold": a graph of calls with other weights every time, 1.2 GB and more of them; else the same ones):
-//   0.8         a 128-row tile (or its padded row) against a 256-row one: micro-batches of 64 to 512 tokens
-//               at 6144 x 16384, 8 experts; 0.55 a half-height tile, 1.25 large tiles in under four rounds:
-//               micro-batches of 1024 and 2048 tokens there
 //   0.82, 0.6   k-step of a 96- or 128-row tile (256 or 128 columns), 0.41 / 0.58 and 0.27 / 0.38 of one 64-row
 //               tile alone on a compute unit / of two: one expert of 4096 x 14336, 512 rows (below)
 //   0.56, 0.8   k-step of a 256-row tile where at most half the compute units have one, weights from cache / from
@@ -166,34 +144,17 @@ int pick_config(const GemmEnv& env, int R, int E, const NTiles& nt) {
     // experts past 64 rows (560 tokens through 64 experts of 2048 x 1408) 207 against 196.
     if (upper <= 64.0) return 2;
     const int cus = compute_units(env.device);
-    int config;
-    if (upper <= 96.0) {
-        config = 4;
-    } else if (upper <= 256.0) {
-        // one row tile per expert either way: the padded rows decide, the large tiles priced at
-        // 0.8 of the time per padded row of the 128-row ones (measured on micro-batches of 64 to
-        // 512 tokens at the 8x22B shape)
-        const double padded_mid = std::ceil(upper / 128.0) * 128.0;
-        config = 256.0 * 0.8 <= padded_mid ? 0 : 1;
-    } else {
-        // several row tiles per expert, for groups one standard deviation below and above the mean
-        double units0[2], tiles0[2], tiles1[2];
-        for (int i = 0; i < 2; ++i) {
-            const double m = i == 0 ? std::max(1.0, avg - sigma) : avg + sigma;
-            const double full = std::floor(m / 256.0), tail = m - full * 256.0;
-            units0[i] = E * nt.large * (full + (tail <= 0.0 ? 0.0 : tail <= 128.0 ? 0.55 : 1.0));
-            tiles0[i] = E * nt.large * std::ceil(m / 256.0);
-            tiles1[i] = E * nt.mid * std::ceil(m / 128.0);
-        }
-        double diff;
-        if (E == 1)        // a single group is one or the other, not half of each
-            diff = large_minus_mid(units0[0], tiles0[0], tiles1[0], cus) +
-                   large_minus_mid(units0[1], tiles0[1], tiles1[1], cus);
-        else
-            diff = large_minus_mid(0.5 * (units0[0] + units0[1]), 0.5 * (tiles0[0] + tiles0[1]),
-                                   0.5 * (tiles1[0] + tiles1[1]), cus);
-        config = diff <= 0.0 ? 0 : 1;
-    }
+    // The 96- and 128-row tiles only where the largest group is expected to fit one: a second tile costs more than
+    // they gain. The largest of E groups lies about sqrt(2 ln E) standard deviations above the mean (two for the
+    // 8 experts that the lines were drawn at). Gate/up and down, 96- / 128- / 256-row tiles: 800 tokens through 64 experts
+    // of 2048 x 1408 (75 rows each) 149 and 96, 147 and 77, 149 and 77 us; 280 through 8 of 6144 x 16384 (70) 529 and 255,
+    // 536 and 270, 577 and 297. 128- / 256-row: 1700 through 128 of 2048 x 768 (106) 182 and 112, 162 and 101;
+    // 420 through 8 of 4096 x 14336 (105) 334 and 178, 344 and 238; 460 (115) 344 and 306, 344 and 243. With more rows the
+    // 256-row tiles and their lower tails are the faster ones (4096 x 14336, 600 tokens 491 and 316, 367 and 246, 2048 1039
+    // and 731, 775 and 488; 6144 x 16384, 1000 tokens 986 and 541, 783 and 412; two experts of 4096 x 14336 with 300 rows
+    // each, gate/up 206 and 139).
+    const double largest = avg + std::max(2.0, std::sqrt(2.0 * std::log(static_cast<double>(E)))) * sigma;
+    const int config = largest <= 96.0 ? 4 : largest <= 128.0 ? 1 : 0;
     // A launch of at most one such tile per compute unit takes one tile's time however many compute
     // units idle: small tiles are worth their extra loads if they use the idle ones. Units of a
     // k-step of a full 256-row tile (about 1 us), measured on one expert of 4096 x 14336 (512 rows,

@@ -544,6 +544,8 @@ def test_expert_ffn_configs_agree_bitwise():
     (1024, 384, [63, 64, 65, 1, 0, 129]),            # 64-row tiles instead of a few 96-row ones
     (512, 1024, [512]),                              # ... and instead of a few 256-row ones
     (512, 1024, [128, 0, 256, 65, 64, 129, 191, 192]),   # ... of a short reduction
+    (512, 256, [90 + 3 * (e % 12) for e in range(64)]),  # 256-row tiles at half height where some of many groups pass 128 rows
+    (512, 1024, [300, 280, 260, 310, 250, 200, 330]),    # ... and at three quarters
 ])
 @pytest.mark.parametrize("fp32_outputs", [False, True])
 def test_automatic_tile_choice_agrees_bitwise(d, f, rows, fp32_outputs):
