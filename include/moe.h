@@ -147,7 +147,9 @@ int moe_permute_static(const int32_t* topk_idx, int32_t T, int32_t k, int32_t E,
  * bf16 operands, fp32 accumulation on the matrix cores, the intermediate H and y_perm
  * rounded to bf16 (nearest even). R = number of rows = offsets[E] (R <= T_max*k).
  * x_perm [R,d_model]; offsets [E+1] int32 (device); W1, W3 [E,d_ff,d_model]; W2 [E,d_model,d_ff];
- * y_perm [R,d_model] bf16 out. Per-element accumulation order does not depend on R. */
+ * y_perm [R,d_model] bf16 out. Every sum runs over ascending k
+ * from the first, whatever R, an expert's number of rows and its place among the E: a call of some
+ * experts gives the bits of a call of all. */
 int moe_expert_ffn(moe_ctx* ctx, const moe_bf16* x_perm, const int32_t* offsets, int32_t R,
                    const moe_bf16* W1, const moe_bf16* W3, const moe_bf16* W2, moe_bf16* y_perm,
                    void* stream);

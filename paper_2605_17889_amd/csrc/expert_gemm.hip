@@ -7,10 +7,10 @@
 //
 // A workgroup owns a BM x BN output tile of ONE expert; tiles are enumerated on the device
 // from `offsets` (no host synchronisation, variable rows per expert, empty experts produce no
-// tile). Every output element is one accumulator chain over ascending k, from a start that depends on the
-// shape, the expert and the output column alone (gemm::KStart), with the same MFMA instruction in every
-// tile configuration, so results do not depend on how many rows an expert has or which
-// configuration is picked (coalesced == micro-batched, bit for bit).
+// tile). Every output element is one accumulator chain over k = 0,16,32,... with the same
+// MFMA instruction in every tile configuration, so results do not depend on how many rows an
+// expert has, on its place among the experts of a call or on which configuration is picked
+// (coalesced == micro-batched, some experts == all of them, bit for bit).
 #include <algorithm>
 #include <atomic>
 #include <cmath>
@@ -68,14 +68,14 @@ long long most_row_tiles(int R, int E, int BM) { return R / BM + std::min(E, R);
 // The generic kernel with Cfg::NSTAGE stages.
 template <class Cfg>
 int launch_grouped(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, const moe_bf16* B1, moe_bf16* C,
-                   const int32_t* offsets, const int32_t* row_index, int index_div, gemm::KStart kstart,
+                   const int32_t* offsets, const int32_t* row_index, int index_div,
                    int R, int E, int N, int K, hipStream_t s) {
     if (N % Cfg::BN_OUT != 0 || K % Cfg::BK != 0) return MOE_ERR_UNSUPPORTED_SHAPE;
     static std::atomic<uint64_t> attr_set{0};
     const long long max_mt = most_row_tiles(R, E, Cfg::BM);
     return launch_tiles(env, attr_set, gemm::grouped_gemm_kernel<Cfg>, Cfg::SMEM, Cfg::NTHREADS,
                         max_mt * (N / Cfg::BN_OUT), s, A, B0, B1, C, offsets, row_index,
-                        gemm::RowDiv(index_div), kstart, E, N, K);
+                        gemm::RowDiv(index_div), E, N, K);
 }
 
 // The pipelined kernel with operand rings of NA and NB stages; tiles of at most LowCfg::BM rows run at three
@@ -83,7 +83,7 @@ int launch_grouped(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, co
 // half full at half of it.
 template <class Cfg, class LowCfg, class HalfCfg, int NA, int NB>
 int launch_ring(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, const moe_bf16* B1, moe_bf16* C,
-                const int32_t* offsets, const int32_t* row_index, int index_div, gemm::KStart kstart,
+                const int32_t* offsets, const int32_t* row_index, int index_div,
                 int R, int E, int N, int K, hipStream_t s) {
     if (N % Cfg::BN_OUT != 0 || K % Cfg::BK != 0) return MOE_ERR_UNSUPPORTED_SHAPE;
     if (K / Cfg::BK < (NA > NB ? NA : NB)) return MOE_ERR_UNSUPPORTED_SHAPE;
@@ -94,7 +94,7 @@ int launch_ring(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, const
     const long long grid = max_mt * (N / Cfg::BN_OUT) + kXcds * ((cus / 2 + kXcds - 1) / kXcds + 1);
     return launch_tiles(env, attr_set, gemm::grouped_gemm_ring_kernel<Cfg, LowCfg, HalfCfg, NA, NB>,
                         gemm::RingCfg<Cfg, NA, NB>::SMEM, Cfg::NTHREADS, grid, s, A, B0, B1, C,
-                        offsets, row_index, gemm::RowDiv(index_div), kstart, E, N, K, cus);
+                        offsets, row_index, gemm::RowDiv(index_div), E, N, K, cus);
 }
 
 // Expected row tiles of height h: groups one standard deviation below and above the mean.
@@ -257,54 +257,34 @@ using DownTinyS    = Config<32, 64, 64, 2, 2, 4, false, true>;
 using DownFew      = Config<16, 32, 64, 1, 2, 6, false>;
 using DownFewS     = Config<16, 32, 64, 1, 2, 6, false, true>;
 
-// Start of the reductions of K for N output columns: staggered over long ones, thirteen k-steps from block to block
-// of columns, or one where a reduction has fewer than 64. Before -> after, cold weights.
-// Down: 2 tokens through 8 experts of 4096 x 14336 87 -> 72 us, 16 140 -> 139, 40 150 -> 140, 256 158 -> 153, 2048
-// 508 -> 491 (one apart: 16 tokens 157, 256 174); 6144 x 16384, 16 tokens 267 -> 244, 256 266 -> 248, 4096
-// 1323 -> 1310; 32 experts of 2048 x 2048, 4 per token, 16 tokens 46 -> 39, 500 68 -> 49 (thirteen apart 40 and 50).
-// Gate/up: 4096 x 14336, 16 tokens 286 -> 275, 64 291 -> 280, 256 331 to 350 (with the place of the weights in
-// memory) -> 314, 1024 500 -> 488 (one apart 288, 288, 317, 485); 6144 x 16384, 16 tokens 492 -> 465; 128 experts of 2048 x 768,
-// 500 tokens 140 to 153 -> 129 to 135, 1000 148 -> 141, 2000 163 -> 157 (thirteen apart 136, 143, 159); 32 of
-// 2048 x 2048, 500 tokens 127 -> 91. Reductions whose rows are no power of two apart gain nothing and lose nothing
-// (32 experts of 3072 x 3072), 6144 x 16384 at 8192 tokens neither.
-// A reduction of 12 or 22 steps only loses the sharing between large tiles (down, 8192 tokens through 128 experts of
-// 2048 x 768 248 -> 255 us).
-gemm::KStart reduction_start(bool dual, int e0, int N, int K) {
-    if (K < 2048) return gemm::KStart{0, 0, 0};
-    const int cols = gemm::KStart::columns(dual);
-    return gemm::KStart{K < 4096 ? 1 : 13, e0, (N + cols - 1) / cols};
-}
-
 }  // namespace
 
 // `a` is the grouped activation matrix [R, d] when row_index is NULL; otherwise it is the
 // token matrix [T, d] and grouped row p reads token row_index[p] / index_div (the caller makes
 // sure that T * d * 2 bytes fit a 32-bit offset). R bounds the rows of the E launched experts
 // (it sizes the grid); R_hint is how many rows they are expected to hold together (it picks the
-// tile configuration): the two differ when a call covers a subset of a layer's experts, which are
-// then the layer's experts e0, e0 + 1, ...
+// tile configuration): the two differ when a call covers a subset of a layer's experts.
 int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_index, int index_div,
-                  const int32_t* offsets, int R, int R_hint, int d, int f, int e0, int E,
+                  const int32_t* offsets, int R, int R_hint, int d, int f, int E,
                   const moe_bf16* W1, const moe_bf16* W3, moe_bf16* H, hipStream_t s) {
     if (R == 0) return MOE_OK;
     const moe_bf16* x_perm = a;
-    const gemm::KStart ks = reduction_start(true, e0, f, d);
     int config = pick_config(env, R_hint, E, NTiles{f / 128, f / 128, f / 64, 0.82, 0.41, 0.58,
                                                     4e-6 * E * d * f, d / 64});
     if (config == 0 && d / 64 < 3) config = 1;     // the pipelined kernel needs three k-steps
     switch (config) {
         case 0:
             if (use_one_wave_per_simd(env, f, d))
-                return launch_ring<GateUpLarge1W, GateUpLow1W, GateUpHalf1W, 2, 3>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
-            return launch_ring<GateUpLarge, GateUpLarge, GateUpMid, 2, 3>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
+                return launch_ring<GateUpLarge1W, GateUpLow1W, GateUpHalf1W, 2, 3>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
+            return launch_ring<GateUpLarge, GateUpLarge, GateUpMid, 2, 3>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
         case 1:
             if (single_m_tile(env, R_hint, E, 128))
-                return launch_grouped<GateUpMidS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
-            return launch_grouped<GateUpMid>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
+                return launch_grouped<GateUpMidS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
+            return launch_grouped<GateUpMid>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
         case 4:
             if (single_m_tile(env, R_hint, E, 96))
-                return launch_grouped<GateUpMid96S>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
-            return launch_grouped<GateUpMid96>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
+                return launch_grouped<GateUpMid96S>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
+            return launch_grouped<GateUpMid96>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
         case 3:
             if (single_m_tile(env, R_hint, E, 32)) {
                 const double nt = touched_experts(R_hint, E) * (f / 64);
@@ -316,20 +296,20 @@ int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_inde
                 // 41.8 and 41.2; 4 tokens, 6 of 64, 4.0: 46.9 and 43.4)
                 if (2.0 * nt <= 2.5 * cus) {
                     if (2.0 * nt <= cus)
-                        return launch_grouped<GateUpFewDeepS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
-                    return launch_grouped<GateUpFewS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
+                        return launch_grouped<GateUpFewDeepS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
+                    return launch_grouped<GateUpFewS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
                 }
                 // 16 tokens through 8 experts of 4096 x 14336, 7 rounds of one workgroup per compute unit or
                 // 3.5 of two: 280 against 284 us; 4 tokens at 6144 x 16384, 6 or 3 rounds: 397 against 367
                 if (last_round_use(nt, 2.0 * cus) < 0.93 * last_round_use(nt, cus))
-                    return launch_grouped<GateUpTinyDeepS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
-                return launch_grouped<GateUpTinyS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
+                    return launch_grouped<GateUpTinyDeepS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
+                return launch_grouped<GateUpTinyS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
             }
-            return launch_grouped<GateUpTiny>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
+            return launch_grouped<GateUpTiny>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
         default:
             if (single_m_tile(env, R_hint, E, 64))
-                return launch_grouped<GateUpSmallS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
-            return launch_grouped<GateUpSmall>(env, x_perm, W1, W3, H, offsets, row_index, index_div, ks, R, E, f, d, s);
+                return launch_grouped<GateUpSmallS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
+            return launch_grouped<GateUpSmall>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
     }
 }
 
@@ -338,9 +318,8 @@ namespace {
 // F32: the same tilings with a float output matrix (gemm::F32Out).
 template <bool F32>
 int launch_down_as(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets, int R, int R_hint,
-                   int d, int f, int e0, int E, const moe_bf16* W2, moe_bf16* y_perm, hipStream_t s) {
+                   int d, int f, int E, const moe_bf16* W2, moe_bf16* y_perm, hipStream_t s) {
     if (R == 0) return MOE_OK;
-    const gemm::KStart ks = reduction_start(false, e0, d, f);
     const bool wide_mid = static_cast<long long>(E) * (d / 256) >= 160 && d % 256 == 0;
     const int cus = compute_units(env.device);
     // Tiles of 128 columns make one per compute unit: the row tiles of 32 and 64 rows are then 64 x 128 (64 x 64 for
@@ -355,50 +334,50 @@ int launch_down_as(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets
     switch (config) {
         case 0:
             if (use_one_wave_per_simd(env, d, f))
-                return launch_ring<Out<F32, DownLarge1W>, Out<F32, DownLow1W>, Out<F32, DownHalf1W>, 2, 3>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
-            return launch_ring<Out<F32, DownLarge>, Out<F32, DownLarge>, Out<F32, DownMidWide>, 2, 3>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+                return launch_ring<Out<F32, DownLarge1W>, Out<F32, DownLow1W>, Out<F32, DownHalf1W>, 2, 3>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
+            return launch_ring<Out<F32, DownLarge>, Out<F32, DownLarge>, Out<F32, DownMidWide>, 2, 3>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
         case 1:
             // HBM-bound: wide tiles stream more bytes per workgroup, but only if there are
             // enough of them to occupy the 256 compute units (about one m-tile per expert).
             if (wide_mid) {
                 if (single_m_tile(env, R_hint, E, 128))
-                    return launch_grouped<Out<F32, DownMidWideS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
-                return launch_grouped<Out<F32, DownMidWide>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+                    return launch_grouped<Out<F32, DownMidWideS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
+                return launch_grouped<Out<F32, DownMidWide>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
             }
             if (single_m_tile(env, R_hint, E, 128))
-                return launch_grouped<Out<F32, DownMidS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
-            return launch_grouped<Out<F32, DownMid>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+                return launch_grouped<Out<F32, DownMidS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
+            return launch_grouped<Out<F32, DownMid>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
         case 4:
             // wide tiles where there are enough of them for the 256 compute units, as for case 1
             if (wide_mid) {
                 if (single_m_tile(env, R_hint, E, 96))
-                    return launch_grouped<Out<F32, DownMid96WideS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
-                return launch_grouped<Out<F32, DownMid96Wide>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+                    return launch_grouped<Out<F32, DownMid96WideS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
+                return launch_grouped<Out<F32, DownMid96Wide>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
             }
             if (single_m_tile(env, R_hint, E, 96))
-                return launch_grouped<Out<F32, DownMid96S>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
-            return launch_grouped<Out<F32, DownMid96>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+                return launch_grouped<Out<F32, DownMid96S>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
+            return launch_grouped<Out<F32, DownMid96>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
         case 3:
             if (one_wide_each && single_m_tile(env, R_hint, E, 64))
-                return launch_grouped<Out<F32, DownSmallWideS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+                return launch_grouped<Out<F32, DownSmallWideS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
             // 32-column tiles where 64-column ones would leave compute units without any: one token through 2 of
             // 8 experts of 4096 x 14336 46 against 70 us; and while all of their row tiles find one: 64 tokens
             // through 2 of 8 of 512 x 1024 7.6 against 8.9 us
             if (touched_experts(R_hint, E) * (d / 64) < cus) {
                 if (single_m_tile(env, R_hint, E, 16))
-                    return launch_grouped<Out<F32, DownFewS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+                    return launch_grouped<Out<F32, DownFewS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
                 if (row_tiles(R_hint, E, 16) * (d / 32) <= cus)
-                    return launch_grouped<Out<F32, DownFew>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+                    return launch_grouped<Out<F32, DownFew>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
             }
             if (single_m_tile(env, R_hint, E, 32)) {
-                return launch_grouped<Out<F32, DownTinyS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+                return launch_grouped<Out<F32, DownTinyS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
             }
-            return launch_grouped<Out<F32, DownTiny>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+            return launch_grouped<Out<F32, DownTiny>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
         default:
             // 32-row tiles where the 64-row ones would leave half of the compute units without any: 256 tokens through
             // 2 of 8 experts of 512 x 1024 (96 tiles) 9.2 against 10.2 us, 600 (192 tiles) 10.9 against 10.2
             if (row_tiles(R_hint, E, 64) * (d / 64) <= 0.5 * cus)
-                return launch_grouped<Out<F32, DownTiny>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+                return launch_grouped<Out<F32, DownTiny>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
             // 128 columns where that makes about two rounds of two workgroups per compute unit, else 64. Layer calls
             // with cold weights, 128 against 64 columns: 500 tokens through 128 experts of 2048 x 768 (8 tiles of 128
             // columns per compute unit) 239 and 243 us, 448 through 56 of 2048 x 1024, 4 per token (3.5) 149.2 and
@@ -406,24 +385,23 @@ int launch_down_as(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets
             // tokens through 48 of 2048 x 1024 128.7 and 134.6, 192 through 24 of 4096 x 2048 242 and 238)
             if (one_wide_each || wide_tiles >= 3.5 * cus) {
                 if (single_m_tile(env, R_hint, E, 64))
-                    return launch_grouped<Out<F32, DownSmallWideS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
-                return launch_grouped<Out<F32, DownSmallWide>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+                    return launch_grouped<Out<F32, DownSmallWideS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
+                return launch_grouped<Out<F32, DownSmallWide>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
             }
             if (single_m_tile(env, R_hint, E, 64))
-                return launch_grouped<Out<F32, DownSmallS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
-            return launch_grouped<Out<F32, DownSmall>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, ks, R, E, d, f, s);
+                return launch_grouped<Out<F32, DownSmallS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
+            return launch_grouped<Out<F32, DownSmall>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
     }
 }
 
 }  // namespace
 
-// y_perm is [R, d] bf16, or [R, d] fp32 when y_f32 is set. The E launched experts are the layer's experts
-// e0, e0 + 1, ...
+// y_perm is [R, d] bf16, or [R, d] fp32 when y_f32 is set.
 int launch_down(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets, int R, int R_hint,
-                int d, int f, int e0, int E, const moe_bf16* W2, void* y_perm, bool y_f32, hipStream_t s) {
+                int d, int f, int E, const moe_bf16* W2, void* y_perm, bool y_f32, hipStream_t s) {
     moe_bf16* out = static_cast<moe_bf16*>(y_perm);
-    return y_f32 ? launch_down_as<true>(env, H, offsets, R, R_hint, d, f, e0, E, W2, out, s)
-                 : launch_down_as<false>(env, H, offsets, R, R_hint, d, f, e0, E, W2, out, s);
+    return y_f32 ? launch_down_as<true>(env, H, offsets, R, R_hint, d, f, E, W2, out, s)
+                 : launch_down_as<false>(env, H, offsets, R, R_hint, d, f, E, W2, out, s);
 }
 
 }  // namespace moe

@@ -274,31 +274,6 @@ __device__ __forceinline__ TileCoord locate_tile(const int32_t* __restrict__ off
     return tc;
 }
 
-// Where a tile's reduction starts: at k-step first(), running to the end and round to the steps before it. The
-// workgroups of a launch of about one round start together and stay in step, so that with all of them at
-// the same k their weight rows, a whole reduction apart, fall on few memory channels at a time. The start
-// depends on the expert of the layer and the block of output columns alone, so that every tile configuration and
-// every call form sums an element in the same order, and the tiles of an expert that share activation rows in
-// an L2 (large tiles: 8 x 4 resident at a time) mostly stay at the same k. Down: blocks of 1024 columns (16 tokens at
-// 6144 x 16384 246 to 253 us, 262 to 267 with 2048). Gate/up has more columns and keeps the large tiles together
-// with blocks of 4096 (8192 tokens at 6144 x 16384 4650 us, with 1024 4665, without a stagger 4646; 1024 tokens at
-// 4096 x 14336 470, 470 and 486).
-struct KStart {
-    int mul;       // k-steps between neighbouring blocks, or 0: all at k = 0
-    int e0;        // the layer's number of the launch's first expert
-    int blocks;    // blocks of columns per expert
-    static constexpr int columns(bool dual) { return dual ? 4096 : 1024; }    // of a block
-    template <class Cfg>
-    __device__ __forceinline__ int first(const TileCoord& tc, int ksteps) const {
-        constexpr int COLS = columns(Cfg::DUAL);
-        static_assert(COLS % Cfg::BN_OUT == 0, "a tile lies in one block");
-        if (mul == 0) return 0;
-        int rem;
-        div_small(((e0 + tc.expert) * blocks + tc.nt * Cfg::BN_OUT / COLS) * mul, ksteps, rem);
-        return rem;
-    }
-};
-
 // LDS tile layout: rows of BK bf16 in 16-byte chunks; logical chunk c of row r is stored at
 // chunk position c ^ swz(r). LDS has 64 four-byte banks and a 16-byte read is served 16 lanes
 // at a time; the 16 lanes of a fragment read the same logical chunk of 16 consecutive rows,
@@ -601,7 +576,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
     const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ row_index, RowDiv index_div,
-    KStart kstart, int E, int N, int K) {
+    int E, int N, int K) {
     constexpr int BM = Cfg::BM, BK = Cfg::BK, WN = Cfg::WN;
     constexpr int TM = Cfg::TM, TN = Cfg::TN, LPW = Cfg::LPW, NSTAGE = Cfg::NSTAGE;
 
@@ -628,14 +603,9 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
 
     // ---- main loop: ring of NSTAGE stages, NSTAGE-1 k-steps of loads in flight.
     const int KT = K / BK;
-    int kload = kstart.first<Cfg>(tc, KT);     // k-step of the next load
-    auto issue = [&](int st) {
-        lp.issue_all(st * Cfg::STAGE_BYTES, static_cast<size_t>(kload) * BK);
-        kload = kload + 1 == KT ? 0 : kload + 1;
-    };
 #pragma unroll
     for (int s = 0; s < NSTAGE - 1; ++s)
-        if (s < KT) issue(s);
+        if (s < KT) lp.issue_all(s * Cfg::STAGE_BYTES, static_cast<size_t>(s) * BK);
     int stage = 0;
     for (int kt = 0; kt < KT; ++kt) {
         // The loads of k-step kt are the oldest in flight; up to NSTAGE-2 newer steps may stay
@@ -643,7 +613,10 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
         if (kt + NSTAGE - 2 < KT) wait_vmcnt<(NSTAGE - 2) * LPW>(); else wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();          // stage `stage` is complete for every wavefront
                                                // and stage (stage-1) is no longer being read
-        if (kt + NSTAGE - 1 < KT) issue(stage == 0 ? NSTAGE - 1 : stage - 1);
+        const int nk = kt + NSTAGE - 1;
+        if (nk < KT)
+            lp.issue_all((stage == 0 ? NSTAGE - 1 : stage - 1) * Cfg::STAGE_BYTES,
+                         static_cast<size_t>(nk) * BK);
         mma_stage<Cfg>(smem + stage * Cfg::STAGE_BYTES, fp, acc);
         stage = (stage + 1 == NSTAGE) ? 0 : stage + 1;
     }
@@ -765,7 +738,7 @@ __device__ __forceinline__ void ring_tile(const TileCoord& tc, unsigned char* sm
                                           const uint16_t* __restrict__ B0,
                                           const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
                                           const int32_t* __restrict__ row_index, RowDiv index_div,
-                                          KStart kstart, int N, int K) {
+                                          int N, int K) {
     using R = RingCfg<Cfg, NA, NB>;
     constexpr int BM = Cfg::BM, BK = Cfg::BK, WN = Cfg::WN, TM = Cfg::TM, TN = Cfg::TN;
     constexpr int LA = R::LA, LB = R::LB, AB = Cfg::A_BYTES, BB = Cfg::B_BYTES;
@@ -793,18 +766,13 @@ __device__ __forceinline__ void ring_tile(const TileCoord& tc, unsigned char* sm
 
     const int KT = K / BK;                           // >= max(NA, NB) (checked by the launcher)
     constexpr int NMAX = NA < NB ? NB : NA;
-    const int k0 = kstart.first<Cfg>(tc, KT);
-    auto k_offset = [&](int step) {                  // of the step-th k-step of this tile
-        step += k0;
-        return static_cast<size_t>(step >= KT ? step - KT : step) * BK;
-    };
 
     auto run = [&](auto compute_tag, auto partial_tag) {
         constexpr bool COMPUTE = decltype(compute_tag)::value, PARTIAL = decltype(partial_tag)::value;
         // prologue: fill both rings in the order the k-loop would have issued them
 #pragma unroll
         for (int s = 0; s < NMAX; ++s) {
-            const size_t koff = k_offset(s);
+            const size_t koff = static_cast<size_t>(s) * BK;
             if (R::A_FIRST) {
                 if (s < NA) for (int i = 0; i < LA; ++i) if (!PARTIAL || lp.a_on[i]) lp.issue_a(i, s * AB, koff);
                 if (s < NB) for (int i = 0; i < LB; ++i) lp.issue_b(i, R::A_RING + s * BB, koff);
@@ -834,7 +802,7 @@ __device__ __forceinline__ void ring_tile(const TileCoord& tc, unsigned char* sm
             ring_kstep<Cfg, NA, NB, COMPUTE, PARTIAL, RT>(
                 acc, fa, fx, fb0, fb1, pa[1] + ra * AB, pb[1] + rb * BB, pa[0] + ra1 * AB,
                 pb[0] + rb1 * BB, lp, ra * AB, R::A_RING + rb * BB,
-                k_offset(kt + NA), k_offset(kt + NB), kt + NA < KT,
+                static_cast<size_t>(kt + NA) * BK, static_cast<size_t>(kt + NB) * BK, kt + NA < KT,
                 kt + NB < KT, kt + 1 < KT);
             ra = ra1; rb = rb1;
         };
@@ -962,23 +930,18 @@ __device__ __forceinline__ void static_for(F&& f) {
 template <class Cfg>
 struct LoadPlan1W {
     static constexpr int LA = Cfg::NIA / Cfg::NW, LB = Cfg::NIB / Cfg::NW;
-    const char *a_base, *b_base[2]; // A origin; the expert's W (and W3 with DUAL)
-    const char *a_ptr, *b_ptr[2];   // the same at the k of the next A / B loads
-    uint32_t k, k_first, k_end;     // in bytes: k of the latest of those, of the tile's first k-step, end of the reduction
+    const uint16_t* a_ptr;          // A origin + current k offset of the A loads
+    const uint16_t* b_ptr[2];       // expert's W (and W3 with DUAL) + current k offset of the B loads
     uint32_t a_voff[LA], b_voff[LB];
     uint32_t a_lds, b_lds;          // this wavefront's first load inside an A / B stage
     __device__ __forceinline__ void init(const TileCoord& tc, int wave, int lane, const uint16_t* A,
                                          const uint16_t* B0, const uint16_t* B1,
-                                         const int32_t* row_index, RowDiv index_div, KStart kstart, int N, int K) {
+                                         const int32_t* row_index, RowDiv index_div, int N, int K) {
         const int lrow = lane / Cfg::CPR, lpos = lane % Cfg::CPR;
-        k_end = K * 2u;
-        k = k_first = kstart.first<Cfg>(tc, K / Cfg::BK) * Cfg::ROW_BYTES;
-        a_base = reinterpret_cast<const char*>(a_origin(A, tc, row_index, K));
+        a_ptr = a_origin(A, tc, row_index, K);
         const size_t expert_off = static_cast<size_t>(tc.expert) * N * K;
-        b_base[0] = reinterpret_cast<const char*>(B0 + expert_off);
-        b_base[1] = Cfg::DUAL ? reinterpret_cast<const char*>(B1 + expert_off) : b_base[0];
-        set_a();
-        set_b();
+        b_ptr[0] = B0 + expert_off;
+        b_ptr[1] = Cfg::DUAL ? B1 + expert_off : b_ptr[0];
         int src[LA];
         source_rows<LA, Cfg::RPI>(src, tc, wave * LA * Cfg::RPI + lrow, row_index, index_div);
 #pragma unroll
@@ -995,16 +958,8 @@ struct LoadPlan1W {
         a_lds = wave * LA * 1024;
         b_lds = wave * LB * 1024;
     }
-    // k of the next k-step, round at the end of the reduction; past the tile's last k-step it stays there
-    __device__ __forceinline__ uint32_t after_k() const { return k + Cfg::ROW_BYTES == k_end ? 0u : k + Cfg::ROW_BYTES; }
-    __device__ __forceinline__ void next_k(uint32_t after) { k = after == k_first ? k : after; }
-    __device__ __forceinline__ void set_a() { a_ptr = a_base + k; }
-    __device__ __forceinline__ void set_b() {
-        b_ptr[0] = b_base[0] + k;
-        if (Cfg::DUAL) b_ptr[1] = b_base[1] + k;
-    }
     // weight matrix of B load i (W1 and W3 rows alternate in blocks of 32 tile rows)
-    __device__ __forceinline__ const char* b_src(int wave, int i) const {
+    __device__ __forceinline__ const uint16_t* b_src(int wave, int i) const {
         return b_ptr[Cfg::DUAL ? (((wave * LB + i) * Cfg::RPI) >> 5) & 1 : 0];
     }
 };
@@ -1026,9 +981,8 @@ __device__ __forceinline__ void mma16_then_dma(const bf16x8& w, const bf16x8& x,
 // Every k-step runs exactly this code, without a branch: the accumulators are operands of inline
 // assembly, which the compiler does not know to be MFMAs, so it must never find a reason (a join
 // of two paths, a second loop) to move them between registers next to one. The first half issues
-// the B loads of k-step kt-1+NB, the second half the A loads of k-step kt+NA, which is the same one. Past the
-// end of the reduction the pointers stop advancing: the loads of the last k-steps fetch the last 64 k again (which
-// are in L2; starting over at the first ones cost 1 % of the 6144 x 16384 gate/up)
+// the B loads of k-step kt-1+NB, the second half the A loads of k-step kt+NA. Past the end of the
+// reduction the pointers stop advancing: the loads of the last k-steps fetch the last 64 k again
 // into stages that nobody reads any more, which keeps the number of loads in flight, and with it
 // the load-counter value to wait for, the same in every k-step. Likewise the last k-step reads
 // "next" fragments from a stage that holds nothing new; they are never used.
@@ -1057,7 +1011,8 @@ template <class Cfg, int NA, int NB>
 __device__ __forceinline__ void kstep_1w(f32x4 (&acc)[Cfg::TM][8], bf16x8 (&fa)[2][Cfg::TM],
                                          bf16x8 (&fb)[2][8], RingState1W& rs, LoadPlan1W<Cfg>& lp,
                                          int wave, const unsigned char* pa0, const unsigned char* pa1,
-                                         const unsigned char* pb0, const unsigned char* pb1) {
+                                         const unsigned char* pb0, const unsigned char* pb1, int kt,
+                                         int KT) {
     using R = RingCfg<Cfg, NA, NB>;
     constexpr int TM = Cfg::TM, NM = TM * 8, NR = TM + 8;      // MFMAs and fragment reads per half
     constexpr int LA = LoadPlan1W<Cfg>::LA, LB = LoadPlan1W<Cfg>::LB;
@@ -1084,21 +1039,19 @@ __device__ __forceinline__ void kstep_1w(f32x4 (&acc)[Cfg::TM][8], bf16x8 (&fa)[
     };
     // ---- first half: MFMAs on f[0]; read f[1] (second half of this k-step); the eight B loads
     //      (with DUAL: four loads of W1 rows, then four of W3 rows)
-    uint32_t after = 0;
     auto first = [&](auto mtag) {
         constexpr int m = decltype(mtag)::value, i = m >> 3, j = m & 7, n = m / (NM / 8);
         const void* src = lp.b_src(wave, n < 8 ? n : 0);
         mma16_slot<m, NM / 8, 8>(fb[0][j], fa[0][i], acc[i][j], b_region, lp.b_voff, src);
         MOE_FENCE();
         read_behind(mtag, std::integral_constant<int, SPAN1>{}, fb[1], fa[1], pb_h1, pa_h1);
-        // the B pointers move on behind the last B load (MFMA 7 * NM / 8 + 3)
+        // the B pointers move on behind the last B load (MFMA 7 * NM / 8 + 3) while a later k-step exists
         constexpr int after_loads = 7 * (NM / 8) + 4;
         if constexpr (m == (after_loads < NM ? after_loads + 1 : NM - 1)) {
-            lp.set_b();
+            lp.b_ptr[0] += (kt + NB < KT) ? Cfg::BK : 0;
+            if (Cfg::DUAL) lp.b_ptr[1] += (kt + NB < KT) ? Cfg::BK : 0;
             MOE_FENCE();
         }
-        if constexpr (m == NM - 6) { after = lp.after_k(); MOE_FENCE(); }
-        if constexpr (m == NM - 5) { lp.next_k(after); MOE_FENCE(); }
     };
     // ---- second half: MFMAs on f[1]; read f[0] of k-step kt+1; the A loads; the next k-step's
     //      ring addresses, one small step behind an MFMA at a time
@@ -1120,7 +1073,7 @@ __device__ __forceinline__ void kstep_1w(f32x4 (&acc)[Cfg::TM][8], bf16x8 (&fa)[
         if constexpr (m == 17) { nx.pb_n0 = pb0 + sb2; MOE_FENCE(); }
         if constexpr (m == 18) { nx.a_region = sa1 + lp.a_lds; MOE_FENCE(); }
         if constexpr (m == 21) { nx.b_region = R::A_RING + rs.sb + lp.b_lds; MOE_FENCE(); }
-        if constexpr (m == NM - 3) { lp.set_a(); MOE_FENCE(); }
+        if constexpr (m == NM - 3) { lp.a_ptr += (kt + NA + 1 < KT) ? Cfg::BK : 0; MOE_FENCE(); }
     };
     static_for<NM>(first);
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(LB) : "memory");
@@ -1140,21 +1093,23 @@ __device__ __forceinline__ void prologue_1w(const TileCoord& tc, LoadPlan1W<Cfg>
                                             const uint16_t* __restrict__ B0,
                                             const uint16_t* __restrict__ B1,
                                             const int32_t* __restrict__ row_index, RowDiv index_div,
-                                            KStart kstart, int N, int K) {
+                                            int N, int K) {
     using R = RingCfg<Cfg, NA, NB>;
-    constexpr int LA = R::LA, LB = R::LB, AB = Cfg::A_BYTES, BB = Cfg::B_BYTES;
+    constexpr int BK = Cfg::BK, LA = R::LA, LB = R::LB, AB = Cfg::A_BYTES, BB = Cfg::B_BYTES;
     static_assert(NB - 1 == NA, "prologue order");
-    lp.init(tc, wave, lane, A, B0, B1, row_index, index_div, kstart, N, K);
+    lp.init(tc, wave, lane, A, B0, B1, row_index, index_div, N, K);
 #pragma unroll
     for (int s = 0; s < NA; ++s) {
 #pragma unroll
         for (int i = 0; i < LA; ++i) dma16(lp.a_ptr, lp.a_voff[i], s * AB + lp.a_lds + i * 1024);
+        lp.a_ptr += BK;
+        if (s < NB - 1) {
 #pragma unroll
-        for (int i = 0; i < LB; ++i)
-            dma16(lp.b_src(wave, i), lp.b_voff[i], R::A_RING + s * BB + lp.b_lds + i * 1024);
-        lp.next_k(lp.after_k());
-        lp.set_a();
-        lp.set_b();
+            for (int i = 0; i < LB; ++i)
+                dma16(lp.b_src(wave, i), lp.b_voff[i], R::A_RING + s * BB + lp.b_lds + i * 1024);
+            lp.b_ptr[0] += BK;
+            if (Cfg::DUAL) lp.b_ptr[1] += BK;
+        }
     }
 }
 
@@ -1204,8 +1159,8 @@ __device__ __forceinline__ void mainloop_1w(f32x4 (&acc)[Cfg::TM][8], LoadPlan1W
     // two k-steps per trip (K is a multiple of 128 for every supported shape): the loop's own
     // compare-and-branch then falls between MFMAs half as often
     for (int kt = 0; kt < KT; kt += 2) {
-        kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1]);
-        kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1]);
+        kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1], kt, KT);
+        kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1], kt + 1, KT);
     }
     mfma_drain(acc[TM - 1]);                         // before anything else touches the accumulators
 }
@@ -1216,12 +1171,12 @@ __device__ __forceinline__ void ring_tile_1w(const TileCoord& tc, unsigned char*
                                              const uint16_t* __restrict__ B0,
                                              const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
                                              const int32_t* __restrict__ row_index, RowDiv index_div,
-                                             KStart kstart, int N, int K) {
+                                             int N, int K) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     LoadPlan1W<Cfg> lp;
-    prologue_1w<Cfg, NA, NB>(tc, lp, wave, lane, A, B0, B1, row_index, index_div, kstart, N, K);
+    prologue_1w<Cfg, NA, NB>(tc, lp, wave, lane, A, B0, B1, row_index, index_div, N, K);
     FragPlan<Cfg> fp;
     fp.init(lane, wave / Cfg::WN, wave % Cfg::WN);
     f32x4 acc[Cfg::TM][Cfg::TN];
@@ -1245,7 +1200,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_ring_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
     const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ row_index, RowDiv index_div,
-    KStart kstart, int E, int N, int K, int split_cus) {
+    int E, int N, int K, int split_cus) {
     constexpr bool LOW = LowCfg::BM != Cfg::BM;
     static_assert(HalfCfg::BM * 2 == Cfg::BM && HalfCfg::BN == Cfg::BN && HalfCfg::BK == Cfg::BK &&
                   HalfCfg::NTHREADS == Cfg::NTHREADS && HalfCfg::DUAL == Cfg::DUAL, "same n-tiling");
@@ -1262,9 +1217,9 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_ring_kernel(
     auto run = [&](auto cfg_tag) {
         using TileCfg = typename decltype(cfg_tag)::type;
         if constexpr (TileCfg::NW == 4 && TileCfg::TN == 8)
-            ring_tile_1w<TileCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, kstart, N, K);
+            ring_tile_1w<TileCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, N, K);
         else
-            ring_tile<TileCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, kstart, N, K);
+            ring_tile<TileCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, N, K);
     };
     if (tc.height == HalfCfg::BM) run(type_tag<HalfCfg>{});
     else if (LOW && tc.height == LowCfg::BM) run(type_tag<LowCfg>{});

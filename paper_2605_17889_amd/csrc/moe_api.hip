@@ -157,12 +157,12 @@ int forward_chunk(moe_ctx* c, const moe_bf16* x, const float* w_router, const fl
     }
     rc = run_stage(c, MOE_STAGE_GATEUP, 1, s, [&] {
         return fuse_gather
-                   ? launch_gateup(c->gemm, x, c->perm, k, c->offsets, R, R, d, f, 0, E, W1, W3, c->H, s)
-                   : launch_gateup(c->gemm, c->x_perm, nullptr, 1, c->offsets, R, R, d, f, 0, E, W1, W3, c->H, s);
+                   ? launch_gateup(c->gemm, x, c->perm, k, c->offsets, R, R, d, f, E, W1, W3, c->H, s)
+                   : launch_gateup(c->gemm, c->x_perm, nullptr, 1, c->offsets, R, R, d, f, E, W1, W3, c->H, s);
     });
     if (rc != MOE_OK) return rc;
     rc = run_stage(c, MOE_STAGE_DOWN, 1, s, [&] {
-        return launch_down(c->gemm, c->H, c->offsets, R, R, d, f, 0, E, W2, expert_out(c), c->y_perm_f32 != nullptr, s);
+        return launch_down(c->gemm, c->H, c->offsets, R, R, d, f, E, W2, expert_out(c), c->y_perm_f32 != nullptr, s);
     });
     if (rc != MOE_OK) return rc;
     return run_stage(c, MOE_STAGE_COMBINE, 1, s, [&] {
@@ -345,11 +345,11 @@ int moe_expert_ffn(moe_ctx* c, const moe_bf16* x_perm, const int32_t* offsets, i
     const moe_shape& sh = c->shape;
     if (c->prof_armed) ++c->prof_calls;
     int rc = run_stage(c, MOE_STAGE_GATEUP, 1, s, [&] {
-        return launch_gateup(c->gemm, x_perm, nullptr, 1, offsets, R, R, sh.d_model, sh.d_ff, 0, sh.E, W1, W3, c->H, s);
+        return launch_gateup(c->gemm, x_perm, nullptr, 1, offsets, R, R, sh.d_model, sh.d_ff, sh.E, W1, W3, c->H, s);
     });
     if (rc != MOE_OK) return rc;
     return run_stage(c, MOE_STAGE_DOWN, 1, s, [&] {
-        return launch_down(c->gemm, c->H, offsets, R, R, sh.d_model, sh.d_ff, 0, sh.E, W2, y_perm, false, s);
+        return launch_down(c->gemm, c->H, offsets, R, R, sh.d_model, sh.d_ff, sh.E, W2, y_perm, false, s);
     });
 }
 
@@ -445,13 +445,13 @@ int moe_layer_forward_streamed(moe_ctx* c, const moe_bf16* x, const float* w_rou
     auto up = [&](int e0, int n, const moe_bf16* w1, const moe_bf16* w3) -> int {
         const int hint = static_cast<int>(static_cast<long long>(R) * n / E);
         return run_stage(c, MOE_STAGE_GATEUP, 1, s, [&] {
-            return launch_gateup(c->gemm, x, c->perm, k, c->offsets + e0, R, hint, d, f, e0, n, w1, w3, c->H, s);
+            return launch_gateup(c->gemm, x, c->perm, k, c->offsets + e0, R, hint, d, f, n, w1, w3, c->H, s);
         });
     };
     auto down = [&](int e0, int n, const moe_bf16* w2) -> int {
         const int hint = static_cast<int>(static_cast<long long>(R) * n / E);
         return run_stage(c, MOE_STAGE_DOWN, 1, s, [&] {
-            return launch_down(c->gemm, c->H, c->offsets + e0, R, hint, d, f, e0, n, w2, expert_out(c), c->y_perm_f32 != nullptr, s);
+            return launch_down(c->gemm, c->H, c->offsets + e0, R, hint, d, f, n, w2, expert_out(c), c->y_perm_f32 != nullptr, s);
         });
     };
     if (E_res > 0) {

@@ -616,6 +616,67 @@ def test_large_tiles_of_every_height(rows, fp32_outputs):
     ctx.close()
 
 
+@pytest.mark.parametrize("first,count", [(0, 3), (1, 1), (2, 5), (6, 1)])
+def test_expert_ffn_of_some_experts_gives_the_bits_of_all(first, count):
+    """A program that holds some of a layer's experts (expert parallelism, replicas) calls the stage with
+    a context of its own: an expert's rows have the bits that they have in a call of all experts."""
+    d, f, rows = 2048, 4224, [3, 130, 40, 0, 300, 70, 20]
+    say(f"experts {first} to {first + count - 1} of {len(rows)}")
+    E = len(rows)
+    offsets = np.concatenate([[0], np.cumsum(rows)]).astype(np.int32)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda *shape: (torch.randn(*shape, generator=g, device="cuda") * 0.05).bfloat16()
+    W1, W3, W2, x = rnd(E, f, d), rnd(E, f, d), rnd(E, d, f), rnd(sum(rows), d)
+
+    def ffn(e0, n):
+        lo, hi = int(offsets[e0]), int(offsets[e0 + n])
+        ctx = B.MoeContext(hi - lo, d, f, n, 1)
+        y = torch.full((hi - lo, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        B.moe_expert_ffn(ctx, x[lo:hi], dev(offsets[e0:e0 + n + 1] - lo), hi - lo, W1[e0:e0 + n], W3[e0:e0 + n],
+                         W2[e0:e0 + n], y)
+        torch.cuda.synchronize()
+        ctx.close()
+        return bits(y)
+
+    want = ffn(0, E)[offsets[first]:offsets[first + count]]
+    assert not np.isnan(bf16_to_f64(want)).any()
+    np.testing.assert_array_equal(ffn(first, count), want)
+
+
+@pytest.mark.parametrize("config", [-1] + ALL_TILE_CONFIGS)
+@pytest.mark.parametrize("projection", ["gate/up", "down"])
+def test_every_sum_runs_from_the_first_k_to_the_last(projection, config):
+    """2^30 at the first k and -2^30 at the last swallow the ones between them (at most 32 of them per
+    matrix instruction, half an ulp of 2^30 is 64) and leave exactly 0; from any other start ones are left over."""
+    d, f, rows = 2048, 4224, [3, 0, 40, 70, 100, 130, 200, 260, 300, 580]
+    say(f"order of sums, {projection}, config {config}")
+    E, R, big = len(rows), sum(rows), 2.0 ** 15
+    K = d if projection == "gate/up" else f
+    terms = torch.ones(K)
+    terms[:64] = terms[-64:] = 0                # nothing beside +-2^30 in the instructions that add those
+    terms[0], terms[-1] = big, -big
+    x, W1, W3 = torch.zeros(d), torch.zeros(f, d), torch.zeros(f, d)
+    W1[:, 64] = 32.0                            # gate: SiLU(32) = 32
+    if projection == "gate/up":
+        x[:] = terms.abs()
+        W3[:] = terms.sign()
+        W3[:, [0, -1]] *= big
+    else:                                       # H = 32 * W3[:, 64]
+        x[64] = 1.0
+        W3[:, 64] = torch.where(terms.abs() == big, terms * big / 32, terms / 32)
+    per_expert = lambda w: w.bfloat16().expand(E, *w.shape).contiguous().cuda()
+    W2 = torch.ones(d, f)
+    offsets = dev(np.concatenate([[0], np.cumsum(rows)]).astype(np.int32))
+    ctx = B.MoeContext(R, d, f, E, 1)
+    B.moe_set_gemm_config(ctx, config)
+    y = torch.full((R, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    B.moe_expert_ffn(ctx, x.bfloat16().expand(R, d).contiguous().cuda(), offsets, R, per_expert(W1),
+                     per_expert(W3), per_expert(W2), y)
+    torch.cuda.synchronize()
+    assert torch.count_nonzero(y) == 0
+    ctx.close()
+
+
 @pytest.mark.parametrize("T,d,k", [(1, 512, 1), (50, 512, 2), (33, 1024, 3), (256, 4096, 2),
                                    (100, 1024, 17), (7, 512, 64)])   # up to the largest k supported
 def test_combine_parity(T, d, k):
@@ -1098,22 +1159,21 @@ def test_layer_other_expert_shapes(T, d, f, E, k, use_bias):
 
 
 @pytest.mark.parametrize("T,d,f,E,k", [
-    (600, 1536, 2048, 10, 2),      # the shortest staggered reduction; starts at its first, last and last but one k-step
-    (90, 512, 2176, 40, 3),        # k-steps that seven does not divide, one block of columns
-    (600, 2048, 4224, 10, 2),      # gate/up: the shortest staggered reduction, two blocks of columns, the second partial
-    (300, 4096, 256, 33, 2),       # ... and one of 64 k-steps, thirteen apart
+    (600, 1536, 2048, 10, 2),      # down: rows of W2 a power of two apart
+    (90, 512, 2176, 40, 3),        # down: an odd number of 128-wide steps
+    (600, 2048, 4224, 10, 2),      # gate/up and down, 33 blocks of 128 columns
+    (300, 4096, 256, 33, 2),       # gate/up: twice that, and no long one down
 ])
-def test_layer_staggered_reductions(T, d, f, E, k):
-    """A long reduction starts at another k per expert and block of columns: every
-    tile configuration and call form has to start at the same one."""
-    say(f"layer T={T} d={d} f={f} E={E} k={k}: staggered reductions")
+def test_layer_long_reductions(T, d, f, E, k):
+    """Reductions of 2048 and more: tile configurations and call forms give the same bits."""
+    say(f"layer T={T} d={d} f={f} E={E} k={k}: long reductions")
     cfg = synth.LayerConfig("custom", T, d, f, E, k, seed=77)
     L = synth.make_layer(cfg, "cuda")
     Hh = host_layer(L)
     y, ctx = run_layer(cfg, L)
     tokens = np.arange(0, T, 7, dtype=np.int32)
     want, _, _ = ref.layer_tokens(Hh["x"], Hh["w_router"], None, Hh["W1"], Hh["W3"], Hh["W2"], k, tokens)
-    assert_close_ffn(bits(y)[tokens], want, "staggered reductions")
+    assert_close_ffn(bits(y)[tokens], want, "long reductions")
     same = lambda other, what: np.testing.assert_array_equal(bits(other), bits(y), what)
     for config in ALL_TILE_CONFIGS:
         B.moe_set_gemm_config(ctx, config)
