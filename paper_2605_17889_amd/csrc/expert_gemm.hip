@@ -125,8 +125,7 @@ struct NTiles {
 //               rows, none is over 1 % slower cold than with the 128- or the 256-row tiles throughout
 //   + 3, + 6    a tile's cost outside its reduction, in k-steps, and 0.9 the margin that small tiles have to win by:
 //               512 and 900 tokens through 8 experts of 512 x 1024 (below)
-//   0.93        seven stages against four, and one 128-column tile per compute unit down; 2.5 narrow gate/up
-//               tiles, 3.5 128 columns down: where they are used
+//   0.93        seven stages against four, 2.5 narrow gate/up tiles, 3.5 128 columns down: where they are used
 int pick_config(const GemmEnv& env, int R, int E, const NTiles& nt) {
     if (env.forced_config >= 0) return env.forced_config;
     // 0: pipelined 256-row tiles (with half-height tails). 1: 128-row tiles (generic kernel).
@@ -322,12 +321,6 @@ int launch_down_as(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets
     if (R == 0) return MOE_OK;
     const bool wide_mid = static_cast<long long>(E) * (d / 256) >= 160 && d % 256 == 0;
     const int cus = compute_units(env.device);
-    // Tiles of 128 columns make one per compute unit: the row tiles of 32 and 64 rows are then 64 x 128 (64 x 64 for
-    // the same rows are two per compute unit and reread the rows): 8 experts of 4096 x 14336, 64 tokens 139 against
-    // 145 us, 120 140 against 153, 200 146 against 169. With 1.5 such tiles per compute unit the narrow ones win
-    // (6144 x 16384, 64 tokens 260 and 242, 200 286 and 264).
-    const double wide_tiles = touched_experts(R_hint, E) * (d / 128);
-    const bool one_wide_each = wide_tiles <= cus && wide_tiles >= 0.93 * cus;
     int config = pick_config(env, R_hint, E, NTiles{d / 256, wide_mid ? d / 256 : d / 128, d / 64,
                                                     wide_mid ? 0.82 : 0.6, 0.27, 0.38, 2e-6 * E * d * f, f / 64});
     if (config == 0 && f / 64 < 3) config = 1;     // the pipelined kernel needs three k-steps
@@ -358,8 +351,6 @@ int launch_down_as(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets
                 return launch_grouped<Out<F32, DownMid96S>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
             return launch_grouped<Out<F32, DownMid96>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
         case 3:
-            if (one_wide_each && single_m_tile(env, R_hint, E, 64))
-                return launch_grouped<Out<F32, DownSmallWideS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
             // 32-column tiles where 64-column ones would leave compute units without any: one token through 2 of
             // 8 experts of 4096 x 14336 46 against 70 us; and while all of their row tiles find one: 64 tokens
             // through 2 of 8 of 512 x 1024 7.6 against 8.9 us
@@ -383,7 +374,7 @@ int launch_down_as(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets
             // columns per compute unit) 239 and 243 us, 448 through 56 of 2048 x 1024, 4 per token (3.5) 149.2 and
             // 150.5; 110 tokens through 8 of 6144 x 16384 (1.5) 806 and 783. In between the sides are mixed (3.0: 384
             // tokens through 48 of 2048 x 1024 128.7 and 134.6, 192 through 24 of 4096 x 2048 242 and 238)
-            if (one_wide_each || wide_tiles >= 3.5 * cus) {
+            if (touched_experts(R_hint, E) * (d / 128) >= 3.5 * cus) {
                 if (single_m_tile(env, R_hint, E, 64))
                     return launch_grouped<Out<F32, DownSmallWideS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
                 return launch_grouped<Out<F32, DownSmallWide>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
