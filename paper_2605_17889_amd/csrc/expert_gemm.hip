@@ -294,7 +294,10 @@ int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_inde
                 // through 2 of 8 of 512 x 1024 (1.0) 8.1 and 9.0; past the line they lose (5 tokens, 8 of 128, 3.3:
                 // 41.8 and 41.2; 4 tokens, 6 of 64, 4.0: 46.9 and 43.4)
                 if (2.0 * nt <= 2.5 * cus) {
-                    if (2.0 * nt <= cus)
+                    // The deep ring where no compute unit gets a second tile, whichever experts are touched: one
+                    // token through 8 of 128 of 2048 x 768 (192 tiles) 14.3 against 14.9 us, through 4 of 32 of 2048 x 2048
+                    // (256) 16.7 against 17.5; through 6 of 64 of 2048 x 1408 (264) 20.2 against 18.2
+                    if (std::min(E, R_hint) * (f / 32) <= cus)
                         return launch_grouped<GateUpFewDeepS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
                     return launch_grouped<GateUpFewS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
                 }
