@@ -153,7 +153,17 @@ int pick_config(const GemmEnv& env, int R, int E, const NTiles& nt) {
     // and 731, 775 and 488; 6144 x 16384, 1000 tokens 986 and 541, 783 and 412; two experts of 4096 x 14336 with 300 rows
     // each, gate/up 206 and 139).
     const double largest = avg + std::max(2.0, std::sqrt(2.0 * std::log(static_cast<double>(E)))) * sigma;
-    const int config = largest <= 96.0 ? 4 : largest <= 128.0 ? 1 : 0;
+    int config = largest <= 96.0 ? 4 : largest <= 128.0 ? 1 : 0;
+    // Groups around 256 rows, where one 256-row tile per expert leaves compute units idle and the few groups of more
+    // than 256 rows start a second round: two or three 128-row tiles per expert are two rounds too, of half the
+    // height. Down, 8 experts of 6144 x 16384, 256- against 128-row tiles: 1000 tokens 656 and 544 us, 1024 671 and 547;
+    // below the lines, one large round, 975 472 and 528; above, three of the others, 1050 633 and 742. With reductions of
+    // 12288, 8192, 6144 438 and 407, 290 and 261, 229 and 217 (1024 tokens); below that a wrong guess of the groups costs as
+    // much as a right one gains (12 experts, K = 4096 102 and 134 or 143 and 132, as the routing falls).
+    const double past256 = 0.5 * E * std::erfc((256.0 - avg) / (std::sqrt(2.0) * sigma));   // groups, expected
+    if (config == 0 && nt.ksteps >= 96 && E * nt.large <= cus && (E + past256) * nt.large > cus &&
+        (2.0 * E + past256) * nt.mid <= 0.95 * 2.0 * cus)
+        config = 1;
     // A launch of at most one such tile per compute unit takes one tile's time however many compute
     // units idle: small tiles are worth their extra loads if they use the idle ones. Units of a
     // k-step of a full 256-row tile (about 1 us), measured on one expert of 4096 x 14336 (512 rows,
