@@ -125,8 +125,6 @@ constexpr int kLowGateUpK = 4096;    // gate/up reductions below this have tiles
 // reductions pay for: there tiles are not cut, and a tail of more than half a tile computes a whole one
 // (8 experts of 6144 x 16384, 16384 tokens with a skewed load 9.15 ms, cut 9.45; 8192 tokens 4.81 and 4.79; of
 // 4096 x 14336, 8192 skewed 2.81 and 2.84). Down, same layers: 4.62 and 4.64 ms, 2.51 and 2.47, 1.46 and 1.45.
-// Experts of more than nine m-tiles are not cut either, where it saves less than 4 % of their tiles (16384 skewed
-// tokens, layer 13.90 -> 13.85 ms).
 template <int BM>
 __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m_e, int local, int NT, int half,
                                                     bool quarters) {
@@ -151,7 +149,7 @@ __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m
     mi += head;
     int first = mi * BM;
     tc.height = BM;
-    if (quarters && mt <= kGroupM + 1) {
+    if (quarters) {
         constexpr int Q = BM / 4;
         const int lower = 4 * mt - (m_e + Q - 1) / Q;      // whole quarters of padding
         if (mi >= mt - lower) tc.height = BM - Q;

@@ -533,8 +533,8 @@ def test_expert_ffn_configs_agree_bitwise():
 
 
 @pytest.mark.parametrize("d,f,rows", [
-    (512, 256, [1, 0, 0, 1, 0, 0, 0, 0]),            # 16-row tiles (at most 16 rows expected)
-    (512, 256, [16, 0, 17, 0, 1, 0, 0, 26]),         # the same with groups past one and past two tiles
+    (512, 256, [1, 0, 0, 1, 0, 0, 0, 0]),            # narrow tiles of 32 rows up, of 16 down (at most 16 rows expected)
+    (512, 256, [16, 0, 17, 0, 1, 0, 0, 26]),         # the same with groups past one tile
     (512, 1024, [5, 0, 33, 1, 16, 17, 3, 8] * 2),    # narrow 32-row gate/up tiles, two per compute unit
     (512, 256, [16, 33, 15, 1, 0, 31, 32, 20]),      # 16-row down tiles, some experts with two or three
     (512, 256, [64, 40, 65, 33, 0, 80, 31, 1]),      # 32-row down tiles for groups of up to 64 rows
@@ -585,6 +585,7 @@ def test_automatic_tile_choice_agrees_bitwise(d, f, rows, fp32_outputs):
     [1, 64, 65, 128, 129, 192, 193, 256, 0, 257],                    # one tile; two from 257 rows on
     [320, 321, 384, 385, 448, 449, 512, 513],                        # eight experts: the lookup on the scalar unit
     [576, 577, 640, 641, 704, 705, 768, 769, 2049, 2240, 2241],      # three and more, two groups of tiles
+    [2305, 4097, 0, 4288, 4289],                                     # ten and more, two and three groups; none to three cut
 ])
 @pytest.mark.parametrize("fp32_outputs", [False, True])
 def test_large_tiles_of_every_height(rows, fp32_outputs):
