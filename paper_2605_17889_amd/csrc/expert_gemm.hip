@@ -139,19 +139,19 @@ int pick_config(const GemmEnv& env, int R, int E, const NTiles& nt) {
     const double upper = avg + 2.0 * sigma;
     if (upper <= 32.0) return 3;
     // The 64-row tiles against the 96-row ones, gate/up + down: 500 tokens through 128 experts of
-    // 2048 x 768 200 us against 210, 200 tokens through 8 of 4096 x 14336 487 against 519; with a few
-    // experts past 64 rows (560 tokens through 64 experts of 2048 x 1408) 207 against 196.
+    // 2048 x 768 205 us against 218; with a few experts past 64 rows (560 tokens through 64 experts of
+    // 2048 x 1408) 226 against 211. Of a few large experts the line takes more than it should: 200 tokens through
+    // 8 of 4096 x 14336 515 against 485.
     if (upper <= 64.0) return 2;
     const int cus = compute_units(env.device);
     // The 96- and 128-row tiles only where the largest group is expected to fit one: a second tile costs more than
     // they gain. The largest of E groups lies about sqrt(2 ln E) standard deviations above the mean (two for the
     // 8 experts that the lines were drawn at). Gate/up and down, 96- / 128- / 256-row tiles: 800 tokens through 64 experts
-    // of 2048 x 1408 (75 rows each) 149 and 96, 147 and 77, 149 and 77 us; 280 through 8 of 6144 x 16384 (70) 529 and 255,
-    // 536 and 270, 577 and 297. 128- / 256-row: 1700 through 128 of 2048 x 768 (106) 182 and 112, 162 and 101;
-    // 420 through 8 of 4096 x 14336 (105) 334 and 178, 344 and 238; 460 (115) 344 and 306, 344 and 243. With more rows the
-    // 256-row tiles and their lower tails are the faster ones (4096 x 14336, 600 tokens 491 and 316, 367 and 246, 2048 1039
-    // and 731, 775 and 488; 6144 x 16384, 1000 tokens 986 and 541, 783 and 412; two experts of 4096 x 14336 with 300 rows
-    // each, gate/up 206 and 139).
+    // of 2048 x 1408 (75 rows each) 154 and 79, 154 and 79, 154 and 77 us; 280 through 8 of 6144 x 16384 (70) 517 and 277,
+    // 520 and 276, 543 and 336. 128- / 256-row: 1700 through 128 of 2048 x 768 (106) 174 and 111, 158 and 103;
+    // 420 through 8 of 4096 x 14336 (105) 354 and 185, 358 and 232; 460 (115) 370 and 306, 362 and 234. With more rows the
+    // 256-row tiles and their lower tails are the faster ones (4096 x 14336, 600 tokens 479 and 313, 393 and 240, 2048 1000
+    // and 725, 761 and 498; two experts of 4096 x 14336 with 300 rows each, gate/up 179 and 147).
     const double largest = avg + std::max(2.0, std::sqrt(2.0 * std::log(static_cast<double>(E)))) * sigma;
     int config = largest <= 96.0 ? 4 : largest <= 128.0 ? 1 : 0;
     // Groups around 256 rows, where one 256-row tile per expert leaves compute units idle and the few groups of more
@@ -256,9 +256,9 @@ using GateUpTiny      = Config<32, 128, 64, 2, 2, 4, true>;
 using GateUpTinyS     = Config<32, 128, 64, 2, 2, 4, true, true>;
 using GateUpTinyDeepS = Config<32, 128, 64, 2, 2, 7, true, true>;
 // A few tokens: more, narrower tiles. Four wavefronts (two, down) share their loads, which leave a wavefront
-// one by one, some 100 cycles apart: one wavefront per tile took 16.2 us for gate/up of one token through 8 of
-// 128 experts of 2048 x 768, four take 14.4, and 13.5 with the deep ring where no second tile has to fit; down
-// of one token through 2 of 8 of 4096 x 14336 61 -> 46 us, of 6144 x 16384 76 -> 70.
+// one by one, some 100 cycles apart: one wavefront per tile took 15.8 us for gate/up of one token through 8 of
+// 128 experts of 2048 x 768, four take 14.9, and 14.2 with the deep ring where no second tile has to fit; down
+// of one token through 2 of 8 of 4096 x 14336 51.4 -> 45.5 us, of 6144 x 16384 73.1 -> 72.3.
 using GateUpFewS     = Config<32, 64, 64, 2, 2, 4, true, true>;
 using GateUpFewDeepS = Config<32, 64, 64, 2, 2, 6, true, true>;
 using DownTiny     = Config<32, 64, 64, 2, 2, 4, false>;
@@ -281,6 +281,9 @@ int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_inde
     int config = pick_config(env, R_hint, E, NTiles{f / 128, f / 128, f / 64, 0.82, 0.41, 0.58,
                                                     4e-6 * E * d * f, d / 64});
     if (config == 0 && d / 64 < 3) config = 1;     // the pipelined kernel needs three k-steps
+    // Row counts that lead to 96- or 128-row tiles let every group fit one, so their weights are streamed; the cached forms
+    // (GateUpMid96, DownMid96 and DownMid96Wide) run under the tuning knob, those of 128 rows also where groups of about
+    // 256 rows take two tiles and where a reduction is too short for the pipelined kernel.
     switch (config) {
         case 0:
             if (use_one_wave_per_simd(env, f, d))
@@ -299,10 +302,10 @@ int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_inde
                 const double nt = touched_experts(R_hint, E) * (f / 64);
                 const int cus = compute_units(env.device);
                 // Tiles of half the width while up to two and a half of them go to a compute unit, gate/up against
-                // the 128-column ones: one token through 8 of 128 experts of 2048 x 768 (0.75 per compute unit) 13.5
-                // and 16.8 us, 2 (1.4) 21.7 and 22.8, 2 through 6 of 64 of 2048 x 1408 (2.1) 29.8 and 34.9, 64
-                // through 2 of 8 of 512 x 1024 (1.0) 8.1 and 9.0; past the line they lose (5 tokens, 8 of 128, 3.3:
-                // 41.8 and 41.2; 4 tokens, 6 of 64, 4.0: 46.9 and 43.4)
+                // the 128-column ones: one token through 8 of 128 experts of 2048 x 768 (0.75 per compute unit) 14.2
+                // and 18.2 us, 2 (1.4) 21.6 and 22.3, 2 through 6 of 64 of 2048 x 1408 (2.1) 23.9 and 25.0, 64 through
+                // 2 of 8 of 512 x 1024 (1.0) 7.7 and 8.7. Past the line the sides are mixed: 4 tokens, 8 of 128 (2.7)
+                // 37.0 and 39.5, 5 (3.3) 44.0 and 42.8; 4 tokens, 6 of 64 (3.8) 43.9 and 42.2, 6 (5.4) 54.6 and 62.4
                 if (2.0 * nt <= 2.5 * cus) {
                     // The deep ring where no compute unit gets a second tile, whichever experts are touched: one
                     // token through 8 of 128 of 2048 x 768 (192 tiles) 14.3 against 14.9 us, through 4 of 32 of 2048 x 2048
@@ -365,21 +368,20 @@ int launch_down_as(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets
             return launch_grouped<Out<F32, DownMid96>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
         case 3:
             // 32-column tiles where 64-column ones would leave compute units without any: one token through 2 of
-            // 8 experts of 4096 x 14336 46 against 70 us; and while all of their row tiles find one: 64 tokens
-            // through 2 of 8 of 512 x 1024 7.6 against 8.9 us
+            // 8 experts of 4096 x 14336 45.5 against 61.7 us; and while all of their row tiles find one: 64 tokens
+            // through 2 of 8 of 512 x 1024 7.9 against 9.1 us
             if (touched_experts(R_hint, E) * (d / 64) < cus) {
                 if (single_m_tile(env, R_hint, E, 16))
                     return launch_grouped<Out<F32, DownFewS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
                 if (row_tiles(R_hint, E, 16) * (d / 32) <= cus)
                     return launch_grouped<Out<F32, DownFew>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
             }
-            if (single_m_tile(env, R_hint, E, 32)) {
+            if (single_m_tile(env, R_hint, E, 32))
                 return launch_grouped<Out<F32, DownTinyS>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
-            }
             return launch_grouped<Out<F32, DownTiny>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
         default:
             // 32-row tiles where the 64-row ones would leave half of the compute units without any: 256 tokens through
-            // 2 of 8 experts of 512 x 1024 (96 tiles) 9.2 against 10.2 us, 600 (192 tiles) 10.9 against 10.2
+            // 2 of 8 experts of 512 x 1024 (96 tiles) 9.2 against 9.9 us, 600 (192 tiles) 10.9 against 10.2
             if (row_tiles(R_hint, E, 64) * (d / 64) <= 0.5 * cus)
                 return launch_grouped<Out<F32, DownTiny>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
             // 128 columns where that makes about two rounds of two workgroups per compute unit, else 64. Layer calls

@@ -119,12 +119,14 @@ constexpr int kLowGateUpK = 4096;    // gate/up reductions below this have tiles
 // quarters of padding (at most three; a single tile takes them all, two tiles with three of them are 3/4 and
 // 1/2 high). 576 rows are 3 x 192 instead of 2 x 256 and a half-height tile of 64: a k-step of 192 rows takes
 // 1536 cycles of matrix instructions and 56 loads, one of 128 rows, bound by its 48 loads, hardly less than
-// that. 8192 tokens through 128 experts of 2048 x 768 (430 to 620 rows each): gate/up 359 -> 347 us, down
-// 244.5 -> 239; 5003 through 64 of 2048 x 1408 gate/up 292 -> 287.
-// A workgroup that ends early is out of step with those whose rows and weights it shares in L2, which long gate/up
-// reductions pay for: there tiles are not cut, and a tail of more than half a tile computes a whole one
-// (8 experts of 6144 x 16384, 16384 tokens with a skewed load 9.15 ms, cut 9.45; 8192 tokens 4.81 and 4.79; of
-// 4096 x 14336, 8192 skewed 2.81 and 2.84). Down, same layers: 4.62 and 4.64 ms, 2.51 and 2.47, 1.46 and 1.45.
+// that. Whole -> cut, gate/up and down: 8192 tokens through 128 experts of 2048 x 768 (430 to 620 rows each) 361 -> 338
+// and 239 -> 236 us, 5000 263 -> 244 and 190 -> 171; 5003 through 64 of 2048 x 1408 290 -> 276 and 179.5 -> 177, 3200
+// 254 -> 227 and 155 -> 142; down, 1200 through 8 of 4096 x 14336 366 -> 297.
+// A workgroup that ends early is out of step with those whose rows and weights it shares in L2, which the largest
+// launches pay for: 16384 tokens with a skewed load through 8 experts of 6144 x 16384 down 4.58 -> 4.62 ms, and
+// gate/up 9.10 -> 9.31 if it were cut. For their sake gate/up reductions of kLowGateUpK and more keep whole tiles (a tail of
+// more than half a tile computes a whole one), though most smaller launches would gain: 8192 even tokens 4.59 and 4.58 ms,
+// 2048 1375 -> 1333 us, 1200 at 4096 x 14336 664 -> 542. Below the line, 2500 through 64 experts of 3584 x 2560 822 -> 703.
 template <int BM>
 __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m_e, int local, int NT, int half,
                                                     bool quarters) {
