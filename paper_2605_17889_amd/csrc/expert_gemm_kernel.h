@@ -108,28 +108,30 @@ __device__ __forceinline__ int slot_to_tile(int total, int split_cus, int xcd, i
     return xcd * per + tile_slot;
 }
 
-constexpr int kLowGateUpK = 4096;    // gate/up reductions below this have tiles of three quarters
+constexpr int kLongK = 4096;         // reductions of this and more cut the tiles of experts of at most
+constexpr int kLongCutTiles = 4;     // so many m-tiles only, shorter ones those of every expert
 
 // Coordinates of tile `local` of the expert whose group is rows [row_e, row_e + m_e). The expert's
 // mt m-tiles form ceil(mt / kGroupM) groups of nearly equal height (the first `extra` groups hold
 // one tile more), so that a short tail tile sweeps the n-tiles together with full tiles of its
 // expert and finds the weight tiles in L2.
 //
-// With `quarters` the m-tiles are as many, but the last ones are a quarter lower: as many as there are whole
+// In an expert of at most cut_tiles m-tiles the last ones are a quarter lower: as many as there are whole
 // quarters of padding (at most three; a single tile takes them all, two tiles with three of them are 3/4 and
 // 1/2 high). 576 rows are 3 x 192 instead of 2 x 256 and a half-height tile of 64: a k-step of 192 rows takes
 // 1536 cycles of matrix instructions and 56 loads, one of 128 rows, bound by its 48 loads, hardly less than
 // that. Whole -> cut, gate/up and down: 8192 tokens through 128 experts of 2048 x 768 (430 to 620 rows each) 361 -> 338
 // and 239 -> 236 us, 5000 263 -> 244 and 190 -> 171; 5003 through 64 of 2048 x 1408 290 -> 276 and 179.5 -> 177, 3200
 // 254 -> 227 and 155 -> 142; down, 1200 through 8 of 4096 x 14336 366 -> 297.
-// A workgroup that ends early is out of step with those whose rows and weights it shares in L2, which the largest
-// launches pay for: 16384 tokens with a skewed load through 8 experts of 6144 x 16384 down 4.58 -> 4.62 ms, and
-// gate/up 9.10 -> 9.31 if it were cut. For their sake gate/up reductions of kLowGateUpK and more keep whole tiles (a tail of
-// more than half a tile computes a whole one), though most smaller launches would gain: 8192 even tokens 4.59 and 4.58 ms,
-// 2048 1375 -> 1333 us, 1200 at 4096 x 14336 664 -> 542. Below the line, 2500 through 64 experts of 3584 x 2560 822 -> 703.
+// A workgroup that ends early is out of step with those whose rows and weights it shares in L2, which long reductions pay
+// for, while the saving shrinks with the number of m-tiles. Nothing cut, experts of at most four m-tiles, of at most six
+// (gate/up): 5500 tokens through 8 experts of 6144 x 16384 3213, 3214, 3358 us; 16384 with a skewed load 9341, 9368, 9515;
+// 2048 1401, 1331, 1343; 1200 at 4096 x 14336 666, 550, 539. Down at 16384 skewed tokens 4677, 4701, 4744, and with all
+// cut 4717. A short reduction loses nothing: 16384 skewed tokens through 128 experts of 2048 x 768 687 us whole, with
+// experts of nine and fewer cut 673, with all 665.
 template <int BM>
 __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m_e, int local, int NT, int half,
-                                                    bool quarters) {
+                                                    int cut_tiles) {
     TileCoord tc{kNoTile, 0, 0, 0, 0};
     const int mt = (m_e + BM - 1) / BM;
     const int ngroups = (mt + kGroupM - 1) / kGroupM;
@@ -151,7 +153,7 @@ __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m
     mi += head;
     int first = mi * BM;
     tc.height = BM;
-    if (quarters) {
+    if (mt <= cut_tiles) {
         constexpr int Q = BM / 4;
         const int lower = 4 * mt - (m_e + Q - 1) / Q;      // whole quarters of padding
         if (mi >= mt - lower) tc.height = BM - Q;
@@ -196,7 +198,7 @@ __device__ __forceinline__ int lane_prefix_sum(int v) {
 // instructions instead of vector loads, a prefix sum across lanes and a ballot.
 template <int BM>
 __device__ __forceinline__ TileCoord locate_tile_scalar8(const int32_t* __restrict__ offsets, int NT,
-                                                         int split_cus, bool quarters, int xcd, int slot) {
+                                                         int split_cus, int cut_tiles, int xcd, int slot) {
     int off[9];
 #pragma unroll
     for (int e = 0; e < 9; ++e) off[e] = offsets[e];
@@ -221,13 +223,13 @@ __device__ __forceinline__ TileCoord locate_tile_scalar8(const int32_t* __restri
             m_e = off[i + 1] - off[i];
             row_e = off[i];
         }
-    return tile_in_expert<BM>(e, row_e, m_e, L - start, NT, half, quarters);
+    return tile_in_expert<BM>(e, row_e, m_e, L - start, NT, half, cut_tiles);
 }
 
 template <int BM>
 __device__ __forceinline__ TileCoord locate_tile_at(const int32_t* __restrict__ offsets, int E,
-                                                    int NT, int split_cus, bool quarters, int xcd, int slot) {
-    if (E == 8) return locate_tile_scalar8<BM>(offsets, NT, split_cus, quarters, xcd, slot);
+                                                    int NT, int split_cus, int cut_tiles, int xcd, int slot) {
+    if (E == 8) return locate_tile_scalar8<BM>(offsets, NT, split_cus, cut_tiles, xcd, slot);
     constexpr int EPL = kMaxExperts / kWave;               // experts per lane
     const int e0 = (threadIdx.x & (kWave - 1)) * EPL;
     int off[EPL + 1], tiles[EPL], sum = 0;
@@ -258,13 +260,13 @@ __device__ __forceinline__ TileCoord locate_tile_at(const int32_t* __restrict__ 
     const int src = __builtin_ctzll(hit);
     return tile_in_expert<BM>(
         __builtin_amdgcn_readlane(e, src), __builtin_amdgcn_readlane(row_e, src),
-        __builtin_amdgcn_readlane(m_e, src), L - __builtin_amdgcn_readlane(start, src), NT, half, quarters);
+        __builtin_amdgcn_readlane(m_e, src), L - __builtin_amdgcn_readlane(start, src), NT, half, cut_tiles);
 }
 
 template <int BM>
 __device__ __forceinline__ TileCoord locate_tile(const int32_t* __restrict__ offsets, int E,
-                                                 int NT, int split_cus = 0, bool quarters = false) {
-    TileCoord tc = locate_tile_at<BM>(offsets, E, NT, split_cus, quarters, blockIdx.x % kXcds, blockIdx.x / kXcds);
+                                                 int NT, int split_cus = 0, int cut_tiles = 0) {
+    TileCoord tc = locate_tile_at<BM>(offsets, E, NT, split_cus, cut_tiles, blockIdx.x % kXcds, blockIdx.x / kXcds);
     // the same in every lane: into scalar registers, where the load addresses are formed
     tc.expert = __builtin_amdgcn_readfirstlane(tc.expert);
     tc.row0 = __builtin_amdgcn_readfirstlane(tc.row0);
@@ -1211,7 +1213,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_ring_kernel(
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
     const TileCoord tc = locate_tile<Cfg::BM>(offsets, E, N / Cfg::BN_OUT, split_cus,
-                                              LOW && (!Cfg::DUAL || K < kLowGateUpK));
+                                              !LOW ? 0 : K < kLongK ? 1 << 30 : kLongCutTiles);
     if (tc.expert < 0) return;                       // uniform for the whole workgroup
     // four wavefronts of (128, 96 or 64) x 128 outputs run the one-wavefront-per-SIMD pipeline
     auto run = [&](auto cfg_tag) {

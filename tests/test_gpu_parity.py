@@ -588,10 +588,9 @@ def test_automatic_tile_choice_agrees_bitwise(d, f, rows, fp32_outputs):
     [2305, 4097, 0, 4288, 4289],                                     # ten and more, two and three groups; none to three cut
 ])
 @pytest.mark.parametrize("fp32_outputs", [False, True])
-def test_large_tiles_of_every_height(rows, fp32_outputs):
+def test_large_tiles_of_every_height(rows, fp32_outputs, d=512, f=256):
     """256-, 192- and 128-row tiles and split last rounds against the 128-row configuration."""
-    d, f = 512, 256
-    say(f"large tiles rows={rows} fp32={fp32_outputs}")
+    say(f"large tiles d={d} f={f} rows={rows} fp32={fp32_outputs}")
     E, R = len(rows), sum(rows)
     g = torch.Generator(device="cuda").manual_seed(R)
     rnd = lambda *shape: (torch.randn(*shape, generator=g, device="cuda") * 0.05).bfloat16()
@@ -615,6 +614,12 @@ def test_large_tiles_of_every_height(rows, fp32_outputs):
     for other in outs[1:]:
         assert np.array_equal(outs[0], other)
     ctx.close()
+
+
+@pytest.mark.parametrize("d,f", [(4096, 4096), (3584, 4224)])     # both projections, down alone past the line
+def test_large_tiles_of_long_reductions(d, f):
+    """Experts of up to four m-tiles are cut in long reductions, those of five and more are not."""
+    test_large_tiles_of_every_height([449, 577, 769, 1024, 1025, 1152, 130], False, d, f)
 
 
 @pytest.mark.parametrize("first,count", [(0, 3), (1, 1), (2, 5), (6, 1)])
