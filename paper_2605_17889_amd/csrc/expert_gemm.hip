@@ -128,7 +128,7 @@ struct NTiles {
 //   0.93        seven stages against four, 2.5 narrow gate/up tiles, 3.5 128 columns down: where they are used
 int pick_config(const GemmEnv& env, int R, int E, const NTiles& nt) {
     if (env.forced_config >= 0) return env.forced_config;
-    // 0: pipelined 256-row tiles (with half-height tails). 1: 128-row tiles (generic kernel).
+    // 0: pipelined 256-row tiles (lower ones at the end). 1: 128-row tiles (generic kernel).
     // 2: up to 64 rows per expert (64-row tiles, two workgroups per compute unit). 3: up to 32
     // (32-row tiles). 4: 96-row tiles of four wavefronts side by side (groups of 65 to 96 rows: a
     // quarter fewer matrix instructions and fragment reads per k-step than the 128-row tile, and
