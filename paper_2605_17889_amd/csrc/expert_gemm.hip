@@ -78,10 +78,15 @@ int launch_grouped(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, co
                         gemm::RowDiv(index_div), E, N, K);
 }
 
-// The pipelined kernel with operand rings of NA and NB stages; tiles of at most LowCfg::BM rows run at three
-// quarters of the height, tiles of at most HalfCfg::BM rows and the tiles of a last round that is less than
-// half full at half of it.
-template <class Cfg, class LowCfg, class HalfCfg, int NA, int NB>
+// Slots of all tiles that R rows in E groups can make: the tiles, and where the last round is split two slots
+// per tile there, at most ceil(cus / 2 / 8) more in every XCD's range.
+long long most_slots(int R, int E, int BM, int NT, int split_cus) {
+    return most_row_tiles(R, E, BM) * NT + kXcds * ((split_cus / 2 + kXcds - 1) / kXcds + 1);
+}
+
+// The pipelined kernel of eight wavefronts with operand rings of NA and NB stages; tiles of at most HalfCfg::BM
+// rows and the tiles of a last round that is less than half full run at half the height.
+template <class Cfg, class HalfCfg, int NA, int NB>
 int launch_ring(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, const moe_bf16* B1, moe_bf16* C,
                 const int32_t* offsets, const int32_t* row_index, int index_div,
                 int R, int E, int N, int K, hipStream_t s) {
@@ -89,12 +94,29 @@ int launch_ring(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, const
     if (K / Cfg::BK < (NA > NB ? NA : NB)) return MOE_ERR_UNSUPPORTED_SHAPE;
     static std::atomic<uint64_t> attr_set{0};
     const int cus = env.split_last_round ? compute_units(env.device) : 0;
-    const long long max_mt = most_row_tiles(R, E, Cfg::BM);
-    // split tiles take two slots each: at most ceil(cus / 2 / 8) more slots in every XCD's range
-    const long long grid = max_mt * (N / Cfg::BN_OUT) + kXcds * ((cus / 2 + kXcds - 1) / kXcds + 1);
-    return launch_tiles(env, attr_set, gemm::grouped_gemm_ring_kernel<Cfg, LowCfg, HalfCfg, NA, NB>,
-                        gemm::RingCfg<Cfg, NA, NB>::SMEM, Cfg::NTHREADS, grid, s, A, B0, B1, C,
+    return launch_tiles(env, attr_set, gemm::grouped_gemm_ring_kernel<Cfg, HalfCfg, NA, NB>,
+                        gemm::RingCfg<Cfg, NA, NB>::SMEM, Cfg::NTHREADS,
+                        most_slots(R, E, Cfg::BM, N / Cfg::BN_OUT, cus), s, A, B0, B1, C,
                         offsets, row_index, gemm::RowDiv(index_div), E, N, K, cus);
+}
+
+// The pipelined kernel of one wavefront per SIMD: a persistent workgroup per compute unit where the reduction is
+// short, a workgroup per tile where it is long.
+template <class Cfg>
+int launch_1w(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, const moe_bf16* B1, moe_bf16* C,
+              const int32_t* offsets, const int32_t* row_index, int index_div,
+              int R, int E, int N, int K, hipStream_t s) {
+    if (N % Cfg::BN_OUT != 0 || K % (2 * Cfg::BK) != 0 || K < 4 * Cfg::BK) return MOE_ERR_UNSUPPORTED_SHAPE;
+    static std::atomic<uint64_t> attr_set[2];
+    const int cus = compute_units(env.device), split = env.split_last_round ? cus : 0;
+    const long long slots = most_slots(R, E, Cfg::BM, N / Cfg::BN_OUT, split);
+    if (K < gemm::kLongK)
+        return launch_tiles(env, attr_set[0], gemm::grouped_gemm_1w_kernel<Cfg, true>, gemm::Ring1W<Cfg>::SMEM,
+                            Cfg::NTHREADS, std::min<long long>(slots, cus), s, A, B0, B1, C, offsets, row_index,
+                            gemm::RowDiv(index_div), E, N, K, split, env.tile_counters);
+    return launch_tiles(env, attr_set[1], gemm::grouped_gemm_1w_kernel<Cfg, false>, gemm::Ring1W<Cfg>::SMEM,
+                        Cfg::NTHREADS, slots, s, A, B0, B1, C, offsets, row_index, gemm::RowDiv(index_div), E, N, K,
+                        split, env.tile_counters);
 }
 
 // Expected row tiles of height h: groups one standard deviation below and above the mean.
@@ -215,14 +237,9 @@ bool single_m_tile(const GemmEnv& env, int R, int E, int BM) {
 
 //                      BM   BN  BK WM WN NSTAGE DUAL [STREAM_B]
 using GateUpLarge = Config<256, 256, 64, 2, 4, 2, true>;
-// one wavefront per SIMD: 2 x 2 wavefronts of 128 x 128 outputs, of 96 x 128 at three quarters of the height or
-// of 64 x 128 at half
+// one wavefront per SIMD: 2 x 2 wavefronts of 128 x 128 outputs, fewer rows in lower tiles
 using GateUpLarge1W = Config<256, 256, 64, 2, 2, 2, true>;
-using GateUpLow1W   = Config<192, 256, 64, 2, 2, 2, true>;
-using GateUpHalf1W  = Config<128, 256, 64, 2, 2, 3, true>;
 using DownLarge1W   = Config<256, 256, 64, 2, 2, 2, false>;
-using DownLow1W     = Config<192, 256, 64, 2, 2, 2, false>;
-using DownHalf1W    = Config<128, 256, 64, 2, 2, 3, false>;
 using GateUpMid   = Config<128, 256, 64, 2, 4, 3, true>;   // also the half-height tile of GateUpLarge
 // 64 rows: four wavefronts of 32 rows share a workgroup, and its ring leaves room for a second
 // workgroup on the compute unit, so that one streams weights while the other looks its tile up,
@@ -287,8 +304,8 @@ int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_inde
     switch (config) {
         case 0:
             if (use_one_wave_per_simd(env, f, d))
-                return launch_ring<GateUpLarge1W, GateUpLow1W, GateUpHalf1W, 2, 3>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
-            return launch_ring<GateUpLarge, GateUpLarge, GateUpMid, 2, 3>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
+                return launch_1w<GateUpLarge1W>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
+            return launch_ring<GateUpLarge, GateUpMid, 2, 3>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
         case 1:
             if (single_m_tile(env, R_hint, E, 128))
                 return launch_grouped<GateUpMidS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
@@ -343,8 +360,8 @@ int launch_down_as(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets
     switch (config) {
         case 0:
             if (use_one_wave_per_simd(env, d, f))
-                return launch_ring<Out<F32, DownLarge1W>, Out<F32, DownLow1W>, Out<F32, DownHalf1W>, 2, 3>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
-            return launch_ring<Out<F32, DownLarge>, Out<F32, DownLarge>, Out<F32, DownMidWide>, 2, 3>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
+                return launch_1w<Out<F32, DownLarge1W>>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
+            return launch_ring<Out<F32, DownLarge>, Out<F32, DownMidWide>, 2, 3>(env, H, W2, nullptr, y_perm, offsets, nullptr, 1, R, E, d, f, s);
         case 1:
             // HBM-bound: wide tiles stream more bytes per workgroup, but only if there are
             // enough of them to occupy the 256 compute units (about one m-tile per expert).

@@ -33,15 +33,16 @@ namespace gemm {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kGroupM = 8;   // at most this many m-tiles that sweep the n-tiles together (share weight tiles)
 
 struct TileCoord {
     int expert;      // -1: no tile for this workgroup
     int row0;        // first row (in the permuted matrix) of the tile
-    int rows;        // valid rows in the tile (1..BM)
+    int rows;        // valid rows in the tile (1..BM; 0: the lower half of a tile that has none)
     int nt;          // n-tile index
-    int height;      // rows that its workgroup computes: BM, 3/4 BM (see tile_in_expert) or BM / 2
+    int height;      // rows that its workgroup computes: BM / 2 to BM (see tile_in_expert)
 };
 
 // Map a workgroup to its tile. Logical tile order: expert by expert; inside an expert, groups
@@ -65,9 +66,9 @@ struct TileCoord {
 // halves are the highest slots of every XCD's range, hence the last workgroups dispatched.
 //
 // The tile is named by (xcd, slot): slot-th entry of XCD xcd's range; the kernels take both from
-// the workgroup index. Result: expert >= 0: a tile; kNoTile: the range is exhausted (every later
-// slot is too); kEmptySlot: this slot holds nothing (the lower half of a tile that has none).
-constexpr int kNoTile = -1, kEmptySlot = -2;
+// the workgroup index. Result: expert >= 0: a tile, with no rows if the slot is the lower half of a tile
+// that has none; kNoTile: the range is exhausted (every later slot is too).
+constexpr int kNoTile = -1;
 
 // a / b and a % b for a >= 0, b >= 1. A wavefront-uniform integer division takes some forty
 // instructions of the vector unit; below 2^22 the float quotient is off by at most one.
@@ -86,27 +87,31 @@ __device__ __forceinline__ int div_small(int a, int b, int& rem) {
     return q;
 }
 
-// Tile number `slot` of XCD xcd's range of `total` tiles: the tile's place in the logical order, or
-// -1 past the end of the range; `half` is 0 / 1 for the upper / lower half of a split tile, else -1.
-__device__ __forceinline__ int slot_to_tile(int total, int split_cus, int xcd, int slot, int& half) {
-    const int per = (total + kXcds - 1) / kXcds;
-    const int len = max(0, min(per, total - xcd * per));   // tiles in this XCD's range
-    int halved = 0;                                        // of those, the last `halved` are split
-    if (split_cus > 0) {
-        int rem;
-        div_small(total, split_cus, rem);
-        if (rem > 0 && 2 * rem <= split_cus) halved = min(len, (rem + kXcds - 1) / kXcds);
+// The slots of one XCD's range of `total` tiles. A lookup gives a slot's place in the logical order, or -1 past
+// the end of the range; `half` is 0 / 1 for the upper / lower half of a split tile, else -1.
+struct SlotRange {
+    int first, whole, slots;       // first tile; tiles that are not split, each one slot; all slots
+    __device__ __forceinline__ void init(int total, int split_cus, int xcd) {
+        const int per = (total + kXcds - 1) / kXcds;
+        const int len = max(0, min(per, total - xcd * per));   // tiles in this XCD's range
+        int halved = 0;                                        // of those, the last `halved` are split
+        if (split_cus > 0) {
+            int rem;
+            div_small(total, split_cus, rem);
+            if (rem > 0 && 2 * rem <= split_cus) halved = min(len, (rem + kXcds - 1) / kXcds);
+        }
+        first = xcd * per;
+        whole = len - halved;
+        slots = len + halved;
     }
-    int tile_slot = slot;
-    half = -1;
-    if (slot >= len - halved) {
-        const int j = slot - (len - halved);
-        if (j >= 2 * halved) return -1;
-        tile_slot = len - halved + (j >> 1);
-        half = j & 1;
+    __device__ __forceinline__ int tile(int slot, int& half) const {
+        half = -1;
+        if (slot < whole) return first + slot;
+        if (slot >= slots) return -1;
+        half = (slot - whole) & 1;
+        return first + whole + ((slot - whole) >> 1);
     }
-    return xcd * per + tile_slot;
-}
+};
 
 constexpr int kLongK = 4096;         // reductions of this and more cut the tiles of experts of at most
 constexpr int kLongCutTiles = 4;     // so many m-tiles only, shorter ones those of every expert
@@ -116,19 +121,20 @@ constexpr int kLongCutTiles = 4;     // so many m-tiles only, shorter ones those
 // one tile more), so that a short tail tile sweeps the n-tiles together with full tiles of its
 // expert and finds the weight tiles in L2.
 //
-// In an expert of at most cut_tiles m-tiles the last ones are a quarter lower: as many as there are whole
-// quarters of padding (at most three; a single tile takes them all, two tiles with three of them are 3/4 and
-// 1/2 high). 576 rows are 3 x 192 instead of 2 x 256 and a half-height tile of 64: a k-step of 192 rows takes
-// 1536 cycles of matrix instructions and 56 loads, one of 128 rows, bound by its 48 loads, hardly less than
-// that. Whole -> cut, gate/up and down: 8192 tokens through 128 experts of 2048 x 768 (430 to 620 rows each) 361 -> 338
-// and 239 -> 236 us, 5000 263 -> 244 and 190 -> 171; 5003 through 64 of 2048 x 1408 290 -> 276 and 179.5 -> 177, 3200
-// 254 -> 227 and 155 -> 142; down, 1200 through 8 of 4096 x 14336 366 -> 297.
+// The m-tiles of an expert of at most cut_tiles of them share its rows in units of an eighth of a tile: 576 rows
+// are 3 x 192 instead of 2 x 256 and a tail of 64, 520 are 192, 192 and 160. No tile is lower than half of one: a
+// k-step of 192 rows takes 1536 cycles of matrix instructions and 56 loads, one of 128 rows, bound by its 48
+// loads, hardly less than that. Rows that are padding cost time and, under the board's power limit, clock.
+// Units of a quarter -> of an eighth, gate/up and down: 8192 tokens through 64 experts of 2048 x 1408 (664 to 871 rows
+// each) 462 -> 431 and 257 -> 241 us, 5003 282 -> 270 and 196 -> 191 (fp32 outputs), 8192 through 128 of 2048 x 768
+// 336 -> 325 and 234 -> 222, 1200 through 8 of 4096 x 14336 515 -> 520 and 295 -> 274 (those of short reductions
+// together with the persistent workgroups, see grouped_gemm_1w_kernel).
 // A workgroup that ends early is out of step with those whose rows and weights it shares in L2, which long reductions pay
-// for, while the saving shrinks with the number of m-tiles. Nothing cut, experts of at most four m-tiles, of at most six
-// (gate/up): 5500 tokens through 8 experts of 6144 x 16384 3213, 3214, 3358 us; 16384 with a skewed load 9341, 9368, 9515;
-// 2048 1401, 1331, 1343; 1200 at 4096 x 14336 666, 550, 539. Down at 16384 skewed tokens 4677, 4701, 4744, and with all
-// cut 4717. A short reduction loses nothing: 16384 skewed tokens through 128 experts of 2048 x 768 687 us whole, with
-// experts of nine and fewer cut 673, with all 665.
+// for, while the saving shrinks with the number of m-tiles. In quarters, nothing cut, experts of at most four m-tiles, of
+// at most six (gate/up): 5500 tokens through 8 experts of 6144 x 16384 3213, 3214, 3358 us; 16384 with a skewed load 9341,
+// 9368, 9515; 2048 1401, 1331, 1343; 1200 at 4096 x 14336 666, 550, 539. Down at 16384 skewed tokens 4677, 4701, 4744, and
+// with all cut 4717. A short reduction loses nothing: 16384 skewed tokens through 128 experts of 2048 x 768 687 us whole,
+// with experts of nine and fewer cut 673, with all 665.
 template <int BM>
 __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m_e, int local, int NT, int half,
                                                     int cut_tiles) {
@@ -154,21 +160,18 @@ __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m
     int first = mi * BM;
     tc.height = BM;
     if (mt <= cut_tiles) {
-        constexpr int Q = BM / 4;
-        const int lower = 4 * mt - (m_e + Q - 1) / Q;      // whole quarters of padding
-        if (mi >= mt - lower) tc.height = BM - Q;
-        first -= Q * max(0, mi - max(0, mt - lower));
+        constexpr int U = BM / 8;
+        int extra;
+        const int base = div_small((m_e + U - 1) / U, mt, extra);   // in units of U rows; `extra` tiles one more
+        tc.height = max(BM / 2, (base + (mi < extra ? 1 : 0)) * U);
+        first = (mi * base + min(mi, extra)) * U;
     }
     tc.row0 = row_e + first;
     tc.rows = min(tc.height, m_e - first);
     if (half >= 0) {
         const int h0 = half * (BM / 2);
-        if (tc.rows <= h0) {                               // the tile has no lower half
-            tc.expert = kEmptySlot;
-            return tc;
-        }
-        tc.row0 += h0;
-        tc.rows = min(BM / 2, tc.rows - h0);
+        tc.rows = max(0, min(BM / 2, tc.rows - h0));
+        tc.row0 += tc.rows > 0 ? h0 : 0;
     }
     if (tc.rows <= BM / 2) tc.height = BM / 2;
     tc.expert = expert;
@@ -209,9 +212,11 @@ __device__ __forceinline__ TileCoord locate_tile_scalar8(const int32_t* __restri
         total += ((off[e + 1] - off[e] + BM - 1) / BM) * NT;
         incl[e] = total;
     }
+    SlotRange range;
+    range.init(total, split_cus, xcd);
     int half;
-    const int L = slot_to_tile(total, split_cus, xcd, slot, half);
-    if (L < 0 || L >= total) return TileCoord{kNoTile, 0, 0, 0, 0};
+    const int L = range.tile(slot, half);
+    if (L < 0) return TileCoord{kNoTile, 0, 0, 0, 0};
     int e = 0;
 #pragma unroll
     for (int i = 0; i < 7; ++i) e += (L >= incl[i]) ? 1 : 0;      // first expert whose range holds L
@@ -226,54 +231,84 @@ __device__ __forceinline__ TileCoord locate_tile_scalar8(const int32_t* __restri
     return tile_in_expert<BM>(e, row_e, m_e, L - start, NT, half, cut_tiles);
 }
 
+// An XCD's range of the tiles, prepared for lookups: the tile counts of all experts over the lanes of a
+// wavefront (lane l holds experts 4 l to 4 l + 3) and the range's slots.
 template <int BM>
-__device__ __forceinline__ TileCoord locate_tile_at(const int32_t* __restrict__ offsets, int E,
-                                                    int NT, int split_cus, int cut_tiles, int xcd, int slot) {
-    if (E == 8) return locate_tile_scalar8<BM>(offsets, NT, split_cus, cut_tiles, xcd, slot);
-    constexpr int EPL = kMaxExperts / kWave;               // experts per lane
-    const int e0 = (threadIdx.x & (kWave - 1)) * EPL;
-    int off[EPL + 1], tiles[EPL], sum = 0;
+struct TileTable {
+    static constexpr int EPL = kMaxExperts / kWave;        // experts per lane
+    int off[EPL + 1], start[EPL + 1];                      // offsets; number of the first tile of each expert
+    SlotRange range;
+    __device__ __forceinline__ void init(const int32_t* __restrict__ offsets, int E, int NT, int split_cus, int xcd,
+                                         int lane) {
+        static_assert(EPL == 4, "in-lane search");
 #pragma unroll
-    for (int w = 0; w <= EPL; ++w) off[w] = offsets[min(e0 + w, E)];
+        for (int w = 0; w <= EPL; ++w) off[w] = offsets[min(lane * EPL + w, E)];
+        start[0] = 0;
 #pragma unroll
-    for (int w = 0; w < EPL; ++w) {
-        tiles[w] = ((off[w + 1] - off[w] + BM - 1) / BM) * NT;
-        sum += tiles[w];
+        for (int w = 0; w < EPL; ++w) start[w + 1] = start[w] + ((off[w + 1] - off[w] + BM - 1) / BM) * NT;
+        const int incl = lane_prefix_sum(start[EPL]), before = incl - start[EPL];
+#pragma unroll
+        for (int w = 0; w <= EPL; ++w) start[w] += before;
+        range.init(__builtin_amdgcn_readlane(incl, kWave - 1), split_cus, xcd);
     }
-    const int incl = lane_prefix_sum(sum);
-    const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
-    int half;
-    const int L = slot_to_tile(total, split_cus, xcd, slot, half);
-    if (L < 0 || L >= total) return TileCoord{kNoTile, 0, 0, 0, 0};
-    // the one lane whose experts hold the tile finds the expert, then hands it to all
-    int start = incl - sum, e = e0, row_e = off[0], m_e = off[1] - off[0];
-    const uint64_t hit = __ballot(L >= start && L < incl);
+    // `magic`: lane g holds floor(2^32 / g) + 1, so that a / g == (a * magic) >> 32 for 2 <= g and a * g < 2^32.
+    __device__ __forceinline__ TileCoord find(int NT, int cut_tiles, int slot, uint32_t magic) const {
+        int half;
+        const int L = range.tile(slot, half);
+        if (L < 0) return TileCoord{kNoTile, 0, 0, 0, 0};
+        // The last lane whose first expert starts at or before tile L holds it. From there on everything is the
+        // same in all lanes and computed on the scalar unit.
+        const int src = 63 - __builtin_clzll(__ballot(L >= start[0]));
+        int e = 0, first = __builtin_amdgcn_readlane(start[0], src);
+        int row_e = __builtin_amdgcn_readlane(off[0], src), next = __builtin_amdgcn_readlane(off[1], src);
 #pragma unroll
-    for (int w = 1; w < EPL; ++w)
-        if (L >= incl - sum + tiles[0] + (w > 1 ? tiles[1] : 0) + (w > 2 ? tiles[2] : 0)) {
-            start = incl - sum + tiles[0] + (w > 1 ? tiles[1] : 0) + (w > 2 ? tiles[2] : 0);
-            e = e0 + w;
-            row_e = off[w];
-            m_e = off[w + 1] - off[w];
+        for (int w = 1; w < EPL; ++w) {
+            const int s = __builtin_amdgcn_readlane(start[w], src), o = __builtin_amdgcn_readlane(off[w + 1], src);
+            const bool on = L >= s;
+            e = on ? w : e;
+            first = on ? s : first;
+            row_e = on ? next : row_e;
+            next = on ? o : next;
         }
-    static_assert(EPL == 4, "in-lane search");
-    const int src = __builtin_ctzll(hit);
-    return tile_in_expert<BM>(
-        __builtin_amdgcn_readlane(e, src), __builtin_amdgcn_readlane(row_e, src),
-        __builtin_amdgcn_readlane(m_e, src), L - __builtin_amdgcn_readlane(start, src), NT, half, cut_tiles);
-}
+        e += src * EPL;
+        const int m_e = next - row_e, mt = (m_e + BM - 1) / BM;
+        if (mt > kGroupM || half >= 0) return tile_in_expert<BM>(e, row_e, m_e, L - first, NT, half, cut_tiles);
+        // tile_in_expert where the expert's tiles are one group and nothing is split
+        constexpr uint32_t U = BM / 8;
+        const uint32_t in = L - first, mul = __builtin_amdgcn_readlane(magic, mt), one = mt == 1 ? ~0u : 0u;
+        const uint32_t nt = __umulhi(in, mul) + (in & one), mi = in - nt * mt;
+        uint32_t base = 8, extra = 0;
+        if (mt <= cut_tiles) {
+            const uint32_t units = (m_e + U - 1) / U;
+            base = __umulhi(units, mul) + (units & one);
+            extra = units - base * mt;
+        }
+        const int at = (mi * base + min(mi, extra)) * U, height = max(4u, base + (mi < extra ? 1u : 0u)) * U;
+        const int rows = min(height, m_e - at);
+        return TileCoord{e, row_e + at, rows, static_cast<int>(nt), rows <= BM / 2 ? BM / 2 : height};
+    }
+};
+__device__ __forceinline__ uint32_t division_magic(int lane) { return lane < 2 ? 0u : 0xffffffffu / lane + 1u; }
 
-template <int BM>
-__device__ __forceinline__ TileCoord locate_tile(const int32_t* __restrict__ offsets, int E,
-                                                 int NT, int split_cus = 0, int cut_tiles = 0) {
-    TileCoord tc = locate_tile_at<BM>(offsets, E, NT, split_cus, cut_tiles, blockIdx.x % kXcds, blockIdx.x / kXcds);
-    // the same in every lane: into scalar registers, where the load addresses are formed
+// The same in every lane: into scalar registers, where the load addresses are formed.
+__device__ __forceinline__ TileCoord uniform_tile(TileCoord tc) {
     tc.expert = __builtin_amdgcn_readfirstlane(tc.expert);
     tc.row0 = __builtin_amdgcn_readfirstlane(tc.row0);
     tc.rows = __builtin_amdgcn_readfirstlane(tc.rows);
     tc.nt = __builtin_amdgcn_readfirstlane(tc.nt);
     tc.height = __builtin_amdgcn_readfirstlane(tc.height);
     return tc;
+}
+
+// The tile of this workgroup where every workgroup has one.
+template <int BM>
+__device__ __forceinline__ TileCoord locate_tile(const int32_t* __restrict__ offsets, int E, int NT, int split_cus = 0,
+                                                 int cut_tiles = 0) {
+    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
+    if (E == 8) return uniform_tile(locate_tile_scalar8<BM>(offsets, NT, split_cus, cut_tiles, xcd, slot));
+    TileTable<BM> table;
+    table.init(offsets, E, NT, split_cus, xcd, threadIdx.x & (kWave - 1));
+    return uniform_tile(table.find(NT, cut_tiles, slot, division_magic(threadIdx.x & (kWave - 1))));
 }
 
 // LDS tile layout: rows of BK bf16 in 16-byte chunks; logical chunk c of row r is stored at
@@ -347,6 +382,15 @@ struct F32Out : Cfg {
     static constexpr bool OUT_F32 = true;
     static_assert(!Cfg::DUAL, "the gate/up intermediate stays bf16");
 };
+// The same tile with H rows.
+template <class Cfg, int H> struct WithHeight;
+template <int BM, int BN, int BK, int WM, int WN, int NSTAGE, bool DUAL, bool STREAM_B, int H>
+struct WithHeight<Config<BM, BN, BK, WM, WN, NSTAGE, DUAL, STREAM_B>, H> {
+    using type = Config<H, BN, BK, WM, WN, NSTAGE, DUAL, STREAM_B>;
+};
+template <class Cfg, int H>
+struct WithHeight<F32Out<Cfg>, H> { using type = F32Out<typename WithHeight<Cfg, H>::type>; };
+template <class Cfg, int H> using AtHeight = typename WithHeight<Cfg, H>::type;
 template <class Cfg, class = void>
 struct out_is_f32 : std::false_type {};
 template <class Cfg>
@@ -830,76 +874,104 @@ __device__ __forceinline__ void ring_tile(const TileCoord& tc, unsigned char* sm
 // sees whole cache lines. In the accumulator layout a lane holds four consecutive columns of one
 // row per fragment, so a direct store writes sixteen separate 32-byte pieces; 256 compute units
 // finishing their tiles together then queue at the L2 for thousands of cycles. Here a wavefront
-// writes the sixteen rows of fragment row i into a small region of its own (`stage`) and reads them
-// back 16 bytes per lane, whole rows at a time, so that each store instruction covers full 128-byte
-// lines; the region is reused for the next fragment row. LDS serves a wavefront's requests in
-// order, so neither the read after the write nor the next write after the read needs a wait, and
-// the next row is converted and written while the reads of this one are on their way. The 16-byte
-// chunks of a row are XOR-swizzled by the row so that both the writes (16 rows at one column) and
-// the reads (whole rows) spread over all banks. `before_stores` runs once, ahead of the first store.
+// writes the sixteen rows of fragment row i (of half of it with fp32 outputs) into a 4 KB region of
+// its own (`stage`) and reads them back 16 bytes per lane, whole rows at a time, so that each store
+// instruction covers full 128-byte lines; the region is reused for the next fragment row. LDS serves
+// a wavefront's requests in order, so neither the read after the write nor the next write after the
+// read needs a wait, and the next row is converted and written while the reads of this one are on
+// their way. The 16-byte chunks of a row are XOR-swizzled by the row so that both the writes (16 rows
+// at one column) and the reads (whole rows) spread over all banks. `before_stores` runs once, ahead of
+// the first store.
+//
+// The accumulators are read where they are converted: left to the compiler, all of a tile's were copied to
+// ordinary registers ahead of the first conversion, which took 222 of those and spilled what lives from tile to tile.
+__device__ __forceinline__ float read_acc(const f32x4& acc, int r) {
+    float v;
+    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(acc[r]));
+    return v;
+}
+constexpr int kEpilogueBytes = 4096;                 // LDS that a wavefront stages its outputs through
 template <class Cfg, class Before>
 __device__ __forceinline__ void store_tile_via_lds(const f32x4 (&acc)[Cfg::TM][8], const TileCoord& tc,
                                                    const FragPlan<Cfg>& fp, int wave, int lane,
-                                                   unsigned char* stages, uint16_t* __restrict__ C,
+                                                   unsigned char* stage, uint16_t* __restrict__ C,
                                                    int ldc, Before&& before_stores) {
     constexpr bool DUAL = Cfg::DUAL, F32 = out_is_f32<Cfg>::value;
-    constexpr int TM = Cfg::TM, WN = Cfg::WN;
+    constexpr int WN = Cfg::WN;
+    constexpr int PASSES = F32 ? 2 : 1;              // pieces that a fragment row is staged in
     constexpr int COLS = DUAL ? 64 : 128;            // output columns of this wavefront
     constexpr int ESZ = F32 ? 4 : 2;                 // bytes per output element
-    constexpr int ROWB = COLS * ESZ;                 // bytes of one output row of this wavefront
+    constexpr int ROWB = COLS * ESZ / PASSES;        // bytes of one output row of a piece
     constexpr int CP = ROWB / 16;                    // 16-byte chunks per row
     constexpr int RSH = CP == 8 ? 1 : 0;             // log2 of the rows that share 256 bytes of LDS
-    constexpr int SWM = (CP < 16 ? CP : 16) - 1;     // the swizzle permutes chunks inside 256 bytes
-    constexpr int NJ = DUAL ? 4 : 8;                 // output fragments per fragment row
+    constexpr int SWM = CP - 1;                      // the swizzle permutes chunks inside 256 bytes
+    constexpr int NJ = (DUAL ? 4 : 8) / PASSES;      // output fragments per piece
     constexpr int RPI = 64 / CP;                     // rows per store instruction
-    static_assert(Cfg::TN == 8 && Cfg::NW * 16 * ROWB <= Cfg::B_BYTES, "fits one B stage");
+    constexpr int PIECES = Cfg::TM * PASSES;
+    static_assert(Cfg::TN == 8 && 16 * ROWB <= kEpilogueBytes && CP <= 16, "fits the region");
     const int wm = wave / WN, wn = wave % WN;
-    unsigned char* stage = stages + wave * (16 * ROWB);
     const uint32_t wswz = (fp.frag_row >> RSH) & SWM;
     unsigned char* wbase = stage + fp.frag_row * ROWB;
     const int rrow = lane / CP, rchunk = lane % CP;
-    const size_t row_bytes = static_cast<size_t>(ldc) * ESZ;
-    unsigned char* cbase = reinterpret_cast<unsigned char*>(C) +
-                           static_cast<size_t>(tc.row0 + wm * Cfg::WTM) * row_bytes +
-                           static_cast<size_t>(tc.nt * Cfg::BN_OUT + wn * COLS) * ESZ + rchunk * 16;
-    const int rows_here = tc.rows - wm * Cfg::WTM;   // rows of this wavefront inside the tile
-    auto write_row = [&](int i) {
+    // Stores through a buffer resource that ends behind the wavefront's last row: those of rows past the end of
+    // the group are dropped by its bounds check, with no comparison, branch or 64-bit address per store (of the
+    // 700 cycles that a fragment row of the down projection took, those were half).
+    const int rows_here = max(0, tc.rows - wm * Cfg::WTM);   // rows of this wavefront inside the tile
+    const uint32_t row_bytes = static_cast<uint32_t>(ldc) * ESZ;
+    const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(
+        reinterpret_cast<unsigned char*>(C) + static_cast<size_t>(tc.row0 + wm * Cfg::WTM) * row_bytes, 0,
+        rows_here * row_bytes, 0x00027000);
+    const uint32_t ccol = static_cast<uint32_t>(tc.nt * Cfg::BN_OUT + wn * COLS) * ESZ + rchunk * 16;
+    uint32_t coff[16 / RPI];
 #pragma unroll
-        for (int jj = 0; jj < NJ; ++jj) {
-            const int j = DUAL ? (jj & 1) + (jj >> 1) * 4 : jj;     // gate fragments; up = j + 2
-            if constexpr (F32) {
+    for (int q = 0; q < 16 / RPI; ++q) coff[q] = (q * RPI + rrow) * row_bytes + ccol;
+    auto write_piece = [&](int u) {
+        const int i = u / PASSES, j0 = (u % PASSES) * NJ;
+        auto frag = [&](int jj) { return j0 + (DUAL ? (jj & 1) + (jj >> 1) * 4 : jj); };   // gate; up = + 2
+        if constexpr (F32) {
+#pragma unroll
+            for (int jj = 0; jj < NJ; ++jj) {
                 const uint32_t chunk = (static_cast<uint32_t>(jj * 4 + fp.frag_kg) ^ wswz) * 16;
-                *reinterpret_cast<f32x4*>(wbase + chunk) = acc[i][j];
-            } else {
-                bf16x4 o;
+                *reinterpret_cast<f32x4*>(wbase + chunk) = acc[i][frag(jj)];
+            }
+        } else {
+            f32x4 v[NJ], up[NJ];                     // all reads first: the conversions then interleave
+#pragma unroll
+            for (int jj = 0; jj < NJ; ++jj)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float v = DUAL ? silu(acc[i][j][r]) * acc[i][DUAL ? j + 2 : j][r] : acc[i][j][r];
-                    o[r] = static_cast<__bf16>(v);                 // round to nearest even
+                    v[jj][r] = read_acc(acc[i][frag(jj)], r);
+                    if constexpr (DUAL) up[jj][r] = read_acc(acc[i][frag(jj) + 2], r);
                 }
+#pragma unroll
+            for (int jj = 0; jj < NJ; ++jj) {
+                bf16x4 o;
+#pragma unroll
+                for (int r = 0; r < 4; ++r)          // round to nearest even
+                    o[r] = static_cast<__bf16>(DUAL ? silu(v[jj][r]) * up[jj][r] : v[jj][r]);
                 const uint32_t chunk = (static_cast<uint32_t>(jj * 2 + (fp.frag_kg >> 1)) ^ wswz) * 16;
                 *reinterpret_cast<bf16x4*>(wbase + chunk + (fp.frag_kg & 1) * 8) = o;
             }
         }
-        MOE_FENCE();                                 // one fragment row's registers at a time
+        MOE_FENCE();                                 // one piece's registers at a time
     };
-    write_row(0);
+    write_piece(0);
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-        bf16x8 v[16 / RPI];
+    for (int u = 0; u < PIECES; ++u) {
+        u32x4 v[16 / RPI];
 #pragma unroll
         for (int q = 0; q < 16 / RPI; ++q) {
             const int rl = q * RPI + rrow;                          // row inside the fragment row
             const uint32_t chunk = (static_cast<uint32_t>(rchunk) ^ ((rl >> RSH) & SWM)) * 16;
-            v[q] = *reinterpret_cast<const bf16x8*>(stage + rl * ROWB + chunk);
+            v[q] = *reinterpret_cast<const u32x4*>(stage + rl * ROWB + chunk);
         }
         MOE_FENCE();
-        if (i + 1 < TM) write_row(i + 1);
-        if (i == 0) before_stores();
+        if (u + 1 < PIECES) write_piece(u + 1);
+        if (u == 0) before_stores();
 #pragma unroll
         for (int q = 0; q < 16 / RPI; ++q) {
-            const int r = i * 16 + q * RPI + rrow;
-            if (r < rows_here) *reinterpret_cast<bf16x8*>(cbase + static_cast<size_t>(r) * row_bytes) = v[q];
+            __builtin_amdgcn_raw_buffer_store_b128(v[q], out, coff[q] + (u % PASSES) * ROWB, 0, 0);
+            if (u % PASSES == PASSES - 1) coff[q] += 16 * row_bytes;
         }
         MOE_FENCE();
     }
@@ -916,7 +988,7 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
-// ---- the full tile with ONE wavefront per SIMD (4 wavefronts, 128 x 128 outputs each) --------
+// ---- the large tiles with ONE wavefront per SIMD (4 wavefronts, 128 x 128 outputs each) -------
 // Four wavefronts read 128 KB of fragments from LDS per k-step where eight read 192 KB, and hold
 // all 256 accumulator registers of a lane's SIMD, so every fragment set can be double-buffered
 // in the other 256 registers. With a single wavefront per SIMD nothing covers for it: a wavefront
@@ -926,45 +998,83 @@ __device__ __forceinline__ void static_for(F&& f) {
 // MFMA of its own: per half-step of 64 MFMAs, 16 fragment reads (after every fourth MFMA), 8
 // loads (in every group of eight MFMAs: M0 is written before one MFMA and the load issued after
 // it, the MFMA serving as the wait state that a write to M0 needs) and the pointer updates.
-// The A loads of k-step kt+NA go out in the second half of k-step kt, the B loads of k-step
-// kt+NB in the first half of k-step kt+1, so the texture-address unit sees one load per SIMD
+// The A loads of k-step kt+2 go out in the second half of k-step kt, the B loads of k-step
+// kt+3 in the first half of k-step kt+1, so the texture-address unit sees one load per SIMD
 // every 128 cycles throughout instead of all sixteen within one half.
-template <class Cfg>
-struct LoadPlan1W {
-    static constexpr int LA = Cfg::NIA / Cfg::NW, LB = Cfg::NIB / Cfg::NW;
-    const uint16_t* a_ptr;          // A origin + current k offset of the A loads
-    const uint16_t* b_ptr[2];       // expert's W (and W3 with DUAL) + current k offset of the B loads
-    uint32_t a_voff[LA], b_voff[LB];
-    uint32_t a_lds, b_lds;          // this wavefront's first load inside an A / B stage
-    __device__ __forceinline__ void init(const TileCoord& tc, int wave, int lane, const uint16_t* A,
-                                         const uint16_t* B0, const uint16_t* B1,
-                                         const int32_t* row_index, RowDiv index_div, int N, int K) {
-        const int lrow = lane / Cfg::CPR, lpos = lane % Cfg::CPR;
-        a_ptr = a_origin(A, tc, row_index, K);
-        const size_t expert_off = static_cast<size_t>(tc.expert) * N * K;
-        b_ptr[0] = B0 + expert_off;
-        b_ptr[1] = Cfg::DUAL ? B1 + expert_off : b_ptr[0];
-        int src[LA];
-        source_rows<LA, Cfg::RPI>(src, tc, wave * LA * Cfg::RPI + lrow, row_index, index_div);
-#pragma unroll
-        for (int i = 0; i < LA; ++i) {
-            const int r = (wave * LA + i) * Cfg::RPI + lrow;
-            a_voff[i] = (static_cast<uint32_t>(src[i]) * K + ((lpos ^ swz<Cfg::BK>(r)) * 8)) * 2u;
-        }
-#pragma unroll
-        for (int i = 0; i < LB; ++i) {
-            const int r0 = (wave * LB + i) * Cfg::RPI;          // first tile row of the load
-            const int col0 = tc.nt * Cfg::BN_OUT + (Cfg::DUAL ? (r0 >> 6) * 32 + (r0 & 31) : r0);
-            b_voff[i] = (static_cast<uint32_t>(col0 + lrow) * K + ((lpos ^ swz<Cfg::BK>(r0 + lrow)) * 8)) * 2u;
-        }
-        a_lds = wave * LA * 1024;
-        b_lds = wave * LB * 1024;
-    }
-    // weight matrix of B load i (W1 and W3 rows alternate in blocks of 32 tile rows)
-    __device__ __forceinline__ const uint16_t* b_src(int wave, int i) const {
-        return b_ptr[Cfg::DUAL ? (((wave * LB + i) * Cfg::RPI) >> 5) & 1 : 0];
-    }
+//
+// The workgroup is PERSISTENT: it runs one tile after the other, and the loads never stop in
+// between. In the last two k-steps of a tile the load pointers already stand on the next tile, so
+// those k-steps fill the rings with its first two k-steps (nothing else is left to load there), and
+// they arrive under the conversion and stores of the finished tile. A workgroup per tile paid for its
+// lookup (2.6 k cycles), its first loads (4.6 k, bound by their issue: 32 per wavefront about 100
+// cycles apart), the launch gap and the last two k-steps' loads of nothing: a tile of 256 rows takes 35.6 k
+// cycles at K = 768 (45 before) and 79.5 k at 2048 (89). About half of that arrives as time, the rest as a
+// lower clock under the board's power limit: 8192 tokens through 128 experts of 2048 x 768 gate/up 354 -> 337
+// and down 241 -> 218 us, 5003 through 64 of 2048 x 1408 294 -> 277 and 197 -> 189 (fp32 outputs), 8192 479 -> 432 and
+// 262 -> 237, lower tiles (tile_in_expert) included.
+// Long reductions keep a workgroup per tile (PERSISTENT false): the dispatcher starts workgroups in order, which
+// brings those that share rows and weights in L2 back into step at every tile; persistent ones drift apart by
+// what lower tiles save, and a k-step out of step is fetched again (8192 tokens at 6144 x 16384 7276 -> 7464 us
+// a layer, at a clock 2 % lower for the same power).
+//
+// The LDS layout is that of the full tile whatever the height of a tile: A stages of Full::A_BYTES.
+// Load i of wavefront w fetches tile rows 8 * (4 i + w) to + 7 of A, so that the first TM loads of
+// all wavefronts are the rows of a tile of TM * 32 rows for every height, and a lower tile can fetch
+// the first rows of a higher one (the others follow before its first store, see ring_tile_1w).
+template <class Full>
+struct Ring1W {
+    static constexpr int NA = 2, NB = 3;
+    static constexpr int AB = Full::A_BYTES, BB = Full::B_BYTES, A_RING = NA * AB, SMEM = A_RING + NB * BB;
+    static constexpr int LA = Full::NIA / Full::NW, LB = Full::NIB / Full::NW;     // loads per wavefront and k-step
+    static_assert(Full::NW == 4 && Full::TN == 8 && Full::BK == 64 && Full::RPI == 8 && LA == 8 && LB == 8 &&
+                  SMEM <= 160 * 1024, "256 x 256 x 64, rings of 2 + 3 stages");
 };
+
+// Loads of one tile: pointers that advance by a k-step at a time, byte offsets per lane.
+struct LoadPlan1W {
+    const uint16_t* a_ptr;          // A origin + current k offset of the A loads
+    const uint16_t* b_ptr[2];       // first row of the n-tile in W (and W3 with DUAL) + current k offset
+    uint32_t a_voff[8], b_voff[8];  // of A load i (this tile's rows); of B load i (the same for every tile)
+};
+
+// The A row that lane l looks up for its wavefront: row 8 * (4 i + w) + r of the tile with i = l / 8, r = l % 8
+// (rows past the end of the group: its last one).
+__device__ __forceinline__ int a_row_1w(const TileCoord& tc, int wave, int lane) {
+    return min((lane >> 3) * 32 + wave * 8 + (lane & 7), max(tc.rows, 1) - 1);
+}
+
+// lp becomes the plan of tile tc at its first k. With an index (gate/up only), `id` is its entry for every lane's
+// a_row_1w.
+template <class Full>
+__device__ __forceinline__ void start_loads_1w(LoadPlan1W& lp, const TileCoord& tc, int id, int wave, int lane,
+                                               const uint16_t* A, const uint16_t* B0, const uint16_t* B1,
+                                               const int32_t* row_index, RowDiv div, int N, int K) {
+    uint32_t row_off = a_row_1w(tc, wave, lane);
+    if (Full::DUAL && row_index != nullptr) {
+        asm volatile("" : "+v"(id));   // keeps what waits for the index load where this stands
+        row_off = id;
+        if (div.mul != 0) row_off = __umulhi(row_off, div.mul) >> div.shift;
+    }
+    row_off *= static_cast<uint32_t>(K) * 2u;
+    lp.a_ptr = a_origin(A, tc, row_index, K);
+    const size_t first = (static_cast<size_t>(tc.expert) * N + static_cast<size_t>(tc.nt) * Full::BN_OUT) * K;
+    lp.b_ptr[0] = B0 + first;
+    lp.b_ptr[1] = Full::DUAL ? B1 + first : lp.b_ptr[0];
+    const uint32_t chunk = static_cast<uint32_t>((lane & 7) ^ swz<64>(wave * 8 + (lane >> 3))) * 16u;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)        // lane l needs row l / 8 of load i, which lane 8 i + l / 8 looked up
+        lp.a_voff[i] = static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute((i * 8 + (lane >> 3)) * 4,
+                                                                         static_cast<int>(row_off))) + chunk;
+}
+template <class Full>
+__device__ __forceinline__ void init_b_offsets(LoadPlan1W& lp, int wave, int lane, int K) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int r0 = (wave * 8 + i) * 8;                      // first tile row of the load
+        const int col0 = Full::DUAL ? (r0 >> 6) * 32 + (r0 & 31) : r0;
+        lp.b_voff[i] = (static_cast<uint32_t>(col0 + (lane >> 3)) * K + (((lane & 7) ^ swz<64>(r0 + (lane >> 3))) * 8)) * 2u;
+    }
+}
 
 // acc += W_frag * X_frag with the accumulator pinned to AGPRs; then one direct-to-LDS load whose
 // LDS address (lds_base + LDS_OFF) was put into M0 before the MFMA.
@@ -983,11 +1093,10 @@ __device__ __forceinline__ void mma16_then_dma(const bf16x8& w, const bf16x8& x,
 // Every k-step runs exactly this code, without a branch: the accumulators are operands of inline
 // assembly, which the compiler does not know to be MFMAs, so it must never find a reason (a join
 // of two paths, a second loop) to move them between registers next to one. The first half issues
-// the B loads of k-step kt-1+NB, the second half the A loads of k-step kt+NA. Past the end of the
-// reduction the pointers stop advancing: the loads of the last k-steps fetch the last 64 k again
-// into stages that nobody reads any more, which keeps the number of loads in flight, and with it
-// the load-counter value to wait for, the same in every k-step. Likewise the last k-step reads
-// "next" fragments from a stage that holds nothing new; they are never used.
+// the B loads of k-step kt+2, the second half the A loads of k-step kt+2 (in the last two k-steps of
+// a tile: those of the next tile's first two, or these two's again where there is no next one),
+// which keeps the number of loads in flight, and with it the load-counter value to wait for, the
+// same in every k-step. Likewise the last k-step reads "next" fragments that are never used.
 // LDS addresses of one k-step: fragment pointers of this k-step's second half (h1) and of the
 // next k-step's first half (n0), the stages that this k-step's loads refill, and the ring
 // positions (as byte offsets) they derive from.
@@ -998,37 +1107,34 @@ struct RingState1W {
 };
 
 // MFMA number m of a half-step with its load, if it has one: load n = m / STRIDE goes out behind
-// MFMA m when m % STRIDE == 3 and n < NLOADS.
-template <int M, int STRIDE, int NLOADS>
+// MFMA m when m % STRIDE == 3 and n < NLOADS; it lands LDS_STEP bytes behind load n - 1.
+template <int M, int STRIDE, int NLOADS, int LDS_STEP>
 __device__ __forceinline__ void mma16_slot(const bf16x8& w, const bf16x8& x, f32x4& acc,
                                            uint32_t lds_base, const uint32_t* voff,
                                            const void* sbase) {
     if constexpr (M % STRIDE == 3 && M / STRIDE < NLOADS)
-        mma16_then_dma<(M / STRIDE) * 1024>(w, x, acc, lds_base, voff[M / STRIDE], sbase);
+        mma16_then_dma<(M / STRIDE) * LDS_STEP>(w, x, acc, lds_base, voff[M / STRIDE], sbase);
     else
         mma16_agpr(w, x, acc);
 }
 
-template <class Cfg, int NA, int NB>
+template <class Cfg, class R>
 __device__ __forceinline__ void kstep_1w(f32x4 (&acc)[Cfg::TM][8], bf16x8 (&fa)[2][Cfg::TM],
-                                         bf16x8 (&fb)[2][8], RingState1W& rs, LoadPlan1W<Cfg>& lp,
+                                         bf16x8 (&fb)[2][8], RingState1W& rs, LoadPlan1W& lp,
                                          int wave, const unsigned char* pa0, const unsigned char* pa1,
-                                         const unsigned char* pb0, const unsigned char* pb1, int kt,
-                                         int KT) {
-    using R = RingCfg<Cfg, NA, NB>;
+                                         const unsigned char* pb0, const unsigned char* pb1) {
     constexpr int TM = Cfg::TM, NM = TM * 8, NR = TM + 8;      // MFMAs and fragment reads per half
-    constexpr int LA = LoadPlan1W<Cfg>::LA, LB = LoadPlan1W<Cfg>::LB;
-    constexpr uint32_t AB = Cfg::A_BYTES, BB = Cfg::B_BYTES;
-    static_assert((TM == 8 || TM == 6 || TM == 4) && Cfg::TN == 8 && LA == TM && LB == 8 && NA == 2,
-                  "128, 96 or 64 rows x 128 columns per wavefront");
+    constexpr int LA = TM, LB = R::LB;
+    constexpr uint32_t AB = R::AB, BB = R::BB;
+    static_assert(TM >= 4 && TM <= 8 && Cfg::TN == 8, "64 to 128 rows x 128 columns per wavefront");
     const uint32_t a_region = rs.a_region, b_region = rs.b_region;
     const unsigned char *pa_h1 = rs.pa_h1, *pb_h1 = rs.pb_h1, *pa_n0 = rs.pa_n0, *pb_n0 = rs.pb_n0;
     // fragment read r of a half goes out behind MFMA r * SPAN / NR: B fragments first (every MFMA
     // row needs all of them), then the A fragments in the order the MFMA rows use them. The reads
     // of the first half must all have returned at the barrier in the middle of the k-step, so
-    // they are spread over the first three quarters of it only; those of the second half have
+    // they are spread over its first part only (three quarters of it at full height); those of the second half have
     // until their MFMA in the next k-step and are spread over the whole half.
-    constexpr int SPAN1 = (3 * NR <= NM) ? 3 * NR : 2 * NR;
+    constexpr int SPAN1 = (3 * NR <= NM - 4) ? 3 * NR : 2 * NR;
     auto read_behind = [&](auto mtag, auto spantag, bf16x8 (&dfb)[8], bf16x8 (&dfa)[TM],
                            const unsigned char* pbq, const unsigned char* paq) {
         constexpr int m = decltype(mtag)::value, SPAN = decltype(spantag)::value;
@@ -1043,15 +1149,15 @@ __device__ __forceinline__ void kstep_1w(f32x4 (&acc)[Cfg::TM][8], bf16x8 (&fa)[
     //      (with DUAL: four loads of W1 rows, then four of W3 rows)
     auto first = [&](auto mtag) {
         constexpr int m = decltype(mtag)::value, i = m >> 3, j = m & 7, n = m / (NM / 8);
-        const void* src = lp.b_src(wave, n < 8 ? n : 0);
-        mma16_slot<m, NM / 8, 8>(fb[0][j], fa[0][i], acc[i][j], b_region, lp.b_voff, src);
+        const void* src = lp.b_ptr[Cfg::DUAL ? (n >> 2) & 1 : 0];
+        mma16_slot<m, NM / 8, 8, 1024>(fb[0][j], fa[0][i], acc[i][j], b_region, lp.b_voff, src);
         MOE_FENCE();
         read_behind(mtag, std::integral_constant<int, SPAN1>{}, fb[1], fa[1], pb_h1, pa_h1);
-        // the B pointers move on behind the last B load (MFMA 7 * NM / 8 + 3) while a later k-step exists
+        // the B pointers move on behind the last B load (MFMA 7 * NM / 8 + 3)
         constexpr int after_loads = 7 * (NM / 8) + 4;
-        if constexpr (m == (after_loads < NM ? after_loads + 1 : NM - 1)) {
-            lp.b_ptr[0] += (kt + NB < KT) ? Cfg::BK : 0;
-            if (Cfg::DUAL) lp.b_ptr[1] += (kt + NB < KT) ? Cfg::BK : 0;
+        if constexpr (m == (after_loads + 1 < NM ? after_loads + 1 : NM - 1)) {
+            lp.b_ptr[0] += Cfg::BK;
+            if (Cfg::DUAL) lp.b_ptr[1] += Cfg::BK;
             MOE_FENCE();
         }
     };
@@ -1061,21 +1167,21 @@ __device__ __forceinline__ void kstep_1w(f32x4 (&acc)[Cfg::TM][8], bf16x8 (&fa)[
     RingState1W nx;
     auto second = [&](auto mtag) {
         constexpr int m = decltype(mtag)::value, i = m >> 3, j = m & 7;
-        mma16_slot<m, 8, LA>(fb[1][j], fa[1][i], acc[i][j], a_region, lp.a_voff, lp.a_ptr);
+        mma16_slot<m, 8, LA, 4096>(fb[1][j], fa[1][i], acc[i][j], a_region, lp.a_voff, lp.a_ptr);
         MOE_FENCE();
         read_behind(mtag, std::integral_constant<int, NM>{}, fb[0], fa[0], pb_n0, pa_n0);
         if constexpr (m == 1) { sb1 = rs.sb + BB; MOE_FENCE(); }
-        if constexpr (m == 2) { sb1 = (sb1 == NB * BB) ? 0u : sb1; MOE_FENCE(); }        // stage of k-step kt+1
+        if constexpr (m == 2) { sb1 = (sb1 == R::NB * BB) ? 0u : sb1; MOE_FENCE(); }     // stage of k-step kt+1
         if constexpr (m == 5) { sb2 = sb1 + BB; MOE_FENCE(); }
-        if constexpr (m == 6) { sb2 = (sb2 == NB * BB) ? 0u : sb2; MOE_FENCE(); }        // ... of kt+2
+        if constexpr (m == 6) { sb2 = (sb2 == R::NB * BB) ? 0u : sb2; MOE_FENCE(); }     // ... of kt+2
         if constexpr (m == 9) { sa1 = rs.sa ^ AB; MOE_FENCE(); }                         // two A stages
         if constexpr (m == 10) { nx.pa_h1 = pa1 + sa1; MOE_FENCE(); }
         if constexpr (m == 13) { nx.pb_h1 = pb1 + sb1; MOE_FENCE(); }
         if constexpr (m == 14) { nx.pa_n0 = pa0 + rs.sa; MOE_FENCE(); }
         if constexpr (m == 17) { nx.pb_n0 = pb0 + sb2; MOE_FENCE(); }
-        if constexpr (m == 18) { nx.a_region = sa1 + lp.a_lds; MOE_FENCE(); }
-        if constexpr (m == 21) { nx.b_region = R::A_RING + rs.sb + lp.b_lds; MOE_FENCE(); }
-        if constexpr (m == NM - 3) { lp.a_ptr += (kt + NA + 1 < KT) ? Cfg::BK : 0; MOE_FENCE(); }
+        if constexpr (m == 18) { nx.a_region = sa1 + wave * 1024; MOE_FENCE(); }
+        if constexpr (m == 21) { nx.b_region = R::A_RING + rs.sb + wave * (LB * 1024); MOE_FENCE(); }
+        if constexpr (m == NM - 3) { lp.a_ptr += Cfg::BK; MOE_FENCE(); }
     };
     static_for<NM>(first);
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(LB) : "memory");
@@ -1087,145 +1193,229 @@ __device__ __forceinline__ void kstep_1w(f32x4 (&acc)[Cfg::TM][8], bf16x8 (&fa)[
     rs = nx;
 }
 
-// The first loads of a tile: A stages 0..NA-1 and B stages 0..NB-2, in the order the k-loop
-// issues them; the first half of k-step 0 adds B stage NB-1 like any other k-step.
-template <class Cfg, int NA, int NB>
-__device__ __forceinline__ void prologue_1w(const TileCoord& tc, LoadPlan1W<Cfg>& lp, int wave, int lane,
-                                            const uint16_t* __restrict__ A,
-                                            const uint16_t* __restrict__ B0,
-                                            const uint16_t* __restrict__ B1,
-                                            const int32_t* __restrict__ row_index, RowDiv index_div,
-                                            int N, int K) {
-    using R = RingCfg<Cfg, NA, NB>;
-    constexpr int BK = Cfg::BK, LA = R::LA, LB = R::LB, AB = Cfg::A_BYTES, BB = Cfg::B_BYTES;
-    static_assert(NB - 1 == NA, "prologue order");
-    lp.init(tc, wave, lane, A, B0, B1, row_index, index_div, N, K);
-#pragma unroll
-    for (int s = 0; s < NA; ++s) {
-#pragma unroll
-        for (int i = 0; i < LA; ++i) dma16(lp.a_ptr, lp.a_voff[i], s * AB + lp.a_lds + i * 1024);
-        lp.a_ptr += BK;
-        if (s < NB - 1) {
-#pragma unroll
-            for (int i = 0; i < LB; ++i)
-                dma16(lp.b_src(wave, i), lp.b_voff[i], R::A_RING + s * BB + lp.b_lds + i * 1024);
-            lp.b_ptr[0] += BK;
-            if (Cfg::DUAL) lp.b_ptr[1] += BK;
-        }
-    }
-}
-
-// From the landing of k-step 0 to the last MFMA: on return the accumulators hold the tile and the
-// B stage of the last k-step (last_b_stage) is idle: every wavefront had read it at that k-step's
-// barrier, and the refills of the last k-steps, which may still be on their way, go to the others.
-template <class Cfg, int NB>
-__device__ __forceinline__ int last_b_stage(int K) { return (K / Cfg::BK - 1) % NB; }
-template <class Cfg, int NA, int NB>
-__device__ __forceinline__ void mainloop_1w(f32x4 (&acc)[Cfg::TM][8], LoadPlan1W<Cfg>& lp,
-                                            const FragPlan<Cfg>& fp, unsigned char* smem, int wave,
-                                            int K) {
-    using R = RingCfg<Cfg, NA, NB>;
-    constexpr int BK = Cfg::BK, TM = Cfg::TM, TN = Cfg::TN;
-    constexpr int LA = R::LA, LB = R::LB, AB = Cfg::A_BYTES, BB = Cfg::B_BYTES;
-    static_assert(BK == 64 && NA == 2 && NB == 3 && TN == 8, "rings of 2 + 3 stages of 64 k");
+// One tile of a persistent workgroup. On entry its first two k-steps are in the rings (stages 0 and 1 of
+// A, sb and the one behind it of B) and every wavefront knows it; on return those of the next tile are
+// in the rings or on their way, sb is its B stage, and the stores of this one are on their way.
+//   lp        loads of this tile at k-step 2, then of the next one
+//   nxt       the next tile, id as for start_loads_1w; this one if it is the last
+//   draw      called once in each wavefront two k-steps before the end; drawn() before the first store, when
+//             all loads of the wavefront have landed
+template <class Cfg, class Full, class Draw, class Drawn>
+__device__ __forceinline__ void ring_tile_1w(const TileCoord& tc, const TileCoord& nxt, LoadPlan1W& lp,
+                                             int id, bool last, uint32_t& sb, unsigned char* smem, int wave, int lane,
+                                             const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
+                                             const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
+                                             const int32_t* __restrict__ row_index, RowDiv index_div, int N, int K,
+                                             Draw&& draw, Drawn&& drawn) {
+    using R = Ring1W<Full>;
+    constexpr int TM = Cfg::TM, TN = Cfg::TN;
+    constexpr uint32_t AB = R::AB, BB = R::BB;
+    static_assert(Cfg::NW == 4 && Cfg::BN == Full::BN && Cfg::BK == 64, "same n-tiling");
+    FragPlan<Cfg> fp;
+    fp.init(lane, wave / Cfg::WN, wave % Cfg::WN);
     const unsigned char* pa[2] = {smem + fp.a_off[0], smem + fp.a_off[1]};
-    const unsigned char* pb[2] = {smem + R::A_RING + (fp.b_off[0] - AB), smem + R::A_RING + (fp.b_off[1] - AB)};
+    const unsigned char* pb[2] = {smem + R::A_RING + (fp.b_off[0] - Cfg::A_BYTES),
+                                  smem + R::A_RING + (fp.b_off[1] - Cfg::A_BYTES)};
+    bf16x8 fa[2][TM], fb[2][TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) fb[0][j] = lds16(pb[0] + sb + j * Cfg::TILE_STEP);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) fa[0][i] = lds16(pa[0] + i * Cfg::TILE_STEP);
+    MOE_FENCE();
     // The accumulators start as the result of an MFMA, 0 * 0 + 0, not as ordinary register
-    // writes: the compiler may sink those to just in front of the k-loop, and it cannot know
-    // that the inline assembly there is an MFMA that needs wait states after them (it did
-    // exactly that once the zeroing stood after the first loads, and a few fragments came out
-    // wrong). MFMA after MFMA on the same registers needs nothing.
+    // writes: the compiler may sink those to just in front of the k-loop, where it cannot
+    // know that the inline assembly there is an MFMA that needs wait states after them.
+    // MFMA after MFMA on the same registers needs nothing.
+    f32x4 acc[TM][TN];
     {
-        const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+        const bf16x4 zero = {0, 0, 0, 0};
         asm volatile("s_nop 4" :: "v"(zero));
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-                asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %1, 0" : "=a"(acc[i][j]) : "v"(zero));
+            for (int j = 0; j < TN; ++j)             // four registers in half the time of the 16x16x32 instruction
+                asm volatile("v_mfma_f32_4x4x4_16b_bf16 %0, %1, %1, 0" : "=a"(acc[i][j]) : "v"(zero));
     }
-
-    const int KT = K / BK;                           // >= NB (checked by the launcher)
-    wait_vmcnt<(NA - 1) * (LA + LB)>();              // k-step 0 landed
-    __builtin_amdgcn_s_barrier();
-    bf16x8 fa[2][TM], fb[2][TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) fb[0][j] = lds16(pb[0] + j * Cfg::TILE_STEP);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) fa[0][i] = lds16(pa[0] + i * Cfg::TILE_STEP);
-    MOE_FENCE();
-
-    // k-step 0: stages 0; its B loads refill the stage "before" it, NB-1, which is still empty
-    RingState1W rs{pa[1], pb[1], pa[0] + AB, pb[0] + BB, lp.a_lds,
-                   R::A_RING + (NB - 1) * BB + lp.b_lds, 0u, 0u};
+    const uint32_t sb_next = sb + BB == R::NB * BB ? 0u : sb + BB;
+    RingState1W rs{pa[1], pb[1] + sb, pa[0] + AB, pb[0] + sb_next, wave * 1024u,
+                   R::A_RING + (sb == 0 ? (R::NB - 1) * BB : sb - BB) + wave * (R::LB * 1024u), 0u, sb};
     // two k-steps per trip (K is a multiple of 128 for every supported shape): the loop's own
     // compare-and-branch then falls between MFMAs half as often
-    for (int kt = 0; kt < KT; kt += 2) {
-        kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1], kt, KT);
-        kstep_1w<Cfg, NA, NB>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1], kt + 1, KT);
+    int left = K / Cfg::BK - 2;                      // k-steps whose loads are this tile's
+    for (;; left -= 2) {
+        if (left == 0) {                             // from here on the loads are the next tile's
+            if (last) {                              // or the last two k-steps again, from L2 and to no use
+                lp.a_ptr -= 2 * Cfg::BK;
+                lp.b_ptr[0] -= 2 * Cfg::BK;
+                if (Cfg::DUAL) lp.b_ptr[1] -= 2 * Cfg::BK;
+            } else {
+                start_loads_1w<Full>(lp, nxt, id, wave, lane, A, B0, B1, row_index, index_div, N, K);
+                draw();
+            }
+        }
+        kstep_1w<Cfg, R>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1]);
+        kstep_1w<Cfg, R>(acc, fa, fb, rs, lp, wave, pa[0], pa[1], pb[0], pb[1]);
+        if (left == 0) break;
     }
     mfma_drain(acc[TM - 1]);                         // before anything else touches the accumulators
+    sb = rs.sb;                                      // B stage of the next tile's first k-step
+    // rows of a higher next tile that this one's loads did not reach, of both its k-steps
+    if constexpr (TM < 8) {
+        if (!last && nxt.height > Cfg::BM) {
+#pragma unroll
+            for (int i = TM; i < 8; ++i) {
+                dma16(lp.a_ptr - 2 * Cfg::BK, lp.a_voff[i], wave * 1024 + i * 4096);
+                dma16(lp.a_ptr - Cfg::BK, lp.a_voff[i], AB + wave * 1024 + i * 4096);
+            }
+        }
+    }
+    // The B stage of the last k-step is idle: every wavefront had read it at that k-step's barrier, and the
+    // next load into it is the next tile's first. A wavefront stages its outputs in the 8 KB that it will
+    // then fill by itself.
+    unsigned char* idle = smem + R::A_RING + (sb == 0 ? (R::NB - 1) * BB : sb - BB);
+    store_tile_via_lds<Cfg>(acc, tc, fp, wave, lane, idle + wave * (R::LB * 1024), C, N, [&] {
+        __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0): the next tile's first loads, and what draw() asked for
+        drawn(idle);
+    });
 }
 
-template <class Cfg, int NA, int NB>
-__device__ __forceinline__ void ring_tile_1w(const TileCoord& tc, unsigned char* smem,
-                                             const uint16_t* __restrict__ A,
-                                             const uint16_t* __restrict__ B0,
-                                             const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
-                                             const int32_t* __restrict__ row_index, RowDiv index_div,
-                                             int N, int K) {
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    LoadPlan1W<Cfg> lp;
-    prologue_1w<Cfg, NA, NB>(tc, lp, wave, lane, A, B0, B1, row_index, index_div, N, K);
-    FragPlan<Cfg> fp;
-    fp.init(lane, wave / Cfg::WN, wave % Cfg::WN);
-    f32x4 acc[Cfg::TM][Cfg::TN];
-    mainloop_1w<Cfg, NA, NB>(acc, lp, fp, smem, wave, K);
-    // The refills of the last k-steps must have landed before the workgroup gives its LDS back. Waiting for
-    // them here instead of between the last MFMA and the first conversion (with a barrier), and writing
-    // the next fragment row under the reads of this one: layer 745 -> 739 us at 8192 tokens through 128
-    // experts of 2048 x 768, 592 -> 586 us at 5003 through 64 of 2048 x 1408.
-    store_tile_via_lds<Cfg>(acc, tc, fp, wave, lane,
-                            smem + RingCfg<Cfg, NA, NB>::A_RING + last_b_stage<Cfg, NB>(K) * Cfg::B_BYTES, C, N,
-                            [] { wait_vmcnt<0>(); });
+constexpr int kCounterInts = 32;                     // a counter per XCD, on a cache line of its own
+
+// Tiles are enumerated at Cfg::BM rows and run at the height that tile_in_expert gives them, half of that and
+// up in steps of an eighth (an expert's short tail, or a half of a tile of the last, partial round, at half).
+// Every output element is one accumulator chain over k, so the bits do not depend on which height computed it.
+//
+// PERSISTENT: workgroup b serves XCD b % 8's range of tiles: first its slot b / 8, then whichever slot it draws, one
+// tile ahead of the one it computes, so that workgroups even out tiles of unequal cost among themselves as
+// the dispatcher did. No workgroup waits for another one; each ends when it has drawn past the end of its
+// range. Slots and draws: a range of S slots and P workgroups of which min(S, P) have a first tile; each of
+// those draws until it is past the end, S - min(S, P) draws hand out a tile and min(S, P) do not, so draw
+// number S - 1 is the launch's last in this range and whoever gets it sets the counter back to zero for the next
+// launch.
+template <class Cfg, bool PERSISTENT>
+__global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_1w_kernel(
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
+    const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
+    const int32_t* __restrict__ offsets, const int32_t* __restrict__ row_index, RowDiv index_div,
+    int E, int N, int K, int split_cus, int32_t* __restrict__ counters) {
+    using R = Ring1W<Cfg>;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int xcd = blockIdx.x % kXcds, workgroups = gridDim.x / kXcds;
+    int32_t* counter = counters + xcd * kCounterInts;
+    const int NT = N / Cfg::BN_OUT, cut_tiles = K < kLongK ? 1 << 30 : kLongCutTiles;
+    TileTable<Cfg::BM> table;                        // kept over the tiles: a lookup then reads no memory
+    TileCoord tc;
+    const uint32_t magic = division_magic(lane);
+    if constexpr (PERSISTENT) {
+        table.init(offsets, E, NT, split_cus, xcd, lane);
+        tc = uniform_tile(table.find(NT, cut_tiles, blockIdx.x / kXcds, magic));
+    } else {
+        tc = locate_tile<Cfg::BM>(offsets, E, NT, split_cus, cut_tiles);
+    }
+    if (tc.expert < 0) return;                       // uniform for the whole workgroup
+    bool last = !PERSISTENT;
+    int ahead = 0;                                   // lane 0 of wavefront 0: the latest draw
+    auto draw = [&] {
+        if (PERSISTENT && threadIdx.x == 0) {
+            // an address that the compiler does not know to be uniform: of one that is it makes a sum over
+            // the lanes, and waits for the result on the spot to hand it to them
+            int at = 0;
+            asm volatile("" : "+v"(at));
+            ahead = __hip_atomic_fetch_add(counter + at, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    };
+    // handed to the other wavefronts in the 4 KB of the idle B stage behind each one's staging region
+    auto drawn = [&](unsigned char* idle) {
+        if (PERSISTENT && wave == 0) {
+            const int v = __builtin_amdgcn_readfirstlane(ahead);
+            if (lane < 4) *reinterpret_cast<int*>(idle + lane * (R::LB * 1024) + kEpilogueBytes) = v;
+        }
+    };
+    auto row_id = [&](const TileCoord& t) {          // without an index some load, so that no path sets it otherwise
+        if constexpr (!Cfg::DUAL) return 0;
+        return row_index != nullptr ? row_index[t.row0 + a_row_1w(t, wave, lane)] : offsets[0];
+    };
+    draw();
+    LoadPlan1W lp;
+    init_b_offsets<Cfg>(lp, wave, lane, K);
+    start_loads_1w<Cfg>(lp, tc, row_id(tc), wave, lane, A, B0, B1, row_index, index_div, N, K);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (i < 4 || i * 32 < tc.height) dma16(lp.a_ptr, lp.a_voff[i], s * R::AB + wave * 1024 + i * 4096);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            dma16(lp.b_ptr[Cfg::DUAL ? i >> 2 : 0], lp.b_voff[i], R::A_RING + s * R::BB + wave * (R::LB * 1024) + i * 1024);
+        lp.a_ptr += Cfg::BK;
+        lp.b_ptr[0] += Cfg::BK;
+        if (Cfg::DUAL) lp.b_ptr[1] += Cfg::BK;
+    }
+    uint32_t sb = 0;
+    unsigned char* idle = smem + R::A_RING + (R::NB - 1) * R::BB;
+    if constexpr (PERSISTENT) {
+        __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0): the first draw too
+        drawn(idle);
+    } else {
+        if (tc.height == Cfg::BM) wait_vmcnt<R::LA + R::LB>();   // k-step 0 landed
+        else wait_vmcnt<4 + R::LB>();
+    }
+    while (true) {
+        // lane-dependent addresses are formed anew for every tile: kept over the loop they would take the
+        // registers of fragments
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(lane) :: "memory");
+        __builtin_amdgcn_s_barrier();                // the tile's first k-step has landed for every wavefront
+        TileCoord nxt = tc;
+        if constexpr (PERSISTENT) {
+            const int slot = __builtin_amdgcn_readfirstlane(
+                *reinterpret_cast<const int*>(idle + wave * (R::LB * 1024) + kEpilogueBytes));
+            const TileCoord found = uniform_tile(table.find(NT, cut_tiles, workgroups + slot, magic));
+            last = found.expert < 0;
+            if (!last)
+                nxt = found;
+            else if (slot == table.range.slots - 1 && threadIdx.x == 0)
+                __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const int id = row_id(nxt);
+        auto run = [&](auto cfg_tag) {
+            using TileCfg = typename decltype(cfg_tag)::type;
+            ring_tile_1w<TileCfg, Cfg>(tc, nxt, lp, id, last, sb, smem, wave, lane, A, B0, B1, C, row_index, index_div,
+                                       N, K, draw, drawn);
+        };
+        switch (tc.height) {
+            case 128: run(type_tag<AtHeight<Cfg, 128>>{}); break;
+            case 160: run(type_tag<AtHeight<Cfg, 160>>{}); break;
+            case 192: run(type_tag<AtHeight<Cfg, 192>>{}); break;
+            case 224: run(type_tag<AtHeight<Cfg, 224>>{}); break;
+            default: run(type_tag<Cfg>{}); break;
+        }
+        if (last) break;
+        tc = nxt;
+        idle = smem + R::A_RING + (sb == 0 ? (R::NB - 1) * R::BB : sb - R::BB);
+    }
 }
 
-// Tiles are enumerated at Cfg::BM rows, the last ones of an expert lower (see tile_in_expert). A tile that
-// holds at most HalfCfg::BM = Cfg::BM / 2 rows (an expert's short tail, or a half of a tile of the last,
-// partial round: see locate_tile) runs the same pipeline at half height, one that was cut to LowCfg::BM =
-// Cfg::BM * 3 / 4 rows at three quarters (LowCfg = Cfg: none is). Every output element is still one
-// accumulator chain over k, so the bits do not depend on which height computed it.
-template <class Cfg, class LowCfg, class HalfCfg, int NA, int NB>
+// The 256-row tiles of eight wavefronts, a workgroup per tile; tiles of at most HalfCfg::BM rows run at half
+// the height.
+template <class Cfg, class HalfCfg, int NA, int NB>
 __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_ring_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
     const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ row_index, RowDiv index_div,
     int E, int N, int K, int split_cus) {
-    constexpr bool LOW = LowCfg::BM != Cfg::BM;
     static_assert(HalfCfg::BM * 2 == Cfg::BM && HalfCfg::BN == Cfg::BN && HalfCfg::BK == Cfg::BK &&
                   HalfCfg::NTHREADS == Cfg::NTHREADS && HalfCfg::DUAL == Cfg::DUAL, "same n-tiling");
-    static_assert((!LOW || LowCfg::BM * 4 == Cfg::BM * 3) && LowCfg::BN == Cfg::BN && LowCfg::BK == Cfg::BK &&
-                  LowCfg::NTHREADS == Cfg::NTHREADS && LowCfg::DUAL == Cfg::DUAL, "same n-tiling");
-    static_assert(RingCfg<HalfCfg, NA, NB>::SMEM <= RingCfg<Cfg, NA, NB>::SMEM &&
-                  RingCfg<LowCfg, NA, NB>::SMEM <= RingCfg<Cfg, NA, NB>::SMEM, "LDS of the full tile");
+    static_assert(RingCfg<HalfCfg, NA, NB>::SMEM <= RingCfg<Cfg, NA, NB>::SMEM, "LDS of the full tile");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
-    const TileCoord tc = locate_tile<Cfg::BM>(offsets, E, N / Cfg::BN_OUT, split_cus,
-                                              !LOW ? 0 : K < kLongK ? 1 << 30 : kLongCutTiles);
-    if (tc.expert < 0) return;                       // uniform for the whole workgroup
-    // four wavefronts of (128, 96 or 64) x 128 outputs run the one-wavefront-per-SIMD pipeline
-    auto run = [&](auto cfg_tag) {
-        using TileCfg = typename decltype(cfg_tag)::type;
-        if constexpr (TileCfg::NW == 4 && TileCfg::TN == 8)
-            ring_tile_1w<TileCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, N, K);
-        else
-            ring_tile<TileCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, N, K);
-    };
-    if (tc.height == HalfCfg::BM) run(type_tag<HalfCfg>{});
-    else if (LOW && tc.height == LowCfg::BM) run(type_tag<LowCfg>{});
-    else run(type_tag<Cfg>{});
+    const TileCoord tc = locate_tile<Cfg::BM>(offsets, E, N / Cfg::BN_OUT, split_cus);
+    if (tc.expert < 0 || tc.rows == 0) return;       // uniform for the whole workgroup
+    if (tc.height == HalfCfg::BM)
+        ring_tile<HalfCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, N, K);
+    else
+        ring_tile<Cfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, N, K);
 }
 
 }  // namespace gemm

@@ -63,7 +63,7 @@ bool on_own_device(const moe_ctx* c) {
 }
 
 struct Layout {
-    size_t topk_idx, topk_w, counts, offsets, perm, inv_perm, scratch, logits, x_perm, H, y_perm, total;
+    size_t topk_idx, topk_w, counts, offsets, perm, inv_perm, scratch, logits, x_perm, H, y_perm, counters, total;
 };
 
 Layout layout_for(const moe_shape* s) {
@@ -82,6 +82,7 @@ Layout layout_for(const moe_shape* s) {
     L.x_perm = take(R * s->d_model * 2);
     L.H = take(R * s->d_ff * 2);
     L.y_perm = take(R * s->d_model * 2);
+    L.counters = take(kTileCounterBytes);
     L.total = off ? off : 256;
     return L;
 }
@@ -246,6 +247,9 @@ int moe_create(moe_ctx** out, const moe_shape* shape, int device_id) {
     // allocate on the context's device, then give the caller its current device back
     hipError_t err = hipSetDevice(device_id);
     if (err == hipSuccess) err = hipMalloc(&p, L.total);
+    const unsigned char zeros[kTileCounterBytes] = {};
+    if (err == hipSuccess)
+        err = hipMemcpy(static_cast<unsigned char*>(p) + L.counters, zeros, sizeof(zeros), hipMemcpyHostToDevice);
     const hipError_t back = hipSetDevice(caller_device);
     if (err != hipSuccess || back != hipSuccess) {
         (void)hipGetLastError();
@@ -266,6 +270,7 @@ int moe_create(moe_ctx** out, const moe_shape* shape, int device_id) {
     c->H = reinterpret_cast<moe_bf16*>(c->base + L.H);
     c->y_perm = reinterpret_cast<moe_bf16*>(c->base + L.y_perm);
     c->y_perm_f32 = nullptr;
+    c->gemm.tile_counters = reinterpret_cast<int32_t*>(c->base + L.counters);
     c->prof_armed = false;
     c->prof_max_calls = c->prof_calls = 0;
     for (auto& v : c->prof_launches) v = 0;

@@ -589,7 +589,7 @@ def test_automatic_tile_choice_agrees_bitwise(d, f, rows, fp32_outputs):
 ])
 @pytest.mark.parametrize("fp32_outputs", [False, True])
 def test_large_tiles_of_every_height(rows, fp32_outputs, d=512, f=256):
-    """256-, 192- and 128-row tiles and split last rounds against the 128-row configuration."""
+    """256- to 128-row tiles and split last rounds against the 128-row configuration."""
     say(f"large tiles d={d} f={f} rows={rows} fp32={fp32_outputs}")
     E, R = len(rows), sum(rows)
     g = torch.Generator(device="cuda").manual_seed(R)
@@ -620,6 +620,42 @@ def test_large_tiles_of_every_height(rows, fp32_outputs, d=512, f=256):
 def test_large_tiles_of_long_reductions(d, f):
     """Experts of up to four m-tiles are cut in long reductions, those of five and more are not."""
     test_large_tiles_of_every_height([449, 577, 769, 1024, 1025, 1152, 130], False, d, f)
+
+
+@pytest.mark.parametrize("d,f", [(512, 3840), (3584, 256)])    # many tiles per workgroup up; down, at four k-steps
+@pytest.mark.parametrize("split", [0, 128])
+def test_persistent_workgroups_run_tiles_of_all_heights_in_turn(d, f, split):
+    """Each workgroup draws several tiles: lower ones before higher ones and the reverse, groups without rows,
+    counters that the launch before has cleared, from a graph too."""
+    rows = [1, 257, 300, 160, 0, 512, 130, 420, 33, 256, 193, 600, 225, 128, 769, 0, 161, 480]
+    say(f"persistent workgroups d={d} f={f} split={split}")
+    E, R = len(rows), sum(rows)
+    g = torch.Generator(device="cuda").manual_seed(d)
+    rnd = lambda *shape: (torch.randn(*shape, generator=g, device="cuda") * 0.05).bfloat16()
+    W1, W3, W2, x = rnd(E, f, d), rnd(E, f, d), rnd(E, d, f), rnd(R, d)
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(rows)]), dtype=torch.int32, device="cuda")
+    ctx = B.MoeContext(R, d, f, E, 1)
+    want, y = (torch.full((R, d), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    B.moe_set_gemm_config(ctx, 1)
+    B.moe_expert_ffn(ctx, x, offsets, R, W1, W3, W2, want)
+    B.moe_set_gemm_config(ctx, 0 + split)
+
+    def check(call):
+        y.fill_(float("nan"))
+        call()
+        torch.cuda.synchronize()
+        assert torch.equal(y.view(torch.int16), want.view(torch.int16))
+
+    eager = lambda: B.moe_expert_ffn(ctx, x, offsets, R, W1, W3, W2, y)
+    check(eager)
+    check(eager)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        B.moe_expert_ffn(ctx, x, offsets, R, W1, W3, W2, y, stream=side)
+    for _ in range(3):
+        check(graph.replay)
+        check(eager)
+    ctx.close()
 
 
 @pytest.mark.parametrize("first,count", [(0, 3), (1, 1), (2, 5), (6, 1)])
