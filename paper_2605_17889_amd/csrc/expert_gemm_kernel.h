@@ -617,12 +617,23 @@ struct LoadPlan {
 };
 
 // ---- kernel 1: ring of stages, every wavefront loads and computes ---------------------------
+// Workgroups that start together stay at the same k, where weight rows whose pitch is a multiple of 4 KB fall on
+// few memory channels. In long reductions the first workgroup of every compute unit starts later by its place in its
+// XCD: they then stream different k, and what a late start costs is less than what the channels gain; the
+// order of the sums is the same. `spread` is the step in units of 768 cycles (spread_steps in expert_gemm.hip).
+constexpr int kSpreadSlots = 32;     // compute units of an XCD
+__device__ __forceinline__ void spread_start(int spread) {
+    const int slot = blockIdx.x / kXcds;
+    if (slot >= kSpreadSlots) return;
+    for (int i = slot * spread; i > 0; --i) __builtin_amdgcn_s_sleep(12);
+}
+
 template <class Cfg>
 __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
     const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ row_index, RowDiv index_div,
-    int E, int N, int K) {
+    int E, int N, int K, int spread) {
     constexpr int BM = Cfg::BM, BK = Cfg::BK, WN = Cfg::WN;
     constexpr int TM = Cfg::TM, TN = Cfg::TN, LPW = Cfg::LPW, NSTAGE = Cfg::NSTAGE;
 
@@ -630,6 +641,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
 
     const TileCoord tc = locate_tile<BM>(offsets, E, N / Cfg::BN_OUT);
     if (tc.expert < 0) return;
+    spread_start(spread);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
