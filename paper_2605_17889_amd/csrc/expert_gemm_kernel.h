@@ -502,25 +502,6 @@ __device__ __forceinline__ void store_tile(const f32x4 (&acc)[Cfg::TM][Cfg::TN],
     }
 }
 
-// Weight row (and matrix) that tile row r0 of the B tile comes from. With DUAL the tile rows
-// alternate between W1 and W3 in blocks of Cfg::DB.
-template <class Cfg>
-__device__ __forceinline__ const uint16_t* weight_row_ptr(const TileCoord& tc, int r0,
-                                                          const uint16_t* B0, const uint16_t* B1,
-                                                          int N, int K) {
-    int col0;
-    const uint16_t* base;
-    if (Cfg::DUAL) {
-        const int block = r0 / Cfg::DB;
-        col0 = tc.nt * Cfg::BN_OUT + (block >> 1) * Cfg::DB + r0 % Cfg::DB;
-        base = (block & 1) ? B1 : B0;
-    } else {
-        col0 = tc.nt * Cfg::BN_OUT + r0;
-        base = B0;
-    }
-    return base + (static_cast<size_t>(tc.expert) * N + col0) * K;
-}
-
 // Division of a flat id (below 2^31) by the number of experts per token as a multiplication:
 // id / div == (id * mul) >> (32 + shift) with mul = floor(2^(32 + shift) / div) + 1 and
 // 2^shift < div <= 2^(shift + 1): the error term id * (mul * div - 2^(32 + shift)) stays below
@@ -535,26 +516,36 @@ struct RowDiv {
     }
 };
 
-// Rows of A, relative to a_origin(), that feed rows r0 + i * STEP of the tile (rows past the end of
-// the group read its last row). Without an index the A matrix is already grouped: the origin is
+// Rows of A, relative to a_origin(), that feed rows r0 + i * RPI + lrow of the tile, lrow < RPI by lane (rows past
+// the end of the group read its last row). Without an index the A matrix is already grouped: the origin is
 // the tile's first row and the answer is the row itself. With one, A holds one row per token, the
 // origin is A itself and grouped row p reads the token row_index[p] / div (the permutation's flat
 // id t*k+s divided by k) — the row gather fused into the operand load. Offsets from the origin
 // are 32-bit: the caller guarantees that the token matrix is smaller than 4 GiB when it passes
-// an index. All index loads go out before the first is used: one after the other, each with an
-// integer division behind it, the eight of a 256-row tile took 3 to 7 % of the gate/up launch
-// (330 -> 307 us at 5003 tokens through 64 experts of 2048 x 1408).
-template <int COUNT, int STEP>
-__device__ __forceinline__ void source_rows(int (&src)[COUNT], const TileCoord& tc, int r0,
+// an index. The index comes through the scalar cache, RPI entries together, and a lane picks its own: a
+// vector load would be counted with the direct-to-LDS loads, and to wait for it would be to wait for all of those
+// that are on their way. A group shorter than RPI rows reads past its end, up to RPI - 1 entries past the end of
+// the index, which the caller's buffer has to hold.
+template <int COUNT, int RPI>
+__device__ __forceinline__ void source_rows(int (&src)[COUNT], const TileCoord& tc, int r0, int lrow,
                                             const int32_t* __restrict__ row_index, RowDiv div) {
 #pragma unroll
-    for (int i = 0; i < COUNT; ++i) src[i] = min(r0 + i * STEP, tc.rows - 1);
+    for (int i = 0; i < COUNT; ++i) src[i] = min(r0 + i * RPI + lrow, tc.rows - 1);
     if (row_index != nullptr) {
+        int ids[COUNT][RPI];
+        int at[COUNT];
 #pragma unroll
-        for (int i = 0; i < COUNT; ++i) src[i] = row_index[tc.row0 + src[i]];
-        if (div.mul != 0) {
+        for (int i = 0; i < COUNT; ++i) {
+            at[i] = max(0, min(r0 + i * RPI, tc.rows - RPI));
 #pragma unroll
-            for (int i = 0; i < COUNT; ++i) src[i] = __umulhi(static_cast<uint32_t>(src[i]), div.mul) >> div.shift;
+            for (int q = 0; q < RPI; ++q) ids[i][q] = row_index[tc.row0 + at[i] + q];
+        }
+#pragma unroll
+        for (int i = 0; i < COUNT; ++i) {
+            int id = ids[i][0];
+#pragma unroll
+            for (int q = 1; q < RPI; ++q) id = src[i] - at[i] >= q ? ids[i][q] : id;
+            src[i] = div.mul == 0 ? id : static_cast<int>(__umulhi(static_cast<uint32_t>(id), div.mul) >> div.shift);
         }
     }
 }
@@ -570,45 +561,72 @@ __device__ __forceinline__ const uint16_t* a_origin(const uint16_t* A, const Til
 template <class Cfg>
 struct LoadPlan {
     static constexpr int LA = Cfg::NIA / Cfg::NW, LB = Cfg::NIB / Cfg::NW;
+    // The B-tile rows of a wavefront come in blocks of Cfg::DB from W1 and W3 in turn with DUAL.
+    static constexpr int BLOCKS = Cfg::DUAL && LB * Cfg::RPI > Cfg::DB ? LB * Cfg::RPI / Cfg::DB : 1;
     const uint16_t* a_base;
-    const uint16_t* b_base[LB];
-    uint32_t a_voff[LA], a_lds[LA], b_voff[LB], b_lds[LB];
+    const uint16_t* b_base[BLOCKS];     // the n-tile's first row in the block's matrix
+    uint32_t a_voff[LA], b_voff[LB], a_lds, b_lds;      // a_lds, b_lds: this wavefront's first load inside a stage
     bool a_on[LA];      // false: every row of this A load lies past the end of the group
-    __device__ __forceinline__ void init(const TileCoord& tc, int wave, int lane, const uint16_t* A,
-                                         const uint16_t* B0, const uint16_t* B1,
-                                         const int32_t* row_index, RowDiv index_div, int N, int K) {
+    __device__ __forceinline__ void init_a(const TileCoord& tc, int wave, int lane, const uint16_t* A,
+                                           const int32_t* row_index, RowDiv index_div, int K) {
         const int lrow = lane / Cfg::CPR, lpos = lane % Cfg::CPR;
         a_base = a_origin(A, tc, row_index, K);
         int src[LA];
-        source_rows<LA, Cfg::RPI>(src, tc, wave * LA * Cfg::RPI + lrow, row_index, index_div);
+        source_rows<LA, Cfg::RPI>(src, tc, wave * LA * Cfg::RPI, lrow, row_index, index_div);
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
             const int q = wave * LA + i;
             const int r = q * Cfg::RPI + lrow;
             a_voff[i] = (static_cast<uint32_t>(src[i]) * K + ((lpos ^ swz<Cfg::BK>(r)) * 8)) * 2u;
-            a_lds[i] = q * 1024;
             a_on[i] = q * Cfg::RPI < tc.rows;
         }
+    }
+    // what is the same for every tile
+    __device__ __forceinline__ void init_fixed(int wave, int lane, int K) {
+        static_assert(!Cfg::DUAL || LB * Cfg::RPI % Cfg::DB == 0 || Cfg::DB % (LB * Cfg::RPI) == 0, "whole blocks");
+        const int lrow = lane / Cfg::CPR, lpos = lane % Cfg::CPR;
+        a_lds = wave * LA * 1024;
+        b_lds = Cfg::A_BYTES + wave * LB * 1024;
 #pragma unroll
         for (int i = 0; i < LB; ++i) {
-            const int q = wave * LB + i;
-            const int r = q * Cfg::RPI + lrow;
-            b_base[i] = weight_row_ptr<Cfg>(tc, q * Cfg::RPI, B0, B1, N, K);
-            b_voff[i] = (static_cast<uint32_t>(lrow) * K + ((lpos ^ swz<Cfg::BK>(r)) * 8)) * 2u;
-            b_lds[i] = Cfg::A_BYTES + q * 1024;
+            const int q = wave * LB + i, r0 = q * Cfg::RPI;
+            const int col0 = Cfg::DUAL ? r0 / (2 * Cfg::DB) * Cfg::DB + r0 % Cfg::DB : r0;
+            b_voff[i] = (static_cast<uint32_t>(col0 + lrow) * K + ((lpos ^ swz<Cfg::BK>(r0 + lrow)) * 8)) * 2u;
         }
     }
+    __device__ __forceinline__ void init_b(const TileCoord& tc, int wave, const uint16_t* B0, const uint16_t* B1,
+                                           int N, int K) {
+        const size_t first = (static_cast<size_t>(tc.expert) * N + static_cast<size_t>(tc.nt) * Cfg::BN_OUT) * K;
+#pragma unroll
+        for (int b = 0; b < BLOCKS; ++b)
+            b_base[b] = (Cfg::DUAL && ((wave * LB * Cfg::RPI / Cfg::DB + b) & 1) ? B1 : B0) + first;
+    }
+    __device__ __forceinline__ void init(const TileCoord& tc, int wave, int lane, const uint16_t* A,
+                                         const uint16_t* B0, const uint16_t* B1,
+                                         const int32_t* row_index, RowDiv index_div, int N, int K) {
+        init_b(tc, wave, B0, B1, N, K);
+        init_a(tc, wave, lane, A, row_index, index_div, K);
+    }
+    __device__ __forceinline__ const uint16_t* b_src(int i) const { return b_base[i * BLOCKS / LB]; }
     // load number n (0 <= n < LA + LB) of k-step kt into the stage at LDS byte offset sbase
     __device__ __forceinline__ void issue_one(int n, uint32_t sbase, size_t koff) const {
-        if (n < LA) dma16(a_base + koff, a_voff[n], sbase + a_lds[n]);
-        else dma16<Cfg::STREAM_B>(b_base[n - LA] + koff, b_voff[n - LA], sbase + b_lds[n - LA]);
+        if (n < LA) dma16(a_base + koff, a_voff[n], sbase + a_lds + n * 1024);
+        else dma16<Cfg::STREAM_B>(b_src(n - LA) + koff, b_voff[n - LA], sbase + b_lds + (n - LA) * 1024);
     }
     // single loads with explicit LDS region bases (operand rings of different depth)
     __device__ __forceinline__ void issue_a(int i, uint32_t region, size_t koff) const {
-        dma16(a_base + koff, a_voff[i], region + a_lds[i]);
+        dma16(a_base + koff, a_voff[i], region + a_lds + i * 1024);
     }
     __device__ __forceinline__ void issue_b(int i, uint32_t region, size_t koff) const {
-        dma16(b_base[i] + koff, b_voff[i], region + (b_lds[i] - Cfg::A_BYTES));
+        dma16(b_src(i) + koff, b_voff[i], region + (b_lds - Cfg::A_BYTES) + i * 1024);
+    }
+    __device__ __forceinline__ void issue_a_all(uint32_t sbase, size_t koff) const {
+#pragma unroll
+        for (int n = 0; n < LA; ++n) issue_one(n, sbase, koff);
+    }
+    __device__ __forceinline__ void issue_b_all(uint32_t sbase, size_t koff) const {
+#pragma unroll
+        for (int n = LA; n < LA + LB; ++n) issue_one(n, sbase, koff);
     }
     __device__ __forceinline__ void issue_all(uint32_t sbase, size_t koff) const {
 #pragma unroll
@@ -628,7 +646,7 @@ __device__ __forceinline__ void spread_start(int spread) {
     for (int i = slot * spread; i > 0; --i) __builtin_amdgcn_s_sleep(12);
 }
 
-template <class Cfg>
+template <class Cfg, bool PERSISTENT>
 __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
     const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
@@ -639,46 +657,75 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
 
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
-    const TileCoord tc = locate_tile<BM>(offsets, E, N / Cfg::BN_OUT);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int xcd = blockIdx.x % kXcds, step = gridDim.x / kXcds, NT = N / Cfg::BN_OUT;
+    int slot = blockIdx.x / kXcds;
+    TileTable<BM> table;                 // kept over the tiles: a lookup then reads no memory
+    const uint32_t magic = division_magic(lane);
+    TileCoord tc;
+    if constexpr (PERSISTENT) {
+        table.init(offsets, E, NT, 0, xcd, lane);
+        tc = uniform_tile(table.find(NT, 0, slot, magic));
+    } else {
+        tc = locate_tile<BM>(offsets, E, NT);
+    }
     if (tc.expert < 0) return;
     spread_start(spread);
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN;
-
+    // The loads run up to NSTAGE-1 k-steps ahead, into the workgroup's next tile near the end of one. First loads:
+    // weights of two stages go out under the latency of the row index.
+    const int KT = K / BK;               // a grid with fewer slots than tiles has KT >= NSTAGE - 1
     LoadPlan<Cfg> lp;
-    lp.init(tc, wave, lane, A, B0, B1, row_index, index_div, N, K);
-
-    f32x4 acc[TM][TN];
+    lp.init_fixed(wave, lane, K);
+    lp.init_b(tc, wave, B0, B1, N, K);
+    constexpr int AHEAD = NSTAGE > 2 ? 2 : 1;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int s = 0; s < AHEAD; ++s)
+        if (s < KT) lp.issue_b_all(s * Cfg::STAGE_BYTES, static_cast<size_t>(s) * BK);
+    lp.init_a(tc, wave, lane, A, row_index, index_div, K);
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < NSTAGE - 1; ++s) {
+        if (s < KT) lp.issue_a_all(s * Cfg::STAGE_BYTES, static_cast<size_t>(s) * BK);
+        if (s >= AHEAD && s < KT) lp.issue_b_all(s * Cfg::STAGE_BYTES, static_cast<size_t>(s) * BK);
+    }
+    // k-step 0 has landed when only the later A loads and stages are on their way
+    if (KT >= NSTAGE - 1) wait_vmcnt<(AHEAD - 1) * LoadPlan<Cfg>::LA + (NSTAGE - 1 - AHEAD) * LPW>();
+    int loaded = min(NSTAGE - 1, KT);    // k-steps of lp's tile that are on their way
     FragPlan<Cfg> fp;
     fp.init(lane, wm, wn);
-
-    // ---- main loop: ring of NSTAGE stages, NSTAGE-1 k-steps of loads in flight.
-    const int KT = K / BK;
-#pragma unroll
-    for (int s = 0; s < NSTAGE - 1; ++s)
-        if (s < KT) lp.issue_all(s * Cfg::STAGE_BYTES, static_cast<size_t>(s) * BK);
     int stage = 0;
-    for (int kt = 0; kt < KT; ++kt) {
-        // The loads of k-step kt are the oldest in flight; up to NSTAGE-2 newer steps may stay
-        // pending. Near the tail fewer are in flight, so wait for everything.
-        if (kt + NSTAGE - 2 < KT) wait_vmcnt<(NSTAGE - 2) * LPW>(); else wait_vmcnt<0>();
-        __builtin_amdgcn_s_barrier();          // stage `stage` is complete for every wavefront
-                                               // and stage (stage-1) is no longer being read
-        const int nk = kt + NSTAGE - 1;
-        if (nk < KT)
-            lp.issue_all((stage == 0 ? NSTAGE - 1 : stage - 1) * Cfg::STAGE_BYTES,
-                         static_cast<size_t>(nk) * BK);
-        mma_stage<Cfg>(smem + stage * Cfg::STAGE_BYTES, fp, acc);
-        stage = (stage + 1 == NSTAGE) ? 0 : stage + 1;
+    while (true) {
+        TileCoord nxt{kNoTile, 0, 0, 0, 0};
+        if constexpr (PERSISTENT) nxt = uniform_tile(table.find(NT, 0, slot += step, magic));
+        const bool more = PERSISTENT && nxt.expert >= 0;
+        f32x4 acc[TM][TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int kt = 0; kt < KT; ++kt) {
+            // The loads of k-step kt are the oldest in flight; up to NSTAGE-2 newer steps may stay
+            // pending. Near the end of the last tile fewer are in flight, so wait for everything.
+            if (more || kt + NSTAGE - 2 < KT) wait_vmcnt<(NSTAGE - 2) * LPW>(); else wait_vmcnt<0>();
+            __builtin_amdgcn_s_barrier();          // stage `stage` is complete for every wavefront
+                                                   // and stage (stage-1) is no longer being read
+            if (loaded == KT && more) {
+                lp.init(nxt, wave, lane, A, B0, B1, row_index, index_div, N, K);
+                loaded = 0;
+            }
+            if (loaded < KT) {
+                lp.issue_all((stage == 0 ? NSTAGE - 1 : stage - 1) * Cfg::STAGE_BYTES, static_cast<size_t>(loaded) * BK);
+                ++loaded;
+            }
+            mma_stage<Cfg>(smem + stage * Cfg::STAGE_BYTES, fp, acc);
+            stage = (stage + 1 == NSTAGE) ? 0 : stage + 1;
+        }
+        store_tile<Cfg>(acc, tc, fp, wm, wn, C, N);
+        if (!more) break;
+        tc = nxt;
     }
-    store_tile<Cfg>(acc, tc, fp, wm, wn, C, N);
 }
 
 // ---- kernel 2: operand rings of different depth, hand-placed software pipeline ---------------
@@ -808,6 +855,7 @@ __device__ __forceinline__ void ring_tile(const TileCoord& tc, unsigned char* sm
     const int wm = wave / WN, wn = wave % WN;
 
     LoadPlan<Cfg> lp;
+    lp.init_fixed(wave, lane, K);
     lp.init(tc, wave, lane, A, B0, B1, row_index, index_div, N, K);
     FragPlan<Cfg> fp;
     fp.init(lane, wm, wn);
