@@ -113,8 +113,8 @@ struct SlotRange {
     }
 };
 
-constexpr int kLongK = 4096;         // reductions of this and more cut the tiles of experts of at most
-constexpr int kLongCutTiles = 4;     // so many m-tiles only, shorter ones those of every expert
+constexpr int kLongK = 4096;         // gate/up reductions of this and more cut the tiles of experts of at most
+constexpr int kLongCutTiles = 5;     // so many m-tiles only; shorter ones and the down projection those of every expert
 
 // Coordinates of tile `local` of the expert whose group is rows [row_e, row_e + m_e). The expert's
 // mt m-tiles form ceil(mt / kGroupM) groups of nearly equal height (the first `extra` groups hold
@@ -129,12 +129,13 @@ constexpr int kLongCutTiles = 4;     // so many m-tiles only, shorter ones those
 // each) 462 -> 431 and 257 -> 241 us, 5003 282 -> 270 and 196 -> 191 (fp32 outputs), 8192 through 128 of 2048 x 768
 // 336 -> 325 and 234 -> 222, 1200 through 8 of 4096 x 14336 515 -> 520 and 295 -> 274 (those of short reductions
 // together with the persistent workgroups, see grouped_gemm_1w_kernel).
-// A workgroup that ends early is out of step with those whose rows and weights it shares in L2, which long reductions pay
-// for, while the saving shrinks with the number of m-tiles. In quarters, nothing cut, experts of at most four m-tiles, of
-// at most six (gate/up): 5500 tokens through 8 experts of 6144 x 16384 3213, 3214, 3358 us; 16384 with a skewed load 9341,
-// 9368, 9515; 2048 1401, 1331, 1343; 1200 at 4096 x 14336 666, 550, 539. Down at 16384 skewed tokens 4677, 4701, 4744, and
-// with all cut 4717. A short reduction loses nothing: 16384 skewed tokens through 128 experts of 2048 x 768 687 us whole,
-// with experts of nine and fewer cut 673, with all 665.
+// A workgroup that ends early is out of step with those whose rows and weights it shares in L2, which the long reductions
+// of gate/up pay for, while the saving shrinks with the number of m-tiles. Gate/up, experts of at most four m-tiles cut, of
+// at most six, all: 4096 tokens through 8 experts of 6144 x 16384 (four or five m-tiles) 2399, 2349, 2353 us; 5500 (six)
+// 3221, 3274, 3247; 8192 4602, 4612, 4661; 16384 with a skewed load 9013, 9100, 9332; 8192 at 4096 x 14336 2623, 2642, 2650.
+// Down: 1342, 1314, 1310; 1641, 1588, 1603; 2386, 2392, 2370; 4612, 4637, 4584; 1467, 1465, 1478. A short reduction loses
+// nothing: 16384 skewed tokens through 128 experts of 2048 x 768 687 us whole, with experts of nine and fewer cut 673, with
+// all 665 (in quarters).
 template <int BM>
 __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m_e, int local, int NT, int half,
                                                     int cut_tiles) {
@@ -1364,7 +1365,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_1w_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int xcd = blockIdx.x % kXcds, workgroups = gridDim.x / kXcds;
     int32_t* counter = counters + xcd * kCounterInts;
-    const int NT = N / Cfg::BN_OUT, cut_tiles = K < kLongK ? 1 << 30 : kLongCutTiles;
+    const int NT = N / Cfg::BN_OUT, cut_tiles = Cfg::DUAL && K >= kLongK ? kLongCutTiles : 1 << 30;
     TileTable<Cfg::BM> table;                        // kept over the tiles: a lookup then reads no memory
     TileCoord tc;
     const uint32_t magic = division_magic(lane);
