@@ -73,23 +73,17 @@ long long most_row_tiles(int R, int E, int BM) { return R / BM + std::min(E, R);
 // 16 tokens at 4096 x 14336 279 together, 290 with eight starts over the same span.
 int spread_steps(int K) { return K < 6144 ? 0 : K % 16384 == 0 ? 2 : 1; }
 
-// The generic kernel with Cfg::NSTAGE stages. Tiles whose ring leaves no room for a second workgroup on the compute
-// unit run in persistent workgroups, unless the reduction is shorter than the ring.
+// The generic kernel with Cfg::NSTAGE stages.
 template <class Cfg>
 int launch_grouped(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, const moe_bf16* B1, moe_bf16* C,
                    const int32_t* offsets, const int32_t* row_index, int index_div,
                    int R, int E, int N, int K, hipStream_t s) {
     if (N % Cfg::BN_OUT != 0 || K % Cfg::BK != 0) return MOE_ERR_UNSUPPORTED_SHAPE;
-    static std::atomic<uint64_t> attr_set[2];
-    const long long tiles = most_row_tiles(R, E, Cfg::BM) * (N / Cfg::BN_OUT);
-    if constexpr (2 * Cfg::SMEM > 160 * 1024) {
-        const int cus = compute_units(env.device);
-        if (tiles > cus && K / Cfg::BK >= Cfg::NSTAGE - 1)
-            return launch_tiles(env, attr_set[1], gemm::grouped_gemm_kernel<Cfg, true>, Cfg::SMEM, Cfg::NTHREADS, cus, s,
-                                A, B0, B1, C, offsets, row_index, gemm::RowDiv(index_div), E, N, K, spread_steps(K));
-    }
-    return launch_tiles(env, attr_set[0], gemm::grouped_gemm_kernel<Cfg, false>, Cfg::SMEM, Cfg::NTHREADS, tiles, s, A,
-                        B0, B1, C, offsets, row_index, gemm::RowDiv(index_div), E, N, K, spread_steps(K));
+    static std::atomic<uint64_t> attr_set{0};
+    const long long max_mt = most_row_tiles(R, E, Cfg::BM);
+    return launch_tiles(env, attr_set, gemm::grouped_gemm_kernel<Cfg>, Cfg::SMEM, Cfg::NTHREADS,
+                        max_mt * (N / Cfg::BN_OUT), s, A, B0, B1, C, offsets, row_index,
+                        gemm::RowDiv(index_div), E, N, K, spread_steps(K));
 }
 
 // Slots of all tiles that R rows in E groups can make: the tiles, and where the last round is split two slots

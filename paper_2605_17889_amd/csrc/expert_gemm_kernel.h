@@ -647,7 +647,7 @@ __device__ __forceinline__ void spread_start(int spread) {
     for (int i = slot * spread; i > 0; --i) __builtin_amdgcn_s_sleep(12);
 }
 
-template <class Cfg, bool PERSISTENT>
+template <class Cfg>
 __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
     const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
@@ -658,26 +658,18 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
 
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wm = wave / WN, wn = wave % WN;
-    const int xcd = blockIdx.x % kXcds, step = gridDim.x / kXcds, NT = N / Cfg::BN_OUT;
-    int slot = blockIdx.x / kXcds;
-    TileTable<BM> table;                 // kept over the tiles: a lookup then reads no memory
-    const uint32_t magic = division_magic(lane);
-    TileCoord tc;
-    if constexpr (PERSISTENT) {
-        table.init(offsets, E, NT, 0, xcd, lane);
-        tc = uniform_tile(table.find(NT, 0, slot, magic));
-    } else {
-        tc = locate_tile<BM>(offsets, E, NT);
-    }
+    const TileCoord tc = locate_tile<BM>(offsets, E, N / Cfg::BN_OUT);
     if (tc.expert < 0) return;
     spread_start(spread);
 
-    // The loads run up to NSTAGE-1 k-steps ahead, into the workgroup's next tile near the end of one. First loads:
-    // weights of two stages go out under the latency of the row index.
-    const int KT = K / BK;               // a grid with fewer slots than tiles has KT >= NSTAGE - 1
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+
+    // ---- first loads: the weights of two stages go out under the latency of the row index (one token through 8 of
+    // 128 experts of 2048 x 768: gate/up 13.6 -> 13.3 us)
+    const int KT = K / BK;
     LoadPlan<Cfg> lp;
     lp.init_fixed(wave, lane, K);
     lp.init_b(tc, wave, B0, B1, N, K);
@@ -693,40 +685,31 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
     }
     // k-step 0 has landed when only the later A loads and stages are on their way
     if (KT >= NSTAGE - 1) wait_vmcnt<(AHEAD - 1) * LoadPlan<Cfg>::LA + (NSTAGE - 1 - AHEAD) * LPW>();
-    int loaded = min(NSTAGE - 1, KT);    // k-steps of lp's tile that are on their way
+
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     FragPlan<Cfg> fp;
     fp.init(lane, wm, wn);
+
+    // ---- main loop: ring of NSTAGE stages, NSTAGE-1 k-steps of loads in flight.
     int stage = 0;
-    while (true) {
-        TileCoord nxt{kNoTile, 0, 0, 0, 0};
-        if constexpr (PERSISTENT) nxt = uniform_tile(table.find(NT, 0, slot += step, magic));
-        const bool more = PERSISTENT && nxt.expert >= 0;
-        f32x4 acc[TM][TN];
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int kt = 0; kt < KT; ++kt) {
-            // The loads of k-step kt are the oldest in flight; up to NSTAGE-2 newer steps may stay
-            // pending. Near the end of the last tile fewer are in flight, so wait for everything.
-            if (more || kt + NSTAGE - 2 < KT) wait_vmcnt<(NSTAGE - 2) * LPW>(); else wait_vmcnt<0>();
-            __builtin_amdgcn_s_barrier();          // stage `stage` is complete for every wavefront
-                                                   // and stage (stage-1) is no longer being read
-            if (loaded == KT && more) {
-                lp.init(nxt, wave, lane, A, B0, B1, row_index, index_div, N, K);
-                loaded = 0;
-            }
-            if (loaded < KT) {
-                lp.issue_all((stage == 0 ? NSTAGE - 1 : stage - 1) * Cfg::STAGE_BYTES, static_cast<size_t>(loaded) * BK);
-                ++loaded;
-            }
-            mma_stage<Cfg>(smem + stage * Cfg::STAGE_BYTES, fp, acc);
-            stage = (stage + 1 == NSTAGE) ? 0 : stage + 1;
-        }
-        store_tile<Cfg>(acc, tc, fp, wm, wn, C, N);
-        if (!more) break;
-        tc = nxt;
+    for (int kt = 0; kt < KT; ++kt) {
+        // The loads of k-step kt are the oldest in flight; up to NSTAGE-2 newer steps may stay
+        // pending. Near the tail fewer are in flight, so wait for everything.
+        if (kt + NSTAGE - 2 < KT) wait_vmcnt<(NSTAGE - 2) * LPW>(); else wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();          // stage `stage` is complete for every wavefront
+                                               // and stage (stage-1) is no longer being read
+        const int nk = kt + NSTAGE - 1;
+        if (nk < KT)
+            lp.issue_all((stage == 0 ? NSTAGE - 1 : stage - 1) * Cfg::STAGE_BYTES,
+                         static_cast<size_t>(nk) * BK);
+        mma_stage<Cfg>(smem + stage * Cfg::STAGE_BYTES, fp, acc);
+        stage = (stage + 1 == NSTAGE) ? 0 : stage + 1;
     }
+    store_tile<Cfg>(acc, tc, fp, wm, wn, C, N);
 }
 
 // ---- kernel 2: operand rings of different depth, hand-placed software pipeline ---------------
