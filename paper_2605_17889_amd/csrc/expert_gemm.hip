@@ -65,13 +65,21 @@ int launch_tiles(const GemmEnv& env, std::atomic<uint64_t>& attr_set, Kernel ker
 // min(E, R) in place of E it takes 9.0 us (gate/up 18.5 -> 16.5 us).
 long long most_row_tiles(int R, int E, int BM) { return R / BM + std::min(E, R); }
 
+// Experts that R rows are expected to touch.
+double touched_experts(int R, int E) { return E * (1.0 - std::exp(-static_cast<double>(R) / E)); }
+
 // Step of the staggered first starts of the weight-bound tiles (gemm::spread_start), 0: together. Together -> steps of
 // 1 -> of 2, in us: pitch of 32 KB (down, 8 experts of 6144 x 16384) 16 tokens 257, 251, 246; 64 261, 256, 252; 256 291, 279,
 // 271; 420 314, 306, 297. Pitch of 12 KB (gate/up there) 489, 485, 480; 501, 501, 501; 549, 547, 543; 594, 594, 590; 200 tokens
 // 582, 536, 531. Pitch of 28 KB (down, 4096 x 14336) 64 tokens 154, 152, 150; 128 160, 160, 159; 200 188, 187, 186; but 256, a tile
 // per compute unit, 168, 169, 176, so steps of 2 only at the worst pitch. A reduction of 4096 ends too soon for it: gate/up,
-// 16 tokens at 4096 x 14336 279 together, 290 with eight starts over the same span.
-int spread_steps(int K) { return K < 6144 ? 0 : K % 16384 == 0 ? 2 : 1; }
+// 16 tokens at 4096 x 14336 279 together, 290 with eight starts over the same span; nor does a launch of few weights pay for
+// the last starts, 11 us late with steps of 1 (one token through 2 of 8 experts of 4096 x 14336, 235 MB of W2: layer call
+// 126.8 us together, 137.5; of 6144 x 16384, 403 MB, 202.7 and 211).
+int spread_steps(int R, int E, int N, int K, bool dual) {
+    const double bytes = touched_experts(R, E) * (dual ? 4.0 : 2.0) * N * K;
+    return K < 6144 || bytes < 0.8e9 ? 0 : K % 16384 == 0 ? 2 : 1;
+}
 
 // The generic kernel with Cfg::NSTAGE stages.
 template <class Cfg>
@@ -83,7 +91,7 @@ int launch_grouped(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, co
     const long long max_mt = most_row_tiles(R, E, Cfg::BM);
     return launch_tiles(env, attr_set, gemm::grouped_gemm_kernel<Cfg>, Cfg::SMEM, Cfg::NTHREADS,
                         max_mt * (N / Cfg::BN_OUT), s, A, B0, B1, C, offsets, row_index,
-                        gemm::RowDiv(index_div), E, N, K, spread_steps(K));
+                        gemm::RowDiv(index_div), E, N, K, spread_steps(R, E, N, K, Cfg::DUAL));
 }
 
 // Slots of all tiles that R rows in E groups can make: the tiles, and where the last round is split two slots
@@ -219,9 +227,6 @@ double row_tiles(int R, int E, int h) {
     const double avg = static_cast<double>(R) / (E > 0 ? E : 1);
     return E * mean_row_tiles(avg, std::sqrt(avg), h);
 }
-
-// Experts that R rows are expected to touch.
-double touched_experts(int R, int E) { return E * (1.0 - std::exp(-static_cast<double>(R) / E)); }
 
 // Workgroups of `tiles` tiles that find a free slot per round, over the slots of those rounds.
 double last_round_use(double tiles, double slots) { return tiles / (slots * std::ceil(tiles / slots)); }
