@@ -212,7 +212,9 @@ int moe_last_routing(moe_ctx* ctx, int32_t T, int32_t* topk_idx, float* topk_w, 
  * two GEMM stages for moe_expert_ffn). moe_profile_end() waits for those events and
  * writes, per stage, the total milliseconds (stage_ms[MOE_NUM_STAGES], host), the number of
  * kernel launches (stage_launches[MOE_NUM_STAGES], host) and the number of layer calls
- * covered (*calls), then disarms. Costs two event records per stage while armed. */
+ * covered (*calls), then disarms. Costs two event records per stage while armed.
+ * An armed call launches its stages one by one; otherwise a call of few tokens makes its permutation
+ * inside the gate/up launch (same results). */
 int moe_profile_begin(moe_ctx* ctx, int32_t max_calls);
 int moe_profile_end(moe_ctx* ctx, double* stage_ms, int64_t* stage_launches, int32_t* calls);
 /* The same, per call instead of summed: per_call_ms[c * MOE_NUM_STAGES + stage] (host, room for

@@ -73,6 +73,12 @@ struct GemmEnv {
 int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_index, int index_div,
                   const int32_t* offsets, int R, int R_hint, int d, int f, int E,
                   const moe_bf16* W1, const moe_bf16* W3, moe_bf16* H, hipStream_t s);
+// Gate/up of a few tokens without a permutation launch: it derives the groups from the selected experts, for more than
+// 16 experts from the logits, and writes the routing tables. gateup_routes: whether it takes such a call.
+bool gateup_routes(const GemmEnv& env, int T, int d, int f, int E, int k);
+int launch_gateup_routed(const GemmEnv& env, const moe_bf16* x, const float* logits, int32_t* topk_idx, float* topk_w,
+                         int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv_perm, int T, int d, int f,
+                         int E, int k, const moe_bf16* W1, const moe_bf16* W3, moe_bf16* H, hipStream_t s);
 int launch_down(const GemmEnv& env, const moe_bf16* H, const int32_t* offsets, int R, int R_hint,
                 int d, int f, int E, const moe_bf16* W2, void* y_perm, bool y_f32, hipStream_t s);
 int launch_combine(const void* y_perm, bool y_f32, const int32_t* inv_perm, const float* topk_w, int T,

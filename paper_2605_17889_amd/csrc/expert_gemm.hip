@@ -228,6 +228,22 @@ double row_tiles(int R, int E, int h) {
     return E * mean_row_tiles(avg, std::sqrt(avg), h);
 }
 
+NTiles gateup_tiles(int E, int d, int f) {
+    return NTiles{f / 128, f / 128, f / 64, 0.82, 0.41, 0.58, 4e-6 * E * d * f, d / 64};
+}
+
+// Tiles of half the width while up to two and a half of them go to a compute unit, gate/up against
+// the 128-column ones: one token through 8 of 128 experts of 2048 x 768 (0.75 per compute unit) 14.2
+// and 18.2 us, 2 (1.4) 21.6 and 22.3, 2 through 6 of 64 of 2048 x 1408 (2.1) 23.9 and 25.0, 64 through
+// 2 of 8 of 512 x 1024 (1.0) 7.7 and 8.7. Past the line the sides are mixed: 4 tokens, 8 of 128 (2.7)
+// 37.0 and 39.5, 5 (3.3) 44.0 and 42.8; 4 tokens, 6 of 64 (3.8) 43.9 and 42.2, 6 (5.4) 54.6 and 62.4
+bool narrow_gateup_tiles(int R, int E, int f, int cus) { return 2.0 * touched_experts(R, E) * (f / 64) <= 2.5 * cus; }
+
+// The deep ring where no compute unit gets a second tile, whichever experts are touched: one
+// token through 8 of 128 of 2048 x 768 (192 tiles) 14.3 against 14.9 us, through 4 of 32 of 2048 x 2048
+// (256) 16.7 against 17.5; through 6 of 64 of 2048 x 1408 (264) 20.2 against 18.2
+bool one_tile_per_cu(int R, int E, int f, int cus) { return std::min(E, R) * (f / 32) <= cus; }
+
 // Workgroups of `tiles` tiles that find a free slot per round, over the slots of those rounds.
 double last_round_use(double tiles, double slots) { return tiles / (slots * std::ceil(tiles / slots)); }
 
@@ -296,7 +312,67 @@ using DownTinyS    = Config<32, 64, 64, 2, 2, 4, false, true>;
 using DownFew      = Config<16, 32, 64, 1, 2, 6, false>;
 using DownFewS     = Config<16, 32, 64, 1, 2, 6, false, true>;
 
+// Tile of a gate/up launch that derives the groups from the selected experts (grouped_gemm_routed_kernel): those of
+// launch_gateup's choice that leave every workgroup one tile or two. Beyond that each tile would pay for the
+// derivation again.
+enum class RoutedTile { none, few_deep, few, small_stream, small };
+RoutedTile routed_tile(const GemmEnv& env, int R, int E, int d, int f) {
+    if (R > gemm::kRoutedIds || env.forced_config >= 0 || env.stream_mode >= 0) return RoutedTile::none;
+    const int cus = compute_units(env.device);
+    switch (pick_config(env, R, E, gateup_tiles(E, d, f))) {
+        case 3:
+            if (!single_m_tile(env, R, E, 32) || !narrow_gateup_tiles(R, E, f, cus)) return RoutedTile::none;
+            return one_tile_per_cu(R, E, f, cus) ? RoutedTile::few_deep : RoutedTile::few;
+        case 2:
+            if (most_row_tiles(R, E, 64) * (f / 64) > 2 * cus) return RoutedTile::none;
+            return single_m_tile(env, R, E, 64) ? RoutedTile::small_stream : RoutedTile::small;
+        default: return RoutedTile::none;
+    }
+}
+
+template <class Cfg, int EW>
+int launch_routed(const GemmEnv& env, const moe_bf16* x, const gemm::Routing& rt, int d, int f, int E,
+                  const moe_bf16* W1, const moe_bf16* W3, moe_bf16* H, hipStream_t s) {
+    static std::atomic<uint64_t> attr_set{0};
+    const long long tiles = most_row_tiles(rt.T * rt.k, E, Cfg::BM) * (f / Cfg::BN_OUT);
+    return launch_tiles(env, attr_set, gemm::grouped_gemm_routed_kernel<Cfg, EW>, Cfg::SMEM, Cfg::NTHREADS,
+                        tiles + kXcds, s, x, W1, W3, H, rt, gemm::RowDiv(rt.k), E, f, d);
+}
+
 }  // namespace
+
+bool gateup_routes(const GemmEnv& env, int T, int d, int f, int E, int k) {
+    const RoutedTile t = routed_tile(env, T * k, E, d, f);
+    if (t == RoutedTile::none) return false;
+    // Ids at hand (device time of a layer call, separate launch -> without): 8 experts of 512 x 1024, 1 token 19.3 -> 17.4 us,
+    // 16 20.1 -> 18.9, 256 24.8 -> 23.0, 500 27.9 -> 26.5. With the selection on the way, about one tile per compute unit: one
+    // token through 8 of 128 experts of 2048 x 768 33.8 -> 32.2, 6 of 64 of 2048 x 1408 (1.03) 37.4 -> 36.7; two through 8 of 128
+    // (1.5) 41.8 -> 43.1. Up to 16 tokens, which a workgroup selects in one pass.
+    return E <= 16 || (T <= 16 && (t == RoutedTile::few || t == RoutedTile::few_deep) &&
+                       4 * most_row_tiles(T * k, E, 32) * (f / 32) <= 5 * compute_units(env.device));
+}
+
+int launch_gateup_routed(const GemmEnv& env, const moe_bf16* x, const float* logits, int32_t* topk_idx, float* topk_w,
+                         int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv_perm, int T, int d, int f,
+                         int E, int k, const moe_bf16* W1, const moe_bf16* W3, moe_bf16* H, hipStream_t s) {
+    const gemm::Routing rt{logits, topk_idx, topk_w, counts, offsets, perm, inv_perm, T, k};
+    const RoutedTile tile = routed_tile(env, T * k, E, d, f);
+    auto with = [&](auto cfg) {
+        using Cfg = decltype(cfg);
+        if (E <= 16) return launch_routed<Cfg, 0>(env, x, rt, d, f, E, W1, W3, H, s);
+        if (E <= 32) return launch_routed<Cfg, 2>(env, x, rt, d, f, E, W1, W3, H, s);
+        if (E <= 64) return launch_routed<Cfg, 4>(env, x, rt, d, f, E, W1, W3, H, s);
+        if (E <= 128) return launch_routed<Cfg, 8>(env, x, rt, d, f, E, W1, W3, H, s);
+        return launch_routed<Cfg, 16>(env, x, rt, d, f, E, W1, W3, H, s);
+    };
+    switch (tile) {
+        case RoutedTile::few_deep: return with(GateUpFewDeepS{});
+        case RoutedTile::few: return with(GateUpFewS{});
+        case RoutedTile::small_stream: return launch_routed<GateUpSmallS, 0>(env, x, rt, d, f, E, W1, W3, H, s);
+        case RoutedTile::small: return launch_routed<GateUpSmall, 0>(env, x, rt, d, f, E, W1, W3, H, s);
+        default: return MOE_ERR_UNSUPPORTED_SHAPE;
+    }
+}
 
 // `a` is the grouped activation matrix [R, d] when row_index is NULL; otherwise it is the
 // token matrix [T, d] and grouped row p reads token row_index[p] / index_div (the caller makes
@@ -308,8 +384,7 @@ int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_inde
                   const moe_bf16* W1, const moe_bf16* W3, moe_bf16* H, hipStream_t s) {
     if (R == 0) return MOE_OK;
     const moe_bf16* x_perm = a;
-    int config = pick_config(env, R_hint, E, NTiles{f / 128, f / 128, f / 64, 0.82, 0.41, 0.58,
-                                                    4e-6 * E * d * f, d / 64});
+    int config = pick_config(env, R_hint, E, gateup_tiles(E, d, f));
     if (config == 0 && d / 64 < 3) config = 1;     // the pipelined kernel needs three k-steps
     // Row counts that lead to 96- or 128-row tiles let every group fit one, so their weights are streamed; the cached forms
     // (GateUpMid96, DownMid96 and DownMid96Wide) run under the tuning knob, those of 128 rows also where groups of about
@@ -331,16 +406,8 @@ int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_inde
             if (single_m_tile(env, R_hint, E, 32)) {
                 const double nt = touched_experts(R_hint, E) * (f / 64);
                 const int cus = compute_units(env.device);
-                // Tiles of half the width while up to two and a half of them go to a compute unit, gate/up against
-                // the 128-column ones: one token through 8 of 128 experts of 2048 x 768 (0.75 per compute unit) 14.2
-                // and 18.2 us, 2 (1.4) 21.6 and 22.3, 2 through 6 of 64 of 2048 x 1408 (2.1) 23.9 and 25.0, 64 through
-                // 2 of 8 of 512 x 1024 (1.0) 7.7 and 8.7. Past the line the sides are mixed: 4 tokens, 8 of 128 (2.7)
-                // 37.0 and 39.5, 5 (3.3) 44.0 and 42.8; 4 tokens, 6 of 64 (3.8) 43.9 and 42.2, 6 (5.4) 54.6 and 62.4
-                if (2.0 * nt <= 2.5 * cus) {
-                    // The deep ring where no compute unit gets a second tile, whichever experts are touched: one
-                    // token through 8 of 128 of 2048 x 768 (192 tiles) 14.3 against 14.9 us, through 4 of 32 of 2048 x 2048
-                    // (256) 16.7 against 17.5; through 6 of 64 of 2048 x 1408 (264) 20.2 against 18.2
-                    if (std::min(E, R_hint) * (f / 32) <= cus)
+                if (narrow_gateup_tiles(R_hint, E, f, cus)) {
+                    if (one_tile_per_cu(R_hint, E, f, cus))
                         return launch_grouped<GateUpFewDeepS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
                     return launch_grouped<GateUpFewS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
                 }

@@ -26,6 +26,8 @@
 #include <type_traits>
 
 #include "common.h"
+#include "permute_block.h"
+#include "route_select.h"
 
 namespace moe {
 namespace gemm {
@@ -244,6 +246,25 @@ struct TileTable {
         static_assert(EPL == 4, "in-lane search");
 #pragma unroll
         for (int w = 0; w <= EPL; ++w) off[w] = offsets[min(lane * EPL + w, E)];
+        init_tiles(NT, split_cus, xcd);
+    }
+    // the same from the number of rows of each expert
+    __device__ __forceinline__ void init_from_counts(const int32_t* cnt, int E, int NT, int xcd, int lane) {
+        off[0] = 0;
+#pragma unroll
+        for (int w = 0; w < EPL; ++w) off[w + 1] = off[w] + (lane * EPL + w < E ? cnt[lane * EPL + w] : 0);
+        const int before = lane_prefix_sum(off[EPL]) - off[EPL];
+#pragma unroll
+        for (int w = 0; w <= EPL; ++w) off[w] += before;
+        init_tiles(NT, 0, xcd);
+    }
+    __device__ __forceinline__ int first_row(int expert) const {
+        int v = off[0];
+#pragma unroll
+        for (int w = 1; w < EPL; ++w) v = (expert & (EPL - 1)) == w ? off[w] : v;
+        return __builtin_amdgcn_readlane(v, expert / EPL);
+    }
+    __device__ __forceinline__ void init_tiles(int NT, int split_cus, int xcd) {
         start[0] = 0;
 #pragma unroll
         for (int w = 0; w < EPL; ++w) start[w + 1] = start[w] + ((off[w + 1] - off[w] + BM - 1) / BM) * NT;
@@ -582,6 +603,18 @@ struct LoadPlan {
             a_on[i] = q * Cfg::RPI < tc.rows;
         }
     }
+    // A rows one by one from row_of(row of the tile)
+    template <class RowOf>
+    __device__ __forceinline__ void init_a_from(const TileCoord& tc, int wave, int lane, const uint16_t* A, int K,
+                                                RowOf&& row_of) {
+        const int lrow = lane / Cfg::CPR, lpos = lane % Cfg::CPR;
+        a_base = A;
+#pragma unroll
+        for (int i = 0; i < LA; ++i) {
+            const int r = (wave * LA + i) * Cfg::RPI + lrow;
+            a_voff[i] = (static_cast<uint32_t>(row_of(min(r, tc.rows - 1))) * K + ((lpos ^ swz<Cfg::BK>(r)) * 8)) * 2u;
+        }
+    }
     // what is the same for every tile
     __device__ __forceinline__ void init_fixed(int wave, int lane, int K) {
         static_assert(!Cfg::DUAL || LB * Cfg::RPI % Cfg::DB == 0 || Cfg::DB % (LB * Cfg::RPI) == 0, "whole blocks");
@@ -647,37 +680,24 @@ __device__ __forceinline__ void spread_start(int spread) {
     for (int i = slot * spread; i > 0; --i) __builtin_amdgcn_s_sleep(12);
 }
 
-template <class Cfg>
-__global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
-    const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
-    const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
-    const int32_t* __restrict__ offsets, const int32_t* __restrict__ row_index, RowDiv index_div,
-    int E, int N, int K, int spread) {
-    constexpr int BM = Cfg::BM, BK = Cfg::BK, WN = Cfg::WN;
-    constexpr int TM = Cfg::TM, TN = Cfg::TN, LPW = Cfg::LPW, NSTAGE = Cfg::NSTAGE;
-
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-
-    const TileCoord tc = locate_tile<BM>(offsets, E, N / Cfg::BN_OUT);
-    if (tc.expert < 0) return;
-    spread_start(spread);
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN;
-
+// One tile: `init_a` sets the A addresses of the load plan, after the first weights have gone out.
+template <class Cfg, class InitA>
+__device__ __forceinline__ void ring_of_stages(const TileCoord& tc, LoadPlan<Cfg>& lp, InitA&& init_a, unsigned char* smem,
+                                               int wave, int lane, const uint16_t* __restrict__ B0,
+                                               const uint16_t* __restrict__ B1, uint16_t* __restrict__ C, int N,
+                                               int K) {
+    constexpr int BK = Cfg::BK, TM = Cfg::TM, TN = Cfg::TN, LPW = Cfg::LPW, NSTAGE = Cfg::NSTAGE;
+    const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
     // ---- first loads: the weights of two stages go out under the latency of the row index (one token through 8 of
     // 128 experts of 2048 x 768: gate/up 13.6 -> 13.3 us)
     const int KT = K / BK;
-    LoadPlan<Cfg> lp;
     lp.init_fixed(wave, lane, K);
     lp.init_b(tc, wave, B0, B1, N, K);
     constexpr int AHEAD = NSTAGE > 2 ? 2 : 1;
 #pragma unroll
     for (int s = 0; s < AHEAD; ++s)
         if (s < KT) lp.issue_b_all(s * Cfg::STAGE_BYTES, static_cast<size_t>(s) * BK);
-    lp.init_a(tc, wave, lane, A, row_index, index_div, K);
+    init_a();
 #pragma unroll
     for (int s = 0; s < NSTAGE - 1; ++s) {
         if (s < KT) lp.issue_a_all(s * Cfg::STAGE_BYTES, static_cast<size_t>(s) * BK);
@@ -710,6 +730,112 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
         stage = (stage + 1 == NSTAGE) ? 0 : stage + 1;
     }
     store_tile<Cfg>(acc, tc, fp, wm, wn, C, N);
+}
+
+template <class Cfg>
+__global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_kernel(
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
+    const uint16_t* __restrict__ B1, uint16_t* __restrict__ C,
+    const int32_t* __restrict__ offsets, const int32_t* __restrict__ row_index, RowDiv index_div,
+    int E, int N, int K, int spread) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const TileCoord tc = locate_tile<Cfg::BM>(offsets, E, N / Cfg::BN_OUT);
+    if (tc.expert < 0) return;
+    spread_start(spread);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    LoadPlan<Cfg> lp;
+    ring_of_stages<Cfg>(tc, lp, [&] { lp.init_a(tc, wave, lane, A, row_index, index_div, K); }, smem, wave, lane, B0, B1,
+                        C, N, K);
+}
+
+// ---- kernel 1, few tokens: tiles straight from the selected experts ---------------------------
+// Gate/up of a call whose permutation no launch has made: every workgroup derives the groups from the R = T * k
+// flat ids by itself (a histogram in LDS, its prefix sums, then the ids of its own tile by ballots), and the
+// first workgroup of the grid, which has no tile, writes the tables for the kernels behind this one. EW > 0: the
+// selection too, from the logits of at most NTHREADS / 16 tokens and at most 16 * EW experts. What that costs a
+// workgroup is less than a launch with the latencies around it; layer calls with the separate launch -> without, see
+// gateup_routes in expert_gemm.hip.
+constexpr int kRoutedIds = 1024;         // ids at most: sixteen per lane
+template <int WAVES> constexpr int kMaxKeepRouted = kRoutedIds / (WAVES * kWave);
+struct Routing {
+    const float* logits;                 // [T, E], with EW > 0
+    int32_t* topk_idx;                   // [T, k]: read, written with EW > 0
+    float* topk_w;                       // [T, k], written with EW > 0
+    int32_t *counts, *offsets, *perm, *inv_perm;      // written
+    int T, k;
+};
+
+template <class Cfg, int EW>
+__global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_routed_kernel(
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0, const uint16_t* __restrict__ B1,
+    uint16_t* __restrict__ C, Routing rt, RowDiv index_div, int E, int N, int K) {
+    constexpr int BM = Cfg::BM, ROUNDS = kRoutedIds / kWave;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    // scratch in the stage that no load reaches before the first barrier of the k-loop
+    static_assert((kMaxExperts + kRoutedIds + BM) * 4 <= Cfg::STAGE_BYTES, "fits a stage");
+    static_assert(sizeof(SmallTables<Cfg::NW>) <= (Cfg::NSTAGE - 1) * Cfg::STAGE_BYTES, "fits in front of it");
+    static_assert(Cfg::NW * kWave * kMaxKeepRouted<Cfg::NW> >= kRoutedIds, "ids of the tables' workgroup");
+    int32_t* cnt = reinterpret_cast<int32_t*>(smem + (Cfg::NSTAGE - 1) * Cfg::STAGE_BYTES);
+    int32_t *ids = cnt + kMaxExperts, *list = ids + kRoutedIds;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int R = rt.T * rt.k, NT = N / Cfg::BN_OUT;
+    const bool tables = blockIdx.x == 0;             // tiles start at slot 1 of every XCD
+    if (tid < E) cnt[tid] = 0;
+    int my[ROUNDS];                      // every wavefront holds all ids, 64 a round
+    if constexpr (EW > 0) {
+        const int t = tid / 16;
+        if (__builtin_amdgcn_readfirstlane(t) < rt.T)
+            select_by_16_lanes<EW>(rt.logits, t, t < rt.T, tid & 15, E, rt.k, [&](int s, int e, float w) {
+                ids[t * rt.k + s] = e;
+                if (tables) {
+                    rt.topk_idx[t * rt.k + s] = e;
+                    rt.topk_w[t * rt.k + s] = w;
+                }
+            });
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int i = r * kWave + lane;
+        my[r] = i < R ? (EW > 0 ? ids : rt.topk_idx)[i] : -1;
+    }
+    if constexpr (EW == 0) __syncthreads();          // the counters are clear
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r)
+        if (r % Cfg::NW == wave && my[r] >= 0) atomicAdd(&cnt[my[r]], 1);     // counts only: any order
+    __syncthreads();
+    if (blockIdx.x < kXcds) {
+        if (tables)
+            permute_block<Cfg::NW, kMaxKeepRouted<Cfg::NW>, false>(
+                *reinterpret_cast<SmallTables<Cfg::NW>*>(smem), EW > 0 ? ids : rt.topk_idx, 0, R, E, rt.counts,
+                rt.offsets, rt.perm, rt.inv_perm);
+        return;
+    }
+    TileTable<BM> table;
+    table.init_from_counts(cnt, E, NT, blockIdx.x % kXcds, lane);
+    const TileCoord tc = uniform_tile(table.find(NT, 0, blockIdx.x / kXcds - 1, division_magic(lane)));
+    if (tc.expert < 0) return;
+    LoadPlan<Cfg> lp;
+    ring_of_stages<Cfg>(tc, lp, [&] {
+        // each wavefront lists the tile's ids for itself (all write the same values)
+        const int first = tc.row0 - table.first_row(tc.expert);
+        int found = 0;
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            if (r * kWave >= R) break;
+            const uint64_t m = __ballot(my[r] == tc.expert);
+            const int at = found + __popcll(m & ((1ull << lane) - 1ull)) - first;
+            if (my[r] == tc.expert && at >= 0 && at < tc.rows) list[at] = r * kWave + lane;
+            found += __popcll(m);
+        }
+        __builtin_amdgcn_wave_barrier();
+        lp.init_a_from(tc, wave, lane, A, K, [&](int row) {
+            const int id = list[row];
+            return index_div.mul == 0 ? id : static_cast<int>(__umulhi(static_cast<uint32_t>(id), index_div.mul) >> index_div.shift);
+        });
+    }, smem, wave, lane, B0, B1, C, N, K);
 }
 
 // ---- kernel 2: operand rings of different depth, hand-placed software pipeline ---------------

@@ -144,24 +144,34 @@ int forward_chunk(moe_ctx* c, const moe_bf16* x, const float* w_router, const fl
     const moe_shape& sh = c->shape;
     const int d = sh.d_model, f = sh.d_ff, E = sh.E, k = sh.k, R = T * k;
     int rc;
-    rc = route_and_permute(c, x, w_router, bias, T, s);
-    if (rc != MOE_OK) return rc;
     // The row gather x -> x_perm is fused into the gate/up kernel's operand loads (it reads
     // token row perm[p] / k directly) whenever a token row's byte offset fits 32 bits.
     const bool fuse_gather =
         !c->gemm.materialise_gather && static_cast<unsigned long long>(T) * d * 2ull < (1ull << 32);
-    if (!fuse_gather) {
-        rc = run_stage(c, MOE_STAGE_GATHER, 1, s, [&] {
-            return launch_gather(x, c->perm, c->offsets, R, d, k, E, c->x_perm, s);
+    if (fuse_gather && !c->prof_armed && gateup_routes(c->gemm, T, d, f, E, k)) {
+        // few tokens: no permutation launch. Stage timing keeps the stages apart.
+        rc = E > 16 ? launch_route_logits(x, w_router, bias, T, d, E, c->logits, s)
+                    : launch_route(x, w_router, bias, T, d, E, k, c->topk_idx, c->topk_w, nullptr, c->logits, s);
+        if (rc != MOE_OK) return rc;
+        rc = launch_gateup_routed(c->gemm, x, c->logits, c->topk_idx, c->topk_w, c->counts, c->offsets, c->perm,
+                                  c->inv_perm, T, d, f, E, k, W1, W3, c->H, s);
+        if (rc != MOE_OK) return rc;
+    } else {
+        rc = route_and_permute(c, x, w_router, bias, T, s);
+        if (rc != MOE_OK) return rc;
+        if (!fuse_gather) {
+            rc = run_stage(c, MOE_STAGE_GATHER, 1, s, [&] {
+                return launch_gather(x, c->perm, c->offsets, R, d, k, E, c->x_perm, s);
+            });
+            if (rc != MOE_OK) return rc;
+        }
+        rc = run_stage(c, MOE_STAGE_GATEUP, 1, s, [&] {
+            return fuse_gather
+                       ? launch_gateup(c->gemm, x, c->perm, k, c->offsets, R, R, d, f, E, W1, W3, c->H, s)
+                       : launch_gateup(c->gemm, c->x_perm, nullptr, 1, c->offsets, R, R, d, f, E, W1, W3, c->H, s);
         });
         if (rc != MOE_OK) return rc;
     }
-    rc = run_stage(c, MOE_STAGE_GATEUP, 1, s, [&] {
-        return fuse_gather
-                   ? launch_gateup(c->gemm, x, c->perm, k, c->offsets, R, R, d, f, E, W1, W3, c->H, s)
-                   : launch_gateup(c->gemm, c->x_perm, nullptr, 1, c->offsets, R, R, d, f, E, W1, W3, c->H, s);
-    });
-    if (rc != MOE_OK) return rc;
     rc = run_stage(c, MOE_STAGE_DOWN, 1, s, [&] {
         return launch_down(c->gemm, c->H, c->offsets, R, R, d, f, E, W2, expert_out(c), c->y_perm_f32 != nullptr, s);
     });

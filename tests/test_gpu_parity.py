@@ -1326,6 +1326,47 @@ def test_profile_stage_times_of_layer_and_expert_ffn():
     ctx.close()
 
 
+@pytest.mark.parametrize("T,E,k,d,f", [
+    (1, 8, 2, 512, 1024), (37, 8, 2, 512, 1024), (64, 8, 2, 512, 1024),     # 32-row tiles, groups of up to 20 and more rows
+    (256, 8, 2, 512, 1024), (300, 8, 2, 512, 512), (512, 8, 2, 512, 512),   # 64-row tiles, 1024 ids
+    (5, 1, 1, 512, 256), (2, 16, 16, 512, 256), (40, 13, 4, 512, 256),      # one expert, all experts, odd counts
+    (1, 128, 8, 2048, 768), (16, 128, 8, 512, 128), (16, 64, 6, 512, 128),  # selected on the way, up to 16 tokens
+    (3, 17, 3, 512, 384), (7, 32, 5, 512, 128), (16, 256, 64, 512, 128), (1, 256, 64, 512, 128),
+    (17, 128, 8, 512, 128),                                                 # one token too many
+])
+@pytest.mark.parametrize("one_expert", [False, True])
+def test_few_tokens_without_a_permutation_launch(T, E, k, d, f, one_expert):
+    """Gate/up that derives the groups by itself against the separate launches of a call with stage timing
+    armed: outputs and routing tables. With one_expert a bias sends every token to the same k experts."""
+    say(f"few tokens T={T} E={E} k={k} d={d} f={f} one_expert={one_expert}")
+    g = torch.Generator(device="cuda").manual_seed(T * E + k)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    x, wr = rnd(T, d).bfloat16(), rnd(d, E) * 0.02
+    bias = torch.arange(E, device="cuda").float() * 100 if one_expert else None
+    W1, W3, W2 = ((rnd(*s) * 0.05).bfloat16() for s in ((E, f, d), (E, f, d), (E, d, f)))
+    ctx = B.MoeContext(T, d, f, E, k)
+    got = []
+    for armed in (True, False, False):
+        y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        i32 = lambda n: torch.full((n,), -7, dtype=torch.int32, device="cuda")
+        tables = {"topk_idx": i32(T * k), "topk_w": torch.zeros(T * k, device="cuda"), "counts": i32(E),
+                  "offsets": i32(E + 1), "perm": i32(T * k), "inv_perm": i32(T * k)}
+        if armed:
+            B.moe_profile_begin(ctx, 1)
+        B.moe_layer_forward(ctx, x, wr, bias, W1, W3, W2, T, y)
+        if armed:
+            B.moe_profile_end(ctx)
+        B.moe_last_routing(ctx, T, **tables)
+        torch.cuda.synchronize()
+        got.append({"y": y.view(torch.int16), **tables})
+        x2 = rnd(T, d).bfloat16()                       # other groups in between
+        B.moe_layer_forward(ctx, x2, wr, None, W1, W3, W2, T, torch.empty_like(y))
+    for other in got[1:]:
+        for name in got[0]:
+            assert torch.equal(got[0][name], other[name]), name
+    ctx.close()
+
+
 @pytest.mark.parametrize("T,E,k,route,permute", [
     (300, 8, 2, 1, 1),      # up to 16 experts the router kernel selects; up to 4096 ids one permutation launch
     (2100, 8, 2, 1, 2),     # ... then two
