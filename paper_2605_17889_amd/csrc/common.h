@@ -60,7 +60,12 @@ int launch_gather(const moe_bf16* x, const int32_t* perm, const int32_t* offsets
                   int k, int E, moe_bf16* x_perm, hipStream_t s);
 // Where and how a context launches its expert GEMMs: its device and the tuning knobs of
 // moe_set_gemm_config (all settings give identical bits).
-constexpr size_t kTileCounterBytes = kXcds * 128;   // from which persistent workgroups draw their tiles
+// Counters from which persistent workgroups draw their tiles, zero between launches. A context takes a set of its
+// device's 64 and gives it back; set -1: there is none left (the caller then zeroes memory of its own). The
+// calling thread's current device must be `device`.
+constexpr size_t kTileCounterBytes = kXcds * 128;
+int32_t* take_tile_counters(int device, int* set);
+void give_tile_counters(int device, int set);
 struct GemmEnv {
     int device = 0;
     int forced_config = -1;           // -1: automatic; 0..4: force a tile configuration
@@ -68,7 +73,7 @@ struct GemmEnv {
     bool materialise_gather = false;  // layer calls write x_perm instead of fusing the gather
     bool split_last_round = true;     // large tiles: halve the tiles of a last round under half full
     int large_tile_waves = 0;         // 0: automatic; 4 / 8: wavefronts of the 256 x 256 tile
-    int32_t* tile_counters = nullptr; // kTileCounterBytes of the context's workspace, zero between launches
+    int32_t* tile_counters = nullptr; // kTileCounterBytes, zero between launches
 };
 int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_index, int index_div,
                   const int32_t* offsets, int R, int R_hint, int d, int f, int E,

@@ -19,6 +19,38 @@
 
 namespace moe {
 
+constexpr int kCounterSets = 64;
+static __device__ __align__(256) int32_t tile_counter_sets[kCounterSets][kTileCounterBytes / sizeof(int32_t)];
+static std::atomic<uint64_t> counter_sets_taken[64];         // one bit per set and device
+static std::atomic<int32_t*> counter_sets_at[64];
+
+int32_t* take_tile_counters(int device, int* set) {
+    *set = -1;
+    int32_t* base = counter_sets_at[device].load(std::memory_order_acquire);
+    if (base == nullptr) {
+        void* p = nullptr;
+        if (hipGetSymbolAddress(&p, HIP_SYMBOL(tile_counter_sets)) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        base = static_cast<int32_t*>(p);
+        counter_sets_at[device].store(base, std::memory_order_release);
+    }
+    uint64_t taken = counter_sets_taken[device].load(std::memory_order_relaxed);
+    while (~taken != 0) {
+        const int n = __builtin_ctzll(~taken);
+        if (counter_sets_taken[device].compare_exchange_weak(taken, taken | (1ull << n), std::memory_order_acq_rel)) {
+            *set = n;
+            return base + n * (kTileCounterBytes / sizeof(int32_t));
+        }
+    }
+    return nullptr;
+}
+
+void give_tile_counters(int device, int set) {
+    if (set >= 0) counter_sets_taken[device].fetch_and(~(1ull << set), std::memory_order_acq_rel);
+}
+
 int compute_units(int device) {
     static std::atomic<int> cached[64];
     int n = cached[device].load(std::memory_order_relaxed);

@@ -9,6 +9,7 @@ struct moe_ctx {
     moe_shape shape;
     int device;
     moe::GemmEnv gemm;   // device + tuning knobs of moe_set_gemm_config
+    int counter_set;     // of gemm.tile_counters (take_tile_counters)
     // workspace (device)
     unsigned char* base;
     size_t bytes;
@@ -251,19 +252,24 @@ int moe_create(moe_ctx** out, const moe_shape* shape, int device_id) {
     c->shape = *shape;
     c->device = device_id;
     c->gemm.device = device_id;
+    c->counter_set = -1;
     const Layout L = layout_for(shape);
     c->bytes = L.total;
     void* p = nullptr;
     // allocate on the context's device, then give the caller its current device back
     hipError_t err = hipSetDevice(device_id);
     if (err == hipSuccess) err = hipMalloc(&p, L.total);
-    const unsigned char zeros[kTileCounterBytes] = {};
-    if (err == hipSuccess)
-        err = hipMemcpy(static_cast<unsigned char*>(p) + L.counters, zeros, sizeof(zeros), hipMemcpyHostToDevice);
+    int32_t* counters = err == hipSuccess ? take_tile_counters(device_id, &c->counter_set) : nullptr;
+    if (err == hipSuccess && counters == nullptr) {          // a copy of the host's: it has ended when it returns
+        const unsigned char zeros[kTileCounterBytes] = {};
+        counters = reinterpret_cast<int32_t*>(static_cast<unsigned char*>(p) + L.counters);
+        err = hipMemcpy(counters, zeros, sizeof(zeros), hipMemcpyHostToDevice);
+    }
     const hipError_t back = hipSetDevice(caller_device);
     if (err != hipSuccess || back != hipSuccess) {
         (void)hipGetLastError();
         if (p) (void)hipFree(p);
+        give_tile_counters(device_id, c->counter_set);
         delete c;
         return err != hipSuccess && back == hipSuccess ? MOE_ERR_WORKSPACE : MOE_ERR_HIP;
     }
@@ -280,7 +286,7 @@ int moe_create(moe_ctx** out, const moe_shape* shape, int device_id) {
     c->H = reinterpret_cast<moe_bf16*>(c->base + L.H);
     c->y_perm = reinterpret_cast<moe_bf16*>(c->base + L.y_perm);
     c->y_perm_f32 = nullptr;
-    c->gemm.tile_counters = reinterpret_cast<int32_t*>(c->base + L.counters);
+    c->gemm.tile_counters = counters;
     c->prof_armed = false;
     c->prof_max_calls = c->prof_calls = 0;
     for (auto& v : c->prof_launches) v = 0;
@@ -307,6 +313,7 @@ int moe_destroy(moe_ctx* c) {
     if (c->slot[0] && hipFree(c->slot[0]) != hipSuccess) rc = MOE_ERR_HIP;
     if (c->y_perm_f32 && hipFree(c->y_perm_f32) != hipSuccess) rc = MOE_ERR_HIP;
     if (c->base && hipFree(c->base) != hipSuccess) rc = MOE_ERR_HIP;
+    give_tile_counters(c->device, c->counter_set);
     delete c;
     return rc;
 }

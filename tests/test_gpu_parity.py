@@ -659,6 +659,29 @@ def test_persistent_workgroups_run_tiles_of_all_heights_in_turn(d, f, split):
     ctx.close()
 
 
+def test_persistent_workgroups_of_many_contexts():
+    """More contexts at once than there are sets of counters; sets that were given back are taken again."""
+    say("persistent workgroups, 70 contexts")
+    d, f, E, R = 512, 3840, 8, 2048
+    g = torch.Generator(device="cuda").manual_seed(9)
+    rnd = lambda *shape: (torch.randn(*shape, generator=g, device="cuda") * 0.05).bfloat16()
+    W1, W3, W2, x = rnd(E, f, d), rnd(E, f, d), rnd(E, d, f), rnd(R, d)
+    offsets = torch.arange(E + 1, device="cuda", dtype=torch.int32) * (R // E)
+    outs = []
+    for _ in range(2):
+        ctxs = [B.MoeContext(R, d, f, E, 1) for _ in range(70)]
+        for c in (0, 1, 63, 64, 69):
+            B.moe_set_gemm_config(ctxs[c], 0)
+            y = torch.full((R, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+            for _ in range(2):
+                B.moe_expert_ffn(ctxs[c], x, offsets, R, W1, W3, W2, y)
+            outs.append(bits(y))
+        for c in ctxs:
+            c.close()
+    assert not np.isnan(bf16_to_f64(outs[0])).any()
+    assert all(np.array_equal(outs[0], o) for o in outs[1:])
+
+
 @pytest.mark.parametrize("first,count", [(0, 3), (1, 1), (2, 5), (6, 1)])
 def test_expert_ffn_of_some_experts_gives_the_bits_of_all(first, count):
     """A program that holds some of a layer's experts (expert parallelism, replicas) calls the stage with
