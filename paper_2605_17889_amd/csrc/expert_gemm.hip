@@ -379,8 +379,8 @@ bool gateup_routes(const GemmEnv& env, int T, int d, int f, int E, int k) {
     // Ids at hand (device time of a layer call, separate launch -> without): 8 experts of 512 x 1024, 1 token 19.3 -> 17.4 us,
     // 16 20.1 -> 18.9, 256 24.8 -> 23.0, 500 27.9 -> 26.5. With the selection on the way, about one tile per compute unit: one
     // token through 8 of 128 experts of 2048 x 768 33.8 -> 32.2, 6 of 64 of 2048 x 1408 (1.03) 37.4 -> 36.7; two through 8 of 128
-    // (1.5) 41.8 -> 43.1. Up to 16 tokens, which a workgroup selects in one pass.
-    return E <= 16 || (T <= 16 && (t == RoutedTile::few || t == RoutedTile::few_deep) &&
+    // (1.5) 41.8 -> 43.1. Up to a token per wavefront.
+    return E <= 16 || (T <= GateUpFewS::NW && (t == RoutedTile::few || t == RoutedTile::few_deep) &&
                        4 * most_row_tiles(T * k, E, 32) * (f / 32) <= 5 * compute_units(env.device));
 }
 
@@ -392,10 +392,9 @@ int launch_gateup_routed(const GemmEnv& env, const moe_bf16* x, const float* log
     auto with = [&](auto cfg) {
         using Cfg = decltype(cfg);
         if (E <= 16) return launch_routed<Cfg, 0>(env, x, rt, d, f, E, W1, W3, H, s);
-        if (E <= 32) return launch_routed<Cfg, 2>(env, x, rt, d, f, E, W1, W3, H, s);
-        if (E <= 64) return launch_routed<Cfg, 4>(env, x, rt, d, f, E, W1, W3, H, s);
-        if (E <= 128) return launch_routed<Cfg, 8>(env, x, rt, d, f, E, W1, W3, H, s);
-        return launch_routed<Cfg, 16>(env, x, rt, d, f, E, W1, W3, H, s);
+        if (E <= 64) return launch_routed<Cfg, 1>(env, x, rt, d, f, E, W1, W3, H, s);
+        if (E <= 128) return launch_routed<Cfg, 2>(env, x, rt, d, f, E, W1, W3, H, s);
+        return launch_routed<Cfg, 4>(env, x, rt, d, f, E, W1, W3, H, s);
     };
     switch (tile) {
         case RoutedTile::few_deep: return with(GateUpFewDeepS{});

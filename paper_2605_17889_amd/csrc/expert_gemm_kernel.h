@@ -785,26 +785,30 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_routed_kernel(
     if (tid < E) cnt[tid] = 0;
     int my[ROUNDS];                      // every wavefront holds all ids, 64 a round
     if constexpr (EW > 0) {
-        const int t = tid / 16;
-        if (__builtin_amdgcn_readfirstlane(t) < rt.T)
-            select_by_16_lanes<EW>(rt.logits, t, t < rt.T, tid & 15, E, rt.k, [&](int s, int e, float w) {
-                ids[t * rt.k + s] = e;
-                if (tables) {
-                    rt.topk_idx[t * rt.k + s] = e;
-                    rt.topk_w[t * rt.k + s] = w;
-                }
-            });
+        const int at = wave * rt.k;
+        if (wave < rt.T) {
+            if (tables)
+                select_by_wavefront<EW>(rt.logits, wave, lane, E, rt.k, [&](int s, int e, float w) {
+                    ids[at + s] = e;
+                    rt.topk_idx[at + s] = e;
+                    rt.topk_w[at + s] = w;
+                });
+            else                         // the gates drop out of this one
+                select_by_wavefront<EW>(rt.logits, wave, lane, E, rt.k, [&](int s, int e, float) { ids[at + s] = e; });
+        }
         __syncthreads();
     }
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) {
+        my[r] = -1;
+        if (r * kWave >= R) continue;    // the same for all lanes: rounds without ids cost a branch
         const int i = r * kWave + lane;
-        my[r] = i < R ? (EW > 0 ? ids : rt.topk_idx)[i] : -1;
+        if (i < R) my[r] = (EW > 0 ? ids : rt.topk_idx)[i];
     }
     if constexpr (EW == 0) __syncthreads();          // the counters are clear
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r)
-        if (r % Cfg::NW == wave && my[r] >= 0) atomicAdd(&cnt[my[r]], 1);     // counts only: any order
+        if (r * kWave < R && r % Cfg::NW == wave && my[r] >= 0) atomicAdd(&cnt[my[r]], 1);   // counts: any order
     __syncthreads();
     if (blockIdx.x < kXcds) {
         if (tables)
@@ -824,7 +828,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_routed_kernel(
         int found = 0;
 #pragma unroll
         for (int r = 0; r < ROUNDS; ++r) {
-            if (r * kWave >= R) break;
+            if (r * kWave >= R) continue;
             const uint64_t m = __ballot(my[r] == tc.expert);
             const int at = found + __popcll(m & ((1ull << lane) - 1ull)) - first;
             if (my[r] == tc.expert && at >= 0 && at < tc.rows) list[at] = r * kWave + lane;

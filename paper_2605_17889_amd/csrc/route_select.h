@@ -1,5 +1,5 @@
-// Selection and gates of one token by a group of 16 lanes (device code; included by route.hip and
-// permute.hip).
+// Selection and gates of one token by a group of 16 lanes or by a wavefront (device code; included by route.hip,
+// permute.hip and the expert GEMMs).
 #pragma once
 #include "common.h"
 
@@ -78,6 +78,52 @@ __device__ __forceinline__ void select_by_16_lanes(const float* __restrict__ log
         const int s = j * G + g;
         if (s < k) emit(s, my_idx[j], my_w[j] / den);
     }
+}
+
+// The same for a few tokens, a wavefront per token: lane g holds experts g, g + 64, ... (EW of them). A round is
+// shorter: six row moves to the maximum, then the lowest index that has it by ballots on the scalar unit. The same keys,
+// order and gates, so the same results. emit(slot, expert, gate) is called once for every slot.
+template <int EW, class Emit>
+__device__ __forceinline__ void select_by_wavefront(const float* __restrict__ logits, int t, int lane, int E, int k,
+                                                    Emit&& emit) {
+    uint32_t key[EW];
+#pragma unroll
+    for (int w = 0; w < EW; ++w) {
+        const int e = w * kWave + lane;
+        key[w] = e < E ? logit_key(logits[static_cast<size_t>(t) * E + e]) : 0u;
+    }
+    float top = 0.f, den = 0.f, my_w = 0.f;               // lane s keeps slot s: k <= 64
+    int my_e = 0;
+    for (int s = 0; s < k; ++s) {
+        uint32_t v = key[0];
+#pragma unroll
+        for (int w = 1; w < EW; ++w) v = max(v, key[w]);
+#define MOE_UP(CTRL, ROWS) \
+    v = max(v, static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xf, false)))
+        MOE_UP(0x111, 0xf);        // from the lanes 1, 2, 4, 8 below inside rows of 16; 0 is below every key
+        MOE_UP(0x112, 0xf);
+        MOE_UP(0x114, 0xf);
+        MOE_UP(0x118, 0xf);
+        MOE_UP(0x142, 0xa);        // lane 15 of a row to the row behind it, lane 31 to the upper half
+        MOE_UP(0x143, 0xc);
+#undef MOE_UP
+        const uint32_t best = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), kWave - 1));
+        int e = -1;                // k <= E, so there is one
+#pragma unroll
+        for (int w = EW - 1; w >= 0; --w) {
+            const uint64_t has = __ballot(key[w] == best);
+            e = has != 0 ? w * kWave + __builtin_ctzll(has) : e;
+        }
+#pragma unroll
+        for (int w = 0; w < EW; ++w) key[w] = e == w * kWave + lane ? 0u : key[w];
+        const float bv = key_logit(best);
+        if (s == 0) top = bv;
+        const float g = expf(bv - top);
+        den += g;
+        my_w = s == lane ? g : my_w;
+        my_e = s == lane ? e : my_e;
+    }
+    if (lane < k) emit(lane, my_e, my_w / den);
 }
 
 }  // namespace moe

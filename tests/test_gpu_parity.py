@@ -1353,9 +1353,9 @@ def test_profile_stage_times_of_layer_and_expert_ffn():
     (1, 8, 2, 512, 1024), (37, 8, 2, 512, 1024), (64, 8, 2, 512, 1024),     # 32-row tiles, groups of up to 20 and more rows
     (256, 8, 2, 512, 1024), (300, 8, 2, 512, 512), (512, 8, 2, 512, 512),   # 64-row tiles, 1024 ids
     (5, 1, 1, 512, 256), (2, 16, 16, 512, 256), (40, 13, 4, 512, 256),      # one expert, all experts, odd counts
-    (1, 128, 8, 2048, 768), (16, 128, 8, 512, 128), (16, 64, 6, 512, 128),  # selected on the way, up to 16 tokens
-    (3, 17, 3, 512, 384), (7, 32, 5, 512, 128), (16, 256, 64, 512, 128), (1, 256, 64, 512, 128),
-    (17, 128, 8, 512, 128),                                                 # one token too many
+    (1, 128, 8, 2048, 768), (4, 128, 8, 512, 128), (3, 64, 6, 512, 128),    # selected on the way, up to 4 tokens
+    (3, 17, 3, 512, 384), (2, 32, 5, 512, 128), (1, 256, 64, 512, 128), (4, 65, 2, 512, 128),
+    (16, 256, 64, 512, 128), (17, 128, 8, 512, 128),                        # more: separate launches
 ])
 @pytest.mark.parametrize("one_expert", [False, True])
 def test_few_tokens_without_a_permutation_launch(T, E, k, d, f, one_expert):
