@@ -148,8 +148,20 @@ int launch_ring(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, const
                         offsets, row_index, gemm::RowDiv(index_div), E, N, K, cus);
 }
 
+// Expected row tiles of height h: groups one standard deviation below and above the mean.
+double mean_row_tiles(double avg, double sigma, int h) {
+    return 0.5 * (std::ceil(std::max(1.0, avg - sigma) / h) + std::ceil((avg + sigma) / h));
+}
+
+// Expected row tiles of height h of a launch.
+double row_tiles(int R, int E, int h) {
+    const double avg = static_cast<double>(R) / (E > 0 ? E : 1);
+    return E * mean_row_tiles(avg, std::sqrt(avg), h);
+}
+
 // The pipelined kernel of one wavefront per SIMD: a persistent workgroup per compute unit where the reduction is
-// short, a workgroup per tile where it is long.
+// short and most of them get two tiles and more, else a workgroup per tile (4000 tokens through 8 experts of 512 x 1024,
+// one tile per compute unit, 62.4 us a layer with persistent ones, 60.9 without).
 template <class Cfg>
 int launch_1w(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, const moe_bf16* B1, moe_bf16* C,
               const int32_t* offsets, const int32_t* row_index, int index_div,
@@ -158,18 +170,13 @@ int launch_1w(const GemmEnv& env, const moe_bf16* A, const moe_bf16* B0, const m
     static std::atomic<uint64_t> attr_set[2];
     const int cus = compute_units(env.device), split = env.split_last_round ? cus : 0;
     const long long slots = most_slots(R, E, Cfg::BM, N / Cfg::BN_OUT, split);
-    if (K < gemm::kLongK)
+    if (K < gemm::kLongK && row_tiles(R, E, Cfg::BM) * (N / Cfg::BN_OUT) > 1.5 * cus)
         return launch_tiles(env, attr_set[0], gemm::grouped_gemm_1w_kernel<Cfg, true>, gemm::Ring1W<Cfg>::SMEM,
                             Cfg::NTHREADS, std::min<long long>(slots, cus), s, A, B0, B1, C, offsets, row_index,
                             gemm::RowDiv(index_div), E, N, K, split, env.tile_counters);
     return launch_tiles(env, attr_set[1], gemm::grouped_gemm_1w_kernel<Cfg, false>, gemm::Ring1W<Cfg>::SMEM,
                         Cfg::NTHREADS, slots, s, A, B0, B1, C, offsets, row_index, gemm::RowDiv(index_div), E, N, K,
                         split, env.tile_counters);
-}
-
-// Expected row tiles of height h: groups one standard deviation below and above the mean.
-double mean_row_tiles(double avg, double sigma, int h) {
-    return 0.5 * (std::ceil(std::max(1.0, avg - sigma) / h) + std::ceil((avg + sigma) / h));
 }
 
 // The n-tiles of one projection in each kind of tile, and what the small tiles of config 2 cost.
@@ -252,12 +259,6 @@ int pick_config(const GemmEnv& env, int R, int E, const NTiles& nt) {
         if ((nt.ksteps + 3.0) * fill < 0.9 * (nt.ksteps + 6.0) * step) return 2;
     }
     return config;
-}
-
-// Expected row tiles of height h of a launch.
-double row_tiles(int R, int E, int h) {
-    const double avg = static_cast<double>(R) / (E > 0 ? E : 1);
-    return E * mean_row_tiles(avg, std::sqrt(avg), h);
 }
 
 NTiles gateup_tiles(int E, int d, int f) {

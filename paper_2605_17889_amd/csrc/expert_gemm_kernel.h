@@ -469,24 +469,6 @@ __device__ __forceinline__ void mfma_drain(f32x4 (&last)[N]) {
     for (int j = 0; j < N; ++j) asm volatile("" : "+a"(last[j]));
 }
 
-// All k-substeps of one stage: acc[i][j] += A_i * B_j, k ascending.
-template <class Cfg>
-__device__ __forceinline__ void mma_stage(const unsigned char* s, const FragPlan<Cfg>& fp,
-                                          f32x4 (&acc)[Cfg::TM][Cfg::TN]) {
-#pragma unroll
-    for (int kk = 0; kk < Cfg::KSUB; ++kk) {
-        bf16x8 af[Cfg::TM], bfr[Cfg::TN];
-#pragma unroll
-        for (int i = 0; i < Cfg::TM; ++i) af[i] = lds16(s + fp.a_off[kk] + i * Cfg::TILE_STEP);
-#pragma unroll
-        for (int j = 0; j < Cfg::TN; ++j) bfr[j] = lds16(s + fp.b_off[kk] + j * Cfg::TILE_STEP);
-#pragma unroll
-        for (int i = 0; i < Cfg::TM; ++i)
-#pragma unroll
-            for (int j = 0; j < Cfg::TN; ++j) acc[i][j] = mma16(bfr[j], af[i], acc[i][j]);
-    }
-}
-
 // Epilogue. Result layout of the transposed 16x16 tile: lane holds activation row (lane & 15)
 // and the four output columns 4 * (lane >> 4) + r in registers r = 0..3. With DUAL, B-tile rows
 // come in blocks of DB W1 rows followed by the DB W3 rows of the same output columns, so accumulator
@@ -687,24 +669,19 @@ __device__ __forceinline__ void ring_of_stages(const TileCoord& tc, LoadPlan<Cfg
                                                const uint16_t* __restrict__ B1, uint16_t* __restrict__ C, int N,
                                                int K) {
     constexpr int BK = Cfg::BK, TM = Cfg::TM, TN = Cfg::TN, LPW = Cfg::LPW, NSTAGE = Cfg::NSTAGE;
+    static_assert(Cfg::KSUB == 2, "two k-substeps a stage");
     const int wm = wave / Cfg::WN, wn = wave % Cfg::WN;
-    // ---- first loads: the weights of two stages go out under the latency of the row index (one token through 8 of
-    // 128 experts of 2048 x 768: gate/up 13.6 -> 13.3 us)
+    // ---- first loads: the first weights go out under the latency of the row index (layer call of 64 tokens through
+    // 8 experts of 512 x 1024 20.5 us, with two stages of weights 21.0; one token through 8 of 128 of 2048 x 768 29.2, 29.4)
     const int KT = K / BK;
     lp.init_fixed(wave, lane, K);
     lp.init_b(tc, wave, B0, B1, N, K);
-    constexpr int AHEAD = NSTAGE > 2 ? 2 : 1;
-#pragma unroll
-    for (int s = 0; s < AHEAD; ++s)
-        if (s < KT) lp.issue_b_all(s * Cfg::STAGE_BYTES, static_cast<size_t>(s) * BK);
+    lp.issue_b_all(0, 0);
     init_a();
+    lp.issue_a_all(0, 0);
 #pragma unroll
-    for (int s = 0; s < NSTAGE - 1; ++s) {
-        if (s < KT) lp.issue_a_all(s * Cfg::STAGE_BYTES, static_cast<size_t>(s) * BK);
-        if (s >= AHEAD && s < KT) lp.issue_b_all(s * Cfg::STAGE_BYTES, static_cast<size_t>(s) * BK);
-    }
-    // k-step 0 has landed when only the later A loads and stages are on their way
-    if (KT >= NSTAGE - 1) wait_vmcnt<(AHEAD - 1) * LoadPlan<Cfg>::LA + (NSTAGE - 1 - AHEAD) * LPW>();
+    for (int s = 1; s < NSTAGE - 1; ++s)
+        if (s < KT) lp.issue_all(s * Cfg::STAGE_BYTES, static_cast<size_t>(s) * BK);
 
     f32x4 acc[TM][TN];
 #pragma unroll
@@ -723,10 +700,31 @@ __device__ __forceinline__ void ring_of_stages(const TileCoord& tc, LoadPlan<Cfg
         __builtin_amdgcn_s_barrier();          // stage `stage` is complete for every wavefront
                                                // and stage (stage-1) is no longer being read
         const int nk = kt + NSTAGE - 1;
-        if (nk < KT)
-            lp.issue_all((stage == 0 ? NSTAGE - 1 : stage - 1) * Cfg::STAGE_BYTES,
-                         static_cast<size_t>(nk) * BK);
-        mma_stage<Cfg>(smem + stage * Cfg::STAGE_BYTES, fp, acc);
+        const unsigned char* st = smem + stage * Cfg::STAGE_BYTES;
+        const uint32_t into = (stage == 0 ? NSTAGE - 1 : stage - 1) * Cfg::STAGE_BYTES;
+        const size_t koff = static_cast<size_t>(nk) * BK;
+        // Fragments of the first k-substep are asked for ahead of the loads, which leave a wavefront some 100 cycles
+        // apart, those of the second ahead of the first one's MFMAs (layer calls with the loads first -> so: one token
+        // through 8 experts of 512 x 1024 20.0 -> 19.6 us, 5 through 6 of 64 of 2048 x 1408 93.9 -> 92.3, 37 through 8 of 128
+        // of 2048 x 768 191.0 -> 190.4; large experts within 0.5 %).
+        bf16x8 af[2][TM], bfr[2][TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) af[0][i] = lds16(st + fp.a_off[0] + i * Cfg::TILE_STEP);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) bfr[0][j] = lds16(st + fp.b_off[0] + j * Cfg::TILE_STEP);
+        if (nk < KT) lp.issue_all(into, koff);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) af[1][i] = lds16(st + fp.a_off[1] + i * Cfg::TILE_STEP);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) bfr[1][j] = lds16(st + fp.b_off[1] + j * Cfg::TILE_STEP);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = mma16(bfr[0][j], af[0][i], acc[i][j]);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = mma16(bfr[1][j], af[1][i], acc[i][j]);
         stage = (stage + 1 == NSTAGE) ? 0 : stage + 1;
     }
     store_tile<Cfg>(acc, tc, fp, wm, wn, C, N);
@@ -1459,13 +1457,12 @@ constexpr int kCounterInts = 32;                     // a counter per XCD, on a 
 // up in steps of an eighth (an expert's short tail, or a half of a tile of the last, partial round, at half).
 // Every output element is one accumulator chain over k, so the bits do not depend on which height computed it.
 //
-// PERSISTENT: workgroup b serves XCD b % 8's range of tiles: first its slot b / 8, then whichever slot it draws, one
-// tile ahead of the one it computes, so that workgroups even out tiles of unequal cost among themselves as
+// PERSISTENT: workgroup b of P per XCD serves XCD b % 8's range of tiles: its slots b / 8 and b / 8 + P, then whichever
+// slot it draws, one tile ahead of the one it computes, so that workgroups even out tiles of unequal cost among themselves as
 // the dispatcher did. No workgroup waits for another one; each ends when it has drawn past the end of its
-// range. Slots and draws: a range of S slots and P workgroups of which min(S, P) have a first tile; each of
-// those draws until it is past the end, S - min(S, P) draws hand out a tile and min(S, P) do not, so draw
-// number S - 1 is the launch's last in this range and whoever gets it sets the counter back to zero for the next
-// launch.
+// range. Draws: of a range of S slots, S - 2 P are drawn, and every workgroup that has a second tile, min(P, S - P) of
+// them, draws until it is past the end: S - P draws in all, whose last one sets the counter back to zero for
+// the next launch.
 template <class Cfg, bool PERSISTENT>
 __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_1w_kernel(
     const uint16_t* __restrict__ A, const uint16_t* __restrict__ B0,
@@ -1511,7 +1508,6 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_1w_kernel(
         if constexpr (!Cfg::DUAL) return 0;
         return row_index != nullptr ? row_index[t.row0 + a_row_1w(t, wave, lane)] : offsets[0];
     };
-    draw();
     LoadPlan1W lp;
     init_b_offsets<Cfg>(lp, wave, lane, K);
     start_loads_1w<Cfg>(lp, tc, row_id(tc), wave, lane, A, B0, B1, row_index, index_div, N, K);
@@ -1528,14 +1524,10 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_1w_kernel(
         if (Cfg::DUAL) lp.b_ptr[1] += Cfg::BK;
     }
     uint32_t sb = 0;
-    unsigned char* idle = smem + R::A_RING + (R::NB - 1) * R::BB;
-    if constexpr (PERSISTENT) {
-        __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0): the first draw too
-        drawn(idle);
-    } else {
-        if (tc.height == Cfg::BM) wait_vmcnt<R::LA + R::LB>();   // k-step 0 landed
-        else wait_vmcnt<4 + R::LB>();
-    }
+    if (tc.height == Cfg::BM) wait_vmcnt<R::LA + R::LB>();   // k-step 0 landed
+    else wait_vmcnt<4 + R::LB>();
+    int slot = blockIdx.x / kXcds + workgroups;      // of the next tile
+    unsigned char* idle = nullptr;                   // the B stage in which the latest draw lies, once there is one
     while (true) {
         // lane-dependent addresses are formed anew for every tile: kept over the loop they would take the
         // registers of fragments
@@ -1543,13 +1535,14 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_1w_kernel(
         __builtin_amdgcn_s_barrier();                // the tile's first k-step has landed for every wavefront
         TileCoord nxt = tc;
         if constexpr (PERSISTENT) {
-            const int slot = __builtin_amdgcn_readfirstlane(
-                *reinterpret_cast<const int*>(idle + wave * (R::LB * 1024) + kEpilogueBytes));
-            const TileCoord found = uniform_tile(table.find(NT, cut_tiles, workgroups + slot, magic));
+            if (idle != nullptr)
+                slot = 2 * workgroups + __builtin_amdgcn_readfirstlane(
+                    *reinterpret_cast<const int*>(idle + wave * (R::LB * 1024) + kEpilogueBytes));
+            const TileCoord found = uniform_tile(table.find(NT, cut_tiles, slot, magic));
             last = found.expert < 0;
             if (!last)
                 nxt = found;
-            else if (slot == table.range.slots - 1 && threadIdx.x == 0)
+            else if (idle != nullptr && slot == table.range.slots + workgroups - 1 && threadIdx.x == 0)
                 __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         const int id = row_id(nxt);
