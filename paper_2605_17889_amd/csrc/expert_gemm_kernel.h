@@ -115,15 +115,33 @@ struct SlotRange {
     }
 };
 
-constexpr int kLongK = 4096;         // gate/up reductions of this and more cut the tiles of experts of at most
-constexpr int kLongCutTiles = 5;     // so many m-tiles only; shorter ones and the down projection those of every expert
+constexpr int kLongK = 4096;         // reductions of this and more are long
+
+// Whether the mt m-tiles of an expert of m_e rows share its rows evenly (see tile_in_expert). Short reductions always:
+// 16384 skewed tokens through 128 experts of 2048 x 768 687 us whole, with experts of nine and fewer m-tiles cut 673,
+// with all 665 (in quarters). In long ones a workgroup that ends early is out of step with those whose rows and
+// weights it shares in L2, which costs more than a saving of few rows; with more than kLongCutTiles m-tiles the saving
+// is small, and with six or eight little is gained by one tail less. Experts of at most four m-tiles are cut, whole ->
+// cut: layers of 2500 tokens through 8 experts of 6144 x 16384 (625 rows each) 2658 -> 2488 us. Those of five to seven
+// where the last tile would hold few rows, whole -> cut: 4200 tokens (1050) 4128 -> 3877, 4400 (1100) 4332 -> 3947,
+// 5200 (1300, six) 4770 -> 4647, 6400 (1600, seven) 6059 -> 5677, 5300 at 4096 x 14336 2875 -> 2793. Past the lines,
+// whole -> cut: six m-tiles with tails to 96 (5600) 4999 -> 5009, tails of 129 to 192 in five (4800) 4220 -> 4303, eight
+// with tails to 64 (7200) 6352 -> 6513, eight and nine (8192) 7168 -> 7295.
+enum class Cut { kNever, kLong, kAlways };
+constexpr int kLongCutTiles = 7;
+template <int BM>
+__device__ __forceinline__ bool tiles_are_cut(int m_e, int mt, Cut cut) {
+    if (cut != Cut::kLong) return cut == Cut::kAlways;
+    const int tail = m_e - (mt - 1) * BM;
+    return mt <= 4 || (mt <= kLongCutTiles && tail <= (mt == 6 ? BM / 4 : BM / 2));
+}
 
 // Coordinates of tile `local` of the expert whose group is rows [row_e, row_e + m_e). The expert's
 // mt m-tiles form ceil(mt / kGroupM) groups of nearly equal height (the first `extra` groups hold
 // one tile more), so that a short tail tile sweeps the n-tiles together with full tiles of its
 // expert and finds the weight tiles in L2.
 //
-// The m-tiles of an expert of at most cut_tiles of them share its rows in units of an eighth of a tile: 576 rows
+// Tiles that are cut share the expert's rows in units of an eighth of a tile: 576 rows
 // are 3 x 192 instead of 2 x 256 and a tail of 64, 520 are 192, 192 and 160. No tile is lower than half of one: a
 // k-step of 192 rows takes 1536 cycles of matrix instructions and 56 loads, one of 128 rows, bound by its 48
 // loads, hardly less than that. Rows that are padding cost time and, under the board's power limit, clock.
@@ -131,16 +149,9 @@ constexpr int kLongCutTiles = 5;     // so many m-tiles only; shorter ones and t
 // each) 462 -> 431 and 257 -> 241 us, 5003 282 -> 270 and 196 -> 191 (fp32 outputs), 8192 through 128 of 2048 x 768
 // 336 -> 325 and 234 -> 222, 1200 through 8 of 4096 x 14336 515 -> 520 and 295 -> 274 (those of short reductions
 // together with the persistent workgroups, see grouped_gemm_1w_kernel).
-// A workgroup that ends early is out of step with those whose rows and weights it shares in L2, which the long reductions
-// of gate/up pay for, while the saving shrinks with the number of m-tiles. Gate/up, experts of at most four m-tiles cut, of
-// at most six, all: 4096 tokens through 8 experts of 6144 x 16384 (four or five m-tiles) 2399, 2349, 2353 us; 5500 (six)
-// 3221, 3274, 3247; 8192 4602, 4612, 4661; 16384 with a skewed load 9013, 9100, 9332; 8192 at 4096 x 14336 2623, 2642, 2650.
-// Down: 1342, 1314, 1310; 1641, 1588, 1603; 2386, 2392, 2370; 4612, 4637, 4584; 1467, 1465, 1478. A short reduction loses
-// nothing: 16384 skewed tokens through 128 experts of 2048 x 768 687 us whole, with experts of nine and fewer cut 673, with
-// all 665 (in quarters).
 template <int BM>
 __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m_e, int local, int NT, int half,
-                                                    int cut_tiles) {
+                                                    Cut cut) {
     TileCoord tc{kNoTile, 0, 0, 0, 0};
     const int mt = (m_e + BM - 1) / BM;
     const int ngroups = (mt + kGroupM - 1) / kGroupM;
@@ -162,7 +173,7 @@ __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m
     mi += head;
     int first = mi * BM;
     tc.height = BM;
-    if (mt <= cut_tiles) {
+    if (tiles_are_cut<BM>(m_e, mt, cut)) {
         constexpr int U = BM / 8;
         int extra;
         const int base = div_small((m_e + U - 1) / U, mt, extra);   // in units of U rows; `extra` tiles one more
@@ -204,7 +215,7 @@ __device__ __forceinline__ int lane_prefix_sum(int v) {
 // instructions instead of vector loads, a prefix sum across lanes and a ballot.
 template <int BM>
 __device__ __forceinline__ TileCoord locate_tile_scalar8(const int32_t* __restrict__ offsets, int NT,
-                                                         int split_cus, int cut_tiles, int xcd, int slot) {
+                                                         int split_cus, Cut cut, int xcd, int slot) {
     int off[9];
 #pragma unroll
     for (int e = 0; e < 9; ++e) off[e] = offsets[e];
@@ -231,7 +242,7 @@ __device__ __forceinline__ TileCoord locate_tile_scalar8(const int32_t* __restri
             m_e = off[i + 1] - off[i];
             row_e = off[i];
         }
-    return tile_in_expert<BM>(e, row_e, m_e, L - start, NT, half, cut_tiles);
+    return tile_in_expert<BM>(e, row_e, m_e, L - start, NT, half, cut);
 }
 
 // An XCD's range of the tiles, prepared for lookups: the tile counts of all experts over the lanes of a
@@ -274,7 +285,7 @@ struct TileTable {
         range.init(__builtin_amdgcn_readlane(incl, kWave - 1), split_cus, xcd);
     }
     // `magic`: lane g holds floor(2^32 / g) + 1, so that a / g == (a * magic) >> 32 for 2 <= g and a * g < 2^32.
-    __device__ __forceinline__ TileCoord find(int NT, int cut_tiles, int slot, uint32_t magic) const {
+    __device__ __forceinline__ TileCoord find(int NT, Cut cut, int slot, uint32_t magic) const {
         int half;
         const int L = range.tile(slot, half);
         if (L < 0) return TileCoord{kNoTile, 0, 0, 0, 0};
@@ -294,13 +305,13 @@ struct TileTable {
         }
         e += src * EPL;
         const int m_e = next - row_e, mt = (m_e + BM - 1) / BM;
-        if (mt > kGroupM || half >= 0) return tile_in_expert<BM>(e, row_e, m_e, L - first, NT, half, cut_tiles);
+        if (mt > kGroupM || half >= 0) return tile_in_expert<BM>(e, row_e, m_e, L - first, NT, half, cut);
         // tile_in_expert where the expert's tiles are one group and nothing is split
         constexpr uint32_t U = BM / 8;
         const uint32_t in = L - first, mul = __builtin_amdgcn_readlane(magic, mt), one = mt == 1 ? ~0u : 0u;
         const uint32_t nt = __umulhi(in, mul) + (in & one), mi = in - nt * mt;
         uint32_t base = 8, extra = 0;
-        if (mt <= cut_tiles) {
+        if (tiles_are_cut<BM>(m_e, mt, cut)) {
             const uint32_t units = (m_e + U - 1) / U;
             base = __umulhi(units, mul) + (units & one);
             extra = units - base * mt;
@@ -325,12 +336,12 @@ __device__ __forceinline__ TileCoord uniform_tile(TileCoord tc) {
 // The tile of this workgroup where every workgroup has one.
 template <int BM>
 __device__ __forceinline__ TileCoord locate_tile(const int32_t* __restrict__ offsets, int E, int NT, int split_cus = 0,
-                                                 int cut_tiles = 0) {
+                                                 Cut cut = Cut::kNever) {
     const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-    if (E == 8) return uniform_tile(locate_tile_scalar8<BM>(offsets, NT, split_cus, cut_tiles, xcd, slot));
+    if (E == 8) return uniform_tile(locate_tile_scalar8<BM>(offsets, NT, split_cus, cut, xcd, slot));
     TileTable<BM> table;
     table.init(offsets, E, NT, split_cus, xcd, threadIdx.x & (kWave - 1));
-    return uniform_tile(table.find(NT, cut_tiles, slot, division_magic(threadIdx.x & (kWave - 1))));
+    return uniform_tile(table.find(NT, cut, slot, division_magic(threadIdx.x & (kWave - 1))));
 }
 
 // LDS tile layout: rows of BK bf16 in 16-byte chunks; logical chunk c of row r is stored at
@@ -817,7 +828,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_routed_kernel(
     }
     TileTable<BM> table;
     table.init_from_counts(cnt, E, NT, blockIdx.x % kXcds, lane);
-    const TileCoord tc = uniform_tile(table.find(NT, 0, blockIdx.x / kXcds - 1, division_magic(lane)));
+    const TileCoord tc = uniform_tile(table.find(NT, Cut::kNever, blockIdx.x / kXcds - 1, division_magic(lane)));
     if (tc.expert < 0) return;
     LoadPlan<Cfg> lp;
     ring_of_stages<Cfg>(tc, lp, [&] {
@@ -1475,15 +1486,16 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_1w_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int xcd = blockIdx.x % kXcds, workgroups = gridDim.x / kXcds;
     int32_t* counter = counters + xcd * kCounterInts;
-    const int NT = N / Cfg::BN_OUT, cut_tiles = Cfg::DUAL && K >= kLongK ? kLongCutTiles : 1 << 30;
+    const int NT = N / Cfg::BN_OUT;
+    const Cut cut = K < kLongK ? Cut::kAlways : Cut::kLong;
     TileTable<Cfg::BM> table;                        // kept over the tiles: a lookup then reads no memory
     TileCoord tc;
     const uint32_t magic = division_magic(lane);
     if constexpr (PERSISTENT) {
         table.init(offsets, E, NT, split_cus, xcd, lane);
-        tc = uniform_tile(table.find(NT, cut_tiles, blockIdx.x / kXcds, magic));
+        tc = uniform_tile(table.find(NT, cut, blockIdx.x / kXcds, magic));
     } else {
-        tc = locate_tile<Cfg::BM>(offsets, E, NT, split_cus, cut_tiles);
+        tc = locate_tile<Cfg::BM>(offsets, E, NT, split_cus, cut);
     }
     if (tc.expert < 0) return;                       // uniform for the whole workgroup
     bool last = !PERSISTENT;
@@ -1538,7 +1550,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_1w_kernel(
             if (idle != nullptr)
                 slot = 2 * workgroups + __builtin_amdgcn_readfirstlane(
                     *reinterpret_cast<const int*>(idle + wave * (R::LB * 1024) + kEpilogueBytes));
-            const TileCoord found = uniform_tile(table.find(NT, cut_tiles, slot, magic));
+            const TileCoord found = uniform_tile(table.find(NT, cut, slot, magic));
             last = found.expert < 0;
             if (!last)
                 nxt = found;

@@ -618,9 +618,10 @@ def test_large_tiles_of_every_height(rows, fp32_outputs, d=512, f=256):
 
 @pytest.mark.parametrize("d,f", [(4096, 4096), (3584, 4224)])     # both projections, down alone past the line
 def test_large_tiles_of_long_reductions(d, f):
-    """Gate/up: experts of up to five m-tiles are cut in long reductions, those of six and more are not."""
+    """Experts of up to four m-tiles are cut, those of five to seven by the rows of the last one, larger ones are not."""
     test_large_tiles_of_every_height([449, 577, 769, 1024, 1025, 1152, 130], False, d, f)
     test_large_tiles_of_every_height([1280, 1281, 1500], False, d, f)
+    test_large_tiles_of_every_height([1152, 1153, 1344, 1345, 1664, 1665, 1793, 900], False, d, f)
 
 
 @pytest.mark.parametrize("d,f", [(512, 3840), (3584, 256)])    # many tiles per workgroup up; down, at four k-steps
