@@ -665,7 +665,10 @@ struct RouteFew {
     static constexpr int STAGE = W_BYTES + X_BYTES;
     static constexpr int NSTAGE = EG == 8 ? 7 : 4;
     static constexpr int LOADS = EG / 2 + 1;                          // per wavefront and chunk
-    static constexpr int SMEM = NSTAGE * STAGE + TOK * EG * 4;
+    static constexpr int smem(int stages) { return stages * STAGE + TOK * EG * 4; }
+    static constexpr int SMEM = smem(NSTAGE);
+    // no more stages than chunks: a short reduction leaves room for further workgroups
+    static constexpr int smem_for(int d) { return smem(std::min(NSTAGE, d / 512)); }
     static_assert(SMEM <= 160 * 1024 && (NSTAGE - 1) * LOADS < 64, "LDS and load counter");
     static_assert(TOK == 1 || TOK == 4, "x rows: one per wavefront, or the same for all");
 };
@@ -691,7 +694,7 @@ __global__ __launch_bounds__(256) void route_few_kernel(const uint16_t* __restri
     constexpr int SLICE = 32 * EG;                      // bytes of a lane's 8 x EG weights
     constexpr int WL = EG / 2;                          // W_r loads per wavefront and chunk
     extern __shared__ __attribute__((aligned(1024))) unsigned char rsm[];
-    float* all_logits = reinterpret_cast<float*>(rsm + R::NSTAGE * R::STAGE);     // [TOK][EG]
+    float* all_logits = reinterpret_cast<float*>(rsm + min(R::NSTAGE, d / 512) * R::STAGE);     // [TOK][EG]
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -788,7 +791,7 @@ int launch_route_few(int device, const moe_bf16* x, const float* wr, const float
         attr_set.fetch_or(1ull << device, std::memory_order_release);
     }
     hipLaunchKernelGGL((route_few_kernel<EG, TOK, SELECT>), dim3((T + TOK - 1) / TOK, E / EG), dim3(256),
-                       (RouteFew<EG, TOK>::SMEM), s, x, wr, bias, T, d, E, k, idx, w, logits_out);
+                       (RouteFew<EG, TOK>::smem_for(d)), s, x, wr, bias, T, d, E, k, idx, w, logits_out);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
@@ -872,9 +875,14 @@ int launch_route(const moe_bf16* x, const float* w_router, const float* bias, in
     }
     const int device = current_device();
     if (device < 0) return MOE_ERR_HIP;
-    // One round of few-token workgroups, one per compute unit (their LDS allows no second): 1024 tokens of
-    // 4096 take 8.1 us against 11.4 with the kernels below, 2048 tokens (two rounds) 14.3 against 11.8.
-    const bool few = direct_to_lds_aligned(x, w_router) && (T + 3) / 4 <= compute_units(device);
+    // One round of few-token workgroups, as many per compute unit as their LDS allows: 1024 tokens of 4096 (one) take
+    // 8.1 us against 11.4 with the kernels below, 2048 tokens (two rounds) 14.3 against 11.8. A chunk or two leave
+    // room for seven or three: layers of 512 x 1024, 1030, 2000 and 7100 tokens through 8 experts 35.6 -> 32.6, 47.4 -> 43.9
+    // and 79.2 -> 74.7 us, 3000 of 1024 x 256 41.1 -> 39.6. Rows of one chunk make a chain of one latency, hidden by the
+    // other workgroups, at every number of tokens: 8192 and 60000 through 8 93.3 -> 91.2 and 217 -> 210, 40000 through 16
+    // 175 -> 162. With two chunks 20000 through 8 would take 134 us for 128.
+    const int per_cu = 160 * 1024 / (E == 8 ? RouteFew<8, 4>::smem_for(d) : RouteFew<16, 4>::smem_for(d));
+    const bool few = direct_to_lds_aligned(x, w_router) && (d == 512 || (T + 3) / 4 <= compute_units(device) * per_cu);
     if (E == 8 && few)
         return launch_route_few<8, 4, true>(device, x, w_router, bias, T, d, E, k, topk_idx, topk_w, logits_out, s);
     if (E == 16 && few)

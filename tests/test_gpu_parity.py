@@ -112,6 +112,8 @@ def test_route_bit_exact(T, d, E, k, use_bias):
     (1, 2048, 16, 2), (7, 2560, 16, 16), (1024, 512, 16, 1),
     (1, 2048, 128, 8), (32, 512, 128, 8), (33, 2560, 128, 8), (128, 1024, 128, 2), (129, 512, 128, 8),
     (1, 4608, 256, 64), (16, 512, 256, 8), (17, 512, 256, 3), (85, 2048, 48, 5),
+    # several workgroups per compute unit: 3 with two chunks of 8 experts, 2 with two of 16; a chunk at any number of tokens
+    (7169, 512, 8, 2), (3071, 1024, 8, 8), (3073, 1024, 8, 1), (4099, 512, 16, 3), (2048, 1024, 16, 1), (2049, 1024, 16, 2),
 ])
 def test_route_few_tokens_bit_exact(T, d, E, k):
     test_route_bit_exact(T, d, E, k, T % 2 == 1)
