@@ -217,8 +217,8 @@ int pick_config(const GemmEnv& env, int R, int E, const NTiles& nt) {
     if (upper <= 32.0) return 3;
     // The 64-row tiles against the 96-row ones, gate/up + down: 500 tokens through 128 experts of
     // 2048 x 768 205 us against 218; with a few experts past 64 rows (560 tokens through 64 experts of
-    // 2048 x 1408) 226 against 211. Of a few large experts the line takes more than it should: 200 tokens through
-    // 8 of 4096 x 14336 515 against 485.
+    // 2048 x 1408) 226 against 211. Layers on the same weights: 195 tokens through 8 of 4096 x 14336 502 against 524, of
+    // 6144 x 16384 830 against 817; past the line, 205 there 905 against 849, 810 through 128 of 2048 x 768 281 against 268.
     if (upper <= 64.0) return 2;
     const int cus = compute_units(env.device);
     // The 96- and 128-row tiles only where the largest group is expected to fit one: a second tile costs more than
@@ -268,17 +268,27 @@ NTiles gateup_tiles(int E, int d, int f) {
 // Tiles of half the width while up to two and a half of them go to a compute unit, gate/up against
 // the 128-column ones: one token through 8 of 128 experts of 2048 x 768 (0.75 per compute unit) 14.2
 // and 18.2 us, 2 (1.4) 21.6 and 22.3, 2 through 6 of 64 of 2048 x 1408 (2.1) 23.9 and 25.0, 64 through
-// 2 of 8 of 512 x 1024 (1.0) 7.7 and 8.7. Past the line the sides are mixed: 4 tokens, 8 of 128 (2.7)
-// 37.0 and 39.5, 5 (3.3) 44.0 and 42.8; 4 tokens, 6 of 64 (3.8) 43.9 and 42.2, 6 (5.4) 54.6 and 62.4
+// 2 of 8 of 512 x 1024 (1.0) 7.7 and 8.7. Longer reductions than those below lose past the line: layers of 4096 x 14336,
+// one token through 2 of 8 (3.3) 142 and 129, of 6144 x 16384 (3.7) 229 and 220
 bool narrow_gateup_tiles(int R, int E, int f, int cus) { return 2.0 * touched_experts(R, E) * (f / 64) <= 2.5 * cus; }
+
+// Workgroups of `tiles` tiles that find a free slot per round, over the slots of those rounds.
+double last_round_use(double tiles, double slots) { return tiles / (slots * std::ceil(tiles / slots)); }
+
+// Short reductions, more than that: a tile of half the width leaves half as much of the last round empty, except
+// where both widths take two rounds (three to four narrow tiles per compute unit) or the wide ones fill theirs. Layers
+// through 8 of 128 experts of 2048 x 768, wide -> narrow: 4 tokens (2.6) 66.6 -> 62.8 us, 5 (3.3) 69.8 -> 72.7, 7 (4.4)
+// 99.4 -> 88.6, 20 (8.7) 155 -> 150, 37 (10.8) 184 -> 180, 120 (12, all full) 209 -> 213; 6 of 64 of 2048 x 1408, 4 tokens
+// (3.6) 70.0 -> 70.8, 16 (8.7) 151 -> 145, 80 (11) 182 -> 178; 4 of 60 of 1536 x 1536, 30 tokens 133 -> 127.
+bool narrow_short_gateup_tiles(int R, int E, int d, int f, int cus) {
+    const double wide = touched_experts(R, E) * (f / 64);
+    return d <= 2048 && (2.0 * wide <= 3.0 * cus || wide > 2.0 * cus) && last_round_use(wide, cus) <= 0.97;
+}
 
 // The deep ring where no compute unit gets a second tile, whichever experts are touched: one
 // token through 8 of 128 of 2048 x 768 (192 tiles) 14.3 against 14.9 us, through 4 of 32 of 2048 x 2048
 // (256) 16.7 against 17.5; through 6 of 64 of 2048 x 1408 (264) 20.2 against 18.2
 bool one_tile_per_cu(int R, int E, int f, int cus) { return std::min(E, R) * (f / 32) <= cus; }
-
-// Workgroups of `tiles` tiles that find a free slot per round, over the slots of those rounds.
-double last_round_use(double tiles, double slots) { return tiles / (slots * std::ceil(tiles / slots)); }
 
 // Large tiles: four wavefronts of 128 x 128 outputs (one per SIMD) or eight of 128 x 64. The
 // four-wavefront form addresses a weight row by a 32-bit byte offset from the expert's matrix.
@@ -438,7 +448,7 @@ int launch_gateup(const GemmEnv& env, const moe_bf16* a, const int32_t* row_inde
             if (single_m_tile(env, R_hint, E, 32)) {
                 const double nt = touched_experts(R_hint, E) * (f / 64);
                 const int cus = compute_units(env.device);
-                if (narrow_gateup_tiles(R_hint, E, f, cus)) {
+                if (narrow_gateup_tiles(R_hint, E, f, cus) || narrow_short_gateup_tiles(R_hint, E, d, f, cus)) {
                     if (one_tile_per_cu(R_hint, E, f, cus))
                         return launch_grouped<GateUpFewDeepS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);
                     return launch_grouped<GateUpFewS>(env, x_perm, W1, W3, H, offsets, row_index, index_div, R, E, f, d, s);

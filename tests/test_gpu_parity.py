@@ -540,6 +540,7 @@ def test_expert_ffn_configs_agree_bitwise():
     (512, 1024, [5, 0, 33, 1, 16, 17, 3, 8] * 2),    # narrow 32-row gate/up tiles, two per compute unit
     (512, 256, [16, 33, 15, 1, 0, 31, 32, 20]),      # 16-row down tiles, some experts with two or three
     (512, 256, [64, 40, 65, 33, 0, 80, 31, 1]),      # 32-row down tiles for groups of up to 64 rows
+    (1024, 1024, [1, 0, 3, 2, 33] * 8),              # more than four per compute unit
     (512, 14336, [4, 0, 33, 1, 2, 9, 8, 7]),         # 32-row tiles with the deep ring
     (2048, 256, [32, 0, 1, 33, 65, 31, 2, 16] * 4),  # 32-row tiles, two workgroups per compute unit
     (2048, 128, [43, 64, 0, 65, 1, 33, 130, 8] * 8), # 64-row tiles, 128 and 64 columns wide
