@@ -290,10 +290,9 @@ bool narrow_short_gateup_tiles(int R, int E, int d, int f, int cus) {
 // (256) 16.7 against 17.5; through 6 of 64 of 2048 x 1408 (264) 20.2 against 18.2
 bool one_tile_per_cu(int R, int E, int f, int cus) { return std::min(E, R) * (f / 32) <= cus; }
 
-// Large tiles: four wavefronts of 128 x 128 outputs (one per SIMD) or eight of 128 x 64. The
-// four-wavefront form addresses a weight row by a 32-bit byte offset from the expert's matrix.
+// Large tiles: four wavefronts of 128 x 128 outputs (one per SIMD) or eight of 128 x 64.
 bool use_one_wave_per_simd(const GemmEnv& env, int N, int K) {
-    if (static_cast<unsigned long long>(N) * K * 2ull >= (1ull << 32)) return false;
+    if (!gemm::offsets_fit_1w(N, K)) return false;
     if (K % 128 != 0) return false;       // its k-loop takes two 64-wide steps per trip
     if (env.large_tile_waves != 0) return env.large_tile_waves == 4;
     return true;     // faster at every shape measured (reductions of 768 to 16384)

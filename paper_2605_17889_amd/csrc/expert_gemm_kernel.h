@@ -1074,6 +1074,13 @@ __device__ __forceinline__ float read_acc(const f32x4& acc, int r) {
     return v;
 }
 constexpr int kEpilogueBytes = 4096;                 // LDS that a wavefront stages its outputs through
+// Bytes from a wavefront's first output row to behind its last one inside the tile. The tile has rows_from_here rows
+// from the first one on, which may be more than the wavefront's own: 256 rows of 2^22 floats would be 2^32 bytes, while
+// 128 rows of any width that offsets_fit_1w() lets in are less.
+__host__ __device__ constexpr uint32_t store_bytes(int rows_from_here, int wave_rows, uint32_t row_bytes) {
+    const int rows = rows_from_here < wave_rows ? rows_from_here : wave_rows;
+    return (rows < 0 ? 0 : rows) * row_bytes;
+}
 template <class Cfg, class Before>
 __device__ __forceinline__ void store_tile_via_lds(const f32x4 (&acc)[Cfg::TM][8], const TileCoord& tc,
                                                    const FragPlan<Cfg>& fp, int wave, int lane,
@@ -1099,11 +1106,10 @@ __device__ __forceinline__ void store_tile_via_lds(const f32x4 (&acc)[Cfg::TM][8
     // Stores through a buffer resource that ends behind the wavefront's last row: those of rows past the end of
     // the group are dropped by its bounds check, with no comparison, branch or 64-bit address per store (of the
     // 700 cycles that a fragment row of the down projection took, those were half).
-    const int rows_here = max(0, tc.rows - wm * Cfg::WTM);   // rows of this wavefront inside the tile
     const uint32_t row_bytes = static_cast<uint32_t>(ldc) * ESZ;
     const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(
         reinterpret_cast<unsigned char*>(C) + static_cast<size_t>(tc.row0 + wm * Cfg::WTM) * row_bytes, 0,
-        rows_here * row_bytes, 0x00027000);
+        store_bytes(tc.rows - wm * Cfg::WTM, Cfg::WTM, row_bytes), 0x00027000);
     const uint32_t ccol = static_cast<uint32_t>(tc.nt * Cfg::BN_OUT + wn * COLS) * ESZ + rchunk * 16;
     uint32_t coff[16 / RPI];
 #pragma unroll
@@ -1212,6 +1218,12 @@ struct Ring1W {
     static_assert(Full::NW == 4 && Full::TN == 8 && Full::BK == 64 && Full::RPI == 8 && LA == 8 && LB == 8 &&
                   SMEM <= 160 * 1024, "256 x 256 x 64, rings of 2 + 3 stages");
 };
+
+// Whether the byte offsets of a tile fit 32 bits, for matrices of N weight rows of K per expert: those of weight rows
+// from the expert's matrix, and with K >= 256 those of a wavefront's 128 output rows of N floats.
+__host__ __device__ constexpr bool offsets_fit_1w(int N, int K) {
+    return static_cast<unsigned long long>(N) * static_cast<unsigned long long>(K) * 2ull < (1ull << 32);
+}
 
 // Loads of one tile: pointers that advance by a k-step at a time, byte offsets per lane.
 struct LoadPlan1W {

@@ -627,6 +627,30 @@ def test_large_tiles_of_long_reductions(d, f):
     test_large_tiles_of_every_height([1152, 1153, 1344, 1345, 1664, 1665, 1793, 900], False, d, f)
 
 
+def test_large_tiles_of_very_wide_fp32_outputs():
+    """256 rows of 2^22 floats are 2^32 bytes: the upper wavefronts of a large tile store their rows all the same."""
+    d, f, T = 1 << 22, 256, 256
+    say(f"very wide rows d={d} f={f}")
+    g = torch.Generator(device="cuda").manual_seed(22)
+    rnd = lambda *shape: torch.randn(*shape, generator=g, dtype=torch.bfloat16, device="cuda").mul_(0.05)
+    W1, W3, W2, x = rnd(1, f, d), rnd(1, f, d), rnd(1, d, f), rnd(T, d)
+    wr = torch.zeros(d, 1, device="cuda")
+    ctx = B.MoeContext(T, d, f, 1, 1)
+    B.moe_set_expert_output_fp32(ctx, True)
+    outs = []
+    for config in (0, 1):          # the large tiles first: rows that they leave out hold no earlier result
+        B.moe_set_gemm_config(ctx, config)
+        y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        B.moe_layer_forward(ctx, x, wr, None, W1, W3, W2, T, y)
+        torch.cuda.synchronize()
+        outs.append(y.view(torch.int16))
+    assert not torch.isnan(outs[1].view(torch.bfloat16)).any()
+    assert torch.equal(*outs)
+    ctx.close()
+    del W1, W3, W2, x, y, outs
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("d,f", [(512, 3840), (3584, 256)])    # many tiles per workgroup up; down, at four k-steps
 @pytest.mark.parametrize("split", [0, 128])
 def test_persistent_workgroups_run_tiles_of_all_heights_in_turn(d, f, split):
