@@ -1107,9 +1107,12 @@ __device__ __forceinline__ void store_tile_via_lds(const f32x4 (&acc)[Cfg::TM][8
     // the group are dropped by its bounds check, with no comparison, branch or 64-bit address per store (of the
     // 700 cycles that a fragment row of the down projection took, those were half).
     const uint32_t row_bytes = static_cast<uint32_t>(ldc) * ESZ;
+    // to a scalar register: left alone, the comparisons become one vector instruction, and a resource that is not
+    // known to be uniform puts a loop around every store (8192 tokens through 128 experts of 2048 x 768 680 -> 689 us a layer)
+    const uint32_t bytes = __builtin_amdgcn_readfirstlane(store_bytes(tc.rows - wm * Cfg::WTM, Cfg::WTM, row_bytes));
     const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(
         reinterpret_cast<unsigned char*>(C) + static_cast<size_t>(tc.row0 + wm * Cfg::WTM) * row_bytes, 0,
-        store_bytes(tc.rows - wm * Cfg::WTM, Cfg::WTM, row_bytes), 0x00027000);
+        static_cast<int>(bytes), 0x00027000);
     const uint32_t ccol = static_cast<uint32_t>(tc.nt * Cfg::BN_OUT + wn * COLS) * ESZ + rchunk * 16;
     uint32_t coff[16 / RPI];
 #pragma unroll
