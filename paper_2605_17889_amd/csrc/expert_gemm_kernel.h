@@ -40,9 +40,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kGroupM = 8;   // at most this many m-tiles that sweep the n-tiles together (share weight tiles)
 
 struct TileCoord {
-    int expert;      // -1: no tile for this workgroup
+    int expert;      // negative: no tile for this workgroup (kNoTile, kEmptySlot)
     int row0;        // first row (in the permuted matrix) of the tile
-    int rows;        // valid rows in the tile (1..BM; 0: the lower half of a tile that has none)
+    int rows;        // valid rows in the tile (1..BM)
     int nt;          // n-tile index
     int height;      // rows that its workgroup computes: BM / 2 to BM (see tile_in_expert)
 };
@@ -68,24 +68,26 @@ struct TileCoord {
 // halves are the highest slots of every XCD's range, hence the last workgroups dispatched.
 //
 // The tile is named by (xcd, slot): slot-th entry of XCD xcd's range; the kernels take both from
-// the workgroup index. Result: expert >= 0: a tile, with no rows if the slot is the lower half of a tile
-// that has none; kNoTile: the range is exhausted (every later slot is too).
-constexpr int kNoTile = -1;
+// the workgroup index. Result: expert >= 0: a tile of at least one row; kNoTile: the range is exhausted (every later
+// slot is too); kEmptySlot: this slot holds nothing (the lower half of a tile that has none).
+constexpr int kNoTile = -1, kEmptySlot = -2;
 
 // a / b and a % b for a >= 0, b >= 1. A wavefront-uniform integer division takes some forty
 // instructions of the vector unit; below 2^22 the float quotient is off by at most one.
-__device__ __forceinline__ int div_small(int a, int b, int& rem) {
-    if (a >= (1 << 22)) {
-        const int q = a / b;
-        rem = a - q * b;
+__host__ __device__ __forceinline__ int div_small(int a, int b, int& rem) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    if (a < (1 << 22)) {
+        int q = static_cast<int>(static_cast<float>(a) * __builtin_amdgcn_rcpf(static_cast<float>(b)));
+        q = __builtin_amdgcn_readfirstlane(q);
+        int r = a - q * b;
+        if (r < 0) { --q; r += b; }
+        if (r >= b) { ++q; r -= b; }
+        rem = r;
         return q;
     }
-    int q = static_cast<int>(static_cast<float>(a) * __builtin_amdgcn_rcpf(static_cast<float>(b)));
-    q = __builtin_amdgcn_readfirstlane(q);
-    int r = a - q * b;
-    if (r < 0) { --q; r += b; }
-    if (r >= b) { ++q; r -= b; }
-    rem = r;
+#endif
+    const int q = a / b;
+    rem = a - q * b;
     return q;
 }
 
@@ -130,7 +132,7 @@ constexpr int kLongK = 4096;         // reductions of this and more are long
 enum class Cut { kNever, kLong, kAlways };
 constexpr int kLongCutTiles = 7;
 template <int BM>
-__device__ __forceinline__ bool tiles_are_cut(int m_e, int mt, Cut cut) {
+__host__ __device__ __forceinline__ bool tiles_are_cut(int m_e, int mt, Cut cut) {
     if (cut != Cut::kLong) return cut == Cut::kAlways;
     const int tail = m_e - (mt - 1) * BM;
     return mt <= 4 || (mt <= kLongCutTiles && tail <= (mt == 6 ? BM / 4 : BM / 2));
@@ -150,8 +152,8 @@ __device__ __forceinline__ bool tiles_are_cut(int m_e, int mt, Cut cut) {
 // 336 -> 325 and 234 -> 222, 1200 through 8 of 4096 x 14336 515 -> 520 and 295 -> 274 (those of short reductions
 // together with the persistent workgroups, see grouped_gemm_1w_kernel).
 template <int BM>
-__device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m_e, int local, int NT, int half,
-                                                    Cut cut) {
+__host__ __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m_e, int local, int NT,
+                                                             int half, Cut cut) {
     TileCoord tc{kNoTile, 0, 0, 0, 0};
     const int mt = (m_e + BM - 1) / BM;
     const int ngroups = (mt + kGroupM - 1) / kGroupM;
@@ -184,8 +186,9 @@ __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row_e, int m
     tc.rows = min(tc.height, m_e - first);
     if (half >= 0) {
         const int h0 = half * (BM / 2);
-        tc.rows = max(0, min(BM / 2, tc.rows - h0));
-        tc.row0 += tc.rows > 0 ? h0 : 0;
+        tc.row0 += h0;
+        tc.rows = min(BM / 2, tc.rows - h0);
+        if (tc.rows <= 0) return TileCoord{kEmptySlot, 0, 0, 0, 0};
     }
     if (tc.rows <= BM / 2) tc.height = BM / 2;
     tc.expert = expert;
@@ -1512,7 +1515,9 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_1w_kernel(
     } else {
         tc = locate_tile<Cfg::BM>(offsets, E, NT, split_cus, cut);
     }
-    if (tc.expert < 0) return;                       // uniform for the whole workgroup
+    if (PERSISTENT ? tc.expert == kNoTile : tc.expert < 0) return;     // uniform for the whole workgroup
+    // to a persistent one an empty slot is a tile without rows and without k-steps: it has to go on to its next one
+    if (tc.expert == kEmptySlot) tc = TileCoord{0, 0, 0, 0, Cfg::BM / 2};
     bool last = !PERSISTENT;
     int ahead = 0;                                   // lane 0 of wavefront 0: the latest draw
     auto draw = [&] {
@@ -1536,21 +1541,26 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_1w_kernel(
         return row_index != nullptr ? row_index[t.row0 + a_row_1w(t, wave, lane)] : offsets[0];
     };
     LoadPlan1W lp;
-    init_b_offsets<Cfg>(lp, wave, lane, K);
-    start_loads_1w<Cfg>(lp, tc, row_id(tc), wave, lane, A, B0, B1, row_index, index_div, N, K);
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (i < 4 || i * 32 < tc.height) dma16(lp.a_ptr, lp.a_voff[i], s * R::AB + wave * 1024 + i * 4096);
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            dma16(lp.b_ptr[Cfg::DUAL ? i >> 2 : 0], lp.b_voff[i], R::A_RING + s * R::BB + wave * (R::LB * 1024) + i * 1024);
-        lp.a_ptr += Cfg::BK;
-        lp.b_ptr[0] += Cfg::BK;
-        if (Cfg::DUAL) lp.b_ptr[1] += Cfg::BK;
-    }
     uint32_t sb = 0;
+    // the first two k-steps of tile t into the rings: stages 0 and 1 of A, sb and the one behind it of B
+    auto first_loads = [&](const TileCoord& t, int id) {
+        start_loads_1w<Cfg>(lp, t, id, wave, lane, A, B0, B1, row_index, index_div, N, K);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const uint32_t b_stage = s == 0 ? sb : sb + R::BB == R::NB * R::BB ? 0u : sb + R::BB;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (i < 4 || i * 32 < t.height) dma16(lp.a_ptr, lp.a_voff[i], s * R::AB + wave * 1024 + i * 4096);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                dma16(lp.b_ptr[Cfg::DUAL ? i >> 2 : 0], lp.b_voff[i], R::A_RING + b_stage + wave * (R::LB * 1024) + i * 1024);
+            lp.a_ptr += Cfg::BK;
+            lp.b_ptr[0] += Cfg::BK;
+            if (Cfg::DUAL) lp.b_ptr[1] += Cfg::BK;
+        }
+    };
+    init_b_offsets<Cfg>(lp, wave, lane, K);
+    first_loads(tc, row_id(tc));
     if (tc.height == Cfg::BM) wait_vmcnt<R::LA + R::LB>();   // k-step 0 landed
     else wait_vmcnt<4 + R::LB>();
     int slot = blockIdx.x / kXcds + workgroups;      // of the next tile
@@ -1566,8 +1576,10 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_1w_kernel(
                 slot = 2 * workgroups + __builtin_amdgcn_readfirstlane(
                     *reinterpret_cast<const int*>(idle + wave * (R::LB * 1024) + kEpilogueBytes));
             const TileCoord found = uniform_tile(table.find(NT, cut, slot, magic));
-            last = found.expert < 0;
-            if (!last)
+            last = found.expert == kNoTile;
+            if (found.expert == kEmptySlot)
+                nxt = TileCoord{tc.expert, tc.row0, 0, tc.nt, Cfg::BM / 2};
+            else if (!last)
                 nxt = found;
             else if (idle != nullptr && slot == table.range.slots + workgroups - 1 && threadIdx.x == 0)
                 __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1578,7 +1590,16 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_1w_kernel(
             ring_tile_1w<TileCfg, Cfg>(tc, nxt, lp, id, last, sb, smem, wave, lane, A, B0, B1, C, row_index, index_div,
                                        N, K, draw, drawn);
         };
-        switch (tc.height) {
+        if (PERSISTENT && tc.rows == 0) {            // nothing to compute: the next tile's first loads, as at the start
+            wait_vmcnt<0>();                         // this one's have landed where they go
+            __builtin_amdgcn_s_barrier();            // every wavefront has read the draw that the next one replaces
+            if (!last) {
+                draw();
+                first_loads(nxt, id);
+                wait_vmcnt<0>();
+                drawn(smem + R::A_RING + (sb == 0 ? (R::NB - 1) * R::BB : sb - R::BB));
+            }
+        } else switch (tc.height) {
             case 128: run(type_tag<AtHeight<Cfg, 128>>{}); break;
             case 160: run(type_tag<AtHeight<Cfg, 160>>{}); break;
             case 192: run(type_tag<AtHeight<Cfg, 192>>{}); break;
@@ -1605,7 +1626,7 @@ __global__ __launch_bounds__(Cfg::NTHREADS) void grouped_gemm_ring_kernel(
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
     const TileCoord tc = locate_tile<Cfg::BM>(offsets, E, N / Cfg::BN_OUT, split_cus);
-    if (tc.expert < 0 || tc.rows == 0) return;       // uniform for the whole workgroup
+    if (tc.expert < 0) return;                       // uniform for the whole workgroup
     if (tc.height == HalfCfg::BM)
         ring_tile<HalfCfg, NA, NB>(tc, smem, A, B0, B1, C, row_index, index_div, N, K);
     else

@@ -32,9 +32,50 @@ static long store_bounds(int K) {
     return checked;
 }
 
+// The map of an expert's tiles: whole tiles cover every row of every n-tile once, the halves of a tile its rows, and
+// what the map names a tile has rows; a lower half without any is kEmptySlot.
+static long tiles() {
+    constexpr int BM = 256, NT = 3, ROW0 = 1000;
+    long checked = 0;
+    for (const Cut cut : {Cut::kNever, Cut::kLong, Cut::kAlways})
+        for (int m_e = 1; m_e <= 2700; ++m_e) {
+            static int seen[NT][2700];
+            std::memset(seen, 0, sizeof(seen));
+            const int mt = (m_e + BM - 1) / BM;
+            for (int local = 0; local < mt * NT; ++local) {
+                const TileCoord t = tile_in_expert<BM>(5, ROW0, m_e, local, NT, -1, cut);
+                const int first = t.row0 - ROW0;
+                bool ok = t.expert == 5 && t.rows >= 1 && t.rows <= t.height && t.height >= BM / 2 && t.height <= BM &&
+                          t.height % 32 == 0 && t.nt >= 0 && t.nt < NT && first >= 0 && first + t.rows <= m_e;
+                for (int r = 0; ok && r < t.rows; ++r) ++seen[t.nt][first + r];
+                int rows = 0;
+                for (int half = 0; ok && half < 2; ++half) {
+                    const TileCoord h = tile_in_expert<BM>(5, ROW0, m_e, local, NT, half, cut);
+                    if (half == 1 && t.rows <= BM / 2) {
+                        ok = h.expert == kEmptySlot;
+                        continue;
+                    }
+                    ok = h.expert == 5 && h.nt == t.nt && h.height == BM / 2 && h.row0 == t.row0 + rows && h.rows >= 1 &&
+                         h.rows <= BM / 2;
+                    rows += h.rows;
+                }
+                if (!ok || rows != t.rows) {
+                    std::printf("cut %d, %d rows, tile %d\n", static_cast<int>(cut), m_e, local);
+                    return -1;
+                }
+                ++checked;
+            }
+            for (int nt = 0; nt < NT; ++nt)
+                for (int r = 0; r < m_e; ++r)
+                    if (seen[nt][r] != 1) return -1;
+        }
+    return checked;
+}
+
 int main(int argc, char** argv) {
     long n = -1;
     if (argc == 3 && !std::strcmp(argv[1], "store_bounds")) n = store_bounds(std::atoi(argv[2]));
+    if (argc == 2 && !std::strcmp(argv[1], "tiles")) n = tiles();
     std::printf("checked %ld\n", n);
     return n > 0 ? 0 : 1;
 }

@@ -28,3 +28,9 @@ def check(program, *args):
 def test_store_bounds_of_wide_outputs(program, K):
     """An upper wavefront's rows times the bytes of a very wide row: 256 rows of 2^22 floats are 2^32 bytes."""
     check(program, "store_bounds", K)
+
+
+def test_tiles_cover_every_row_and_empty_halves_are_no_tiles(program):
+    """A lower half without rows is named so: a workgroup that takes it for a tile multiplies over all of the reduction
+    for outputs that are never stored."""
+    check(program, "tiles")

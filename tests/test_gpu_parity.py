@@ -3,6 +3,7 @@ inputs. Integer outputs must match bit for bit; floating-point outputs within
 rel-L2 <= 1e-2 and max-abs <= 2e-2 * max|y_ref| (bf16 operands, fp32 accumulation)."""
 import dataclasses
 import json
+import math
 import os
 import sys
 
@@ -625,6 +626,7 @@ def test_large_tiles_of_long_reductions(d, f):
     test_large_tiles_of_every_height([449, 577, 769, 1024, 1025, 1152, 130], False, d, f)
     test_large_tiles_of_every_height([1280, 1281, 1500], False, d, f)
     test_large_tiles_of_every_height([1152, 1153, 1344, 1345, 1664, 1665, 1793, 900], False, d, f)
+    test_large_tiles_of_every_height([60, 128, 1], False, d, f)        # lower halves without rows
 
 
 def test_large_tiles_of_very_wide_fp32_outputs():
@@ -649,6 +651,45 @@ def test_large_tiles_of_very_wide_fp32_outputs():
     ctx.close()
     del W1, W3, W2, x, y, outs
     torch.cuda.empty_cache()
+
+
+def persistent_projections(R, E, d, f):
+    """Which projections of E experts with R rows run with persistent workgroups when the 256-row tiles are forced:
+    the library's rule, so that a test of them cannot come to test something else."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    avg = R / E
+    m_tiles = E * 0.5 * (math.ceil(max(1.0, avg - avg ** 0.5) / 256) + math.ceil((avg + avg ** 0.5) / 256))
+    return [name for name, N, K in (("gateup", 2 * f, d), ("down", d, f)) if K < 4096 and m_tiles * (N / 256) > 1.5 * cus]
+
+
+@pytest.mark.parametrize("rows,d,f,which", [
+    ([100] * 16, 512, 4608, "gateup"),                                 # drawn, several in a row
+    ([100, 100, 200, 200, 256, 60, 1, 128, 300, 129] * 2, 512, 3328, "gateup"),    # among halves that have rows
+    ([100] * 12 + [0], 512, 4096, "gateup"),                           # a workgroup's second slot
+    ([128] + [0] * 63, 512, 1024, "gateup"),                           # its only one
+    ([100] * 40, 3584, 1024, "down"), ([100] * 40, 3584, 256, "down"),
+])
+def test_persistent_workgroups_pass_slots_without_rows(rows, d, f, which):
+    """Lower halves of split tiles that have no rows, wherever a workgroup meets them; launch after launch, so that
+    the counters were left clear."""
+    say(f"slots without rows d={d} f={f} rows={rows}")
+    E, R = len(rows), sum(rows)
+    assert which in persistent_projections(R, E, d, f)
+    g = torch.Generator(device="cuda").manual_seed(R)
+    rnd = lambda *shape: (torch.randn(*shape, generator=g, device="cuda") * 0.05).bfloat16()
+    W1, W3, W2, x = rnd(E, f, d), rnd(E, f, d), rnd(E, d, f), rnd(R, d)
+    offsets = torch.tensor(np.concatenate([[0], np.cumsum(rows)]), dtype=torch.int32, device="cuda")
+    ctx = B.MoeContext(R, d, f, E, 1)
+    outs = []
+    for config in (1, 0, 0, 0 + 128, 0):
+        B.moe_set_gemm_config(ctx, config)
+        y = torch.full((R, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        B.moe_expert_ffn(ctx, x, offsets, R, W1, W3, W2, y)
+        torch.cuda.synchronize()
+        outs.append(y.view(torch.int16))
+    assert not torch.isnan(outs[0].view(torch.bfloat16)).any()
+    assert all(torch.equal(outs[0], o) for o in outs[1:])
+    ctx.close()
 
 
 @pytest.mark.parametrize("d,f", [(512, 3840), (3584, 256)])    # many tiles per workgroup up; down, at four k-steps
