@@ -692,14 +692,19 @@ def test_persistent_workgroups_pass_slots_without_rows(rows, d, f, which):
     ctx.close()
 
 
-@pytest.mark.parametrize("d,f", [(512, 3840), (3584, 256)])    # many tiles per workgroup up; down, at four k-steps
+MIXED_ROWS = [1, 257, 300, 160, 0, 512, 130, 420, 33, 256, 193, 600, 225, 128, 769, 0, 161, 480]
+
+
+@pytest.mark.parametrize("d,f,rows,which", [
+    (512, 3840, MIXED_ROWS, "gateup"), (3584, 256, MIXED_ROWS * 2, "down"),        # down: four k-steps
+])
 @pytest.mark.parametrize("split", [0, 128])
-def test_persistent_workgroups_run_tiles_of_all_heights_in_turn(d, f, split):
+def test_persistent_workgroups_run_tiles_of_all_heights_in_turn(d, f, rows, which, split):
     """Each workgroup draws several tiles: lower ones before higher ones and the reverse, groups without rows,
     counters that the launch before has cleared, from a graph too."""
-    rows = [1, 257, 300, 160, 0, 512, 130, 420, 33, 256, 193, 600, 225, 128, 769, 0, 161, 480]
     say(f"persistent workgroups d={d} f={f} split={split}")
     E, R = len(rows), sum(rows)
+    assert persistent_projections(R, E, d, f) == [which]
     g = torch.Generator(device="cuda").manual_seed(d)
     rnd = lambda *shape: (torch.randn(*shape, generator=g, device="cuda") * 0.05).bfloat16()
     W1, W3, W2, x = rnd(E, f, d), rnd(E, f, d), rnd(E, d, f), rnd(R, d)
@@ -728,10 +733,46 @@ def test_persistent_workgroups_run_tiles_of_all_heights_in_turn(d, f, split):
     ctx.close()
 
 
+@pytest.mark.parametrize("fp32_outputs", [False, True])
+def test_persistent_workgroups_of_a_layer_call(fp32_outputs, d=3584, f=1792, k=2):
+    """Both projections persistent: gate/up through the row index (and on gathered rows), down with either output."""
+    rows = MIXED_ROWS * 2
+    E, R = len(rows), sum(rows)
+    T = R // k
+    say(f"persistent workgroups of a layer call, fp32={fp32_outputs}")
+    assert R == T * k and persistent_projections(R, E, d, f) == ["gateup", "down"]
+    g = torch.Generator(device="cuda").manual_seed(R)
+    rnd = lambda *shape: (torch.randn(*shape, generator=g, device="cuda") * 0.05).bfloat16()
+    W1, W3, W2, x = rnd(E, f, d), rnd(E, f, d), rnd(E, d, f), rnd(T, d)
+    ids = torch.repeat_interleave(torch.arange(E, device="cuda"), torch.tensor(rows, device="cuda"))
+    t = torch.arange(T, device="cuda")
+    x[:, :E] = 0                                     # routed by the first E input columns
+    x[t, ids[:T]] = 64.0
+    x[t, ids[T:]] = 63.5
+    wr = torch.zeros(d, E, device="cuda")
+    wr[:E] = torch.eye(E, device="cuda")
+    ctx = B.MoeContext(T, d, f, E, k)
+    B.moe_set_expert_output_fp32(ctx, fp32_outputs)
+    outs = []
+    for config in (1, 0, 0 + 64, 0 + 128, 0):
+        B.moe_set_gemm_config(ctx, config)
+        y = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+        B.moe_layer_forward(ctx, x, wr, None, W1, W3, W2, T, y)
+        counts = torch.empty(E, dtype=torch.int32, device="cuda")
+        B.moe_last_routing(ctx, T, counts=counts)
+        torch.cuda.synchronize()
+        assert counts.tolist() == rows
+        outs.append(y.view(torch.int16))
+    assert not torch.isnan(outs[0].view(torch.bfloat16)).any()
+    assert all(torch.equal(outs[0], o) for o in outs[1:])
+    ctx.close()
+
+
 def test_persistent_workgroups_of_many_contexts():
     """More contexts at once than there are sets of counters; sets that were given back are taken again."""
     say("persistent workgroups, 70 contexts")
-    d, f, E, R = 512, 3840, 8, 2048
+    d, f, E, R = 512, 8192, 8, 2048
+    assert persistent_projections(R, E, d, f) == ["gateup"]
     g = torch.Generator(device="cuda").manual_seed(9)
     rnd = lambda *shape: (torch.randn(*shape, generator=g, device="cuda") * 0.05).bfloat16()
     W1, W3, W2, x = rnd(E, f, d), rnd(E, f, d), rnd(E, d, f), rnd(R, d)
@@ -1424,6 +1465,7 @@ def test_profile_stage_times_of_layer_and_expert_ffn():
     (5, 1, 1, 512, 256), (2, 16, 16, 512, 256), (40, 13, 4, 512, 256),      # one expert, all experts, odd counts
     (1, 128, 8, 2048, 768), (4, 128, 8, 512, 128), (3, 64, 6, 512, 128),    # selected on the way, up to 4 tokens
     (3, 17, 3, 512, 384), (2, 32, 5, 512, 128), (1, 256, 64, 512, 128), (4, 65, 2, 512, 128),
+    (1, 64, 6, 2048, 1408), (1, 128, 8, 512, 1152), (1, 256, 8, 512, 1152),        # a few more tiles than compute units
     (16, 256, 64, 512, 128), (17, 128, 8, 512, 128),                        # more: separate launches
 ])
 @pytest.mark.parametrize("one_expert", [False, True])
