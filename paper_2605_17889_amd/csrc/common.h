@@ -58,14 +58,14 @@ int launch_select_hist_permute(const float* logits, int T, int E, int k, int32_t
                                int32_t* seg_tables, hipStream_t s);
 int launch_gather(const moe_bf16* x, const int32_t* perm, const int32_t* offsets, int R, int d,
                   int k, int E, moe_bf16* x_perm, hipStream_t s);
-// Where and how a context launches its expert GEMMs: its device and the tuning knobs of
-// moe_set_gemm_config (all settings give identical bits).
 // Counters from which persistent workgroups draw their tiles, zero between launches. A context takes a set of its
 // device's 64 and gives it back; set -1: there is none left (the caller then zeroes memory of its own). The
 // calling thread's current device must be `device`.
 constexpr size_t kTileCounterBytes = kXcds * 128;
 int32_t* take_tile_counters(int device, int* set);
 void give_tile_counters(int device, int set);
+// Where and how a context launches its expert GEMMs: its device, its tile counters and the tuning knobs of
+// moe_set_gemm_config (all settings give identical bits).
 struct GemmEnv {
     int device = 0;
     int forced_config = -1;           // -1: automatic; 0..4: force a tile configuration

@@ -107,7 +107,10 @@ double touched_experts(int R, int E) { return E * (1.0 - std::exp(-static_cast<d
 // per compute unit, 168, 169, 176, so steps of 2 only at the worst pitch. A reduction of 4096 ends too soon for it: gate/up,
 // 16 tokens at 4096 x 14336 279 together, 290 with eight starts over the same span; nor does a launch of few weights pay for
 // the last starts, 11 us late with steps of 1 (one token through 2 of 8 experts of 4096 x 14336, 235 MB of W2: layer call
-// 126.8 us together, 137.5; of 6144 x 16384, 403 MB, 202.7 and 211).
+// 126.8 us together, 137.5; of 6144 x 16384, 403 MB, 202.7 and 211). Other reductions, both projections of 8 experts with
+// the same rows each, together -> as here: 8192 x 8192 4 rows 514 -> 506, 60 531 -> 519; 10240 x 10240 4 775 -> 738, 32
+// 803 -> 790; 12288 x 8192 32 754 -> 747; 7168 x 18432 60 1101 -> 1072; within 1 % of each other where the pitch is no multiple
+// of 4 KB (11008, 6656, 7680, 17920). A gate/up reduction of 5120 gains nothing: 4 rows 485 -> 487 with steps of 1, 60 593 -> 595.
 int spread_steps(int R, int E, int N, int K, bool dual) {
     const double bytes = touched_experts(R, E) * (dual ? 4.0 : 2.0) * N * K;
     return K < 6144 || bytes < 0.8e9 ? 0 : K % 16384 == 0 ? 2 : 1;

@@ -13,15 +13,20 @@
 // it sustains ~13 % more FLOP/s on random operands. The weight fragment is the first MFMA
 // operand, so a lane ends up with four consecutive output columns of one row (one 8-byte store).
 //
-// Two kernels share the tile mapping, the LDS layout, the fragment plan and the epilogue:
+// Four kernels share the tile mapping, the LDS layout and the fragment plan:
 //   grouped_gemm_kernel       ring of NSTAGE LDS stages, compiler-scheduled k-step (small tiles:
 //                           decode and micro-batch sized expert groups, HBM-bound);
-//   grouped_gemm_ring_kernel  hand-placed software pipeline for the large compute-bound tiles:
-//                           the fragments of the next half k-step are read from LDS while the
-//                           MFMAs of the current one issue, the workgroup barrier sits in the
-//                           middle of a k-step so that MFMAs are ready on both sides of it, the
-//                           direct-to-LDS loads are spread between the MFMAs, and the two
-//                           operands have LDS rings of different depth.
+//   grouped_gemm_routed_kernel  the same tiles for gate/up of a few tokens, which finds its groups
+//                           in the selected experts instead of a permutation's tables;
+//   grouped_gemm_1w_kernel    the large compute-bound tiles, one wavefront per SIMD: hand-placed
+//                           software pipeline with at most a few other instructions behind every
+//                           MFMA, tiles of five heights, in short reductions persistent workgroups;
+//   grouped_gemm_ring_kernel  the large tiles with two wavefronts per SIMD (by moe_set_gemm_config,
+//                           and what the one before does not take): the fragments of the next half
+//                           k-step are read from LDS while the MFMAs of the current one issue, and
+//                           the direct-to-LDS loads are spread between the MFMAs.
+// In the last two the workgroup barrier sits in the middle of a k-step, so that MFMAs are ready on
+// both sides of it, and the two operands have LDS rings of different depth.
 #pragma once
 #include <type_traits>
 
@@ -128,7 +133,12 @@ constexpr int kLongK = 4096;         // reductions of this and more are long
 // where the last tile would hold few rows, whole -> cut: 4200 tokens (1050) 4128 -> 3877, 4400 (1100) 4332 -> 3947,
 // 5200 (1300, six) 4770 -> 4647, 6400 (1600, seven) 6059 -> 5677, 5300 at 4096 x 14336 2875 -> 2793. Past the lines,
 // whole -> cut: six m-tiles with tails to 96 (5600) 4999 -> 5009, tails of 129 to 192 in five (4800) 4220 -> 4303, eight
-// with tails to 64 (7200) 6352 -> 6513, eight and nine (8192) 7168 -> 7295.
+// with tails to 64 (7200) 6352 -> 6513, eight and nine (8192) 7168 -> 7295. The lines at other shapes, 8 experts, exact
+// groups, expert stage alone: 1050 rows of 4096 x 14336 2437 -> 2247, of 8192 x 8192 2742 -> 2520; 1320 of 8192 x 8192
+// 3244 -> 3012; 1660 of 5120 x 12800 4339 -> 4207; 1850 (eight) of 8192 x 8192 4358 -> 4421, 2100 (nine) of 5120 x 12800
+// 5428 -> 5311. Six m-tiles with tails of 65 to 128: where all groups are alike cutting them gains up to 1.1 % (1376 of
+// 5120 x 12800) or nothing, but a layer's groups are not, and cut ones among whole ones lose: layers of 5500 or 5600 tokens
+// 4948 -> 5052 (6144 x 16384), 2843 -> 2861 (4096 x 14336), 3263 -> 3301 (8192 x 8192), 3528 -> 3568 (5120 x 12800).
 enum class Cut { kNever, kLong, kAlways };
 constexpr int kLongCutTiles = 7;
 template <int BM>
@@ -1197,8 +1207,9 @@ __device__ __forceinline__ void static_for(F&& f) {
 // kt+3 in the first half of k-step kt+1, so the texture-address unit sees one load per SIMD
 // every 128 cycles throughout instead of all sixteen within one half.
 //
-// The workgroup is PERSISTENT: it runs one tile after the other, and the loads never stop in
-// between. In the last two k-steps of a tile the load pointers already stand on the next tile, so
+// The workgroup is PERSISTENT: it runs one tile after the other, and the loads go on in
+// between. (Gate/up through a row index waits for all that are on their way once per tile, where the load pointers
+// move on: the next tile's index entries come by vector loads, which are counted with the others.) In the last two k-steps of a tile the load pointers already stand on the next tile, so
 // those k-steps fill the rings with its first two k-steps (nothing else is left to load there), and
 // they arrive under the conversion and stores of the finished tile. A workgroup per tile paid for its
 // lookup (2.6 k cycles), its first loads (4.6 k, bound by their issue: 32 per wavefront about 100
