@@ -81,19 +81,22 @@ constexpr int kNoTile = -1, kEmptySlot = -2;
 // instructions of the vector unit; below 2^22 the float quotient is off by at most one.
 __host__ __device__ __forceinline__ int div_small(int a, int b, int& rem) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    if (a < (1 << 22)) {
-        int q = static_cast<int>(static_cast<float>(a) * __builtin_amdgcn_rcpf(static_cast<float>(b)));
-        q = __builtin_amdgcn_readfirstlane(q);
-        int r = a - q * b;
-        if (r < 0) { --q; r += b; }
-        if (r >= b) { ++q; r -= b; }
-        rem = r;
+    if (a >= (1 << 22)) {
+        const int q = a / b;
+        rem = a - q * b;
         return q;
     }
-#endif
-    const int q = a / b;
-    rem = a - q * b;
+    int q = static_cast<int>(static_cast<float>(a) * __builtin_amdgcn_rcpf(static_cast<float>(b)));
+    q = __builtin_amdgcn_readfirstlane(q);
+    int r = a - q * b;
+    if (r < 0) { --q; r += b; }
+    if (r >= b) { ++q; r -= b; }
+    rem = r;
     return q;
+#else
+    rem = a % b;
+    return a / b;
+#endif
 }
 
 // The slots of one XCD's range of `total` tiles. A lookup gives a slot's place in the logical order, or -1 past
@@ -194,14 +197,14 @@ __host__ __device__ __forceinline__ TileCoord tile_in_expert(int expert, int row
     }
     tc.row0 = row_e + first;
     tc.rows = min(tc.height, m_e - first);
+    tc.expert = expert;
     if (half >= 0) {
         const int h0 = half * (BM / 2);
-        tc.row0 += h0;
-        tc.rows = min(BM / 2, tc.rows - h0);
-        if (tc.rows <= 0) return TileCoord{kEmptySlot, 0, 0, 0, 0};
+        tc.rows = max(0, min(BM / 2, tc.rows - h0));
+        tc.row0 += tc.rows > 0 ? h0 : 0;
+        if (tc.rows == 0) tc.expert = kEmptySlot;
     }
     if (tc.rows <= BM / 2) tc.height = BM / 2;
-    tc.expert = expert;
     return tc;
 }
 
