@@ -35,7 +35,8 @@
  *     current device when a call that takes `stream` is made (MOE_ERR_INVALID_ARG otherwise).
  *   - Supported shapes: d_model a multiple of 512, d_ff a multiple of 128,
  *     1 <= k <= min(E, 64), E <= 256, 0 <= T <= T_max, T_max * k < 2^31 (row offsets into the
- *     tensors are 64-bit inside the kernels). Anything else is MOE_ERR_UNSUPPORTED_SHAPE.
+ *     tensors are 64-bit inside the kernels; inside a tile of up to 256 rows they are 32-bit, which holds
+ *     for d_model and d_ff up to 2^23). Anything else is MOE_ERR_UNSUPPORTED_SHAPE.
  *
  * Weight layout (out, in): W1, W3 are [E, d_ff, d_model]; W2 is [E, d_model, d_ff]; the
  * router matrix is [d_model, E] fp32. These are the three d_h x d_e bf16 matrices per expert
